@@ -97,8 +97,30 @@ inline int gqa_rows_per_block(int rows) {
 }
 inline int gqa_waves_per_block(int rows_per_block) { return gqa_block_uses_helpers(rows_per_block) ? 8 : rows_per_block / 32; }
 
+// The tiled kernel for the other head sizes (seer_attention_tile.hip): any page size, separate K and V pools, two LDS stages
+// of one K and one V tile, row blocks of as many waves as a workgroup holds.
+inline bool tile_shape(int Dqk, int Dv) { return (Dqk == 64 && Dv == 64) || (Dqk == 256 && Dv == 256) || (Dqk == 192 && Dv == 128); }
+inline bool tile_supports(const seer_attn_params& p) {
+    return tile_shape(p.Dqk, p.Dv) && !p.kv_shared_latent && !(p.flags & SEER_ATTN_GENERAL_KERNEL);
+}
+constexpr int tile_stage_kb(int Dqk, int Dv) { return 32 * 2 * (Dqk + Dv) / 1024; }
+constexpr int tile_waves_per_simd(int Dqk) { return Dqk == 64 ? 3 : (Dqk == 256 ? 1 : 2); }
+constexpr int tile_max_waves(int Dqk) { return Dqk == 256 ? 4 : 8; }     // per workgroup
+inline int tile_row_blocks(int rows, int Dqk) { return (rows + tile_max_waves(Dqk) * 32 - 1) / (tile_max_waves(Dqk) * 32); }
+inline int tile_rows_per_block(int rows, int Dqk) {
+    const int nb = tile_row_blocks(rows, Dqk);
+    return ((rows + nb - 1) / nb + 31) / 32 * 32;
+}
+
 // Workgroups of the partition kernel that one CU holds at once, by kernel shape.
 inline int resident_wgs_per_cu(const seer_attn_params& p) {
+    if (tile_supports(p)) {
+        const int waves = tile_rows_per_block((p.Hq / p.Hkv) * p.T, p.Dqk) / 32;
+        const int by_waves = 4 * tile_waves_per_simd(p.Dqk) / waves;
+        const int by_lds = 159 / (2 * tile_stage_kb(p.Dqk, p.Dv) + 1);
+        const int n = by_waves < by_lds ? by_waves : by_lds;
+        return n < 1 ? 1 : (n > 8 ? 8 : n);
+    }
     const bool tiled = p.Dqk == 128 && p.Dv == 128 && gqa_page_size_ok(p.page_size) && !p.kv_shared_latent &&
                        !(p.flags & SEER_ATTN_GENERAL_KERNEL);
     if (!tiled) return 4;
@@ -130,8 +152,10 @@ inline WorkspaceLayout workspace_layout(const seer_attn_params& p) {
         } else {
             const bool tiled = p.Dqk == 128 && p.Dv == 128 && gqa_page_size_ok(p.page_size) && !p.kv_shared_latent &&
                                !(p.flags & SEER_ATTN_GENERAL_KERNEL);
-            const int row_blocks = tiled ? gqa_row_blocks((p.Hq / p.Hkv) * p.T) : 1;
+            const int rows = (p.Hq / p.Hkv) * p.T;
+            const int row_blocks = tiled ? gqa_row_blocks(rows) : (tile_supports(p) ? tile_row_blocks(rows, p.Dqk) : 1);
             w.wgs_per_head = kNumCU * resident_wgs_per_cu(p) / (p.Hkv * row_blocks);
+            if (w.wgs_per_head > kMaxWgsPerHead) w.wgs_per_head = kMaxWgsPerHead;
         }
         if (w.wgs_per_head < 1) w.wgs_per_head = 1;
         // a stretch adds one piece per request boundary it crosses: pieces <= W + B
@@ -193,5 +217,6 @@ bool gqa128_supports(const AttnArgs& a);                            // D = 128, 
 hipError_t launch_gqa128(const AttnArgs& a, hipStream_t stream);
 bool mla_supports(const AttnArgs& a);                               // shared latent 576/512, pages of 32..1024 tokens
 hipError_t launch_mla(const AttnArgs& a, hipStream_t stream);
+hipError_t launch_tile(const AttnArgs& a, hipStream_t stream);      // shapes of tile_supports
 
 }  // namespace seer

@@ -661,6 +661,8 @@ extern "C" const char* seer_verify_attention_kernel(const seer_attn_params* p) {
         return names.text[seer::gqa_rows_per_block(rows) / 32];
     }
     if (tiled_ok && seer::mla_supports(a)) return "attn_mla_kernel";
+    if (seer::tile_supports(*p))
+        return p->Dqk == 64 ? "attn_tile_kernel<64,64>" : p->Dqk == 256 ? "attn_tile_kernel<256,256>" : "attn_tile_kernel<192,128>";
     if (p->Dqk == 64) return "attn_general_kernel<64,64>";
     if (p->Dqk == 128) return "attn_general_kernel<128,128>";
     if (p->Dqk == 256) return "attn_general_kernel<256,256>";
@@ -709,8 +711,10 @@ int run_verify_attention(void* out, const void* q, const void* k_pages, const vo
     a.fixed_split = (p->flags & SEER_ATTN_FIXED_SPLIT) ? 1 : 0;
     a.stream_only = (p->flags & SEER_ATTN_STREAM_ONLY) ? 1 : 0;
     a.stream_partials = (w.total - w.off_acc) < seer::kStreamPartialsBelow ? 1 : 0;
-    a.row_blocks = seer::gqa_row_blocks((p->Hq / p->Hkv) * p->T);
-    a.rows_per_block = seer::gqa_rows_per_block((p->Hq / p->Hkv) * p->T);
+    const bool tile_kernel = seer::tile_supports(*p);
+    const int rows = (p->Hq / p->Hkv) * p->T;
+    a.row_blocks = tile_kernel ? seer::tile_row_blocks(rows, p->Dqk) : seer::gqa_row_blocks(rows);
+    a.rows_per_block = tile_kernel ? seer::tile_rows_per_block(rows, p->Dqk) : seer::gqa_rows_per_block(rows);
     a.items = reinterpret_cast<const seer::WorkItem*>(ws + w.off_items);
     a.part_ml = reinterpret_cast<float*>(ws + w.off_ml);
     a.part_acc = reinterpret_cast<float*>(ws + w.off_acc);
@@ -736,6 +740,7 @@ int run_verify_attention(void* out, const void* q, const void* k_pages, const vo
     const bool tiled_ok = !(p->flags & SEER_ATTN_GENERAL_KERNEL);
     if (tiled_ok && seer::gqa128_supports(a)) err = seer::launch_gqa128(a, stream);
     else if (tiled_ok && seer::mla_supports(a)) err = seer::launch_mla(a, stream);
+    else if (tile_kernel) err = seer::launch_tile(a, stream);
     else err = seer::launch_general(a, stream);
     if (err != hipSuccess) return static_cast<int>(err);
     if (ev_end && (err = hipEventRecord(ev_end, stream)) != hipSuccess) return static_cast<int>(err);

@@ -503,7 +503,7 @@ void attn_mla_kernel(AttnArgs a, int row_blocks) {
             mx_part = fmaxf(mx_part, sc[15]);
             SEER_MLA_PIN(mx_part);
         } else if constexpr (part == 2) {
-            mx_part = max_across_halves(mx_part) * a.scale_log2;
+            mx_part = mla::max_across_halves(mx_part) * a.scale_log2;
             SEER_MLA_PIN(mx_part);
         } else {
             const float m_new = (mx_part > m_run + 8.f) ? mx_part : m_run;

@@ -1,0 +1,405 @@
+// Matrix-core verify-attention partition kernel for the head sizes beside D = 128: (64, 64), (256, 256) and
+// (192, 128), separate K and V pools, pages of any size.
+//
+// What bounds it: HBM.  A KV token is read once for all R = G*T query rows of its head; with the scores and P.V on
+// the matrix cores (48 MFMAs of 32 cycles per 32 KB tile and 32 rows at D = 256, 12 per 8 KB at D = 64) the
+// arithmetic of a CU keeps up with more than its share of the bandwidth even though one wave runs a tile's phases one
+// after the other, so the kernel leaves the overlap to the two to sixteen waves of a CU instead of a hand-placed pipeline.
+// The vector-ALU kernel it stands in for reads every KV token once per query row.  Measured, whole call: 16 requests, 16/4
+// heads of 64, T = 9, 43 687 KV tokens 977 -> 55.9 us; 8/1 heads of 256, T = 5, same lengths 386 -> 65.5 us.
+//
+// Work decomposition as in the D = 128 kernel: workgroup (stretch, KV head, row block), wave i owns query rows
+// [32 i, 32 i + 32), the plan's stretches of 32-token tiles, one partial result per request touched.
+// Data flow: a tile's K and V rows go HBM -> LDS directly, two stages; each lane picks the chunk its fixed LDS
+// slot receives, so a tile may span any number of pages (the row index of every token comes from a 64-entry window of
+// the block table by ds_bpermute).  S^T = K.Q^T, softmax with one query row per lane, O^T += V^T.P^T.
+//
+// Precision: the vector-ALU kernel multiplies fp32 probabilities into V.  A probability goes into the bf16 matrix
+// product as two terms, its bf16 rounding and the bf16 rounding of what that leaves (together 2^-17 of the value or
+// better), and the row sums take the fp32 value, so the output differs from the vector kernel's by single roundings
+// of the bf16 result only.  V rows that hold infinities or NaN in a tile with masked slots are kept out of the product
+// (0 * NaN must not reach rows that do not see the slot) and added per row.
+#include <type_traits>
+
+#include "seer_attention.h"
+#include "seer_device.h"
+#include "seer_tile.h"
+
+namespace seer {
+namespace tile {
+
+constexpr int kTile = kPlanTile;
+
+template <int DQK, int DV>
+struct Shape {
+    static constexpr int kKRow = DQK * 2, kVRow = DV * 2;                    // bytes of a token's row
+    static constexpr int kKBytes = kTile * kKRow, kVBytes = kTile * kVRow;
+    static constexpr int kStage = kKBytes + kVBytes;
+    static constexpr int kKSteps = DQK / 16, kDTiles = DV / 32;
+    static_assert(kKRow % 128 == 0 && kVRow % 128 == 0 && kKBytes % 1024 == 0 && kVBytes % 1024 == 0, "");
+    static_assert(kStage == tile_stage_kb(DQK, DV) * 1024, "the host sizes the launch with the same number");
+};
+
+// LDS swizzles: 16-byte chunk c of row r is stored at chunk position c ^ f(r) of the row.  64 banks of 4 bytes are 16
+// chunks.  K (ds_read_b128, 16 rows at one chunk per quarter-wave): rows of 256 or 512 bytes all start at bank 0 and take
+// four bits of the row; rows of 128 or 384 bytes alternate between two halves of the banks and take three.
+// V (transposing read, 4 rows x 64 bytes per half-wave): the four rows must fall into different 64-byte groups.
+template <int ROW_BYTES>
+__device__ __forceinline__ int k_swz(int row) { return ROW_BYTES % 256 == 0 ? row & 15 : (row >> 1) & 7; }
+template <int ROW_BYTES>
+__device__ __forceinline__ int v_swz(int row) { return ROW_BYTES % 256 == 0 ? (row & 3) << 2 : ((row >> 1) & 1) << 2; }
+
+__device__ __forceinline__ int lds_addr(const unsigned char* p) {
+    return static_cast<int>(reinterpret_cast<uintptr_t>((const SEER_AS3 void*)(p)));
+}
+
+// Operand reads and their wait in one block (through the builtins the compiler would put a vmcnt(0) in front of them: it
+// cannot tell them apart from the tile loads in flight).
+__device__ __forceinline__ void read_k4(u32x4 (&kv)[4], int a0, int a1, int a2, int a3) {
+    asm volatile("ds_read_b128 %0, %4\n"
+                 "ds_read_b128 %1, %5\n"
+                 "ds_read_b128 %2, %6\n"
+                 "ds_read_b128 %3, %7\n"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(kv[0]), "=&v"(kv[1]), "=&v"(kv[2]), "=&v"(kv[3])
+                 : "v"(a0), "v"(a1), "v"(a2), "v"(a3)
+                 : "memory");
+}
+// V^T operands of two d-tiles (lane addresses a0, a1) for the tile's 32 tokens: vr[tile][token rows 0, 8, 16, 24].
+template <int OFF, int ROW8>
+__device__ __forceinline__ void read_v2(u32x2 (&vr)[2][4], int a0, int a1) {
+    asm volatile("ds_read_b64_tr_b16 %0, %8 offset:%10\n"
+                 "ds_read_b64_tr_b16 %1, %8 offset:%11\n"
+                 "ds_read_b64_tr_b16 %2, %8 offset:%12\n"
+                 "ds_read_b64_tr_b16 %3, %8 offset:%13\n"
+                 "ds_read_b64_tr_b16 %4, %9 offset:%10\n"
+                 "ds_read_b64_tr_b16 %5, %9 offset:%11\n"
+                 "ds_read_b64_tr_b16 %6, %9 offset:%12\n"
+                 "ds_read_b64_tr_b16 %7, %9 offset:%13\n"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(vr[0][0]), "=&v"(vr[0][1]), "=&v"(vr[0][2]), "=&v"(vr[0][3]), "=&v"(vr[1][0]),
+                   "=&v"(vr[1][1]), "=&v"(vr[1][2]), "=&v"(vr[1][3])
+                 : "v"(a0), "v"(a1), "n"(OFF), "n"(OFF + ROW8), "n"(OFF + 2 * ROW8), "n"(OFF + 3 * ROW8)
+                 : "memory");
+}
+
+}  // namespace tile
+
+// One wave per 32 query rows.  Registers: 64-wide heads leave room for three waves per SIMD, (192, 128) for two; at D = 256
+// Q^T and O^T alone take 192, so one wave has a SIMD to itself (with 256 registers 40 of them would be spilled, and a
+// spill's reload waits for the tile loads in flight).
+template <int DQK, int DV>
+__global__ __launch_bounds__(tile_max_waves(DQK) * kWave) __attribute__((amdgpu_waves_per_eu(tile_waves_per_simd(DQK))))
+void attn_tile_kernel(AttnArgs a, int n_waves) {
+    using namespace tile;
+    using S = Shape<DQK, DV>;
+    // two stages of K tile, V tile; then two words: the scanned tile's tokens with infinities or NaN, "take the piece again"
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * S::kStage + 16];
+    volatile uint32_t* s_nonfinite = reinterpret_cast<volatile uint32_t*>(lds + 2 * S::kStage);
+    volatile uint32_t* s_again = s_nonfinite + 1;
+
+    int rest = blockIdx.x >> 3;                     // (the grid's layout: see the D = 128 kernel)
+    const int kvh = rest % a.Hkv;
+    rest /= a.Hkv;
+    const int rb = rest % a.row_blocks;
+    const int wg = (rest / a.row_blocks) * 8 + (blockIdx.x & 7);
+    if (wg >= a.wgs_per_head) return;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int ln = lane & 31, lg = lane >> 5, l16 = lane >> 4, p16 = lane & 15;
+
+    const int L = uniform_load(&a.header->tiles_per_wg);
+    int b = uniform_load(a.wg_first + wg);
+    if (b < 0) return;
+    int g = uniform_load(L ? a.wg_start + wg : a.tile_off + b);
+    const int g_end = uniform_load(L ? a.wg_start + wg + 1 : a.tile_off + b + 1);
+    const int g_first = g;
+    const uint64_t clock_begin = __builtin_amdgcn_s_memrealtime();
+    bool bad_page = false;
+
+    const unsigned char* __restrict__ kbase = static_cast<const unsigned char*>(a.k_pages);
+    const unsigned char* __restrict__ vbase = static_cast<const unsigned char*>(a.v_pages);
+    const int lds0 = lds_addr(lds);
+    const bool page_pow2 = (a.P & (a.P - 1)) == 0;
+    const int page_shift = __builtin_ctz(static_cast<unsigned>(a.P));
+    auto page_of = [&](int tok) __attribute__((always_inline)) -> int { return page_pow2 ? tok >> page_shift : tok / a.P; };
+
+    // operand addresses inside a stage: K chunk 2 kk + lg of row ln, V as the transposing read wants it (lane 4k + c of a
+    // 16-lane group points at token row k, columns 4c .. 4c + 3 of the group's 16)
+    constexpr int kXorBits = S::kKRow % 256 == 0 ? 4 : 3;                      // chunk bits the K swizzle touches
+    constexpr int kPerXor = 1 << (kXorBits - 1);                              // contraction steps until those bits repeat
+    const int k_rd = ln * S::kKRow + ((lg ^ k_swz<S::kKRow>(ln)) << 4);       // step kk: ^ (kk % kPerXor) << 5, + whole periods
+    const int v_k = p16 >> 2, v_c4 = p16 & 3;
+    const int v_rd = S::kKBytes + (lg * 4 + v_k) * S::kVRow + ((((l16 & 1) * 2 + (v_c4 >> 1)) ^ v_swz<S::kVRow>(v_k)) << 4) +
+                     (v_c4 & 1) * 8;                                           // d-tile dt: ^ (dt % n) << 6, + whole periods
+
+  for (; g < g_end; ++b) {
+    const int t_lo = uniform_load(a.tile_off + b), t_hi = uniform_load(a.tile_off + b + 1);
+    if (t_hi == t_lo) continue;
+    const int item_idx = uniform_load(a.split_off + b) + (L ? wg - uniform_load(a.req_first + b) : 0);
+    const int n = uniform_load(a.ctx_len + b);
+    const int tok_begin = (g - t_lo) * kTile;
+    const int tok_end = min(n, (min(g_end, t_hi) - t_lo) * kTile);
+    g = t_hi;
+    const int n0 = n - a.T;
+    const int n_tiles = (tok_end - tok_begin + kTile - 1) / kTile;
+    bare_barrier();                                // every wave is done with the previous piece's stages
+    if (tid == 0) *s_again = 0;
+
+    // ---- page window and tile loads ---------------------------------------------------------
+    const int32_t* __restrict__ table = a.block_table + static_cast<size_t>(b) * a.max_pages;
+    const int last_page = (n - 1) / a.P;
+    int win = -0x40000000, pg_win = 0;             // lane l holds the (clamped) page id of logical page win + l
+    auto issue_tile = [&](int tile, int stage) __attribute__((always_inline)) {
+        const int tb = tok_begin + tile * kTile;
+        const int first = page_of(tb);
+        if (first < win || page_of(tb + kTile - 1) >= win + kWave) {          // uniform; a tile spans at most 32 pages
+            win = first;
+            const int idx = win + lane;
+            int pg = table[min(idx, a.max_pages - 1)];
+            if (pg < 0 || pg >= a.num_pages) {
+                if (idx <= last_page) bad_page = true;
+                pg = min(max(pg, 0), a.num_pages - 1);
+            }
+            pg_win = pg;
+        }
+        const int tok = tb + ln, lp = page_of(tok);
+        const int pg = __builtin_amdgcn_ds_bpermute((lp - win) << 2, pg_win);
+        // row index in the pool (of 128 bytes or more each: 32 bits reach past the memory of the GPU)
+        const uint32_t row_idx = (static_cast<uint32_t>(pg) * a.Hkv + kvh) * static_cast<uint32_t>(a.P) + (tok - lp * a.P);
+        constexpr int kKChunks = S::kKRow / 16, kVChunks = S::kVRow / 16;
+        for (int j = wave; j < S::kKBytes / 1024; j += n_waves) {
+            const int c = j * kWave + lane, row = c / kKChunks, pos = c - row * kKChunks;
+            const uint32_t r = __builtin_amdgcn_ds_bpermute(row << 2, row_idx);
+            const unsigned char* src = kbase + static_cast<size_t>(r) * S::kKRow + ((pos ^ k_swz<S::kKRow>(row)) << 4);
+            __builtin_amdgcn_global_load_lds((const SEER_AS1 void*)(src), (SEER_AS3 void*)(lds + stage + j * 1024), 16, 0, 2);
+        }
+        for (int j = wave; j < S::kVBytes / 1024; j += n_waves) {
+            const int c = j * kWave + lane, row = c / kVChunks, pos = c - row * kVChunks;
+            const uint32_t r = __builtin_amdgcn_ds_bpermute(row << 2, row_idx);
+            const unsigned char* src = vbase + static_cast<size_t>(r) * S::kVRow + ((pos ^ v_swz<S::kVRow>(row)) << 4);
+            __builtin_amdgcn_global_load_lds((const SEER_AS1 void*)(src), (SEER_AS3 void*)(lds + stage + S::kKBytes + j * 1024), 16, 0, 2);
+        }
+    };
+
+    // ---- this lane's query row ---------------------------------------------------------------
+    const int r = rb * a.rows_per_block + wave * 32 + ln;
+    const bool row_ok = r < min(a.G * a.T, (rb + 1) * a.rows_per_block);
+    const int t = row_ok ? r / a.G : 0;
+    const int hq = kvh * a.G + (row_ok ? r - t * a.G : 0);
+    uint64_t word = 0;
+    if (row_ok) word = a.tree_mask ? a.tree_mask[static_cast<size_t>(b) * a.T + t] : (t >= 63 ? ~0ull : ((1ull << (t + 1)) - 1));
+    if (a.T < 64) word &= (1ull << a.T) - 1;
+    bf16x8 qreg[S::kKSteps];
+    {
+        const u32x4* qp = reinterpret_cast<const u32x4*>(
+            static_cast<const uint16_t*>(a.q) + ((static_cast<size_t>(b) * a.T + t) * a.Hq + hq) * DQK + lg * 8);
+#pragma unroll
+        for (int kk = 0; kk < S::kKSteps; ++kk) {
+            u32x4 v = {0u, 0u, 0u, 0u};
+            if (row_ok) v = qp[kk * 2];
+            qreg[kk] = as_bf16x8(v);
+        }
+    }
+    // A piece whose accumulators end up with an infinity or a NaN is taken a second time with every tile scanned for V
+    // rows that hold one (see the head of the file); otherwise only the tiles with masked slots are.
+    f32x16 acc[S::kDTiles];
+    float m_run, l_run;
+    for (int scan_all = 0;; scan_all = 1) {
+    issue_tile(0, 0);
+#pragma unroll
+    for (int dt = 0; dt < S::kDTiles; ++dt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[dt][i] = 0.f;
+    m_run = kNegInf, l_run = 0.f;
+
+    for (int u = 0; u < n_tiles; ++u) {
+        const int stage = (u & 1) * S::kStage;
+        wait_vmcnt<0>();
+        bare_barrier();                            // tile u has landed for every wave, every wave is done with tile u - 1
+        if (u + 1 < n_tiles) issue_tile(u + 1, S::kStage - stage);
+        __builtin_amdgcn_sched_barrier(0);
+        const int tb = tok_begin + u * kTile;
+        const int rel = tb - n0;                    // uniform; a tile with masked slots has rel > -32
+        uint32_t nonfinite = 0;                    // uniform: tokens of this tile whose V row is kept out of the product
+        if (rel > -kTile || scan_all) {
+            // V rows past the end of the request are cleared whatever they hold; rows with infinities or NaN are cleared
+            // too and added per row below.
+            unsigned char* vl = lds + stage + S::kKBytes;
+            if (tid == 0) *s_nonfinite = 0;
+            __builtin_amdgcn_s_waitcnt(0xc07f);
+            bare_barrier();
+            uint32_t found = 0;
+            for (int c = tid; c < S::kVBytes / 16; c += n_waves * kWave) {
+                const int row = c / (S::kVRow / 16);
+                const u32x4 x = *reinterpret_cast<const u32x4*>(vl + c * 16);
+#pragma unroll
+                for (int w = 0; w < 4; ++w)
+                    if ((x[w] & 0x7f80u) == 0x7f80u || (x[w] & 0x7f800000u) == 0x7f800000u) found |= 1u << row;
+            }
+            if (tb + kTile > n) found &= (1u << (n - tb)) - 1;
+            if (found) atomicOr(const_cast<uint32_t*>(s_nonfinite), found);
+            __builtin_amdgcn_s_waitcnt(0xc07f);
+            bare_barrier();
+            nonfinite = __builtin_amdgcn_readfirstlane(*s_nonfinite);
+            const uint32_t cleared = nonfinite | (tb + kTile > n ? ~((1u << (n - tb)) - 1) : 0u);
+            if (cleared) {
+                for (int c = tid; c < S::kVBytes / 16; c += n_waves * kWave)
+                    if ((cleared >> (c / (S::kVRow / 16))) & 1u) *reinterpret_cast<u32x4*>(vl + c * 16) = u32x4{0u, 0u, 0u, 0u};
+                __builtin_amdgcn_s_waitcnt(0xc07f);
+            }
+            bare_barrier();
+        }
+
+        // ---- scores: S^T[token][row] ----------------------------------------------------------
+        f32x16 s;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = 0.f;
+        const int ka = lds0 + stage + k_rd;
+#pragma unroll
+        for (int h = 0; h < S::kKSteps; h += 4) {
+            u32x4 kv[4];
+            auto at = [&](int kk) { return (ka ^ ((kk % kPerXor) << 5)) + kk / kPerXor * (kPerXor * 32); };
+            read_k4(kv, at(h), at(h + 1), at(h + 2), at(h + 3));
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kv[kk]), qreg[h + kk], s, 0, 0, 0);
+        }
+        // ---- softmax: register i holds token (i/4)*8 + lg*4 + i%4 of the tile, for this lane's row -----
+        if (rel > -kTile) {
+            uint32_t vis = rel >= 0 ? static_cast<uint32_t>(word >> rel)
+                                    : (static_cast<uint32_t>(word << (-rel)) | ((1u << (-rel)) - 1u));
+            vis >>= lg * 4;
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if (!((vis >> ((i >> 2) * 8 + (i & 3))) & 1u)) s[i] = kNegInf;
+        }
+        float mx = s[0];
+#pragma unroll
+        for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
+        float alpha;
+        const float m_use = move_reference(mx, a.scale_log2, m_run, alpha);
+        float psum = 0.f;
+        uint32_t hi[8], lo[8];
+#pragma unroll
+        for (int i = 0; i < 16; i += 2) {
+            s[i] = fast_exp2(fmaf(s[i], a.scale_log2, -m_use));
+            s[i + 1] = fast_exp2(fmaf(s[i + 1], a.scale_log2, -m_use));
+            psum += s[i] + s[i + 1];
+            hi[i >> 1] = cvt_pk_bf16(s[i], s[i + 1]);
+            lo[i >> 1] = cvt_pk_bf16(s[i] - bf16lo_to_f32(hi[i >> 1]), s[i + 1] - bf16hi_to_f32(hi[i >> 1]));
+        }
+        l_run = l_run * alpha + psum;
+        if (__any(alpha != 1.f)) {
+#pragma unroll
+            for (int dt = 0; dt < S::kDTiles; ++dt)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[dt][i] *= alpha;
+        }
+        // ---- O^T[d][row] += V^T . (hi + lo) -----------------------------------------------------
+        const int va = lds0 + stage + v_rd;
+        constexpr int kPer = S::kVRow % 256 == 0 ? 4 : 2;                      // d-tiles until the address bits repeat
+        auto pv_pair = [&](auto dtc) __attribute__((always_inline)) {
+            constexpr int dt = decltype(dtc)::value;
+            u32x2 vr[2][4];
+            read_v2<dt / kPer * (kPer * 64), 8 * S::kVRow>(vr, va ^ ((dt % kPer) << 6), va ^ (((dt + 1) % kPer) << 6));
+#pragma unroll
+            for (int half = 0; half < 2; ++half)
+#pragma unroll
+                for (int d2 = 0; d2 < 2; ++d2) {
+                    const bf16x8 v = as_bf16x8(u32x4{vr[d2][2 * half][0], vr[d2][2 * half][1], vr[d2][2 * half + 1][0], vr[d2][2 * half + 1][1]});
+                    const bf16x8 ph = as_bf16x8(u32x4{hi[4 * half], hi[4 * half + 1], hi[4 * half + 2], hi[4 * half + 3]});
+                    const bf16x8 pl = as_bf16x8(u32x4{lo[4 * half], lo[4 * half + 1], lo[4 * half + 2], lo[4 * half + 3]});
+                    acc[dt + d2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, ph, acc[dt + d2], 0, 0, 0);
+                    acc[dt + d2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pl, acc[dt + d2], 0, 0, 0);
+                }
+        };
+        pv_pair(std::integral_constant<int, 0>{});
+        if constexpr (S::kDTiles >= 4) pv_pair(std::integral_constant<int, 2>{});
+        if constexpr (S::kDTiles >= 8) {
+            pv_pair(std::integral_constant<int, 4>{});
+            pv_pair(std::integral_constant<int, 6>{});
+        }
+        // ---- V rows with infinities or NaN: added to the rows that see the slot ------------------
+        for (uint32_t left = nonfinite; left; left &= left - 1) {
+            const int j = __builtin_ctz(left), ij = (j >> 3) * 4 + (j & 3);
+            uint32_t h2 = hi[0], l2 = lo[0];
+#pragma unroll
+            for (int i = 1; i < 8; ++i) h2 = (ij >> 1) == i ? hi[i] : h2, l2 = (ij >> 1) == i ? lo[i] : l2;
+            float pj = (ij & 1) ? bf16hi_to_f32(h2) + bf16hi_to_f32(l2) : bf16lo_to_f32(h2) + bf16lo_to_f32(l2);
+            pj = __shfl(pj, ln + ((j >> 2) & 1) * 32, kWave);                  // the half of the lanes that holds token j
+            const bool sees = rel + j < 0 || ((word >> (rel + j)) & 1ull);
+            const int tok = tb + j, lp = page_of(tok);
+            const int pg = min(max(table[min(lp, a.max_pages - 1)], 0), a.num_pages - 1);
+            const uint16_t* vrow = reinterpret_cast<const uint16_t*>(vbase) +
+                                   ((static_cast<size_t>(pg) * a.Hkv + kvh) * a.P + (tok - lp * a.P)) * DV;
+#pragma unroll
+            for (int dt = 0; dt < S::kDTiles; ++dt)
+#pragma unroll
+                for (int i4 = 0; i4 < 4; ++i4) {
+                    const u32x2 v = *reinterpret_cast<const u32x2*>(vrow + dt * 32 + i4 * 8 + lg * 4);
+                    if (sees) {
+                        acc[dt][i4 * 4] = fmaf(pj, bf16lo_to_f32(v[0]), acc[dt][i4 * 4]);
+                        acc[dt][i4 * 4 + 1] = fmaf(pj, bf16hi_to_f32(v[0]), acc[dt][i4 * 4 + 1]);
+                        acc[dt][i4 * 4 + 2] = fmaf(pj, bf16lo_to_f32(v[1]), acc[dt][i4 * 4 + 2]);
+                        acc[dt][i4 * 4 + 3] = fmaf(pj, bf16hi_to_f32(v[1]), acc[dt][i4 * 4 + 3]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);   // (one load at a time: all of them in flight would spill)
+                }
+        }
+    }
+
+    float sum0 = 0.f;                               // NaN iff some accumulator is infinite or NaN
+#pragma unroll
+    for (int dt = 0; dt < S::kDTiles; ++dt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sum0 = fmaf(acc[dt][i], 0.f, sum0);
+    if (scan_all) break;
+    if (__any(sum0 != 0.f) && lane == 0) *s_again = 1;
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    bare_barrier();                                // (also: every wave is done with the stages)
+    if (!__builtin_amdgcn_readfirstlane(*s_again)) break;
+    }
+
+    // ---- partial result: (reference exponent, sum, unnormalised O) per row ---------------------
+    const float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
+    if (row_ok) {
+        const size_t prow = (static_cast<size_t>(item_idx) * a.T + t) * a.Hq + hq;
+        if (lg == 0) {
+            a.part_ml[2 * prow] = m_run;
+            a.part_ml[2 * prow + 1] = l_tot;
+        }
+        float* __restrict__ po = a.part_acc + prow * DV + lg * 4;
+#pragma unroll
+        for (int dt = 0; dt < S::kDTiles; ++dt)
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4)
+                *reinterpret_cast<f32x4*>(po + dt * 32 + i4 * 8) =
+                    f32x4{acc[dt][i4 * 4], acc[dt][i4 * 4 + 1], acc[dt][i4 * 4 + 2], acc[dt][i4 * 4 + 3]};
+    }
+  }  // pieces of the stretch
+    if (bad_page && lane == 0) atomicOr(&a.header->status, 2u);
+    // speed history for the next call's plan (see the D = 128 kernel)
+    if (L && !a.fixed_split && tid == 0) {
+        const uint64_t ticks = __builtin_amdgcn_s_memrealtime() - clock_begin;
+        atomicAdd(a.fb_time + wg, static_cast<uint32_t>(ticks > 0xffffffu ? 0xffffffu : ticks));
+        atomicAdd(a.fb_tiles + wg, static_cast<uint32_t>(g_end - g_first));
+    }
+}
+
+hipError_t launch_tile(const AttnArgs& a, hipStream_t stream) {
+    const int nw = a.rows_per_block / 32;
+    const dim3 grid(static_cast<unsigned>((a.wgs_per_head + 7) / 8) * 8u * static_cast<unsigned>(a.Hkv) *
+                    static_cast<unsigned>(a.row_blocks));
+#define SEER_TILE_CASE(DQK_, DV_)                                                                                      \
+    if (a.Dqk == DQK_ && a.Dv == DV_) {                                                                                \
+        hipLaunchKernelGGL((attn_tile_kernel<DQK_, DV_>), grid, dim3(nw * kWave), 0, stream, a, nw);           \
+        return hipGetLastError();                                                                                      \
+    }
+    SEER_TILE_CASE(64, 64)
+    SEER_TILE_CASE(256, 256)
+    SEER_TILE_CASE(192, 128)
+#undef SEER_TILE_CASE
+    return hipErrorInvalidValue;
+}
+
+}  // namespace seer

@@ -50,4 +50,32 @@ __device__ __forceinline__ void bare_barrier() { __builtin_amdgcn_s_barrier(); }
 // vector loads; without this the control flow that depends on them would be treated as divergent.
 __device__ __forceinline__ int uniform_load(const int32_t* p) { return __builtin_amdgcn_readfirstlane(*p); }
 
+// max over the two lanes that share a query row (lane and lane ^ 32), without touching LDS:
+// v_permlane32_swap exchanges the upper 32 lanes of its first operand with the lower 32 lanes of
+// its second, so from two copies of x one register ends up with the lower half's values in both
+// halves and the other with the upper half's.  (Issued from an asm block: with the builtin this
+// compiler keeps only the first of the two results.  The s_nop covers the wait states the
+// instruction needs after a vector-ALU write of its operands.)
+__device__ __forceinline__ float max_across_halves(float x) {
+    float a = x, b = x;
+    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    float m;
+    asm("v_max_f32 %0, %1, %2" : "=v"(m) : "v"(a), "v"(b));   // (fmaxf would first quieten both operands: two more instructions)
+    return m;
+}
+
+// Softmax bookkeeping of one tile for this lane's row, from the row's raw score maximum mx_raw
+// (masked slots excluded): moves the exponent reference m_run only when the new maximum exceeds
+// it by more than 8 (probabilities then stay below 2^8), returns the reference to subtract (in
+// units of log2 e, scores scaled) and leaves in alpha the factor that brings sums taken under the
+// old reference to the new one.  scale_log2 > 0.
+__device__ __forceinline__ float move_reference(float mx_raw, float scale_log2, float& m_run, float& alpha) {
+    const float mx = max_across_halves(mx_raw) * scale_log2;
+    const float m_new = (mx > m_run + 8.f) ? mx : m_run;      // m_run = -inf: any finite mx moves it
+    const float m_use = (m_new == kNegInf) ? 0.f : m_new;      // nothing visible yet: keep exp2 finite
+    alpha = fast_exp2(m_run - m_use);
+    m_run = m_new;
+    return m_use;
+}
+
 }  // namespace seer
