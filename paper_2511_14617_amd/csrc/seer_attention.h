@@ -20,9 +20,9 @@ namespace seer {
 // them streams about the same number of KV bytes, whatever the mix of lengths
 // -- eight 100k-token stragglers and several hundred short requests both fill
 // all 256 CUs.  A stretch that crosses a request boundary yields one partial
-// result per request it touches; request b therefore owns
-// n_parts(b) = last_wg(b) - first_wg(b) + 1 consecutive partial slots starting at
-// split_off[b], and the combine kernel merges them.
+// result per request it touches.  The piece of request b in stretch w has partial slot w + b: along
+// the line every next piece raises w, b or both, so slots are unique and below W + B, and nobody
+// has to count pieces.  Request b owns consecutive slots, which the combine kernel merges.
 //
 // Stretch lengths follow the measured speed of each workgroup slot.  Workgroups
 // that stream the same number of bytes do not finish together: on this part the
@@ -38,8 +38,7 @@ namespace seer {
 // other W) gives equal stretches; SEER_ATTN_FIXED_SPLIT always does.
 struct PlanHeader {
     uint32_t status;     // bit 0: bad ctx_len somewhere; bit 1: page id out of range
-    int32_t n_items;     // number of (request, stretch) pieces = partial slots in use
-    int32_t tiles_per_wg;  // L; 0 = one workgroup per request (max_splits == 1)
+    int32_t balanced;      // 1: stretches; 0: one workgroup per request (max_splits == 1), slot = request
     int32_t total_tiles;   // tiles per KV head over all requests
     uint32_t fb_magic;     // kFeedbackMagic once the speed history below the header is meaningful
     int32_t fb_w;          // W it was recorded for
@@ -47,11 +46,15 @@ struct PlanHeader {
 constexpr uint32_t kFeedbackMagic = 0x5ee2fb01u;
 constexpr int kMaxWgsPerHead = 1024;   // 256 CUs x 4 resident workgroups, one KV head
 
-struct WorkItem {
-    int32_t b;       // request
-    int32_t begin;   // first logical KV position of the piece
-    int32_t end;     // one past the last
-    int32_t split;   // index of the piece inside the request
+// A stretch as its workgroups need it, in one 16-byte load: the request in which it starts (-1: nothing to do), its tiles
+// on the line, and what to add to a request's index to get the slot of its piece.
+struct StretchRec {
+    int32_t b, tile_begin, tile_end, slot_bias;
+};
+
+// The partial slots of a request.
+struct ReqSlots {
+    int32_t first, count;
 };
 
 constexpr int kPlanTile = 32;          // tokens per scheduling tile
@@ -63,7 +66,7 @@ struct WorkspaceLayout {
     int max_items;
     int wgs_per_head;    // W (balanced mode) or B (one workgroup per request)
     int max_splits;
-    size_t off_header, off_split, off_tiles, off_first, off_start, off_reqfirst, off_shared, off_fb, off_items, off_ml, off_acc, total;
+    size_t off_header, off_slots, off_tiles, off_stretch, off_shared, off_fb, off_ml, off_acc, total;
 };
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -164,16 +167,13 @@ inline WorkspaceLayout workspace_layout(const seer_attn_params& p) {
     const size_t rows = static_cast<size_t>(w.max_items) * p.T * p.Hq;
     const size_t per_b = sizeof(int32_t) * (static_cast<size_t>(p.B) + 1);
     w.off_header = 0;
-    w.off_split = 256;
-    w.off_tiles = align_up(w.off_split + per_b, 256);
-    w.off_first = align_up(w.off_tiles + per_b, 256);
+    w.off_slots = 256;
+    w.off_tiles = align_up(w.off_slots + sizeof(ReqSlots) * p.B, 256);
     const size_t per_w = sizeof(int32_t) * (static_cast<size_t>(w.wgs_per_head) + 1);
-    w.off_start = align_up(w.off_first + per_w, 256);
-    w.off_reqfirst = align_up(w.off_start + per_w, 256);
-    w.off_shared = align_up(w.off_reqfirst + per_b, 256);
+    w.off_stretch = align_up(w.off_tiles + per_b, 256);
+    w.off_shared = align_up(w.off_stretch + sizeof(StretchRec) * w.wgs_per_head, 256);
     w.off_fb = align_up(w.off_shared + per_b, 256);               // time[W], tiles[W], smoothed speed[W]
-    w.off_items = align_up(w.off_fb + 3 * per_w, 256);
-    w.off_ml = align_up(w.off_items + sizeof(WorkItem) * static_cast<size_t>(w.max_items), 256);
+    w.off_ml = align_up(w.off_fb + 3 * per_w, 256);
     w.off_acc = align_up(w.off_ml + 2 * sizeof(float) * rows, 256);
     w.total = align_up(w.off_acc + sizeof(float) * rows * p.Dv, 256);
     return w;
@@ -189,25 +189,30 @@ struct AttnArgs {
     const int32_t* ctx_len;
     const uint64_t* tree_mask;
     PlanHeader* header;
-    const int32_t* split_off;   // [B+1] first partial slot of each request
-    const int32_t* tile_off;    // [B+1] first tile of each request on the per-head tile line
-    const int32_t* wg_first;    // [wgs_per_head] request in which each workgroup's stretch starts, -1 = idle
-    const int32_t* wg_start;    // [wgs_per_head + 1] first tile of each stretch on the tile line (balanced mode)
-    const int32_t* req_first;   // [B] first stretch that touches each request (balanced mode)
+    const ReqSlots* req_slots;      // [B]
+    const int32_t* tile_off;        // [B+1] first tile of each request on the per-head tile line
+    const StretchRec* stretch;      // [wgs_per_head]
     const int32_t* shared_tiles;  // [B] leading tiles of each request whose pages a neighbouring request maps too
     uint32_t* fb_time;          // [wgs_per_head] sum over KV heads of the workgroup's duration, 10 ns ticks
     uint32_t* fb_tiles;         // [wgs_per_head] sum over KV heads of the tiles it streamed
     float* fb_speed;            // [wgs_per_head] smoothed tiles per tick (owned by the plan kernel)
     int32_t fixed_split;        // 1: equal stretches, no history read or written
+    int32_t balanced;           // 0: one workgroup per request (max_splits == 1), no history either
     int32_t stream_only;        // 1: the tiled D = 128 kernel only streams its tiles (diagnostic)
     int32_t stream_partials;    // 1: the tiled D = 128 kernel writes its partial results with non-temporal stores
     int32_t row_blocks, rows_per_block;   // tiled D = 128 kernel: workgroups per (stretch, KV head), rows of each
-    const WorkItem* items;
     float* part_ml;             // [max_items][T][Hq][2]  (running max in log2 units, sum)
     float* part_acc;            // [max_items][T][Hq][Dv] unnormalised
-    int32_t B, T, Hq, Hkv, G, Dqk, Dv, P, num_pages, max_pages, max_items, wgs_per_head;
+    int32_t B, T, Hq, Hkv, G, Dqk, Dv, P, num_pages, max_pages, wgs_per_head;
     float scale_log2;           // scale * log2(e): scores are kept in base-2 units
 };
+
+// A stretch's record, moved to scalar registers (one load; see uniform_load).
+__device__ __forceinline__ StretchRec uniform_stretch(const StretchRec* r) {
+    const int4 v = *reinterpret_cast<const int4*>(r);
+    return {__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y), __builtin_amdgcn_readfirstlane(v.z),
+            __builtin_amdgcn_readfirstlane(v.w)};
+}
 
 hipError_t launch_plan(const AttnArgs& a, const WorkspaceLayout& w, hipStream_t stream);
 hipError_t launch_general(const AttnArgs& a, hipStream_t stream);   // any supported shape

@@ -19,76 +19,59 @@ namespace seer {
 
 // ---------------------------------------------------------------------------
 // Plan: one workgroup turns ctx_len[B] into the tile line, the stretch of every
-// partition workgroup, and the table of (request, stretch) pieces; a second one,
+// partition workgroup and the partial slots of every request; a second one,
 // beside it, compares neighbouring block-table rows (plan_shared_pages).
+//
+// The kernel is one dependent chain in front of every planned call, so it is
+// written for the length of that chain: all global loads (lengths, header, speed
+// history) are requested at once, one request and one stretch per thread, two
+// exchanges between the waves for all sums and scans, and searches in LDS
+// instead of walks over a request's pieces.  With 256 threads, four exchanges and
+// walks it took 8.6 .. 12.5 us of every call, now 4.8 .. 5.8 (4 to 64 requests).
 // ---------------------------------------------------------------------------
-constexpr int kPlanThreads = 256;
+constexpr int kPlanThreads = 1024;
+constexpr int kPlanWaves = kPlanThreads / kWave;
+constexpr int kPlanLdsRequests = 4096;   // tile offsets of this many requests are searched in LDS, of more in global memory
 
 struct PlanArgs {
     const int32_t* ctx_len;
     const int32_t* block_table;
-    int B, T, max_ctx, wgs_per_head, max_splits, max_items, fixed_split, max_pages, page_size;
+    int B, T, max_ctx, wgs_per_head, max_splits, fixed_split, max_pages, page_size;
     PlanHeader* header;
-    int32_t* split_off;
+    ReqSlots* req_slots;
     int32_t* tile_off;
-    int32_t* wg_first;
-    int32_t* wg_start;
-    int32_t* req_first;
+    StretchRec* stretch;
     int32_t* shared_tiles;
     uint32_t* fb_time;
     uint32_t* fb_tiles;
     float* fb_speed;
-    WorkItem* items;
 };
 
-// Block-wide primitives for the 256 threads of the plan kernel (4 waves): wave shuffles, then one
-// value per wave through LDS.  s_tmp: at least 2 * (kPlanThreads / kWave) words, reused call after call.
-template <typename T>
-__device__ __forceinline__ T plan_excl_scan(T v, T* s_tmp, T& total) {
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-    T incl = v;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const T up = __shfl_up(incl, o, kWave);
-        if (lane >= o) incl += up;
-    }
-    __syncthreads();                     // s_tmp may still be read by the previous call
-    if (lane == kWave - 1) s_tmp[wave] = incl;
-    __syncthreads();
-    T base = 0, sum = 0;
-#pragma unroll
-    for (int w = 0; w < kPlanThreads / kWave; ++w) {
-        const T x = s_tmp[w];
-        if (w < wave) base += x;
-        sum += x;
-    }
-    total = sum;
-    return base + incl - v;
+// Inclusive sum over the lanes of a wave through DPP: shifts by 1, 2, 4, 8 inside rows of 16 lanes, then the last lane of a
+// row to the row behind it and of the lower half to the upper (lanes without a source add zero).
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ int dpp_take(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, ROW_MASK, 0xf, true); }
+__device__ __forceinline__ int wave_incl_scan(int v) {
+    v += dpp_take<0x111, 0xf>(v);
+    v += dpp_take<0x112, 0xf>(v);
+    v += dpp_take<0x114, 0xf>(v);
+    v += dpp_take<0x118, 0xf>(v);
+    v += dpp_take<0x142, 0xa>(v);
+    v += dpp_take<0x143, 0xc>(v);
+    return v;
 }
-__device__ __forceinline__ float plan_sum(float v, float* s_tmp) {
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, kWave);
-    __syncthreads();
-    if (lane == 0) s_tmp[wave] = v;
-    __syncthreads();
-    float sum = 0.f;
-#pragma unroll
-    for (int w = 0; w < kPlanThreads / kWave; ++w) sum += s_tmp[w];
-    return sum;
+__device__ __forceinline__ float wave_incl_scan(float v) {
+    auto step = [&](int x) { v += __int_as_float(x); };
+    step(dpp_take<0x111, 0xf>(__float_as_int(v)));
+    step(dpp_take<0x112, 0xf>(__float_as_int(v)));
+    step(dpp_take<0x114, 0xf>(__float_as_int(v)));
+    step(dpp_take<0x118, 0xf>(__float_as_int(v)));
+    step(dpp_take<0x142, 0xa>(__float_as_int(v)));
+    step(dpp_take<0x143, 0xc>(__float_as_int(v)));
+    return v;
 }
-__device__ __forceinline__ int plan_max(int v, int* s_tmp) {
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = max(v, __shfl_xor(v, o, kWave));
-    __syncthreads();
-    if (lane == 0) s_tmp[wave] = v;
-    __syncthreads();
-    int m = s_tmp[0];
-#pragma unroll
-    for (int w = 1; w < kPlanThreads / kWave; ++w) m = max(m, s_tmp[w]);
-    return m;
-}
+__device__ __forceinline__ int last_lane(int v) { return __builtin_amdgcn_readlane(v, kWave - 1); }
+__device__ __forceinline__ float last_lane(float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), kWave - 1)); }
 
 // The plan's second workgroup.  Leading pages that a request has in common with the request before or after it
 // (the prompt that the rollouts of a group share sits in the same physical pages): the partition kernel loads such
@@ -154,114 +137,142 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs p) {
         plan_shared_pages(p);
         return;
     }
-    __shared__ int s_tmp[2 * kPlanThreads / kWave];
+    __shared__ int s_tiles[kPlanWaves], s_longest[kPlanWaves];       // per wave
+    __shared__ float s_speed[kPlanWaves], s_known[kPlanWaves], s_rate[kPlanWaves];
     __shared__ int s_start[kMaxWgsPerHead + 1];
-    const int tid = threadIdx.x;
+    __shared__ int s_off[kPlanLdsRequests + 1];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int W = p.wgs_per_head;
-    for (int w = tid; w < W; w += kPlanThreads) p.wg_first[w] = -1;
+    const bool balanced = p.max_splits > 1, history = balanced && !p.fixed_split;
+    const bool in_lds = p.B <= kPlanLdsRequests;
 
-    // thread `tid` owns a contiguous run of requests
+    // ---- everything this thread reads from global memory: its run of requests (one each up to 1024), its stretch -----
     const int per = (p.B + kPlanThreads - 1) / kPlanThreads;
     const int b0 = min(p.B, tid * per), b1 = min(p.B, b0 + per);
-    auto tiles_of = [&](int b) -> int {
-        const int n = p.ctx_len[b];
-        if (n < p.T || n > p.max_ctx) return 0;   // flagged, gets a zero output
-        return (n + kPlanTile - 1) / kPlanTile;
-    };
+    const int n_first = b0 < b1 ? p.ctx_len[b0] : 0;
+    uint32_t magic = 0u, ticks = 0u, streamed = 0u;
+    int fb_w = 0;
+    float est = 0.f;
+    if (history) {
+        magic = p.header->fb_magic, fb_w = p.header->fb_w;
+        if (tid < W) est = p.fb_speed[tid], ticks = p.fb_time[tid], streamed = p.fb_tiles[tid];
+    }
+    auto tiles_of = [&](int n) -> int { return n < p.T || n > p.max_ctx ? 0 : (n + kPlanTile - 1) / kPlanTile; };
+    auto length = [&](int b) -> int { return b == b0 ? n_first : p.ctx_len[b]; };
 
-    // 1. tile line: exclusive prefix of tiles per request, and the longest request
-    int cnt = 0, mx = 0, bad = 0;
+    // ---- sums inside the wave: tiles of its requests, speeds of its stretches -------------------------------------------
+    int cnt = 0, mx = 0;
+    bool bad = false;
     for (int b = b0; b < b1; ++b) {
-        const int n = p.ctx_len[b];
-        if (n < p.T || n > p.max_ctx) bad = 1;
-        const int t = tiles_of(b);
+        const int n = length(b), t = tiles_of(n);
+        bad |= n < p.T || n > p.max_ctx;                 // flagged, gets a zero output
         cnt += t;
         mx = max(mx, t);
     }
-    int total = 0;
-    const int my_tile_off = plan_excl_scan(cnt, s_tmp, total);
-    const int longest = plan_max(mx, s_tmp);
-    bad = plan_max(bad, s_tmp);
+    // relative speed of each stretch index from the history in the workspace (unknown: 0, also whatever a stale one held)
+    if (!(magic == kFeedbackMagic && fb_w == W)) est = 0.f, ticks = 0u;
+    if (ticks > 0u && streamed > 0u) {
+        const float meas = static_cast<float>(streamed) / static_cast<float>(ticks);
+        est = est > 0.f ? 0.5f * est + 0.5f * meas : meas;
+    }
+    if (!(est > 0.f) || !(est < 1e30f)) est = 0.f;
+    const int incl = wave_incl_scan(cnt);
+    const int wave_bad = __any(bad) ? 1 : 0;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) mx = max(mx, __shfl_xor(mx, o, kWave));
+    const float sum = last_lane(wave_incl_scan(est)), known = last_lane(wave_incl_scan(est > 0.f ? 1.f : 0.f));
+    if (lane == kWave - 1) {
+        s_tiles[wave] = incl;
+        s_longest[wave] = mx * 2 + wave_bad;
+        s_speed[wave] = sum;
+        s_known[wave] = known;
+    }
+    __syncthreads();
+    int total = 0, my_off = incl - cnt, longest = 0;
+    float speed_sum = 0.f, speed_known = 0.f;
+    int any_bad = 0;
+#pragma unroll
+    for (int w = 0; w < kPlanWaves; ++w) {
+        const int t = s_tiles[w], l = s_longest[w];
+        if (w < wave) my_off += t;
+        total += t;
+        longest = max(longest, l >> 1);
+        any_bad |= l & 1;
+        speed_sum += s_speed[w];
+        speed_known += s_known[w];
+    }
     {
-        int off = my_tile_off;
+        int off = my_off;
         for (int b = b0; b < b1; ++b) {
             p.tile_off[b] = off;
-            off += tiles_of(b);
+            if (in_lds) s_off[b] = off;
+            off += tiles_of(length(b));
         }
-        if (tid == 0) p.tile_off[p.B] = total;
+        if (tid == 0) {
+            p.tile_off[p.B] = total;
+            if (in_lds) s_off[p.B] = total;
+        }
     }
 
-    // 2. the stretches (balanced mode; L = 0 means one workgroup per request)
-    int L = 0;
-    if (p.max_splits > 1) {
-        L = max((total + W - 1) / W, 1);
+    if (balanced) {
+        // ---- the stretches ----------------------------------------------------------------------------------------------
         // a request of t tiles touches at most ceil(t / Lmin) + 1 stretches, which must fit max_splits
         const int Lmin = max(kMinTilesPerWg, (longest + p.max_splits - 2) / (p.max_splits - 1));
-        // relative speed of each stretch index from the history in the workspace; thread t owns the
-        // stretch indices [t * per_w, t * per_w + per_w)
-        constexpr int kPerW = kMaxWgsPerHead / kPlanThreads;
-        const int per_w = (W + kPlanThreads - 1) / kPlanThreads;
-        const int w0 = min(W, tid * per_w);
-        const bool have = !p.fixed_split && p.header->fb_magic == kFeedbackMagic && p.header->fb_w == W;
-        float speed[kPerW];
-        float sum = 0.f, known = 0.f;
-#pragma unroll
-        for (int i = 0; i < kPerW; ++i) {
-            const int w = w0 + i;
-            speed[i] = 0.f;
-            if (i < per_w && w < W) {
-                float est = have ? p.fb_speed[w] : 0.f;
-                const uint32_t ticks = have ? p.fb_time[w] : 0u, tiles = have ? p.fb_tiles[w] : 0u;
-                if (ticks > 0u && tiles > 0u) {
-                    const float meas = static_cast<float>(tiles) / static_cast<float>(ticks);
-                    est = est > 0.f ? 0.5f * est + 0.5f * meas : meas;
-                }
-                if (!(est > 0.f) || !(est < 1e30f)) est = 0.f;     // unknown (also whatever a stale workspace held)
-                if (!p.fixed_split) {
-                    p.fb_speed[w] = est;
-                    p.fb_time[w] = 0u;
-                    p.fb_tiles[w] = 0u;
-                }
-                speed[i] = est;
-                if (est > 0.f) {
-                    sum += est;
-                    known += 1.f;
-                }
-            }
-        }
-        sum = plan_sum(sum, reinterpret_cast<float*>(s_tmp));
-        known = plan_sum(known, reinterpret_cast<float*>(s_tmp));
-        const float mean = known > 0.f ? sum / known : 1.f;
         // Stretch w begins at the tile nearest to total * (r_0 + .. + r_{w-1}) / R.  When the line is too
         // short for that to keep every stretch at Lmin tiles or more, cut it into equal stretches of
         // max(Lmin, ceil(total / W)) tiles instead (the last ones are then short or empty).
         const bool weighted = static_cast<long long>(total) >= 2ll * Lmin * W;
-        float rsum = 0.f;
+        const float mean = speed_known > 0.f ? speed_sum / speed_known : 1.f;
+        float rate = 0.f;
+        if (tid < W) rate = fminf(fmaxf((weighted && est > 0.f) ? est / mean : 1.f, 0.75f), 4.f / 3.f);
+        const float rate_incl = wave_incl_scan(rate);
+        if (lane == kWave - 1) s_rate[wave] = rate_incl;
+        __syncthreads();
+        float before = rate_incl - rate, R = 0.f;
 #pragma unroll
-        for (int i = 0; i < kPerW; ++i) {
-            if (i < per_w && w0 + i < W) {
-                const float r = (weighted && speed[i] > 0.f) ? speed[i] / mean : 1.f;
-                speed[i] = fminf(fmaxf(r, 0.75f), 4.f / 3.f);
-                rsum += speed[i];
-            }
+        for (int w = 0; w < kPlanWaves; ++w) {
+            const float x = s_rate[w];
+            if (w < wave) before += x;
+            R += x;
         }
-        float R = 0.f;
-        float before = plan_excl_scan(rsum, reinterpret_cast<float*>(s_tmp), R);
-        const int L_equal = max(Lmin, L);
-#pragma unroll
-        for (int i = 0; i < kPerW; ++i) {
-            if (i < per_w && w0 + i < W) {
-                const int w = w0 + i;
-                const long long cut = weighted ? static_cast<long long>(static_cast<double>(total) * before / R + 0.5)
-                                               : static_cast<long long>(w) * L_equal;
-                s_start[w] = static_cast<int>(cut < total ? cut : total);
-                before += speed[i];
+        if (tid < W) {
+            const int L_equal = max(Lmin, max((total + W - 1) / W, 1));
+            const long long cut = weighted ? static_cast<long long>(static_cast<double>(total) * before / R + 0.5)
+                                           : static_cast<long long>(tid) * L_equal;
+            s_start[tid] = static_cast<int>(cut < total ? cut : total);
+            if (history) {
+                p.fb_speed[tid] = est;
+                p.fb_time[tid] = 0u;
+                p.fb_tiles[tid] = 0u;
             }
         }
         if (tid == 0) s_start[W] = total;
-        __syncthreads();
-        for (int w = tid; w <= W; w += kPlanThreads) p.wg_start[w] = s_start[w];
     }
+    __syncthreads();
+
+    // ---- per stretch: where it starts ------------------------------------------------------------------------------------
+    for (int w = tid; w < W; w += kPlanThreads) {
+        StretchRec r;
+        if (balanced) {
+            r.tile_begin = s_start[w], r.tile_end = s_start[w + 1], r.slot_bias = w;
+            r.b = -1;
+            if (r.tile_begin < r.tile_end) {             // the last request that starts at or before the first tile
+                int lo = 0, hi = p.B - 1;
+                while (lo < hi) {
+                    const int mid = (lo + hi + 1) >> 1;
+                    const int off = in_lds ? s_off[mid] : p.tile_off[mid];
+                    if (off <= r.tile_begin) lo = mid; else hi = mid - 1;
+                }
+                r.b = lo;
+            }
+        } else {
+            r.tile_begin = in_lds ? s_off[w] : p.tile_off[w], r.tile_end = in_lds ? s_off[w + 1] : p.tile_off[w + 1];
+            r.slot_bias = 0;
+            r.b = r.tile_begin < r.tile_end ? w : -1;
+        }
+        p.stretch[w] = r;
+    }
+    // ---- per request: its partial slots ----------------------------------------------------------------------------------
     // stretch that holds tile x (x < total): the last one that starts at or before it
     auto stretch_of = [&](int x) -> int {
         int lo = 0, hi = W - 1;
@@ -271,57 +282,26 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs p) {
         }
         return lo;
     };
-
-    // 3. pieces per request -> first partial slot of each request
-    cnt = 0;
-    {
-        int lo = my_tile_off;
-        for (int b = b0; b < b1; ++b) {
-            const int hi = lo + tiles_of(b);
-            if (hi > lo) cnt += L ? stretch_of(hi - 1) - stretch_of(lo) + 1 : 1;
-            lo = hi;
+    int lo = my_off;
+    for (int b = b0; b < b1; ++b) {
+        const int hi = lo + tiles_of(length(b));
+        ReqSlots s{0, 0};
+        if (hi > lo) {
+            const int first = balanced ? stretch_of(lo) : 0;
+            s.first = first + b;
+            s.count = balanced ? stretch_of(hi - 1) - first + 1 : 1;
         }
+        p.req_slots[b] = s;
+        lo = hi;
     }
-    int n_pieces = 0;
-    int slot = plan_excl_scan(cnt, s_tmp, n_pieces);
     if (tid == 0) {
-        p.header->status = bad ? 1u : 0u;
-        p.header->n_items = min(n_pieces, p.max_items);
-        p.header->tiles_per_wg = L;
+        p.header->status = any_bad ? 1u : 0u;
+        p.header->balanced = balanced ? 1 : 0;
         p.header->total_tiles = total;
-        if (!p.fixed_split) {
+        if (history) {
             p.header->fb_magic = kFeedbackMagic;
             p.header->fb_w = W;
         }
-        p.split_off[p.B] = n_pieces;
-    }
-
-    // 4. piece table and the request each stretch starts in
-    int lo = my_tile_off;
-    for (int b = b0; b < b1; ++b) {
-        const int hi = lo + tiles_of(b);
-        p.split_off[b] = slot;
-        const int n = p.ctx_len[b];
-        const int w_first = hi > lo ? (L ? stretch_of(lo) : b) : 0;
-        const int np = hi > lo ? (L ? stretch_of(hi - 1) - w_first + 1 : 1) : 0;
-        p.req_first[b] = w_first;
-        for (int s = 0; s < np; ++s) {
-            const int w = w_first + s;
-            const int w_begin = L ? s_start[w] : lo, w_end = L ? s_start[w + 1] : hi;
-            const int t_begin = max(lo, w_begin);
-            const int t_end = min(hi, w_end);
-            if (slot + s < p.max_items) {
-                WorkItem it;
-                it.b = b;
-                it.begin = (t_begin - lo) * kPlanTile;
-                it.end = min(n, (t_end - lo) * kPlanTile);
-                it.split = s;
-                p.items[slot + s] = it;
-            }
-            if (t_begin == w_begin && w < W) p.wg_first[w] = b;   // stretch w starts here
-        }
-        slot += np;
-        lo = hi;
     }
 }
 
@@ -338,24 +318,20 @@ hipError_t launch_plan(const AttnArgs& a, const WorkspaceLayout& w, hipStream_t 
     p.max_ctx = max_ctx_ll > 0x7fffffffLL - kPlanTile ? 0x7fffffff - kPlanTile : static_cast<int>(max_ctx_ll);
     p.wgs_per_head = w.wgs_per_head;
     p.max_splits = w.max_splits;
-    p.max_items = w.max_items;
     p.header = a.header;
-    p.split_off = const_cast<int32_t*>(a.split_off);
+    p.req_slots = const_cast<ReqSlots*>(a.req_slots);
     p.tile_off = const_cast<int32_t*>(a.tile_off);
-    p.wg_first = const_cast<int32_t*>(a.wg_first);
-    p.wg_start = const_cast<int32_t*>(a.wg_start);
-    p.req_first = const_cast<int32_t*>(a.req_first);
+    p.stretch = const_cast<StretchRec*>(a.stretch);
     p.fb_time = a.fb_time;
     p.fb_tiles = a.fb_tiles;
     p.fb_speed = a.fb_speed;
     p.fixed_split = a.fixed_split;
-    p.items = const_cast<WorkItem*>(a.items);
     hipLaunchKernelGGL(plan_kernel, dim3(2), dim3(kPlanThreads), 0, stream, p);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
-// General partition kernel: one workgroup per (item, query head, slot).
+// General partition kernel: one workgroup per (stretch, query head, slot).
 // Plain vector arithmetic, one KV token per wave iteration: lanes split the
 // head dimension, the dot product is reduced with shuffles, the running
 // (max, sum, acc) is kept per wave and the four waves are merged through LDS.
@@ -369,13 +345,19 @@ template <int DQK, int DV>
 __global__ __launch_bounds__(kGenThreads) void attn_general_kernel(AttnArgs a) {
     constexpr int NQ = (DQK + 127) / 128;  // bf16 pairs per lane
     constexpr int NV = (DV + 127) / 128;
-    const int item_idx = blockIdx.x;
-    if (item_idx >= a.header->n_items) return;
-    const WorkItem item = a.items[item_idx];
+    const StretchRec rec = a.stretch[blockIdx.x];
     const int hq = blockIdx.y, t = blockIdx.z;
     const int kvh = hq / a.G;
-    const int b = item.b;
+    __shared__ float s_m[kGenWaves], s_l[kGenWaves];
+    __shared__ float s_acc[kGenWaves][DV];
+  int g = rec.tile_begin;
+  for (int b = rec.b; b >= 0 && b < a.B && g < rec.tile_end; ++b) {
+    const int t_lo = a.tile_off[b], t_hi = a.tile_off[b + 1];
+    if (t_hi == t_lo) continue;
     const int n = a.ctx_len[b];
+    const int piece_begin = (g - t_lo) * kPlanTile, piece_end = min(n, (min(rec.tile_end, t_hi) - t_lo) * kPlanTile);
+    g = t_hi;
+    const int item_idx = b + rec.slot_bias;
     const int n0 = n - a.T;
     const uint64_t word = a.tree_mask ? a.tree_mask[static_cast<size_t>(b) * a.T + t]
                                       : (t >= 63 ? ~0ull : ((1ull << (t + 1)) - 1));
@@ -401,10 +383,10 @@ __global__ __launch_bounds__(kGenThreads) void attn_general_kernel(AttnArgs a) {
 
     const int32_t* __restrict__ table = a.block_table + static_cast<size_t>(b) * a.max_pages;
     bool bad_page = false;
-    for (int j = item.begin + wave; j < item.end; j += kGenWaves) {
+    for (int j = piece_begin + wave; j < piece_end; j += kGenWaves) {
         const bool visible = (j < n0) || ((word >> (j - n0)) & 1ull);
         if (!visible) continue;  // uniform across the wave
-        int page = table[j / a.P];
+        int page = table[min(j / a.P, a.max_pages - 1)];
         if (page < 0 || page >= a.num_pages) {
             bad_page = true;
             page = min(max(page, 0), a.num_pages - 1);
@@ -438,8 +420,7 @@ __global__ __launch_bounds__(kGenThreads) void attn_general_kernel(AttnArgs a) {
     }
     if (bad_page && lane == 0) atomicOr(&a.header->status, 2u);
 
-    __shared__ float s_m[kGenWaves], s_l[kGenWaves];
-    __shared__ float s_acc[kGenWaves][DV];
+    __syncthreads();                        // the previous piece's sums have been read
     if (lane == 0) {
         s_m[wave] = m;
         s_l[wave] = l;
@@ -474,6 +455,7 @@ __global__ __launch_bounds__(kGenThreads) void attn_general_kernel(AttnArgs a) {
         for (int w = 0; w < kGenWaves; ++w) v += s_acc[w][d] * f[w];
         a.part_acc[prow * DV + d] = v;
     }
+  }  // pieces of the stretch
 }
 
 bool general_supports(int Dqk, int Dv) {
@@ -482,7 +464,7 @@ bool general_supports(int Dqk, int Dv) {
 }
 
 hipError_t launch_general(const AttnArgs& a, hipStream_t stream) {
-    const dim3 grid(a.max_items, a.Hq, a.T), block(kGenThreads);
+    const dim3 grid(a.wgs_per_head, a.Hq, a.T), block(kGenThreads);
 #define SEER_GEN_CASE(DQK_, DV_)                                                                   \
     if (a.Dqk == DQK_ && a.Dv == DV_) {                                                            \
         hipLaunchKernelGGL((attn_general_kernel<DQK_, DV_>), grid, block, 0, stream, a);           \
@@ -514,9 +496,8 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(AttnArgs a, lo
     const int per_b = a.T * a.Hq;
     const int b = static_cast<int>(row / per_b);
     const int r = static_cast<int>(row - static_cast<long long>(b) * per_b);
-    const int first = a.split_off[b];
-    int ns = a.split_off[b + 1] - first;
-    if (first + ns > a.max_items) ns = max(0, a.max_items - first);
+    const ReqSlots slots = a.req_slots[b];
+    const int first = slots.first, ns = slots.count;
 
     // Both passes request the partial results of several pieces before using any of them (no branch
     // between the loads): a thread otherwise waits one round trip per piece.
@@ -699,11 +680,10 @@ int run_verify_attention(void* out, const void* q, const void* k_pages, const vo
     a.ctx_len = ctx_len;
     a.tree_mask = tree_mask;
     a.header = reinterpret_cast<seer::PlanHeader*>(ws + w.off_header);
-    a.split_off = reinterpret_cast<const int32_t*>(ws + w.off_split);
+    a.req_slots = reinterpret_cast<const seer::ReqSlots*>(ws + w.off_slots);
     a.tile_off = reinterpret_cast<const int32_t*>(ws + w.off_tiles);
-    a.wg_first = reinterpret_cast<const int32_t*>(ws + w.off_first);
-    a.wg_start = reinterpret_cast<const int32_t*>(ws + w.off_start);
-    a.req_first = reinterpret_cast<const int32_t*>(ws + w.off_reqfirst);
+    a.stretch = reinterpret_cast<const seer::StretchRec*>(ws + w.off_stretch);
+    a.balanced = w.max_splits > 1 ? 1 : 0;
     a.shared_tiles = reinterpret_cast<const int32_t*>(ws + w.off_shared);
     a.fb_time = reinterpret_cast<uint32_t*>(ws + w.off_fb);
     a.fb_tiles = a.fb_time + (w.wgs_per_head + 1);
@@ -715,7 +695,6 @@ int run_verify_attention(void* out, const void* q, const void* k_pages, const vo
     const int rows = (p->Hq / p->Hkv) * p->T;
     a.row_blocks = tile_kernel ? seer::tile_row_blocks(rows, p->Dqk) : seer::gqa_row_blocks(rows);
     a.rows_per_block = tile_kernel ? seer::tile_rows_per_block(rows, p->Dqk) : seer::gqa_rows_per_block(rows);
-    a.items = reinterpret_cast<const seer::WorkItem*>(ws + w.off_items);
     a.part_ml = reinterpret_cast<float*>(ws + w.off_ml);
     a.part_acc = reinterpret_cast<float*>(ws + w.off_acc);
     a.B = p->B;
@@ -728,7 +707,6 @@ int run_verify_attention(void* out, const void* q, const void* k_pages, const vo
     a.P = p->page_size;
     a.num_pages = p->num_pages;
     a.max_pages = p->max_pages_per_seq;
-    a.max_items = w.max_items;
     a.wgs_per_head = w.wgs_per_head;
     a.scale_log2 = p->scale * seer::kLog2e;
 

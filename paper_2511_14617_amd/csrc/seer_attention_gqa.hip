@@ -416,11 +416,11 @@ void attn_gqa128_kernel(AttnArgs a) {
     const int l16 = lane >> 4;
     const int p16 = lane & 15;
 
-    const int L = uniform_load(&a.header->tiles_per_wg);
-    int b = uniform_load(a.wg_first + wg);
+    const StretchRec rec = uniform_stretch(a.stretch + wg);
+    int b = rec.b;
     if (b < 0) return;
-    int g = uniform_load(L ? a.wg_start + wg : a.tile_off + b);
-    const int g_end = uniform_load(L ? a.wg_start + wg + 1 : a.tile_off + b + 1);
+    int g = rec.tile_begin;
+    const int g_end = rec.tile_end;
     const int g_first = g;
     const uint64_t clock_begin = __builtin_amdgcn_s_memrealtime();
     bool bad_page = false;
@@ -445,20 +445,18 @@ void attn_gqa128_kernel(AttnArgs a) {
         v_rd[dt] = kVRing + (lg * 4 + v_k) * kRowBytes + ((chunk ^ v_swz(v_k)) << 4) + (v_c4 & 1) * 8;
     }
 
-    // What a piece needs to know about its request comes from five small tables.  Read one after the other
-    // (each value steers the next address or a branch) that is five dependent round trips to the L2 per
+    // What a piece needs to know about its request comes from three small tables.  Read one after the other
+    // (each value steers the next address or a branch) that is several dependent round trips to the L2 per
     // request boundary, several microseconds in which the workgroup has no tile in flight.  Instead one
-    // vector load fetches all five (lane i reads word i), and it is issued a whole piece ahead, together
+    // vector load fetches all four words (lane i reads word i), and it is issued a whole piece ahead, together
     // with the first 64 page ids of that next request: by the time a piece ends, the next one's plan words
     // and page ids are in registers.
     auto piece_words = [&](int bb) __attribute__((always_inline)) -> int {
         const int bc = min(bb, a.B - 1);
         const int32_t* ptr = a.tile_off + bc;
         if (lane == 1) ptr = a.tile_off + bc + 1;
-        if (lane == 2) ptr = a.split_off + bc;
-        if (lane == 3) ptr = (L ? a.req_first : a.split_off) + bc;
-        if (lane == 4) ptr = a.ctx_len + bc;
-        if (lane == 5) ptr = a.shared_tiles + bc;
+        if (lane == 2) ptr = a.ctx_len + bc;
+        if (lane == 3) ptr = a.shared_tiles + bc;
         return *ptr;
     };
     auto first_pages = [&](int bb) __attribute__((always_inline)) -> int {
@@ -470,9 +468,9 @@ void attn_gqa128_kernel(AttnArgs a) {
 
   for (; g < g_end; ++b) {
     const int t_lo = __builtin_amdgcn_readlane(pw, 0), t_hi = __builtin_amdgcn_readlane(pw, 1);
-    const int item_idx = __builtin_amdgcn_readlane(pw, 2) + (L ? wg - __builtin_amdgcn_readlane(pw, 3) : 0);
-    const int n = __builtin_amdgcn_readlane(pw, 4);
-    const int shared_tiles = __builtin_amdgcn_readlane(pw, 5);
+    const int item_idx = b + rec.slot_bias;
+    const int n = __builtin_amdgcn_readlane(pw, 2);
+    const int shared_tiles = __builtin_amdgcn_readlane(pw, 3);
     const int pg_first = pg_ahead;
     const bool have_first = have_ahead;
     pw = piece_words(b + 1);          // in flight while this piece is worked on
@@ -938,7 +936,7 @@ void attn_gqa128_kernel(AttnArgs a) {
   }  // pieces of the stretch
     if (bad_page && lane == 0) atomicOr(&a.header->status, 2u);
     // speed history for the next call's plan: tiles streamed and time taken, by stretch index
-    if (L && !a.fixed_split && tid == 0) {
+    if (a.balanced && !a.fixed_split && tid == 0) {
         const uint64_t ticks = __builtin_amdgcn_s_memrealtime() - clock_begin;
         atomicAdd(a.fb_time + wg, static_cast<uint32_t>(ticks > 0xffffffu ? 0xffffffu : ticks));
         atomicAdd(a.fb_tiles + wg, static_cast<uint32_t>(g_end - g_first));

@@ -304,11 +304,11 @@ void attn_mla_kernel(AttnArgs a, int row_blocks) {
     const int wg = (slot / row_blocks) * 8 + xcd;
     const int rb = slot % row_blocks;
     if (wg >= a.wgs_per_head) return;
-    const int L = uniform_load(&a.header->tiles_per_wg);
-    int b = uniform_load(a.wg_first + wg);
+    const StretchRec rec = uniform_stretch(a.stretch + wg);
+    int b = rec.b;
     if (b < 0) return;
-    int g = uniform_load(L ? a.wg_start + wg : a.tile_off + b);
-    const int g_end = uniform_load(L ? a.wg_start + wg + 1 : a.tile_off + b + 1);
+    int g = rec.tile_begin;
+    const int g_end = rec.tile_end;
     bool bad_page = false;
 
     const unsigned char* __restrict__ kbase = static_cast<const unsigned char*>(a.k_pages);
@@ -342,7 +342,7 @@ void attn_mla_kernel(AttnArgs a, int row_blocks) {
   for (; g < g_end; ++b) {
     const int t_lo = uniform_load(a.tile_off + b), t_hi = uniform_load(a.tile_off + b + 1);
     if (t_hi == t_lo) continue;
-    const int item_idx = uniform_load(a.split_off + b) + (L ? wg - uniform_load(a.req_first + b) : 0);
+    const int item_idx = b + rec.slot_bias;
     const int n = uniform_load(a.ctx_len + b);
     const int tok_begin = (g - t_lo) * kTile;
     const int tok_end = min(n, (min(g_end, t_hi) - t_lo) * kTile);

@@ -108,11 +108,11 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int ln = lane & 31, lg = lane >> 5, l16 = lane >> 4, p16 = lane & 15;
 
-    const int L = uniform_load(&a.header->tiles_per_wg);
-    int b = uniform_load(a.wg_first + wg);
+    const StretchRec rec = uniform_stretch(a.stretch + wg);
+    int b = rec.b;
     if (b < 0) return;
-    int g = uniform_load(L ? a.wg_start + wg : a.tile_off + b);
-    const int g_end = uniform_load(L ? a.wg_start + wg + 1 : a.tile_off + b + 1);
+    int g = rec.tile_begin;
+    const int g_end = rec.tile_end;
     const int g_first = g;
     const uint64_t clock_begin = __builtin_amdgcn_s_memrealtime();
     bool bad_page = false;
@@ -136,7 +136,7 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
   for (; g < g_end; ++b) {
     const int t_lo = uniform_load(a.tile_off + b), t_hi = uniform_load(a.tile_off + b + 1);
     if (t_hi == t_lo) continue;
-    const int item_idx = uniform_load(a.split_off + b) + (L ? wg - uniform_load(a.req_first + b) : 0);
+    const int item_idx = b + rec.slot_bias;
     const int n = uniform_load(a.ctx_len + b);
     const int tok_begin = (g - t_lo) * kTile;
     const int tok_end = min(n, (min(g_end, t_hi) - t_lo) * kTile);
@@ -379,7 +379,7 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
   }  // pieces of the stretch
     if (bad_page && lane == 0) atomicOr(&a.header->status, 2u);
     // speed history for the next call's plan (see the D = 128 kernel)
-    if (L && !a.fixed_split && tid == 0) {
+    if (a.balanced && !a.fixed_split && tid == 0) {
         const uint64_t ticks = __builtin_amdgcn_s_memrealtime() - clock_begin;
         atomicAdd(a.fb_time + wg, static_cast<uint32_t>(ticks > 0xffffffu ? 0xffffffu : ticks));
         atomicAdd(a.fb_tiles + wg, static_cast<uint32_t>(g_end - g_first));
