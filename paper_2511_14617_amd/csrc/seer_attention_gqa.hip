@@ -360,6 +360,497 @@ __device__ __forceinline__ void fused_step(int k_off, int v_off, const int (&k_r
     }
 }
 
+// ---------------------------------------------------------------------------------------------------
+// The helper shape: row blocks of 129 .. 144 rows (the multi-path tree on a group of four heads: 4 x 33 = 132).
+//
+// Four main waves hold the block's first 128 rows, 32 each, and a fifth wave for the rest would run the whole
+// per-tile instruction stream for a handful of rows on a SIMD that a main wave needs.  So four helper waves double the
+// main ones instead: a step works on a PAIR of tiles, the main waves on the even one, the helpers, with the same rows and
+// a softmax state of their own, on the odd one.  Every SIMD has two independent instruction streams over a step, which is
+// what hides operand reads, exponentials and the issue of tile loads; each wave runs the phases of its tile one after the
+// other.  The leftover rows (at most 16) are one 16x16 product per 16 tokens: four of the eight waves, one per SIMD, take one
+// half tile of the pair each (waves 0 and 1 the halves of the even tile, 6 and 7 those of the odd one) at the end of
+// their step and at a raised issue priority; the other wave of the SIMD requests the tile loads, between its scores and its
+// softmax: a direct-to-LDS load holds its wave for some 50 clocks, and with all eight waves requesting behind the barrier
+// nothing else ran meanwhile (5 % of the kernel).
+// At the end of a piece the two states of every row, and the four of a leftover row, become one through LDS, in a fixed order.
+// Three pair slots of 32 KB: two pairs in flight while one is computed (three in flight: no change).
+// What bounds it: the arithmetic alone takes 0.91 ms of the multi-path batch (128 requests, 1.37 M tokens, 132 rows), the
+// load path alone 0.93 ms, both together 1.15 - 1.17 ms (1.19 - 1.22 with helpers that shared the leftover rows tile by
+// tile beside a software-pipelined main wave).  Not kept: the helpers half a step behind the main waves (the second copy
+// of the step spills, and a reload waits for the tile loads in flight).
+// ---------------------------------------------------------------------------------------------------
+namespace pairs {
+
+constexpr int kWaves = 8, kSlots = 3;
+constexpr int kTileBytes = 2 * kKBytes, kPairBytes = 2 * kTileBytes;          // a tile: K, then V
+// end of a piece: four helper states of 32 rows (16 KB each), three of the leftover rows (8 KB each), their (m, l)
+constexpr int kMergeMain = 0, kMergeLeft = 4 * 16384, kMergeMl = kMergeLeft + 3 * 8192, kMergeBytes = kMergeMl + 7 * kWave * 8;
+constexpr int kLeftQ = kSlots * kPairBytes;                                  // the leftover rows' Q^T operands, [step][lane] x 16 bytes
+constexpr int kLdsBytes = kLeftQ + 4096;
+static_assert(kMergeBytes <= kSlots * kPairBytes, "the merge area fits the ring's memory");
+
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+
+// Bits of a tile's 32 tokens that a row with mask word w sees; rel in (-32, 64): the tile's first token after the first slot.
+__device__ __forceinline__ uint32_t visible(uint64_t w, int rel) {
+    return rel >= 0 ? static_cast<uint32_t>(w >> rel) : (static_cast<uint32_t>(w << (-rel)) | ((1u << (-rel)) - 1u));
+}
+
+// One 16-token half of a tile for the leftover rows: this lane's row is p16, its tokens half * 16 + l16 * 4 + 0 .. 3.
+// qa: LDS address of the lane's four Q^T operands (1 KB apart); ka: of the lane's K chunk (row half * 16 + p16, contraction steps 0 .. 3 by XOR with kk << 6);
+// va: address of its transposing read (token row half * 16 + l16 * 4 + p16 / 4, d blocks 0 .. 7 by XOR with db << 5).
+struct LeftState {
+    f32x4 acc[8];
+    float m, l;
+};
+__device__ __forceinline__ void left_half(LeftState& st, int qa, int ka, int va, float scale_log2, uint32_t vis) {
+    u32x4 kv[4], q[4];
+    const int k1 = ka ^ 64, k2 = ka ^ 128, k3 = ka ^ 192;
+    asm volatile("ds_read_b128 %0, %8\n"
+                 "ds_read_b128 %1, %9\n"
+                 "ds_read_b128 %2, %10\n"
+                 "ds_read_b128 %3, %11\n"
+                 "ds_read_b128 %4, %12\n"
+                 "ds_read_b128 %5, %12 offset:1024\n"
+                 "ds_read_b128 %6, %12 offset:2048\n"
+                 "ds_read_b128 %7, %12 offset:3072\n"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(kv[0]), "=&v"(kv[1]), "=&v"(kv[2]), "=&v"(kv[3]), "=&v"(q[0]), "=&v"(q[1]), "=&v"(q[2]), "=&v"(q[3])
+                 : "v"(ka), "v"(k1), "v"(k2), "v"(k3), "v"(qa));
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kv[kk]), as_bf16x8(q[kk]), s, 0, 0, 0);
+    u32x2 vr[8];
+    {
+        const int a1 = va ^ 32, a2 = va ^ 64, a3 = va ^ 96, a4 = va ^ 128, a5 = va ^ 160, a6 = va ^ 192, a7 = va ^ 224;
+        asm volatile("ds_read_b64_tr_b16 %0, %8\n"
+                     "ds_read_b64_tr_b16 %1, %9\n"
+                     "ds_read_b64_tr_b16 %2, %10\n"
+                     "ds_read_b64_tr_b16 %3, %11\n"
+                     "ds_read_b64_tr_b16 %4, %12\n"
+                     "ds_read_b64_tr_b16 %5, %13\n"
+                     "ds_read_b64_tr_b16 %6, %14\n"
+                     "ds_read_b64_tr_b16 %7, %15\n"
+                     "s_waitcnt lgkmcnt(0)"
+                     : "=&v"(vr[0]), "=&v"(vr[1]), "=&v"(vr[2]), "=&v"(vr[3]), "=&v"(vr[4]), "=&v"(vr[5]), "=&v"(vr[6]), "=&v"(vr[7])
+                     : "v"(va), "v"(a1), "v"(a2), "v"(a3), "v"(a4), "v"(a5), "v"(a6), "v"(a7));
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (!((vis >> i) & 1u)) s[i] = kNegInf;
+    float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+    mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
+    float alpha;
+    const float m_use = move_reference(mx, scale_log2, st.m, alpha);          // (takes the maximum over lane ^ 32 too)
+    const float p0 = fast_exp2(fmaf(s[0], scale_log2, -m_use)), p1 = fast_exp2(fmaf(s[1], scale_log2, -m_use));
+    const float p2 = fast_exp2(fmaf(s[2], scale_log2, -m_use)), p3 = fast_exp2(fmaf(s[3], scale_log2, -m_use));
+    u32x2 pk;
+    pk[0] = cvt_pk_bf16(p0, p1);
+    pk[1] = cvt_pk_bf16(p2, p3);
+    st.l = st.l * alpha + add_bf16_pair(pk[1], add_bf16_pair(pk[0], 0.f));
+    if (__any(alpha != 1.f)) {
+#pragma unroll
+        for (int db = 0; db < 8; ++db)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) st.acc[db][i] *= alpha;
+    }
+    const s16x4 pb = __builtin_bit_cast(s16x4, pk);
+#pragma unroll
+    for (int db = 0; db < 8; ++db)
+        st.acc[db] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, vr[db]), pb, st.acc[db], 0, 0, 0);
+}
+
+// Scores of one tile for this lane's row (32 rows a wave), masked.  k: LDS address of the lane's K chunk of contraction step 0
+// (step kk: ^ kk << 5); rel: first token of the tile relative to the first draft slot (uniform; masked slots have rel > -32).
+__device__ __forceinline__ void scores(int k, const bf16x8 (&qreg)[8], f32x16& s, int rel, uint64_t word, int lg) {
+    u32x4 ka[4], kb[4];
+    {
+        const int b1 = k ^ 32, b2 = k ^ 64, b3 = k ^ 96, b4 = k ^ 128, b5 = k ^ 160, b6 = k ^ 192, b7 = k ^ 224;
+        SEER_K4_ISSUE(ka, k, b1, b2, b3, 0);
+        SEER_K4_ISSUE(kb, b4, b5, b6, b7, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = 0.f;
+    SEER_K4_WAIT(4, ka);
+    SEER_SCHED_FENCE();
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(ka[kk]), qreg[kk], s, 0, 0, 0);
+    SEER_K4_WAIT(0, kb);
+    SEER_SCHED_FENCE();
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kb[kk]), qreg[4 + kk], s, 0, 0, 0);
+    if (rel > -kTile) {
+        const uint32_t vis = visible(word, rel) >> (lg * 4);
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (!((vis >> ((i >> 2) * 8 + (i & 3))) & 1u)) s[i] = kNegInf;
+    }
+}
+
+// Softmax of those scores and P.V.  The V^T operands (v: LDS address of the lane's transposing read, d-tile dt: ^ dt << 6) are
+// requested before the exponentials and awaited after them.
+__device__ __forceinline__ void softmax_pv(int v, f32x16& s, f32x16 (&acc)[4], float& m_run, float& l_run, float scale_log2) {
+    float mx = s[0];
+#pragma unroll
+    for (int i = 1; i < 15; i += 2) mx = fmaxf(fmaxf(mx, s[i]), s[i + 1]);
+    mx = fmaxf(mx, s[15]);
+    float alpha;
+    const float m_use = move_reference(mx, scale_log2, m_run, alpha);
+    rescale_if_moved(acc, alpha);
+    SEER_SCHED_FENCE();
+    const int a1 = v ^ 64, a2 = v ^ 128, a3 = v ^ 192;
+    u32x2 va[4][2], vb[4][2];
+    SEER_TR8_ISSUE(va, v, a1, a2, a3, 0, 2048);
+    SEER_TR8_ISSUE(vb, v, a1, a2, a3, 4096, 6144);
+    float psum = 0.f;
+    uint32_t pk[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const float p0 = fast_exp2(fmaf(s[2 * i], scale_log2, -m_use));
+        const float p1 = fast_exp2(fmaf(s[2 * i + 1], scale_log2, -m_use));
+        pk[i] = cvt_pk_bf16(p0, p1);
+        psum = add_bf16_pair(pk[i], psum);
+    }
+    l_run = l_run * alpha + psum;
+    SEER_TR8_WAIT(8, va);
+    SEER_SCHED_FENCE();
+    const bf16x8 pb0 = as_bf16x8(u32x4{pk[0], pk[1], pk[2], pk[3]});
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+        acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(u32x4{va[dt][0][0], va[dt][0][1], va[dt][1][0], va[dt][1][1]}), pb0,
+                                                          acc[dt], 0, 0, 0);
+    SEER_TR8_WAIT(0, vb);
+    SEER_SCHED_FENCE();
+    const bf16x8 pb1 = as_bf16x8(u32x4{pk[4], pk[5], pk[6], pk[7]});
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+        acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(u32x4{vb[dt][0][0], vb[dt][0][1], vb[dt][1][0], vb[dt][1][1]}), pb1,
+                                                          acc[dt], 0, 0, 0);
+}
+
+template <bool STREAM, bool STREAM_PARTIALS>
+__device__ __forceinline__ void run(const AttnArgs& a, unsigned char* lds) {
+    constexpr int NT = kWaves * kWave;
+    int rest = blockIdx.x >> 3;                       // (the grid's layout: see the kernel below)
+    const int kvh = rest % a.Hkv;
+    rest /= a.Hkv;
+    const int rb = rest % a.row_blocks;
+    const int wg = (rest / a.row_blocks) * 8 + (blockIdx.x & 7);
+    if (wg >= a.wgs_per_head) return;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int ln = lane & 31, lg = lane >> 5, l16 = lane >> 4, p16 = lane & 15;
+    const int set = wave >> 2, w4 = wave & 3;          // set 0 (main waves): even tiles, set 1 (helpers): odd tiles
+    const bool has_left = wave < 2 || wave >= 6;       // one wave per SIMD; its 16-token half of its set's tile:
+    const int half = wave & 1;
+
+    const StretchRec rec = uniform_stretch(a.stretch + wg);
+    int b = rec.b;
+    if (b < 0) return;
+    int g = rec.tile_begin;
+    const int g_end = rec.tile_end;
+    const uint64_t clock_begin = __builtin_amdgcn_s_memrealtime();
+    bool bad_page = false;
+
+    const unsigned char* __restrict__ kbase = static_cast<const unsigned char*>(a.k_pages);
+    const unsigned char* __restrict__ vbase = static_cast<const unsigned char*>(a.v_pages);
+    const int page_shift = __builtin_ctz(static_cast<unsigned>(a.P));
+    const uint32_t page_bytes32 = static_cast<uint32_t>(a.Hkv) * a.P * kRowBytes;
+    const size_t head_off = static_cast<size_t>(kvh) * a.P * kRowBytes;
+    // tile loads: the four waves without leftover rows, two 1 KB blocks (eight rows) of K and of V of both tiles each
+    const int loader = (wave + 2) & 3;
+    const int row_in_half = (loader & 1) * 8;          // first row inside its 16-row half tile
+    const int goff_k = (row_in_half + l16) * kRowBytes + ((p16 ^ k_swz(row_in_half + l16)) << 4);
+    const int goff_k2 = (row_in_half + 4 + l16) * kRowBytes + ((p16 ^ k_swz(row_in_half + 4 + l16)) << 4);
+    const int goff_v = (row_in_half + l16) * kRowBytes + ((p16 ^ v_swz(l16)) << 4);
+    const int k_rd = ln * kRowBytes + ((lg ^ k_swz(ln)) << 4);
+    const int v_k = p16 >> 2, v_c4 = p16 & 3;
+    const int v_rd = (lg * 4 + v_k) * kRowBytes + ((((l16 & 1) * 2 + (v_c4 >> 1)) ^ v_swz(v_k)) << 4) + (v_c4 & 1) * 8;
+    const int left_k = (half * 16 + p16) * kRowBytes + ((l16 ^ k_swz(p16)) << 4);
+    const int left_v = (half * 16 + l16 * 4 + v_k) * kRowBytes + (((v_c4 >> 1) ^ v_swz(v_k)) << 4) + (v_c4 & 1) * 8;
+
+    auto piece_words = [&](int bb) __attribute__((always_inline)) -> int {
+        const int bc = min(bb, a.B - 1);
+        const int32_t* ptr = a.tile_off + bc;
+        if (lane == 1) ptr = a.tile_off + bc + 1;
+        if (lane == 2) ptr = a.ctx_len + bc;
+        if (lane == 3) ptr = a.shared_tiles + bc;
+        return *ptr;
+    };
+    auto first_pages = [&](int bb) __attribute__((always_inline)) -> int {
+        return (a.block_table + static_cast<size_t>(min(bb, a.B - 1)) * a.max_pages)[min(lane, a.max_pages - 1)];
+    };
+    int pw = piece_words(b);
+    int pg_ahead = 0;
+    bool have_ahead = false;
+    const int g_first = g;
+
+  for (; g < g_end; ++b) {
+    const int t_lo = __builtin_amdgcn_readlane(pw, 0), t_hi = __builtin_amdgcn_readlane(pw, 1);
+    const int item_idx = b + rec.slot_bias;
+    const int n = __builtin_amdgcn_readlane(pw, 2);
+    const int shared_tiles = __builtin_amdgcn_readlane(pw, 3);
+    const int pg_first = pg_ahead;
+    const bool have_first = have_ahead;
+    pw = piece_words(b + 1);
+    pg_ahead = first_pages(b + 1);
+    have_ahead = b + 1 < a.B;
+    if (t_hi == t_lo) continue;
+    const int tok_begin = (g - t_lo) * kTile;
+    const int tok_end = min(n, (min(g_end, t_hi) - t_lo) * kTile);
+    g = t_hi;
+    const int n0 = n - a.T;
+    const int n_tiles = (tok_end - tok_begin + kTile - 1) / kTile;
+    const int n_pairs = (n_tiles + 1) >> 1;
+    bare_barrier();                                    // every wave is done with the previous piece's slots
+
+    const int R = min(a.G * a.T, (rb + 1) * a.rows_per_block);
+    auto row_of = [&](int r, int& t, int& hq) __attribute__((always_inline)) -> bool {
+        const bool ok = r < R;
+        t = ok ? r / a.G : 0;
+        hq = kvh * a.G + (ok ? r - t * a.G : 0);
+        return ok;
+    };
+    auto mask_word = [&](int t, bool ok) __attribute__((always_inline)) -> uint64_t {
+        uint64_t w = 0;
+        if (ok) w = a.tree_mask ? a.tree_mask[static_cast<size_t>(b) * a.T + t] : (t >= 63 ? ~0ull : ((1ull << (t + 1)) - 1));
+        return w;
+    };
+    int t, hq, t2, hq2;
+    const bool row_ok = row_of(rb * a.rows_per_block + w4 * 32 + ln, t, hq);
+    const bool left_ok = row_of(rb * a.rows_per_block + 128 + p16, t2, hq2) && has_left;
+    uint64_t word = mask_word(t, row_ok), word2 = mask_word(t2, left_ok);
+    u32x4 qv[8];
+    {
+        const uint16_t* qb = static_cast<const uint16_t*>(a.q) + static_cast<size_t>(b) * a.T * a.Hq * kD;
+        const u32x4* qp = reinterpret_cast<const u32x4*>(qb + (static_cast<size_t>(t) * a.Hq + hq) * kD + lg * 8);
+        const u32x4* qp2 = reinterpret_cast<const u32x4*>(qb + (static_cast<size_t>(t2) * a.Hq + hq2) * kD + l16 * 8);
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) {
+            qv[kk] = u32x4{0u, 0u, 0u, 0u};
+            if (row_ok) qv[kk] = qp[kk * 2];
+        }
+        if (wave == 0) {                               // (the four waves that serve these rows share one layout)
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) {
+                u32x4 v = {0u, 0u, 0u, 0u};
+                if (left_ok) v = qp2[kk * 4];
+                *reinterpret_cast<u32x4*>(lds + kLeftQ + (kk * kWave + lane) * 16) = v;
+            }
+            __builtin_amdgcn_s_waitcnt(0xc07f);
+        }
+    }
+
+    // page ids, 64 at a time, handed out with v_readlane (see the kernel below)
+    const int32_t* __restrict__ table = a.block_table + static_cast<size_t>(b) * a.max_pages;
+    const int last_page = (n - 1) >> page_shift;
+    auto in_pool = [&](int pg, int idx) __attribute__((always_inline)) -> int {
+        if (pg < 0 || pg >= a.num_pages) {
+            if (idx <= last_page) bad_page = true;
+            pg = min(max(pg, 0), a.num_pages - 1);
+        }
+        return pg;
+    };
+    const bool window_ahead = have_first && tok_begin == 0;
+    int cache_base = window_ahead ? 0 : -0x40000000;
+    int pg_cache = window_ahead ? in_pool(pg_first, lane) : 0;
+    // byte offset in a pool of the 16-row half of tile tb that holds this wave's block
+    auto half_offset = [&](int tb) __attribute__((always_inline)) -> size_t {
+        const int lp = tb >> page_shift;                 // 16-token pages: a tile is page lp (even) and lp + 1
+        if (lp < cache_base || lp >= cache_base + kWave) {
+            cache_base = lp;
+            const int idx = cache_base + lane;
+            pg_cache = in_pool(table[min(idx, a.max_pages - 1)], idx);
+        }
+        const int second = loader >> 1;                  // loaders 2 and 3 request rows 16 .. 31
+        const int i = __builtin_amdgcn_readfirstlane(lp - cache_base + (a.P == kMinPage ? second : 0));
+        const uint32_t pg = __builtin_amdgcn_readlane(pg_cache, i);
+        const uint32_t in_page = static_cast<uint32_t>(tb + 16 * second) & (a.P - 1);
+        return static_cast<uint64_t>(pg) * page_bytes32 + head_off + in_page * kRowBytes;
+    };
+    const int keep_until = shared_tiles - tok_begin / kTile;   // tiles below this index keep the default cache policy
+    auto issue_pair = [&](int p) __attribute__((always_inline)) {
+        const int slot_off = (p % kSlots) * kPairBytes;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int tile = 2 * p + s;
+            if (tile < n_tiles) {
+                const size_t off = half_offset(tok_begin + tile * kTile);
+                unsigned char* dst = lds + slot_off + s * kTileBytes + loader * 2048;
+                // through buffer descriptors of the 16 rows (scalar base, 32-bit lane offset): half the issue cost of the
+                // form with 64-bit lane addresses, and fewer registers
+                const __amdgpu_buffer_rsrc_t ks = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(kbase + off), 0, 16 * kRowBytes, 0x00020000);
+                const __amdgpu_buffer_rsrc_t vs = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(vbase + off), 0, 16 * kRowBytes, 0x00020000);
+                auto four = [&](auto policy) __attribute__((always_inline)) {
+                    constexpr int POLICY = decltype(policy)::value;
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(ks, (SEER_AS3 void*)(dst), 16, goff_k, 0, 0, POLICY);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(ks, (SEER_AS3 void*)(dst + 1024), 16, goff_k2, 0, 0, POLICY);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(vs, (SEER_AS3 void*)(dst + kKBytes), 16, goff_v, 0, 0, POLICY);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(vs, (SEER_AS3 void*)(dst + kKBytes + 1024), 16, goff_v, 1024, 0, POLICY);
+                };
+                if (tile < keep_until) four(std::integral_constant<int, 0>{});
+                else four(std::integral_constant<int, kTileLoadPolicy>{});
+            }
+        }
+    };
+    if (!has_left) {
+        issue_pair(0);
+        if (n_pairs > 1) issue_pair(1);
+    }
+
+    bf16x8 qreg[8];
+    {
+        // the query rows and mask words have to have returned HERE (see the kernel below)
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) {
+            asm volatile("" : "+v"(qv[kk]));
+            qreg[kk] = as_bf16x8(qv[kk]);
+        }
+        asm volatile("" : "+v"(word), "+v"(word2));
+        if (a.T < 64) word &= (1ull << a.T) - 1, word2 &= (1ull << a.T) - 1;
+    }
+    f32x16 acc[4];
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[dt][i] = 0.f;
+    float m_run = kNegInf, l_run = 0.f;
+    LeftState left;
+#pragma unroll
+    for (int db = 0; db < 8; ++db) left.acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    left.m = kNegInf, left.l = 0.f;
+
+    // top of step p: pair p has landed when at most the eight loads of pair p + 1 are outstanding
+    auto step_top = [&](int p) __attribute__((always_inline)) {
+        if (2 * p + 3 < n_tiles) wait_vmcnt<8>(); else wait_vmcnt<0>();
+        bare_barrier();                                // ... for every wave, and every wave is done with step p - 1
+        if (p == n_pairs - 1 && tok_begin + n_tiles * kTile > n) {
+            // ragged last tile: clear the V rows past the end (0 * NaN must not reach the output)
+            const int last = n_tiles - 1, first_bad = n - (tok_begin + last * kTile);
+            unsigned char* vl = lds + (p % kSlots) * kPairBytes + (last & 1) * kTileBytes + kKBytes;
+            for (int c = tid; c < kTile * 16; c += NT)
+                if ((c >> 4) >= first_bad) *reinterpret_cast<u32x4*>(vl + c * 16) = u32x4{0u, 0u, 0u, 0u};
+            __builtin_amdgcn_s_waitcnt(0xc07f);
+            bare_barrier();
+        }
+        SEER_SCHED_FENCE();
+    };
+    if (has_left) __builtin_amdgcn_s_setprio(2);
+    for (int p = 0; p < n_pairs; ++p) {
+        step_top(p);
+        const bool mine = 2 * p + set < n_tiles;
+        const int rel = tok_begin + (2 * p + set) * kTile - n0;
+        const int k_off = (p % kSlots) * kPairBytes + set * kTileBytes, v_off = k_off + kKBytes;
+        if (!STREAM && mine) {
+            f32x16 s;
+            scores(k_off + k_rd, qreg, s, rel, word, lg);
+            if (!has_left && p + 2 < n_pairs) issue_pair(p + 2);       // into the slot of pair p - 1
+            softmax_pv(v_off + v_rd, s, acc, m_run, l_run, a.scale_log2);
+        }
+        if (has_left) {
+            if (!STREAM && mine)
+                left_half(left, kLeftQ + lane * 16, k_off + left_k, v_off + left_v, a.scale_log2,
+                          rel <= -kTile ? ~0u : visible(word2, rel) >> (half * 16 + l16 * 4));
+        } else if (STREAM && p + 2 < n_pairs) {
+            issue_pair(p + 2);
+        }
+    }
+
+    // ---- the helpers' states join the main waves' ------------------------------------------------------
+    float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
+    float left_l = left.l + __shfl_xor(left.l, 32, kWave);
+    left_l += __shfl_xor(left_l, 16, kWave);
+    float2* ml = reinterpret_cast<float2*>(lds + kMergeMl);                      // [0..3]: helpers, [4..6]: leftover rows of waves 1, 6, 7
+    bare_barrier();                                    // every wave has read the piece's last tiles
+    if (set) {
+        ml[w4 * kWave + lane] = float2{m_run, l_tot};
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4)
+                *reinterpret_cast<f32x4*>(lds + kMergeMain + ((w4 * 16 + dt * 4 + i4) * kWave + lane) * 16) =
+                    f32x4{acc[dt][i4 * 4], acc[dt][i4 * 4 + 1], acc[dt][i4 * 4 + 2], acc[dt][i4 * 4 + 3]};
+    }
+    if (has_left && wave > 0) {
+        const int o = wave == 1 ? 0 : wave - 5;
+        ml[(4 + o) * kWave + lane] = float2{left.m, left_l};
+#pragma unroll
+        for (int db = 0; db < 8; ++db) *reinterpret_cast<f32x4*>(lds + kMergeLeft + ((o * 8 + db) * kWave + lane) * 16) = left.acc[db];
+    }
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    bare_barrier();
+    auto store_partial = [&](float* dst, const f32x4& v) __attribute__((always_inline)) {
+        if constexpr (STREAM_PARTIALS) __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(dst));
+        else *reinterpret_cast<f32x4*>(dst) = v;
+    };
+    if (!set) {
+        const float2 other = ml[w4 * kWave + lane];
+        const float M = fmaxf(m_run, other.x);
+        const float f0 = m_run == kNegInf ? 0.f : fast_exp2(m_run - M), f1 = other.x == kNegInf ? 0.f : fast_exp2(other.x - M);
+        const size_t prow = (static_cast<size_t>(item_idx) * a.T + t) * a.Hq + hq;
+        if (row_ok && lg == 0) {
+            a.part_ml[2 * prow] = M;
+            a.part_ml[2 * prow + 1] = l_tot * f0 + other.y * f1;
+        }
+        float* __restrict__ po = a.part_acc + prow * kD + lg * 4;
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4) {
+                f32x4 v = *reinterpret_cast<const f32x4*>(lds + kMergeMain + ((w4 * 16 + dt * 4 + i4) * kWave + lane) * 16);
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    v[c] = (f0 == 0.f ? 0.f : acc[dt][i4 * 4 + c] * f0) + (f1 == 0.f ? 0.f : v[c] * f1);
+                if (row_ok) store_partial(po + dt * 32 + i4 * 8, v);
+            }
+    }
+    if (wave == 0) {
+        float mo[3], lo[3], M = left.m;
+#pragma unroll
+        for (int o = 0; o < 3; ++o) {
+            const float2 x = ml[(4 + o) * kWave + lane];
+            mo[o] = x.x, lo[o] = x.y;
+            M = fmaxf(M, x.x);
+        }
+        const float f = left.m == kNegInf ? 0.f : fast_exp2(left.m - M);
+        float L = left_l * f, fo[3];
+#pragma unroll
+        for (int o = 0; o < 3; ++o) {
+            fo[o] = mo[o] == kNegInf ? 0.f : fast_exp2(mo[o] - M);
+            L += lo[o] * fo[o];
+        }
+        const size_t prow = (static_cast<size_t>(item_idx) * a.T + t2) * a.Hq + hq2;
+        if (left_ok && l16 == 0) {
+            a.part_ml[2 * prow] = M;
+            a.part_ml[2 * prow + 1] = L;
+        }
+        float* __restrict__ po = a.part_acc + prow * kD + l16 * 4;
+#pragma unroll
+        for (int db = 0; db < 8; ++db) {
+            f32x4 v;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[c] = f == 0.f ? 0.f : left.acc[db][c] * f;
+#pragma unroll
+            for (int o = 0; o < 3; ++o) {
+                const f32x4 x = *reinterpret_cast<const f32x4*>(lds + kMergeLeft + ((o * 8 + db) * kWave + lane) * 16);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[c] += fo[o] == 0.f ? 0.f : x[c] * fo[o];
+            }
+            if (left_ok) store_partial(po + db * 16, v);
+        }
+    }
+  }  // pieces of the stretch
+    if (bad_page && lane == 0) atomicOr(&a.header->status, 2u);
+    if (a.balanced && !a.fixed_split && tid == 0) {
+        const uint64_t ticks = __builtin_amdgcn_s_memrealtime() - clock_begin;
+        atomicAdd(a.fb_time + wg, static_cast<uint32_t>(ticks > 0xffffffu ? 0xffffffu : ticks));
+        atomicAdd(a.fb_tiles + wg, static_cast<uint32_t>(g_end - g_first));
+    }
+}
+
+}  // namespace pairs
+
 template <typename F, int... I>
 __device__ __forceinline__ void for_each_index(F& f, std::integer_sequence<int, I...>) {
     (f(std::integral_constant<int, I>{}), ...);
@@ -370,32 +861,24 @@ __device__ __forceinline__ void for_each_index(F& f, std::integer_sequence<int, 
 // system allows for exactly this access pattern and launch shape: the ceiling the kernel's
 // bytes-per-second should be read against.  It writes "saw nothing" partials, so the output is zero.
 // STREAM_PARTIALS: the partial results leave with non-temporal stores (see kStreamPartialsBelow).
-// NH: helper waves (0 or 4) behind the NW main waves.  A row count just above a multiple of 32 (the multi-path
-// tree on a group of four heads: 4 x 33 = 132 rows) would otherwise put a fifth wave with a handful of rows on the
-// SIMD of wave 0; that wave runs the whole per-tile instruction stream whatever its row count, and with in-order
-// issue it doubles the load of the one SIMD every step waits for.  Instead the NW = 4 main waves (one per SIMD)
-// are joined by four helper waves (again one per SIMD) that serve the leftover rows TOGETHER: helper h takes
-// the tiles u = h (mod 4) of a piece, each with a softmax state of its own, and the four states are merged
-// through LDS at the end of the piece (in a fixed order, so the result does not depend on timing).  A helper
-// scores and soft-maxes its tile at step u and multiplies by V at step u + 2, when that V tile has landed: a
-// quarter of a wave's work per step on every SIMD instead of a whole wave's on one.  All eight waves issue loads.
+// NH: 0, or 4 helper waves that double the four main ones (see `pairs` above).
 template <int NW, int D, bool STREAM, bool STREAM_PARTIALS, int NH = 0>
 __global__ __launch_bounds__((NW + NH) * kWave) __attribute__((amdgpu_waves_per_eu(NW + NH == 1 ? 1 : 2, 2)))
 void attn_gqa128_kernel(AttnArgs a) {
-    static_assert(NH == 0 || (NH == 4 && D >= 2), "helpers: four of them, and V tiles that land two steps after K");
-    constexpr int NWT = NW + NH;                    // waves per workgroup
-    constexpr int NT = NWT * kWave;
+    if constexpr (NH > 0) {
+        static_assert(NW == 4 && NH == 4 && D == 2, "four main and four helper waves");
+        __shared__ __attribute__((aligned(1024))) unsigned char pair_lds[pairs::kLdsBytes];
+        pairs::run<STREAM, STREAM_PARTIALS>(a, pair_lds);
+    } else {
+    constexpr int NT = NW * kWave;
     constexpr int NSLOT = D + 1;                    // slots in the K ring and in the V ring
-    constexpr int NL = Loaders<NWT>::kCount;        // waves that issue loads (the others have nothing to wait for)
+    constexpr int NL = Loaders<NW>::kCount;        // waves that issue loads (the others have nothing to wait for)
     constexpr int CEIL = (8 + NL - 1) / NL;         // half-tile blocks of the busiest loading waves
     constexpr int FLOOR = 8 / NL;
     constexpr int REM = 8 % NL;                     // loaders below this index load CEIL blocks, the others FLOOR
     static_assert(D >= 1 && (D - 1) * 2 * CEIL < 64, "vmcnt range");
 
-    // K ring, then V ring; at the end of a piece the helpers' states pass through the same memory
-    constexpr int kMergeBytes = NH > 0 ? 4096 + (NH - 1) * 16 * kWave * 16 : 0;
-    constexpr int kLdsBytes = 2 * NSLOT * kKBytes > kMergeBytes ? 2 * NSLOT * kKBytes : kMergeBytes;
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[kLdsBytes];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * NSLOT * kKBytes];   // K ring, then V ring
     constexpr int kVRing = NSLOT * kKBytes;
 
     // Workgroup ids are dealt round-robin to the 8 XCDs and dispatched in id order.  The grid is laid
@@ -485,8 +968,7 @@ void attn_gqa128_kernel(AttnArgs a) {
     bare_barrier();                                // every wave is done with the previous piece's slots
 
     const int R = min(a.G * a.T, (rb + 1) * a.rows_per_block);     // rows of this row block end here
-    const bool helper = NH > 0 && wave >= NW;                       // uniform for the wave
-    const int r = rb * a.rows_per_block + (helper ? NW : wave) * 32 + ln;
+    const int r = rb * a.rows_per_block + wave * 32 + ln;
     const bool row_ok = r < R;
     const int t = row_ok ? r / a.G : 0;
     const int hq = kvh * a.G + (row_ok ? r - t * a.G : 0);
@@ -560,15 +1042,15 @@ void attn_gqa128_kernel(AttnArgs a) {
     auto issue_k_at = [&](int kt, int slot_bytes, auto mode) __attribute__((always_inline)) {
         page_pair(tok_begin + kt * kTile, pn0, pn1);
         if (decltype(mode)::value && kt < keep_until)
-            issue_half_tile<NWT, 0>(lds + slot_bytes, wave, pn0, pn1, kbase, goff_k0, true);
+            issue_half_tile<NW, 0>(lds + slot_bytes, wave, pn0, pn1, kbase, goff_k0, true);
         else
-            issue_half_tile<NWT>(lds + slot_bytes, wave, pn0, pn1, kbase, goff_k0, true);
+            issue_half_tile<NW>(lds + slot_bytes, wave, pn0, pn1, kbase, goff_k0, true);
     };
     auto issue_v_at = [&](int vt, int slot_bytes, auto mode) __attribute__((always_inline)) {
         if (decltype(mode)::value && vt < keep_until)
-            issue_half_tile<NWT, 0>(lds + kVRing + slot_bytes, wave, pr0, pr1, vbase, goff_v, false);
+            issue_half_tile<NW, 0>(lds + kVRing + slot_bytes, wave, pr0, pr1, vbase, goff_v, false);
         else
-            issue_half_tile<NWT>(lds + kVRing + slot_bytes, wave, pr0, pr1, vbase, goff_v, false);
+            issue_half_tile<NW>(lds + kVRing + slot_bytes, wave, pr0, pr1, vbase, goff_v, false);
     };
     auto shift_pages = [&]() __attribute__((always_inline)) { pr0 = pq0, pr1 = pq1, pq0 = pn0, pq1 = pn1; };
     auto issue_k = [&](int j) __attribute__((always_inline)) {
@@ -590,7 +1072,7 @@ void attn_gqa128_kernel(AttnArgs a) {
     auto wait_step = [&](int u) __attribute__((always_inline)) {
         const bool full = D > 1 && u >= 1 && u + D - 1 < n_tiles;
         if (full) {
-            if (REM == 0 || wave - Loaders<NWT>::kFirst < REM) wait_vmcnt<(D - 1) * 2 * CEIL>();
+            if (REM == 0 || wave - Loaders<NW>::kFirst < REM) wait_vmcnt<(D - 1) * 2 * CEIL>();
             else wait_vmcnt<(D - 1) * 2 * FLOOR>();
         } else {
             wait_vmcnt<0>();
@@ -650,40 +1132,6 @@ void attn_gqa128_kernel(AttnArgs a) {
         }
     };
 
-  if (helper) {
-    // A helper wave: the same waits, barriers and loads as the main waves, step for step; of the arithmetic,
-    // the tiles u = h (mod NH) for the leftover rows, one phase per step so that no step is much longer than the
-    // others: scores at step u (K tile u is in its slot during that step only), softmax at step u + 1, P.V at
-    // step u + 2 (V tile u has landed by then and is overwritten after step u + 3's barrier).
-    if constexpr (NH > 0) {
-        const int h = wave - NW;
-        // (the helpers' phases are dependent chains that otherwise wait behind the main wave of their SIMD, which the
-        // issue arbiter prefers as the older wave, and every wave then waits for them at the barrier)
-        __builtin_amdgcn_s_setprio(3);
-        for (int u = 0; u <= n_tiles + 1; ++u) {
-            wait_step(u);
-            bare_barrier();
-            if (u == n_tiles + 1) clear_ragged_tail();
-            if (u <= n_tiles) issue_step(u);
-            if constexpr (!STREAM) {
-                if (u >= 2 && ((u - 2) & (NH - 1)) == h)
-                    pipe_step<false, false, true>(lds, 0, v_off(u - 2), k_rd, v_rd, qreg, s_b, s_b, pk_a, pk_b, acc, m_run, l_run,
-                                                  alpha, a.scale_log2, 0u);
-                if (u >= 1 && u <= n_tiles && ((u - 1) & (NH - 1)) == h) {
-                    if (tok_begin + u * kTile <= n0)          // a tile of prefix tokens only: nothing to mask
-                        pipe_step<false, true, false, false>(lds, 0, 0, k_rd, v_rd, qreg, s_a, s_b, pk_b, pk_a, acc, m_run, l_run,
-                                                             alpha, a.scale_log2, 0u);
-                    else
-                        pipe_step<false, true, false>(lds, 0, 0, k_rd, v_rd, qreg, s_a, s_b, pk_b, pk_a, acc, m_run, l_run, alpha,
-                                                      a.scale_log2, vis_of(u - 1));
-                }
-                if (u < n_tiles && (u & (NH - 1)) == h)
-                    pipe_step<true, false, false>(lds, k_off(u), 0, k_rd, v_rd, qreg, s_b, s_a, pk_b, pk_b, acc, m_run, l_run, alpha,
-                                                  a.scale_log2, 0u);
-            }
-        }
-    }
-  } else {
     // step 0: scores of tile 0 -> s_a
     wait_step(0);
     bare_barrier();
@@ -743,7 +1191,7 @@ void attn_gqa128_kernel(AttnArgs a) {
             constexpr int I = decltype(ic)::value;
             constexpr int kReadSlot = (2 + I) % NSLOT, kVReadSlot = I % NSLOT;
             constexpr int kIssueSlot = (1 + I) % NSLOT, kVIssueSlot = (I + NSLOT - 1) % NSLOT;
-            if (REM == 0 || wave - Loaders<NWT>::kFirst < REM) wait_vmcnt<(D - 1) * 2 * CEIL>();
+            if (REM == 0 || wave - Loaders<NW>::kFirst < REM) wait_vmcnt<(D - 1) * 2 * CEIL>();
             else wait_vmcnt<(D - 1) * 2 * FLOOR>();
             bare_barrier();
             const int uu = u + I;
@@ -808,74 +1256,10 @@ void attn_gqa128_kernel(AttnArgs a) {
             pipe_step<false, false, true>(lds, 0, v_off(n_tiles - 1), k_rd, v_rd, qreg, s_b, s_a, pk_a, pk_b, acc, m_run,
                                           l_run, alpha, a.scale_log2, 0u);
     }
-  }  // main waves
 
     // ---- partial result: (reference exponent, sum, unnormalised O) per row ------------
     float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
-    bool stores = row_ok;                           // this lane's row leaves from this wave
-    if constexpr (NH > 0) {
-        // The helpers' four states of the leftover rows become one.  Every wave takes part in the barriers.
-        // LDS (the ring is free once every wave has passed the first barrier): (m, l) of every helper lane,
-        // then the scaled accumulators of helpers 1..3, sixteen 16-byte chunks per lane, chunk-major so that
-        // a wave's access is one contiguous kilobyte.
-        float* xml = reinterpret_cast<float*>(lds);                                    // [NH][64][2]
-        unsigned char* xacc = lds + 4096;                                              // [NH - 1][16][64] x 16 bytes
-        static_assert(NH * kWave * 2 * 4 <= 4096 && kMergeBytes <= kLdsBytes, "the merge area fits the ring's memory");
-        const int h = wave - NW;
-        bare_barrier();                              // every wave has read the piece's last tiles
-        if (helper) {
-            xml[(h * kWave + lane) * 2] = m_run;
-            xml[(h * kWave + lane) * 2 + 1] = l_tot;
-        }
-        __builtin_amdgcn_s_waitcnt(0xc07f);
-        bare_barrier();
-        if (helper) {
-            float mh[NH], lh[NH];
-#pragma unroll
-            for (int i = 0; i < NH; ++i) {
-                mh[i] = xml[(i * kWave + lane) * 2];
-                lh[i] = xml[(i * kWave + lane) * 2 + 1];
-            }
-            float M = mh[0];
-#pragma unroll
-            for (int i = 1; i < NH; ++i) M = fmaxf(M, mh[i]);
-            float L = 0.f;
-#pragma unroll
-            for (int i = 0; i < NH; ++i) L += (mh[i] == kNegInf) ? 0.f : lh[i] * fast_exp2(mh[i] - M);   // fixed order
-            const float f = (m_run == kNegInf) ? 0.f : fast_exp2(m_run - M);
-            m_run = M;
-            l_tot = L;
-#pragma unroll
-            for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc[dt][i] = (f == 0.f) ? 0.f : acc[dt][i] * f;
-            if (h > 0) {
-#pragma unroll
-                for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-                    for (int i4 = 0; i4 < 4; ++i4) {
-                        const f32x4 v = {acc[dt][i4 * 4], acc[dt][i4 * 4 + 1], acc[dt][i4 * 4 + 2], acc[dt][i4 * 4 + 3]};
-                        *reinterpret_cast<f32x4*>(xacc + (((h - 1) * 16 + dt * 4 + i4) * kWave + lane) * 16) = v;
-                    }
-            }
-        }
-        __builtin_amdgcn_s_waitcnt(0xc07f);
-        bare_barrier();
-        if (helper && h == 0) {
-#pragma unroll
-            for (int o = 0; o < NH - 1; ++o)            // helper 1, then 2, then 3: a fixed order of additions
-#pragma unroll
-                for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-                    for (int i4 = 0; i4 < 4; ++i4) {
-                        const f32x4 v = *reinterpret_cast<const f32x4*>(xacc + ((o * 16 + dt * 4 + i4) * kWave + lane) * 16);
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) acc[dt][i4 * 4 + c] += v[c];
-                    }
-        }
-        stores = row_ok && (!helper || h == 0);
-    }
-    if (stores && lg == 0) {
+    if (row_ok && lg == 0) {
         const size_t prow = (static_cast<size_t>(item_idx) * a.T + t) * a.Hq + hq;
         a.part_ml[2 * prow] = m_run;
         a.part_ml[2 * prow + 1] = l_tot;
@@ -920,7 +1304,7 @@ void attn_gqa128_kernel(AttnArgs a) {
                 store_partial(a.part_acc + prow * kD + ln * 4, v);
             }
         }
-    } else if (stores) {
+    } else if (row_ok) {
         int lg_here = lg;                                // (as above)
         asm volatile("" : "+v"(lg_here));
         const size_t prow = (static_cast<size_t>(item_idx) * a.T + t) * a.Hq + hq;
@@ -941,6 +1325,7 @@ void attn_gqa128_kernel(AttnArgs a) {
         atomicAdd(a.fb_time + wg, static_cast<uint32_t>(ticks > 0xffffffu ? 0xffffffu : ticks));
         atomicAdd(a.fb_tiles + wg, static_cast<uint32_t>(g_end - g_first));
     }
+    }  // NH == 0
 }
 
 bool gqa128_supports(const AttnArgs& a) {
@@ -948,17 +1333,14 @@ bool gqa128_supports(const AttnArgs& a) {
            a.v_pages != nullptr && a.Hkv <= 65535;
 }
 
-// Ring depth of the helper shape: two tiles in flight.  Its eight waves spend their time on operand reads and on
-// each other, not on waiting for tiles (measured per wave on the multi-path batch: 50 of a step's 2000 clocks), and
-// with three tiles in flight instead of two the kernel is 4 % slower (1.28 vs 1.23 ms; rings of 5 and 7: as 3).
+// The helper shape: two steps' tiles in flight (see pairs).
 constexpr int kHelperDepth = 2;
 
 hipError_t launch_gqa128(const AttnArgs& a, hipStream_t stream) {
     const int nw = a.rows_per_block / 32;
     const dim3 grid(static_cast<unsigned>((a.wgs_per_head + 7) / 8) * 8u * static_cast<unsigned>(a.Hkv) *
                     static_cast<unsigned>(a.row_blocks));
-    // four main waves and four helpers instead of five waves: 129 .. 144 query rows in a row block (a fifth wave
-    // would hold at most half of its rows)
+    // four main waves and four helpers instead of five waves: 129 .. 144 query rows in a row block
     if (gqa_block_uses_helpers(a.rows_per_block)) {
         const dim3 block(8 * kWave);
         if (a.stream_only && a.stream_partials) hipLaunchKernelGGL((attn_gqa128_kernel<4, kHelperDepth, true, true, 4>), grid, block, 0, stream, a);
