@@ -7,21 +7,23 @@
 // accepted one counts (Section 3.4.2).  The scan below is the HBM-bound part:
 // one pass over B*T*V fp32 logits.
 //
-// Kernel 1 (argmax_chunks): the rows are cut into chunks of 16 384 (sampled: 8192) floats so
+// Kernel 1 (argmax_chunks): the rows are cut into chunks of 16 384 floats (8192 for small batches) so
 //   that a launch has rows*chunks workgroups (thousands, against 256 CUs) no
 //   matter how B*T and V split the work.  Each workgroup streams its chunk
 //   with 16-byte loads, keeps (max, lowest index) per lane, reduces across the
 //   wave with shuffles and across the 4 waves through LDS, and writes one
 //   (value, index) pair.
-// Kernel 2 (accept_walk): one wave per request.  Lane t merges the chunk pairs
-//   of slot t in ascending chunk order (strict '>' keeps the lowest index),
-//   publishes the slot's target token, then lane 0 walks the parent pointers in
-//   slot order: ok[t] = ok[parent] && draft[t] == target[parent], depth = depth
-//   of parent + 1, winner = deepest accepted slot, lowest slot on ties.
+// Kernel 2 (accept_walk): one workgroup per request.  The lanes of a slot share its chunk pairs, all
+//   requested at once; then one wave walks the tree level by level: the accepted nodes of depth d + 1 are
+//   the slots whose parent is an accepted node of depth d and whose draft token is that parent's target,
+//   one ballot per level; the winner is the lowest slot of the last level that has any (a depth counts
+//   deepest first, lowest slot on ties).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
+#include <utility>
 
 #include "../../include/seer_verify.h"
 #include "seer_device.h"
@@ -30,21 +32,45 @@
 namespace seer {
 
 constexpr int kArgmaxThreads = 256;
-// Floats per workgroup: 16 x 16-byte loads per lane for the greedy scan, 8 for the sampled one (measured on
-// V = 152 064: 16 384 instead of 8192 floats takes the greedy scan from 54 to 52 us for 576 rows and from 374 to
-// 364 us for 4224 rows; the sampled scan, bound by its arithmetic, takes the same time with either).
-constexpr int kChunkGreedy = 16384;
-constexpr int kChunkSampled = 8192;
+// Floats per workgroup: 16 x 16-byte loads per lane, 8 where the launch would otherwise leave the chip without eight
+// workgroups per CU.  Measured on V = 152 064, 16 384 against 8192 floats: greedy 52 vs 54 us for 576 rows, 364 vs 374 us
+// for 4224 rows.
+constexpr int kChunkLarge = 16384;
+constexpr int kChunkSmall = 8192;
+constexpr int kFullLaunch = 2048;
 
 __host__ __device__ inline int accept_num_chunks(int V, int chunk) { return (V + chunk - 1) / chunk; }
 // the workspace holds the finer of the two partitions
-__host__ __device__ inline int accept_max_chunks(int V) { return accept_num_chunks(V, kChunkSampled); }
+__host__ __device__ inline int accept_max_chunks(int V) { return accept_num_chunks(V, kChunkSmall); }
+inline int accept_chunk(int64_t rows, int V) { return rows * accept_num_chunks(V, kChunkLarge) >= kFullLaunch ? kChunkLarge : kChunkSmall; }
 
 // (a, ia) beats (b, ib) iff a > b, or a == b and ia < ib.
 __device__ __forceinline__ void take_better(float& v, int& i, float ov, int oi) {
     const bool better = (ov > v) || (ov == v && oi < i);
     v = better ? ov : v;
     i = better ? oi : i;
+}
+
+// f(0), f(1), .. with compile-time indices.
+template <typename F, int... I>
+__device__ __forceinline__ void for_each_index(F&& f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
+// Maximum over the lanes of a wave through DPP (rows of 16 lanes, then across them), in every lane.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_max_step(float v) {
+    const int x = __float_as_int(v);
+    return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(x, x, CTRL, ROW_MASK, 0xf, false)));
+}
+__device__ __forceinline__ float wave_max_dpp(float v) {
+    v = dpp_max_step<0x111, 0xf>(v);
+    v = dpp_max_step<0x112, 0xf>(v);
+    v = dpp_max_step<0x114, 0xf>(v);
+    v = dpp_max_step<0x118, 0xf>(v);
+    v = dpp_max_step<0x142, 0xa>(v);
+    v = dpp_max_step<0x143, 0xc>(v);
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), kWave - 1));
 }
 
 // kSampled: the maximum is taken over logits[v] / tau + G(seed, row, v) (seer_sampling.h) instead of
@@ -58,20 +84,24 @@ struct SampleArgs {
 // generator's word (of its upper 23 bits, which are all that G uses), 1 - u > 2^-(z+1), so G < (z + 1) ln 2.
 // kGumbelBoundC = ln 2 plus 0.05 for the error of the fixed-polynomial logarithms and for the roundings of the
 // three fused multiply-adds involved (checked for every one of the 2^23 words on the host; the roundings stay
-// below the slack while |logit / tau| < 2^17, beyond which the caller takes the exact path).
+// below the slack while |logit / tau| < 2^17).  Beyond that range: a larger positive logit shows in the bound itself, which
+// is then not relied on (kGumbelBoundMax); a larger negative one gives a value below -2^17 + 17, which cannot win
+// as long as the value it is held against is above kGumbelSeenMin (else nothing is skipped).  A NaN never wins.
 constexpr float kLn2 = 0.693147182f;
 constexpr float kGumbelBoundC = 0.693147182f + 0.05f;
-constexpr float kGumbelBoundMaxLogit = 131072.f;
+constexpr float kGumbelBoundMax = 130000.f;
+constexpr float kGumbelSeenMin = -100000.f;
+// (A bound per element: one bound for the four elements of a load, the largest logit with the most leading ones of the four
+// words, costs half but lets enough more loads through to take 165 instead of 140 us on 1056 rows.)
 __device__ __forceinline__ float perturb_upper_bound(float logit, float inv_tau, uint32_t w) {
     const int z = __builtin_clz(~w | 0x1ffu);          // 0 .. 23
     return __builtin_fmaf(static_cast<float>(z), kLn2, __builtin_fmaf(logit, inv_tau, kGumbelBoundC));
 }
 
-template <bool kVec4, bool kSampled>
+template <bool kVec4, bool kSampled, int kChunk>
 __global__ __launch_bounds__(kArgmaxThreads) void argmax_chunks(const float* __restrict__ logits, int V,
                                                                 int n_chunks, float* __restrict__ part_val,
                                                                 int* __restrict__ part_idx, SampleArgs sa) {
-    constexpr int kChunk = kSampled ? kChunkSampled : kChunkGreedy;
     const int row = blockIdx.x / n_chunks;
     const int chunk = blockIdx.x - row * n_chunks;
     const int begin = chunk * kChunk;
@@ -81,59 +111,80 @@ __global__ __launch_bounds__(kArgmaxThreads) void argmax_chunks(const float* __r
     float best = kNegInf;
     int best_i = begin;  // a row of -inf (or an all -inf chunk) resolves to its first index
     if constexpr (kVec4 && kSampled) {
-        // The sampled scan is bound by its arithmetic (ten generator rounds and two polynomial logarithms per
-        // logit), and almost all of the logarithms are spent on elements that cannot win: an element whose upper
-        // bound lies strictly below a perturbed value that the workgroup has already seen is neither the maximum
-        // nor tied with it.  Per 16-byte load a wave evaluates the generator and the bound; only if some lane's
-        // bound reaches the best value seen so far does the wave compute the four exact values of every lane.
+        // The sampled scan is bound by its arithmetic, and what no element can do without is the generator and the
+        // bound; the two polynomial logarithms are for elements that can win.  So a wave first takes the bound of
+        // every one of its loads, then computes the exact values of the load that holds the largest bound, and the
+        // best exact value of the workgroup's waves is what the other bounds are held against: an element whose upper bound
+        // lies strictly below a perturbed value that has been computed is neither the maximum nor tied with it.
+        // A handful of the workgroup's 64 loads reach the second computation (the generator is run again for them).
         // The result is that of the plain scan, bit for bit: only provable losers are skipped.
+        // Measured, 1056 rows of 152 064 logits: 117 us; 158 us when every load was decided as it came (a third of them went
+        // to the logarithms, the first of each wave always).
         constexpr int kIter = kChunk / (kArgmaxThreads * 4);
         constexpr int kWaves = kArgmaxThreads / kWave;
-        __shared__ volatile float s_seen[kWaves];        // per wave: a perturbed value it has met (its maximum so far)
-        if (threadIdx.x < kWaves) s_seen[threadIdx.x] = kNegInf;
-        __syncthreads();
+        __shared__ float s_seen[kWaves];                 // per wave: a perturbed value it has computed
         const int wv = threadIdx.x / kWave;
-        float seen = kNegInf;                            // wave-uniform
+        using Loads = std::make_integer_sequence<int, kIter>;
         f32x4 x[kIter];
-#pragma unroll
-        for (int it = 0; it < kIter; ++it) {
+        for_each_index([&](auto ic) __attribute__((always_inline)) {
+            constexpr int it = decltype(ic)::value;
             const int i = begin + (it * kArgmaxThreads + threadIdx.x) * 4;
             x[it] = (i < end) ? __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(base + i))
                               : f32x4{kNegInf, kNegInf, kNegInf, kNegInf};
-        }
-#pragma unroll
-        for (int it = 0; it < kIter; ++it) {
+        }, Loads{});
+        float ub[kIter], top = kNegInf;
+        int top_it = 0;
+        for_each_index([&](auto ic) __attribute__((always_inline)) {
+            constexpr int it = decltype(ic)::value;
             const int i = begin + (it * kArgmaxThreads + threadIdx.x) * 4;
-            const Philox4 r = philox4x32_10(static_cast<uint32_t>(i) >> 2, static_cast<uint32_t>(row), 0u, 0u,
-                                            sa.seed_lo, sa.seed_hi);
-            // what the other waves of the workgroup have met (a stale value is still a value that was met)
-            float floor_v = seen;
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) floor_v = fmaxf(floor_v, s_seen[w]);
+            const Philox4 r = philox4x32_10(static_cast<uint32_t>(i) >> 2, static_cast<uint32_t>(row), 0u, 0u, sa.seed_lo, sa.seed_hi);
             const float u0 = perturb_upper_bound(x[it].x, sa.inv_tau, r.w[0]);
             const float u1 = perturb_upper_bound(x[it].y, sa.inv_tau, r.w[1]);
             const float u2 = perturb_upper_bound(x[it].z, sa.inv_tau, r.w[2]);
             const float u3 = perturb_upper_bound(x[it].w, sa.inv_tau, r.w[3]);
-            const float ub = fmaxf(fmaxf(u0, u1), fmaxf(u2, u3));
-            const float mag = fmaxf(fmaxf(fabsf(x[it].x), fabsf(x[it].y)), fmaxf(fabsf(x[it].z), fabsf(x[it].w)));
-            // (written so that a NaN anywhere, an infinity or a huge logit takes the exact path)
-            const bool provably_below = i >= end || (ub < floor_v && mag * fabsf(sa.inv_tau) < kGumbelBoundMaxLogit);
-            if (__any(!provably_below)) {
-                if (i < end) {  // indices ascend within a lane: strict '>' keeps the lowest
-                    const float y0 = perturb(x[it].x, sa.inv_tau, r.w[0]);
-                    const float y1 = perturb(x[it].y, sa.inv_tau, r.w[1]);
-                    const float y2 = perturb(x[it].z, sa.inv_tau, r.w[2]);
-                    const float y3 = perturb(x[it].w, sa.inv_tau, r.w[3]);
-                    if (y0 > best) { best = y0; best_i = i; }
-                    if (y1 > best) { best = y1; best_i = i + 1; }
-                    if (y2 > best) { best = y2; best_i = i + 2; }
-                    if (y3 > best) { best = y3; best_i = i + 3; }
-                }
-                float m = best;
+            const float u4 = fmaxf(fmaxf(u0, u1), fmaxf(u2, u3));
+            const float u = u4 < kGumbelBoundMax ? u4 : -kNegInf;          // (too large for the slack, or infinite: always computed)
+            ub[it] = i < end ? u : kNegInf;
+            if (ub[it] > top) top = ub[it], top_it = it;
+            __builtin_amdgcn_sched_barrier(0);           // (load by load: interleaved, they take 6 % longer)
+        }, Loads{});
+        // the exact values of load `it` (uniform), every lane
+        auto compute = [&](int it) __attribute__((always_inline)) {
+            // (by masks: a chain of selects becomes one indexed load, and with it the array moves to scratch memory)
+            u32x4 bits = {0u, 0u, 0u, 0u};
+            for_each_index([&](auto kc) __attribute__((always_inline)) {
+                constexpr int k = decltype(kc)::value;
+                bits |= __builtin_bit_cast(u32x4, x[k]) & (it == k ? 0xffffffffu : 0u);
+            }, Loads{});
+            const f32x4 y = __builtin_bit_cast(f32x4, bits);
+            const int i = begin + (it * kArgmaxThreads + threadIdx.x) * 4;
+            if (i >= end) return;
+            const Philox4 r = philox4x32_10(static_cast<uint32_t>(i) >> 2, static_cast<uint32_t>(row), 0u, 0u, sa.seed_lo, sa.seed_hi);
 #pragma unroll
-                for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, kWave));
-                seen = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(m)));
-                if ((threadIdx.x & (kWave - 1)) == 0) s_seen[wv] = seen;
+            for (int c = 0; c < 4; ++c) take_better(best, best_i, perturb(y[c], sa.inv_tau, r.w[c]), i + c);
+        };
+        const uint64_t holders = __ballot(top == wave_max_dpp(top));
+        int first = holders ? __builtin_amdgcn_readlane(top_it, __builtin_ctzll(holders)) : 0;
+        uint32_t todo = 1u << first;
+        bool exchanged = false;
+        while (todo) {                                   // first the load with the largest bound, then what can still win
+            const int it = __builtin_ctz(todo);
+            todo &= todo - 1;
+            compute(it);
+            if (!exchanged) {
+                exchanged = true;
+                const float m = wave_max_dpp(best);
+                if ((threadIdx.x & (kWave - 1)) == 0) s_seen[wv] = m;
+                __syncthreads();                         // (once per wave, every wave)
+                float seen = s_seen[0];
+#pragma unroll
+                for (int w = 1; w < kWaves; ++w) seen = fmaxf(seen, s_seen[w]);
+                if (!(seen > kGumbelSeenMin)) seen = kNegInf;
+                for_each_index([&](auto kc) __attribute__((always_inline)) {
+                    constexpr int k = decltype(kc)::value;
+                    if (k != first && __any(!(ub[k] < seen) && begin + (k * kArgmaxThreads + static_cast<int>(threadIdx.x)) * 4 < end))
+                        todo |= 1u << k;
+                }, Loads{});
             }
         }
     } else if constexpr (kVec4) {
@@ -150,14 +201,6 @@ __global__ __launch_bounds__(kArgmaxThreads) void argmax_chunks(const float* __r
         for (int it = 0; it < kIter; ++it) {
             const int i = begin + (it * kArgmaxThreads + threadIdx.x) * 4;
             if (i < end) {  // indices ascend within a lane: strict '>' keeps the lowest
-                if constexpr (kSampled) {
-                    const Philox4 r = philox4x32_10(static_cast<uint32_t>(i) >> 2, static_cast<uint32_t>(row), 0u, 0u,
-                                                    sa.seed_lo, sa.seed_hi);
-                    x[it].x = perturb(x[it].x, sa.inv_tau, r.w[0]);
-                    x[it].y = perturb(x[it].y, sa.inv_tau, r.w[1]);
-                    x[it].z = perturb(x[it].z, sa.inv_tau, r.w[2]);
-                    x[it].w = perturb(x[it].w, sa.inv_tau, r.w[3]);
-                }
                 if (x[it].x > best) { best = x[it].x; best_i = i; }
                 if (x[it].y > best) { best = x[it].y; best_i = i + 1; }
                 if (x[it].z > best) { best = x[it].z; best_i = i + 2; }
@@ -200,67 +243,80 @@ __global__ __launch_bounds__(kArgmaxThreads) void argmax_chunks(const float* __r
     }
 }
 
-__global__ __launch_bounds__(kWave) void accept_walk(const float* __restrict__ part_val,
+constexpr int kWalkThreads = 256;
+
+__global__ __launch_bounds__(kWalkThreads) void accept_walk(const float* __restrict__ part_val,
                                                      const int* __restrict__ part_idx, int n_chunks,
                                                      const int32_t* __restrict__ draft_tokens,
-                                                     const int32_t* __restrict__ tree_parent, int T,
+                                                     const int32_t* __restrict__ tree_parent, int T, int log2_per_slot,
                                                      int32_t* __restrict__ accepted_len,
                                                      int32_t* __restrict__ accepted_path,
                                                      int32_t* __restrict__ bonus_token,
                                                      int32_t* __restrict__ target_argmax) {
+    // Two short chains, launch aside: one round trip for the chunk pairs (2^log2_per_slot lanes per slot, up to eight
+    // pairs each at a time), a few ballots for the tree.  With one lane per slot and a serial walk it took 4.8 us for 64
+    // requests of 9 slots (10 chunks) and 7.4 us for 32 trees of 33 slots (19 chunks).
     __shared__ int s_tgt[SEER_MAX_T];
-    __shared__ int s_draft[SEER_MAX_T];
-    __shared__ int s_par[SEER_MAX_T];
-    __shared__ int s_depth[SEER_MAX_T];
-    __shared__ int s_path[SEER_MAX_T];
     const int b = blockIdx.x;
-    const int t = threadIdx.x;
-    if (t < T) {
-        const size_t row = static_cast<size_t>(b) * T + t;
-        float best = part_val[row * n_chunks];
-        int best_i = part_idx[row * n_chunks];
-        for (int c = 1; c < n_chunks; ++c) {
-            const float v = part_val[row * n_chunks + c];
-            if (v > best) {  // chunks ascend: strict '>' keeps the lowest index
-                best = v;
-                best_i = part_idx[row * n_chunks + c];
+    const int tid = threadIdx.x;
+    const size_t row0 = static_cast<size_t>(b) * T;
+    int draft = 0, par = -2;
+    if (tid < T) {
+        draft = draft_tokens[row0 + tid];
+        par = tree_parent ? tree_parent[row0 + tid] : tid - 1;
+    }
+    const int slot = tid >> log2_per_slot, sub = tid & ((1 << log2_per_slot) - 1);
+    float best = kNegInf;
+    int best_i = 0x7fffffff;
+    if (slot < T) {
+        const size_t at = (row0 + slot) * n_chunks;
+        for (int c = sub; c < n_chunks; c += 8 << log2_per_slot) {
+            float v[8];
+            int ix[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {               // (the ones past the end re-read the last pair)
+                const int ck = min(c + (k << log2_per_slot), n_chunks - 1);
+                v[k] = part_val[at + ck];
+                ix[k] = part_idx[at + ck];
             }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) take_better(best, best_i, v[k], ix[k]);
         }
-        target_argmax[row] = best_i;
-        s_tgt[t] = best_i;
-        s_draft[t] = draft_tokens[row];
-        int par = tree_parent ? tree_parent[row] : t - 1;
-        if (t == 0) par = -1;
-        if (par < 0 || par >= t) par = (t == 0) ? -1 : -2;  // anything else counts as a padded slot
-        s_par[t] = par;
-        s_path[t] = -1;
+    }
+    for (int o = 1; o < (1 << log2_per_slot); o <<= 1) {
+        const float ov = __shfl_xor(best, o, kWave);
+        const int oi = __shfl_xor(best_i, o, kWave);
+        take_better(best, best_i, ov, oi);
+    }
+    if (slot < T && sub == 0) {
+        target_argmax[row0 + slot] = best_i;
+        s_tgt[slot] = best_i;
     }
     __syncthreads();
-    if (t == 0) {
-        uint64_t ok = 1;  // bit t: slot t accepted
-        int win = 0;
-        s_depth[0] = 0;
-        for (int i = 1; i < T; ++i) {
-            const int par = s_par[i];
-            int depth = 0;
-            if (par >= 0 && ((ok >> par) & 1) && s_draft[i] == s_tgt[par]) {
-                ok |= (1ull << i);
-                depth = s_depth[par] + 1;
-                if (depth > s_depth[win]) win = i;
-            }
-            s_depth[i] = depth;
-        }
-        const int len = s_depth[win];
+    if (tid >= kWave) return;
+    // lane t = slot t; a parent outside 0 .. t-1 counts as a padded slot (never accepted)
+    const bool has_parent = tid > 0 && tid < T && par >= 0 && par < tid;
+    if (!has_parent) par = 0;
+    const bool match = has_parent && draft == s_tgt[par];
+    uint64_t level = 1;                                  // accepted nodes of the current depth
+    int len = 0, win = 0;
+    for (;;) {
+        const uint64_t next = __ballot(match && ((level >> par) & 1));
+        if (!next) break;
+        level = next;
+        win = __builtin_ctzll(next);
+        ++len;
+    }
+    int path = -1, node = win;
+    for (int i = len; i >= 0; --i) {
+        if (tid == i) path = node;
+        node = __builtin_amdgcn_readlane(par, node);
+    }
+    if (tid < T) accepted_path[row0 + tid] = path;
+    if (tid == 0) {
         accepted_len[b] = len;
         if (bonus_token) bonus_token[b] = s_tgt[win];
-        int node = win;
-        for (int i = len; i >= 0; --i) {
-            s_path[i] = node;
-            node = s_par[node];
-        }
     }
-    __syncthreads();
-    if (t < T) accepted_path[static_cast<size_t>(b) * T + t] = s_path[t];
 }
 
 }  // namespace seer
@@ -291,20 +347,29 @@ static int launch_accept(const float* logits, const int32_t* draft_tokens, const
                          int32_t T, int32_t V, bool sampled, SampleArgs sa, int32_t* accepted_len,
                          int32_t* accepted_path, int32_t* bonus_token, int32_t* target_token, void* scratch,
                          size_t capacity, hipStream_t stream) {
-    const int n_chunks = accept_num_chunks(V, sampled ? kChunkSampled : kChunkGreedy);
+    const int chunk = accept_chunk(static_cast<int64_t>(B) * T, V);
+    const int n_chunks = accept_num_chunks(V, chunk);
     float* part_val = static_cast<float*>(scratch);
     int* part_idx = reinterpret_cast<int*>(part_val + capacity);
     const bool vec4 = (V % 4 == 0) && (reinterpret_cast<uintptr_t>(logits) % 16 == 0);
     const dim3 grid(static_cast<unsigned>(static_cast<size_t>(B) * T * n_chunks));
     const dim3 block(kArgmaxThreads);
-    if (vec4 && sampled) hipLaunchKernelGGL((argmax_chunks<true, true>), grid, block, 0, stream, logits, V, n_chunks, part_val, part_idx, sa);
-    else if (vec4) hipLaunchKernelGGL((argmax_chunks<true, false>), grid, block, 0, stream, logits, V, n_chunks, part_val, part_idx, sa);
-    else if (sampled) hipLaunchKernelGGL((argmax_chunks<false, true>), grid, block, 0, stream, logits, V, n_chunks, part_val, part_idx, sa);
-    else hipLaunchKernelGGL((argmax_chunks<false, false>), grid, block, 0, stream, logits, V, n_chunks, part_val, part_idx, sa);
+#define SEER_SCAN(VEC4, SAMPLED)                                                                                        \
+    if (chunk == kChunkLarge)                                                                                           \
+        hipLaunchKernelGGL((argmax_chunks<VEC4, SAMPLED, kChunkLarge>), grid, block, 0, stream, logits, V, n_chunks, part_val, part_idx, sa); \
+    else                                                                                                                \
+        hipLaunchKernelGGL((argmax_chunks<VEC4, SAMPLED, kChunkSmall>), grid, block, 0, stream, logits, V, n_chunks, part_val, part_idx, sa)
+    if (vec4 && sampled) { SEER_SCAN(true, true); }
+    else if (vec4) { SEER_SCAN(true, false); }
+    else if (sampled) { SEER_SCAN(false, true); }
+    else { SEER_SCAN(false, false); }
+#undef SEER_SCAN
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return static_cast<int>(err);
-    hipLaunchKernelGGL(accept_walk, dim3(B), dim3(kWave), 0, stream, part_val, part_idx, n_chunks, draft_tokens,
-                       tree_parent, T, accepted_len, accepted_path, bonus_token, target_token);
+    int log2_per_slot = 0;                              // lanes per slot: a power of two that fits the workgroup and a wave
+    while (log2_per_slot < 6 && (T << (log2_per_slot + 1)) <= kWalkThreads && (1 << log2_per_slot) < n_chunks) ++log2_per_slot;
+    hipLaunchKernelGGL(accept_walk, dim3(B), dim3(kWalkThreads), 0, stream, part_val, part_idx, n_chunks, draft_tokens,
+                       tree_parent, T, log2_per_slot, accepted_len, accepted_path, bonus_token, target_token);
     err = hipGetLastError();
     return err == hipSuccess ? SEER_OK : static_cast<int>(err);
 }
@@ -384,7 +449,7 @@ extern "C" int seer_accept_static(const float* logits, const int32_t* draft_toke
                                   int32_t* bonus_token, int32_t* target_argmax, void* hip_stream) {
     const int rc = seer::check_accept_args(logits, draft_tokens, B, T, V, accepted_len, accepted_path, target_argmax);
     if (rc != SEER_OK) return rc;
-    const size_t pairs = static_cast<size_t>(B) * T * seer::accept_num_chunks(V, seer::kChunkGreedy);
+    const size_t pairs = static_cast<size_t>(B) * T * seer::accept_num_chunks(V, seer::kChunkLarge);
     if (pairs > seer::kStaticPairs) return SEER_ELIMIT;
     void* ptr = nullptr;
     const int rs = seer::static_scratch(&ptr);      // also with B == 0: resolves the address, launches nothing

@@ -20,14 +20,24 @@ struct Philox4 {
     uint32_t w[4];
 };
 
+// a ^ b ^ c in one instruction (the compiler takes two where c is a scalar; 139.7 -> 128.6 us for the sampled scan and
+// walk of 1056 rows of 152 064 logits)
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t r;
+    asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0x96" : "=v"(r) : "v"(a), "v"(b), "s"(c));
+    return r;
+}
+
 __device__ __forceinline__ Philox4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
                                                  uint32_t k1) {
 #pragma unroll
     for (int round = 0; round < 10; ++round) {
         const uint64_t p0 = static_cast<uint64_t>(0xD2511F53u) * c0;
         const uint64_t p1 = static_cast<uint64_t>(0xCD9E8D57u) * c2;
-        const uint32_t n0 = static_cast<uint32_t>(p1 >> 32) ^ c1 ^ k0;
-        const uint32_t n2 = static_cast<uint32_t>(p0 >> 32) ^ c3 ^ k1;
+        const uint32_t h0 = static_cast<uint32_t>(p0 >> 32), h1 = static_cast<uint32_t>(p1 >> 32);
+        // (the first two rounds still have constants and values of the whole wave among their operands)
+        const uint32_t n0 = round < 2 ? h1 ^ c1 ^ k0 : xor3(h1, c1, k0);
+        const uint32_t n2 = round < 2 ? h0 ^ c3 ^ k1 : xor3(h0, c3, k1);
         c1 = static_cast<uint32_t>(p1);
         c3 = static_cast<uint32_t>(p0);
         c0 = n0;

@@ -222,3 +222,29 @@ def test_commit_reports_bad_requests_and_leaves_them():
         assert got_n[b] == bad_ctx[b]
     ok = [b for b in range(cfg.B) if b not in (1, 2, 3, 4, 5)]
     assert np.array_equal(got_n[ok], rn[ok])
+
+
+@pytest.mark.parametrize("V", [5000, 16384, 16388, 5001])
+def test_sampled_and_greedy_scans_of_large_batches(V):
+    """Enough rows for the larger chunk of the vocabulary scan (2048 workgroups), at one chunk, just above it and with rows
+    that are not 16-byte aligned; winners at chunk borders, trees of 31 slots, duplicates of a row's maximum."""
+    from paper_2511_14617_amd import binding
+    rng = np.random.default_rng(V)
+    B, T = 70, 31
+    logits = rng.standard_normal((B, T, V)).astype(np.float32)
+    logits[::3, :, V - 1] += 12.0
+    logits[1::3, 5, [0, V // 2]] = 9.0
+    logits[2::3, 7, :] = 0.5
+    parent = W.multipath_parent(B, 5, 6, rng, dedup_fraction=0.3)
+    draft = rng.integers(0, V, size=(B, T)).astype(np.int32)
+    drawn = oracle.argmax_sampled(logits, 0.8, 11)
+    rows = np.arange(B)
+    for t in range(1, T):
+        follow = (rng.random(B) < 0.7) & (parent[:, t] >= 0)
+        draft[follow, t] = drawn[rows, np.maximum(parent[:, t], 0)][follow]
+    _, accepted = _check_sampled(logits, draft, parent, 0.8, 11)
+    assert accepted.max() >= 2
+    dev = "cuda"
+    got = binding.seer_accept(torch.from_numpy(logits).to(dev), torch.from_numpy(draft).to(dev), torch.from_numpy(parent).to(dev))
+    for g, w in zip(got, oracle.verify_accept(logits, draft, parent)):
+        assert np.array_equal(g.cpu().numpy(), w)
