@@ -49,7 +49,10 @@ constexpr int kTableSlots = 4096;         // LDS hash table: 4096 x (key, count)
 constexpr uint32_t kEmpty = 0xffffffffu;
 constexpr int kMaxParts = 256;            // stretches a group's tokens are cut into, at most
 constexpr int kReqWindow = 64;            // request ids a match workgroup looks at per round
-constexpr int kQuads = 4;                 // 16-byte loads a match thread has in flight
+// 16-byte loads a match thread has in flight.  Two (2048 tokens a workgroup): the per-request part of the scan is a chain whose
+// length grows with the tokens a thread holds, and the launch has workgroups to spare (whole call, 16 requests of 6 k tokens
+// 44.5 us with four, 37.7 with two, 36.4 with one; 128 requests, four paths: 126, 121, 125).
+constexpr int kQuads = 2;
 constexpr int kTile = 4 * kQuads * kMatchThreads;   // tokens a match workgroup takes per round
 constexpr int kTokensPerPart = kTile;     // target length of a stretch: one round
 constexpr int kSmall = 2048;              // up to this many places the expansion holds in registers
@@ -765,10 +768,28 @@ __global__ __launch_bounds__(kThreads) void draft_expand_kernel(Args a) {
     // places of the longest match, part by part: how many come before part p
     if (tid < a.parts) x.hdr[tid] = make_int2(h.y == p_star ? h.x : 0, h.y);
     __syncthreads();
-    if (tid <= a.parts) {
-        int acc = 0;
-        for (int p = 0; p < tid; ++p) acc += x.hdr[p].x;
-        x.first[tid] = acc;
+    // (at most kMaxParts = 256 of them: wave 0 takes four each; a running sum per thread cost 3 us with 200 stretches)
+    if (tid < 64) {
+        int c[kMaxParts / 64], sum = 0;
+#pragma unroll
+        for (int k = 0; k < kMaxParts / 64; ++k) {
+            const int p = tid * (kMaxParts / 64) + k;
+            c[k] = p < a.parts ? x.hdr[p].x : 0;
+            sum += c[k];
+        }
+        int incl = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int up = __shfl_up(incl, o, 64);
+            if (tid >= o) incl += up;
+        }
+        int before = incl - sum;
+#pragma unroll
+        for (int k = 0; k < kMaxParts / 64; ++k) {
+            x.first[tid * (kMaxParts / 64) + k] = before;
+            before += c[k];
+        }
+        if (tid == 63) x.first[kMaxParts] = before;
     }
     __syncthreads();
     const int n_kept = p_star > 0 ? x.first[a.parts] : 0;        // >= the places of the longest match
