@@ -58,7 +58,14 @@ struct ReqSlots {
 };
 
 constexpr int kPlanTile = 32;          // tokens per scheduling tile
-constexpr int kMinTilesPerWg = 4;      // do not cut finer than 128 tokens
+// Tiles of a stretch, at least, where the batch is too short for the chip: one tile where a workgroup's time is the chain of its
+// tiles (whole call, 4 requests of 64 .. 512 tokens: 22.7 us with four tiles, 21.1 with two, 17.9 with one; 2 requests of
+// 64 .. 600 with heads of 64: 21.5, 18.6, 17.7; batches that fill the chip do not change).  The shared-latent kernel, whose pieces
+// leave partial results of 256 KB per row block, and the general kernel keep four (2 requests of 1000 .. 4000 tokens: 56.2 us
+// with four, 58.4 with one).
+constexpr int kMinTilesLatent = 4, kMinTiles = 1;
+// Stretches follow the measured speeds only from here on (tiles per stretch): below, rounding to tiles decides.
+constexpr int kMinTilesWeighted = 8;
 constexpr int kDefaultMaxSplits = 256;
 constexpr int kNumCU = 256;            // MI355X
 
@@ -198,6 +205,7 @@ struct AttnArgs {
     float* fb_speed;            // [wgs_per_head] smoothed tiles per tick (owned by the plan kernel)
     int32_t fixed_split;        // 1: equal stretches, no history read or written
     int32_t balanced;           // 0: one workgroup per request (max_splits == 1), no history either
+    int32_t min_tiles;          // tiles of a stretch, at least (see kMinTiles)
     int32_t stream_only;        // 1: the tiled D = 128 kernel only streams its tiles (diagnostic)
     int32_t stream_partials;    // 1: the tiled D = 128 kernel writes its partial results with non-temporal stores
     int32_t row_blocks, rows_per_block;   // tiled D = 128 kernel: workgroups per (stretch, KV head), rows of each

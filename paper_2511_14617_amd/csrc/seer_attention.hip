@@ -36,7 +36,7 @@ constexpr int kPlanLdsRequests = 4096;   // tile offsets of this many requests a
 struct PlanArgs {
     const int32_t* ctx_len;
     const int32_t* block_table;
-    int B, T, max_ctx, wgs_per_head, max_splits, fixed_split, max_pages, page_size;
+    int B, T, max_ctx, wgs_per_head, max_splits, fixed_split, max_pages, page_size, min_tiles;
     PlanHeader* header;
     ReqSlots* req_slots;
     int32_t* tile_off;
@@ -217,11 +217,11 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs p) {
     if (balanced) {
         // ---- the stretches ----------------------------------------------------------------------------------------------
         // a request of t tiles touches at most ceil(t / Lmin) + 1 stretches, which must fit max_splits
-        const int Lmin = max(kMinTilesPerWg, (longest + p.max_splits - 2) / (p.max_splits - 1));
+        const int Lmin = max(p.min_tiles, (longest + p.max_splits - 2) / (p.max_splits - 1));
         // Stretch w begins at the tile nearest to total * (r_0 + .. + r_{w-1}) / R.  When the line is too
         // short for that to keep every stretch at Lmin tiles or more, cut it into equal stretches of
         // max(Lmin, ceil(total / W)) tiles instead (the last ones are then short or empty).
-        const bool weighted = static_cast<long long>(total) >= 2ll * Lmin * W;
+        const bool weighted = static_cast<long long>(total) >= static_cast<long long>(max(2 * Lmin, kMinTilesWeighted)) * W;
         const float mean = speed_known > 0.f ? speed_sum / speed_known : 1.f;
         float rate = 0.f;
         if (tid < W) rate = fminf(fmaxf((weighted && est > 0.f) ? est / mean : 1.f, 0.75f), 4.f / 3.f);
@@ -326,6 +326,7 @@ hipError_t launch_plan(const AttnArgs& a, const WorkspaceLayout& w, hipStream_t 
     p.fb_tiles = a.fb_tiles;
     p.fb_speed = a.fb_speed;
     p.fixed_split = a.fixed_split;
+    p.min_tiles = a.min_tiles;
     hipLaunchKernelGGL(plan_kernel, dim3(2), dim3(kPlanThreads), 0, stream, p);
     return hipGetLastError();
 }
@@ -726,12 +727,14 @@ int run_verify_attention(void* out, const void* q, const void* k_pages, const vo
     a.wgs_per_head = w.wgs_per_head;
     a.scale_log2 = p->scale * seer::kLog2e;
 
+    const bool tiled_ok = !(p->flags & SEER_ATTN_GENERAL_KERNEL);
+    a.min_tiles = tile_kernel || (tiled_ok && seer::gqa128_supports(a)) ? seer::kMinTiles : seer::kMinTilesLatent;
+
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     // the plan depends on the shape and on ctx_len only: the layers of one step can share it
     hipError_t err = (p->flags & SEER_ATTN_REUSE_PLAN) ? hipSuccess : seer::launch_plan(a, w, stream);
     if (err != hipSuccess) return static_cast<int>(err);
     if (ev_begin && (err = hipEventRecord(ev_begin, stream)) != hipSuccess) return static_cast<int>(err);
-    const bool tiled_ok = !(p->flags & SEER_ATTN_GENERAL_KERNEL);
     if (tiled_ok && seer::gqa128_supports(a)) err = seer::launch_gqa128(a, stream);
     else if (tiled_ok && seer::mla_supports(a)) err = seer::launch_mla(a, stream);
     else if (tile_kernel) err = seer::launch_tile(a, stream);
