@@ -248,3 +248,26 @@ def test_sampled_and_greedy_scans_of_large_batches(V):
     got = binding.seer_accept(torch.from_numpy(logits).to(dev), torch.from_numpy(draft).to(dev), torch.from_numpy(parent).to(dev))
     for g, w in zip(got, oracle.verify_accept(logits, draft, parent)):
         assert np.array_equal(g.cpu().numpy(), w)
+
+
+@pytest.mark.parametrize("dims,Hkv,page", [((128, 128), 8, 16), ((256, 256), 5, 32), ((64, 64), 16, 7)])
+def test_commit_moves_the_heads_of_long_paths_in_batches(dims, Hkv, page):
+    """Two paths of 30 nodes: the rows of all heads are more than a workgroup holds at once; the second path is accepted to
+    every depth from nothing to its end, so that rows move onto rows that are still to be read."""
+    from paper_2511_14617_amd import binding
+    B, T = 8, 61
+    cfg = W.CONFIGS[5].scaled(B=B, group_size=B, T=T, tree=(2, 30), Hq=Hkv, Hkv=Hkv, Dqk=dims[0], Dv=dims[1], page_size=page,
+                              ctx=("uniform", 61, 300), shared_prefix=0)
+    inp = W.make_attention_inputs(cfg, values="peaked")
+    alen = np.array([0, 1, 2, 7, 15, 29, 30, 30], dtype=np.int32)
+    path = np.full((B, T), -1, dtype=np.int32)
+    for b in range(B):
+        path[b, : alen[b] + 1] = [0] + [31 + i for i in range(alen[b])]
+    rk, rv, rn = oracle.kv_commit(inp.k_pages, inp.v_pages, inp.block_table, inp.ctx_len, alen, path)
+    d = attention_device_inputs(inp)
+    binding.seer_kv_commit(d["k_pages"], d["v_pages"], d["block_table"], d["ctx_len"], torch.from_numpy(alen).cuda(),
+                           torch.from_numpy(path).cuda())
+    torch.cuda.synchronize()
+    assert np.array_equal(d["ctx_len"].cpu().numpy(), rn)
+    assert np.array_equal(d["k_pages"].view(torch.int16).cpu().numpy().view(np.uint16), rk)
+    assert np.array_equal(d["v_pages"].view(torch.int16).cpu().numpy().view(np.uint16), rv)
