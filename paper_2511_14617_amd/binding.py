@@ -118,13 +118,20 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+# The handle of the current device's current stream without building a Stream object (1.5 us of a call that launches
+# for 10); torch versions without the raw accessor take the object.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_handle(stream: Optional[torch.cuda.Stream]) -> Optional[int]:
+    if stream is None and _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device()) or None
     s = torch.cuda.current_stream() if stream is None else stream
     return s.cuda_stream or None
 
 
 def _want(t: torch.Tensor, dtype, shape, name: str) -> None:
-    if t.dtype != dtype or tuple(t.shape) != tuple(shape) or not t.is_contiguous() or not t.is_cuda:
+    if t.dtype != dtype or t.shape != shape or not t.is_contiguous() or not t.is_cuda:
         raise ValueError("%s: want contiguous device %s%s, got %s%s on %s" %
                          (name, dtype, tuple(shape), t.dtype, tuple(t.shape), t.device))
 
@@ -177,8 +184,8 @@ def seer_verify_attention(q: torch.Tensor, k_pages: torch.Tensor, v_pages: Optio
         out = torch.empty((p.B, p.T, p.Hq, p.Dv), dtype=torch.bfloat16, device=q.device)
     else:
         _want(out, torch.bfloat16, (p.B, p.T, p.Hq, p.Dv), "out")
-    need = int(lib.seer_verify_attention_workspace(ctypes.byref(p)))
     if workspace is None:
+        need = int(lib.seer_verify_attention_workspace(ctypes.byref(p)))
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=q.device)
     args = (_ptr(out), _ptr(q), _ptr(k_pages), _ptr(v_pages), _ptr(block_table), _ptr(ctx_len), _ptr(tree_mask),
             ctypes.byref(p), _ptr(workspace), workspace.numel(), _stream_handle(stream))
@@ -231,8 +238,8 @@ def seer_accept(logits: torch.Tensor, draft_tokens: torch.Tensor, tree_parent: O
         _want(path, torch.int32, (B, T), "accepted_path")
         _want(bonus, torch.int32, (B,), "bonus_token")
         _want(tgt, torch.int32, (B, T), "target_argmax")
-    need = int(lib.seer_accept_workspace(B, T, V))
     if workspace is None:
+        need = int(lib.seer_accept_workspace(B, T, V))
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=dev)
     if temperature is None:
         _check(lib.seer_accept(_ptr(logits), _ptr(draft_tokens), _ptr(tree_parent), B, T, V, _ptr(alen), _ptr(path),
@@ -391,8 +398,8 @@ def seer_draft(tokens: torch.Tensor, seq_start: torch.Tensor, seq_len: torch.Ten
         _want(d_len, torch.int32, (B,), "match_len")
     if status is not None:
         _want(status, torch.int32, (1,), "status")
-    need = int(lib.seer_draft_workspace(ctypes.byref(p)))
     if workspace is None:
+        need = int(lib.seer_draft_workspace(ctypes.byref(p)))
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
     _check(lib.seer_draft(_ptr(tokens), _ptr(seq_start), _ptr(seq_len), _ptr(group_first), _ptr(req_group),
                           _ptr(pattern), _ptr(pattern_len), _ptr(max_spec_tokens), ctypes.byref(p), _ptr(d_tok),
