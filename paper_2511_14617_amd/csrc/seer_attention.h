@@ -47,9 +47,10 @@ constexpr uint32_t kFeedbackMagic = 0x5ee2fb01u;
 constexpr int kMaxWgsPerHead = 1024;   // 256 CUs x 4 resident workgroups, one KV head
 
 // A stretch as its workgroups need it, in one 16-byte load: the request in which it starts (-1: nothing to do), its tiles
-// on the line, and what to add to a request's index to get the slot of its piece.
+// on the line, and that request's first tile (with it the first page ids can be requested beside the request's other words
+// instead of behind them).
 struct StretchRec {
-    int32_t b, tile_begin, tile_end, slot_bias;
+    int32_t b, tile_begin, tile_end, req_begin;
 };
 
 // The partial slots of a request.

@@ -253,21 +253,22 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs p) {
     // ---- per stretch: where it starts ------------------------------------------------------------------------------------
     for (int w = tid; w < W; w += kPlanThreads) {
         StretchRec r;
+        auto off = [&](int b) -> int { return in_lds ? s_off[b] : p.tile_off[b]; };
         if (balanced) {
-            r.tile_begin = s_start[w], r.tile_end = s_start[w + 1], r.slot_bias = w;
-            r.b = -1;
+            r.tile_begin = s_start[w], r.tile_end = s_start[w + 1];
+            r.b = -1, r.req_begin = 0;
             if (r.tile_begin < r.tile_end) {             // the last request that starts at or before the first tile
                 int lo = 0, hi = p.B - 1;
                 while (lo < hi) {
                     const int mid = (lo + hi + 1) >> 1;
-                    const int off = in_lds ? s_off[mid] : p.tile_off[mid];
-                    if (off <= r.tile_begin) lo = mid; else hi = mid - 1;
+                    if (off(mid) <= r.tile_begin) lo = mid; else hi = mid - 1;
                 }
                 r.b = lo;
+                r.req_begin = off(lo);
             }
         } else {
-            r.tile_begin = in_lds ? s_off[w] : p.tile_off[w], r.tile_end = in_lds ? s_off[w + 1] : p.tile_off[w + 1];
-            r.slot_bias = 0;
+            r.tile_begin = off(w), r.tile_end = off(w + 1);
+            r.req_begin = r.tile_begin;
             r.b = r.tile_begin < r.tile_end ? w : -1;
         }
         p.stretch[w] = r;
@@ -358,7 +359,7 @@ __global__ __launch_bounds__(kGenThreads) void attn_general_kernel(AttnArgs a) {
     const int n = a.ctx_len[b];
     const int piece_begin = (g - t_lo) * kPlanTile, piece_end = min(n, (min(rec.tile_end, t_hi) - t_lo) * kPlanTile);
     g = t_hi;
-    const int item_idx = b + rec.slot_bias;
+    const int item_idx = b + (a.balanced ? static_cast<int>(blockIdx.x) : 0);
     const int n0 = n - a.T;
     const uint64_t word = a.tree_mask ? a.tree_mask[static_cast<size_t>(b) * a.T + t]
                                       : (t >= 63 ? ~0ull : ((1ull << (t + 1)) - 1));

@@ -548,6 +548,7 @@ __device__ __forceinline__ void run(const AttnArgs& a, unsigned char* lds) {
     const StretchRec rec = uniform_stretch(a.stretch + wg);
     int b = rec.b;
     if (b < 0) return;
+    const int slot_bias = a.balanced ? wg : 0;
     int g = rec.tile_begin;
     const int g_end = rec.tile_end;
     const uint64_t clock_begin = __builtin_amdgcn_s_memrealtime();
@@ -578,24 +579,24 @@ __device__ __forceinline__ void run(const AttnArgs& a, unsigned char* lds) {
         if (lane == 3) ptr = a.shared_tiles + bc;
         return *ptr;
     };
-    auto first_pages = [&](int bb) __attribute__((always_inline)) -> int {
-        return (a.block_table + static_cast<size_t>(min(bb, a.B - 1)) * a.max_pages)[min(lane, a.max_pages - 1)];
+    auto first_pages = [&](int bb, int page0) __attribute__((always_inline)) -> int {
+        return (a.block_table + static_cast<size_t>(min(bb, a.B - 1)) * a.max_pages)[min(page0 + lane, a.max_pages - 1)];
     };
     int pw = piece_words(b);
-    int pg_ahead = 0;
-    bool have_ahead = false;
+    int page_ahead = ((g - rec.req_begin) * kTile) >> page_shift;       // (see the kernel below)
+    int pg_ahead = first_pages(b, page_ahead);
     const int g_first = g;
 
   for (; g < g_end; ++b) {
     const int t_lo = __builtin_amdgcn_readlane(pw, 0), t_hi = __builtin_amdgcn_readlane(pw, 1);
-    const int item_idx = b + rec.slot_bias;
+    const int item_idx = b + slot_bias;
     const int n = __builtin_amdgcn_readlane(pw, 2);
     const int shared_tiles = __builtin_amdgcn_readlane(pw, 3);
     const int pg_first = pg_ahead;
-    const bool have_first = have_ahead;
+    const int page_first = page_ahead;
     pw = piece_words(b + 1);
-    pg_ahead = first_pages(b + 1);
-    have_ahead = b + 1 < a.B;
+    pg_ahead = first_pages(b + 1, 0);
+    page_ahead = 0;
     if (t_hi == t_lo) continue;
     const int tok_begin = (g - t_lo) * kTile;
     const int tok_end = min(n, (min(g_end, t_hi) - t_lo) * kTile);
@@ -652,9 +653,8 @@ __device__ __forceinline__ void run(const AttnArgs& a, unsigned char* lds) {
         }
         return pg;
     };
-    const bool window_ahead = have_first && tok_begin == 0;
-    int cache_base = window_ahead ? 0 : -0x40000000;
-    int pg_cache = window_ahead ? in_pool(pg_first, lane) : 0;
+    int cache_base = page_first;
+    int pg_cache = in_pool(pg_first, page_first + lane);
     // byte offset in a pool of the 16-row half of tile tb that holds this wave's block
     auto half_offset = [&](int tb) __attribute__((always_inline)) -> size_t {
         const int lp = tb >> page_shift;                 // 16-token pages: a tile is page lp (even) and lp + 1
@@ -902,6 +902,7 @@ void attn_gqa128_kernel(AttnArgs a) {
     const StretchRec rec = uniform_stretch(a.stretch + wg);
     int b = rec.b;
     if (b < 0) return;
+    const int slot_bias = a.balanced ? wg : 0;
     int g = rec.tile_begin;
     const int g_end = rec.tile_end;
     const int g_first = g;
@@ -942,23 +943,25 @@ void attn_gqa128_kernel(AttnArgs a) {
         if (lane == 3) ptr = a.shared_tiles + bc;
         return *ptr;
     };
-    auto first_pages = [&](int bb) __attribute__((always_inline)) -> int {
-        return (a.block_table + static_cast<size_t>(min(bb, a.B - 1)) * a.max_pages)[min(lane, a.max_pages - 1)];
+    auto first_pages = [&](int bb, int page0) __attribute__((always_inline)) -> int {
+        return (a.block_table + static_cast<size_t>(min(bb, a.B - 1)) * a.max_pages)[min(page0 + lane, a.max_pages - 1)];
     };
     int pw = piece_words(b);
-    int pg_ahead = 0;                 // the first 64 page ids of request b, if have_ahead
-    bool have_ahead = false;
+    // 64 page ids of request b from page page_ahead on, where its next piece starts (a stretch starts inside a request, every
+    // other piece at its request's first page)
+    int page_ahead = ((g - rec.req_begin) * kTile) >> page_shift;
+    int pg_ahead = first_pages(b, page_ahead);
 
   for (; g < g_end; ++b) {
     const int t_lo = __builtin_amdgcn_readlane(pw, 0), t_hi = __builtin_amdgcn_readlane(pw, 1);
-    const int item_idx = b + rec.slot_bias;
+    const int item_idx = b + slot_bias;
     const int n = __builtin_amdgcn_readlane(pw, 2);
     const int shared_tiles = __builtin_amdgcn_readlane(pw, 3);
     const int pg_first = pg_ahead;
-    const bool have_first = have_ahead;
+    const int page_first = page_ahead;
     pw = piece_words(b + 1);          // in flight while this piece is worked on
-    pg_ahead = first_pages(b + 1);
-    have_ahead = b + 1 < a.B;
+    pg_ahead = first_pages(b + 1, 0);
+    page_ahead = 0;
     if (t_hi == t_lo) continue;
     const int tok_begin = (g - t_lo) * kTile;
     const int tok_end = min(n, (min(g_end, t_hi) - t_lo) * kTile);
@@ -1009,10 +1012,9 @@ void attn_gqa128_kernel(AttnArgs a) {
         }
         return pg;
     };
-    // a piece that starts at its request's first tile finds that window of page ids fetched ahead
-    const bool window_ahead = have_first && tok_begin == 0;
-    int cache_base = window_ahead ? 0 : -0x40000000;
-    int pg_cache = window_ahead ? in_pool(pg_first, lane) : 0;
+    // the window of page ids that the piece starts in has been fetched ahead
+    int cache_base = page_first;
+    int pg_cache = in_pool(pg_first, page_first + lane);
     auto page_pair = [&](int tb, size_t& p0, size_t& p1) __attribute__((always_inline)) {
         const int lp = tb >> page_shift;
         if (lp < cache_base || lp >= cache_base + kWave) {   // uniform

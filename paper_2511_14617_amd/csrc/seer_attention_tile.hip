@@ -111,6 +111,7 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
     const StretchRec rec = uniform_stretch(a.stretch + wg);
     int b = rec.b;
     if (b < 0) return;
+    const int slot_bias = a.balanced ? wg : 0;
     int g = rec.tile_begin;
     const int g_end = rec.tile_end;
     const int g_first = g;
@@ -136,7 +137,7 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
   for (; g < g_end; ++b) {
     const int t_lo = uniform_load(a.tile_off + b), t_hi = uniform_load(a.tile_off + b + 1);
     if (t_hi == t_lo) continue;
-    const int item_idx = b + rec.slot_bias;
+    const int item_idx = b + slot_bias;
     const int n = uniform_load(a.ctx_len + b);
     const int tok_begin = (g - t_lo) * kTile;
     const int tok_end = min(n, (min(g_end, t_hi) - t_lo) * kTile);
