@@ -111,9 +111,10 @@ inline int gqa_waves_per_block(int rows_per_block) { return gqa_block_uses_helpe
 // The tiled kernel for the other head sizes (seer_attention_tile.hip): any page size, separate K and V pools, two LDS stages
 // of one K and one V tile, row blocks of as many waves as a workgroup holds.
 inline bool tile_shape(int Dqk, int Dv) { return (Dqk == 64 && Dv == 64) || (Dqk == 256 && Dv == 256) || (Dqk == 192 && Dv == 128); }
-inline bool tile_supports(const seer_attn_params& p) {
-    return tile_shape(p.Dqk, p.Dv) && !p.kv_shared_latent && !(p.flags & SEER_ATTN_GENERAL_KERNEL);
-}
+// The workspace of these shapes is laid out by the shape alone, also for calls that force the general kernel (it walks whatever
+// stretches it finds): a plan is reused by calls whose flags differ.
+inline bool tile_layout(const seer_attn_params& p) { return tile_shape(p.Dqk, p.Dv) && !p.kv_shared_latent; }
+inline bool tile_supports(const seer_attn_params& p) { return tile_layout(p) && !(p.flags & SEER_ATTN_GENERAL_KERNEL); }
 constexpr int tile_stage_kb(int Dqk, int Dv) { return 32 * 2 * (Dqk + Dv) / 1024; }
 constexpr int tile_waves_per_simd(int Dqk) { return Dqk == 64 ? 3 : (Dqk == 256 ? 1 : 2); }
 constexpr int tile_max_waves(int Dqk) { return Dqk == 256 ? 4 : 8; }     // per workgroup
@@ -125,7 +126,7 @@ inline int tile_rows_per_block(int rows, int Dqk) {
 
 // Workgroups of the partition kernel that one CU holds at once, by kernel shape.
 inline int resident_wgs_per_cu(const seer_attn_params& p) {
-    if (tile_supports(p)) {
+    if (tile_layout(p)) {
         const int waves = tile_rows_per_block((p.Hq / p.Hkv) * p.T, p.Dqk) / 32;
         const int by_waves = 4 * tile_waves_per_simd(p.Dqk) / waves;
         const int by_lds = 159 / (2 * tile_stage_kb(p.Dqk, p.Dv) + 1);
@@ -164,7 +165,7 @@ inline WorkspaceLayout workspace_layout(const seer_attn_params& p) {
             const bool tiled = p.Dqk == 128 && p.Dv == 128 && gqa_page_size_ok(p.page_size) && !p.kv_shared_latent &&
                                !(p.flags & SEER_ATTN_GENERAL_KERNEL);
             const int rows = (p.Hq / p.Hkv) * p.T;
-            const int row_blocks = tiled ? gqa_row_blocks(rows) : (tile_supports(p) ? tile_row_blocks(rows, p.Dqk) : 1);
+            const int row_blocks = tiled ? gqa_row_blocks(rows) : (tile_layout(p) ? tile_row_blocks(rows, p.Dqk) : 1);
             w.wgs_per_head = kNumCU * resident_wgs_per_cu(p) / (p.Hkv * row_blocks);
             if (w.wgs_per_head > kMaxWgsPerHead) w.wgs_per_head = kMaxWgsPerHead;
         }

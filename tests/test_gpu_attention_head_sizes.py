@@ -59,6 +59,29 @@ def test_parity(name, dims):
 
 
 @pytest.mark.parametrize("dims", SIZES, ids=lambda d: "%dx%d" % d)
+@pytest.mark.parametrize("max_splits", [0, 1])
+def test_a_plan_serves_calls_whose_flags_differ(dims, max_splits):
+    """The matrix-core and the general kernel share the workspace's layout, so either runs on the other's plan."""
+    from paper_2511_14617_amd import binding
+    # three row blocks at least: where a layout that followed the flag would differ most
+    inp = W.make_attention_inputs(_cfg(dims, B=5, Hq=32, Hkv=2, T=33, tree=(4, 8), ctx=("uniform", 33, 900)), values="peaked")
+    d = attention_device_inputs(inp)
+    kinds = (0, binding.SEER_ATTN_GENERAL_KERNEL)
+    args = (d["q"], d["k_pages"], d["v_pages"], d["block_table"], d["ctx_len"], d["tree_mask"], inp.scale)
+    sizes = [binding.seer_verify_attention_workspace(binding.attn_params(d["q"], d["k_pages"], d["v_pages"], d["block_table"], inp.scale,
+                                                                         dims[1], max_splits, f)) for f in kinds]
+    assert sizes[0] == sizes[1]
+    ws = torch.empty(sizes[0], dtype=torch.uint8, device="cuda")
+    want = binding.seer_verify_attention(*args, Dv=dims[1], max_splits=max_splits).float()
+    for plan in kinds:
+        for use in kinds:
+            binding.seer_verify_attention(*args, Dv=dims[1], max_splits=max_splits, workspace=ws, flags=plan)
+            got = binding.seer_verify_attention(*args, Dv=dims[1], max_splits=max_splits, workspace=ws,
+                                                flags=use | binding.SEER_ATTN_REUSE_PLAN).float()
+            assert float((got - want).abs().max() / want.abs().max()) < 2.0 ** -8   # a bf16 rounding of either
+
+
+@pytest.mark.parametrize("dims", SIZES, ids=lambda d: "%dx%d" % d)
 def test_infinities_and_nan_in_values_reach_only_the_rows_that_see_them(dims):
     """As the general kernel has it: a draft slot that a query does not see must not touch it whatever its V row holds, and
     an infinite V at a visible position gives that infinity."""
