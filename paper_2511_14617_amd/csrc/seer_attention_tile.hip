@@ -6,7 +6,8 @@
 // arithmetic of a CU keeps up with more than its share of the bandwidth even though one wave runs a tile's phases one
 // after the other, so the kernel leaves the overlap to the two to sixteen waves of a CU instead of a hand-placed pipeline.
 // The vector-ALU kernel it stands in for reads every KV token once per query row.  Measured, whole call: 16 requests, 16/4
-// heads of 64, T = 9, 43 687 KV tokens 977 -> 55.9 us; 8/1 heads of 256, T = 5, same lengths 386 -> 65.5 us.
+// heads of 64, T = 9, 43 687 KV tokens 997 -> 32.3 us; 8/1 heads of 256, T = 5, same lengths 396 -> 39.5 us (with the plan
+// and combine kernels as they are now; this kernel alone 21 and 30 us).
 //
 // Work decomposition as in the D = 128 kernel: workgroup (stretch, KV head, row block), wave i owns query rows
 // [32 i, 32 i + 32), the plan's stretches of 32-token tiles, one partial result per request touched.
@@ -134,11 +135,26 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
     const int v_rd = S::kKBytes + (lg * 4 + v_k) * S::kVRow + ((((l16 & 1) * 2 + (v_c4 >> 1)) ^ v_swz<S::kVRow>(v_k)) << 4) +
                      (v_c4 & 1) * 8;                                           // d-tile dt: ^ (dt % n) << 6, + whole periods
 
+    // A piece's start needs the request's first and last tile and its length (lanes 0, 1, 2 of `words`) and its first window of
+    // page ids.  They are requested together, for the first piece right behind the stretch's record and for each further
+    // one while the piece before it is worked on: loaded where they are used they were three round trips more per piece (whole call,
+    // 16 requests, heads of 64: 33.2 -> 32.0 us, of 192/128: 45.5 -> 44.0, of 256: 39.7 -> 39.5).
+    int words = 0, pages = 0;
+    auto request = [&](int req, int first_page) __attribute__((always_inline)) {
+        req = min(req, a.B - 1);
+        words = *(lane < 2 ? a.tile_off + req + lane : a.ctx_len + req);
+        pages = a.block_table[static_cast<size_t>(req) * a.max_pages + min(first_page + lane, a.max_pages - 1)];
+    };
+    request(b, page_of((g - rec.req_begin) * kTile));
+
   for (; g < g_end; ++b) {
-    const int t_lo = uniform_load(a.tile_off + b), t_hi = uniform_load(a.tile_off + b + 1);
-    if (t_hi == t_lo) continue;
+    const int t_lo = __builtin_amdgcn_readlane(words, 0), t_hi = __builtin_amdgcn_readlane(words, 1);
+    if (t_hi == t_lo) {
+        request(b + 1, 0);
+        continue;
+    }
     const int item_idx = b + slot_bias;
-    const int n = uniform_load(a.ctx_len + b);
+    const int n = __builtin_amdgcn_readlane(words, 2);
     const int tok_begin = (g - t_lo) * kTile;
     const int tok_end = min(n, (min(g_end, t_hi) - t_lo) * kTile);
     g = t_hi;
@@ -150,20 +166,21 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
     // ---- page window and tile loads ---------------------------------------------------------
     const int32_t* __restrict__ table = a.block_table + static_cast<size_t>(b) * a.max_pages;
     const int last_page = (n - 1) / a.P;
-    int win = -0x40000000, pg_win = 0;             // lane l holds the (clamped) page id of logical page win + l
+    int win = 0, pg_win = 0;                       // lane l holds the (clamped) page id of logical page win + l
+    auto set_window = [&](int first, int pg) __attribute__((always_inline)) {
+        win = first;
+        if (pg < 0 || pg >= a.num_pages) {
+            if (first + lane <= last_page) bad_page = true;
+            pg = min(max(pg, 0), a.num_pages - 1);
+        }
+        pg_win = pg;
+    };
+    set_window(page_of(tok_begin), pages);
     auto issue_tile = [&](int tile, int stage) __attribute__((always_inline)) {
         const int tb = tok_begin + tile * kTile;
         const int first = page_of(tb);
-        if (first < win || page_of(tb + kTile - 1) >= win + kWave) {          // uniform; a tile spans at most 32 pages
-            win = first;
-            const int idx = win + lane;
-            int pg = table[min(idx, a.max_pages - 1)];
-            if (pg < 0 || pg >= a.num_pages) {
-                if (idx <= last_page) bad_page = true;
-                pg = min(max(pg, 0), a.num_pages - 1);
-            }
-            pg_win = pg;
-        }
+        if (first < win || page_of(tb + kTile - 1) >= win + kWave)            // uniform; a tile spans at most 32 pages
+            set_window(first, table[min(first + lane, a.max_pages - 1)]);
         const int tok = tb + ln, lp = page_of(tok);
         const int pg = __builtin_amdgcn_ds_bpermute((lp - win) << 2, pg_win);
         // row index in the pool (of 128 bytes or more each: 32 bits reach past the memory of the GPU)
@@ -202,6 +219,7 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
             qreg[kk] = as_bf16x8(v);
         }
     }
+    if (g < g_end) request(b + 1, 0);
     // A piece whose accumulators end up with an infinity or a NaN is taken a second time with every tile scanned for V
     // rows that hold one (see the head of the file); otherwise only the tiles with masked slots are.
     f32x16 acc[S::kDTiles];
