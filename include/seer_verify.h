@@ -88,8 +88,8 @@ typedef struct seer_attn_params {
 /* (bit 4 is a measurement aid, see seer_verify_diag.h) */
 /* flags: use the plan that the previous call on this workspace computed instead of planning again.  How the
  * KV stream is cut depends on the shape parameters and on ctx_len only, and a model calls this function
- * once per layer with the same ctx_len: the first layer plans, the others pass this flag (saves a ~10 us
- * kernel per call).  The caller guarantees that the previous call on this workspace had the same
+ * once per layer with the same ctx_len: the first layer plans, the others pass this flag (saves a ~5 us
+ * kernel and its launch per call).  The caller guarantees that the previous call on this workspace had the same
  * parameters (flags apart) and that ctx_len and block_table are unchanged; if not, the output is
  * undefined (every access still stays in bounds).  The status word then accumulates over the calls. */
 #define SEER_ATTN_REUSE_PLAN 8
@@ -98,8 +98,9 @@ typedef struct seer_attn_params {
  * (576,512)} with any page_size >= 1.  Tiled matrix-core kernels exist for
  * Dqk = Dv = 128 with separate K and V pools and a power-of-two page_size of
  * 16..1024 (any G*T: more than 256 query rows per KV head are cut into row
- * blocks), and for the shared latent Dqk = 576, Dv = 512 with a power-of-two
- * page_size of 32..1024; every other combination runs a slower general kernel.
+ * blocks), for the shared latent Dqk = 576, Dv = 512 with a power-of-two
+ * page_size of 32..1024, and for (64,64), (256,256) and (192,128) with separate
+ * pools and any page_size; every other combination runs a slower general kernel.
  *
  * Shared prompt pages (Section 2.3: the responses of a group are sampled for the same prompt): where a request's
  * block_table row starts with the same page ids as the row before or after it, the D = 128 kernel reads
