@@ -116,44 +116,48 @@ struct GroupTable {
     int bad;
 };
 
+// By one wave (every lane of it calls; the caller has the barrier behind it), two sequences per lane: other waves use
+// the three dependent loads' time for what does not depend on them.
+static_assert(kMaxGroupSeqs == 128, "two sequences per lane");
 __device__ __forceinline__ void load_group(const Args& a, int g, GroupTable& gt) {
-    const int tid = threadIdx.x;
-    if (tid == 0) {
-        gt.bad = 0;
-        gt.n_seq = 0;
-    }
-    __syncthreads();
-    int q0 = 0, q1 = 0;
+    const int lane = lane_id();
+    int bad = 0, q0 = 0, q1 = 0;
     if (g < 0 || g >= a.n_groups) {
-        if (tid == 0) gt.bad = 1;
+        bad = 1;
     } else {
         q0 = a.group_first[g];
         q1 = a.group_first[g + 1];
         if (q0 < 0 || q1 < q0 || q1 > a.n_seq || q1 - q0 > kMaxGroupSeqs) {
-            if (tid == 0) gt.bad = 1;
+            bad = 1;
             q1 = q0 = 0;
         }
     }
     const int n = q1 - q0;
-    if (tid < n) {
-        const int st = a.seq_start[q0 + tid], ln = a.seq_len[q0 + tid];
-        if (st < 0 || ln < 0 || ln >= (1 << kMaxSeqLenLog2) || static_cast<int64_t>(st) + ln > a.pool_tokens) {
-            atomicOr(&gt.bad, 1);
-            gt.start[tid] = 0, gt.len[tid] = 0;
-        } else {
-            gt.start[tid] = st, gt.len[tid] = ln;
-        }
+    int st[2], ln[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int j = 2 * lane + k;
+        st[k] = ln[k] = 0;
+        if (j < n) st[k] = a.seq_start[q0 + j], ln[k] = a.seq_len[q0 + j];
     }
-    __syncthreads();
-    if (tid <= n) {                               // tokens of the group before sequence tid (lengths are below 2^20)
-        int acc = 0;
-        for (int j = 0; j < tid; ++j) acc += gt.len[j];
-        gt.flat[tid] = acc;
-        if (tid == n && acc > a.max_group_tokens) gt.bad |= 2;
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+        if (st[k] < 0 || ln[k] < 0 || ln[k] >= (1 << kMaxSeqLenLog2) || static_cast<int64_t>(st[k]) + ln[k] > a.pool_tokens)
+            bad = 1, st[k] = ln[k] = 0;
+    const int sum = ln[0] + ln[1];                // tokens of the group before a sequence (lengths are below 2^20)
+    int incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int up = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += up;
     }
-    __syncthreads();
-    if (tid == 0) gt.n_seq = gt.bad ? 0 : n;
-    __syncthreads();
+    const int total = __builtin_amdgcn_readlane(incl, 63);
+    const int before[2] = {incl - sum, incl - ln[1]};
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+        if (2 * lane + k < n) gt.start[2 * lane + k] = st[k], gt.len[2 * lane + k] = ln[k], gt.flat[2 * lane + k] = before[k];
+    bad = (__ballot(bad != 0) != 0 ? 1 : 0) | (total > a.max_group_tokens ? 2 : 0);
+    if (lane == 0) gt.flat[n] = total, gt.bad = bad, gt.n_seq = bad ? 0 : n;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -178,7 +182,25 @@ struct MatchShared {
 __global__ __launch_bounds__(kMatchThreads) void draft_match_kernel(Args a, int B) {
     __shared__ MatchShared sh;
     const int g = blockIdx.y, part = blockIdx.x, tid = threadIdx.x;
-    load_group(a, g, sh.gt);
+    // The second wave takes the requests of this group among the kReqWindow consecutive ids from b0 on; for the first window
+    // while the first wave waits for the group's table.
+    auto take_requests = [&](int b0) __attribute__((always_inline)) {
+        const int lane = lane_id(), b = b0 + lane;
+        const int len = b < B ? a.pattern_len[b] : 0;
+        const bool mine = b < B && a.req_group[b] == g;
+        const uint64_t mask = __ballot(mine);
+        if (mine) {
+            const int r = __popcll(mask & ((1ull << lane) - 1));
+            sh.req[r] = b;
+            sh.plen[r] = min(max(len, 0), a.p_max);
+            sh.best[r] = max(a.p_min, 1), sh.kept[r] = 0;
+        }
+        if (lane == 0) sh.n_req = __popcll(mask);
+    };
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    if (wave == 0) load_group(a, g, sh.gt);
+    if (wave == 1) take_requests(0);
+    __syncthreads();
     const int need = max(a.p_min, 1);
     const bool two = need >= 2;
     const int n_seq = sh.gt.n_seq;
@@ -186,15 +208,11 @@ __global__ __launch_bounds__(kMatchThreads) void draft_match_kernel(Args a, int 
     const int lo = part * a.chunk, hi = min(lo + a.chunk, total);
     // requests are taken in windows of kReqWindow consecutive ids: at most that many belong to this group
     for (int b0 = 0; b0 < B; b0 += kReqWindow) {
-        if (tid == 0) sh.n_req = 0;
-        __syncthreads();
-        if (tid < kReqWindow && b0 + tid < B && a.req_group[b0 + tid] == g) {
-            const int r = atomicAdd(&sh.n_req, 1);
-            sh.req[r] = b0 + tid;
-            sh.plen[r] = min(max(a.pattern_len[b0 + tid], 0), a.p_max);
-            sh.best[r] = need, sh.kept[r] = 0;
+        if (b0 > 0) {
+            __syncthreads();                                        // (a window without requests has none behind its n_req)
+            if (wave == 1) take_requests(b0);
+            __syncthreads();
         }
-        __syncthreads();
         const int n_req = sh.n_req;
         if (n_req == 0) continue;
         for (int i = tid; i < n_req * a.p_max; i += kMatchThreads) {
@@ -358,7 +376,6 @@ struct Expand {
     uint64_t cand[kSmall];                 // candidates of a level: count << 32 | ~key
     uint32_t place[kSmall];                // hand-over of places between the phases
     int8_t owner[kSmall];                  // rank of the member a place belongs to, -1 = dropped
-    int2 hdr[kMaxParts];
     int first[kMaxParts + 1];              // places of the longest match before part p
     Member mem[kMaxTopK], next[kMaxTopK];  // members while the places live in global memory
     int mem_slot[2][kMaxTopK];             // members while the places live in registers: slot and ancestor mask,
@@ -746,35 +763,30 @@ __global__ __launch_bounds__(kThreads) void draft_expand_kernel(Args a) {
     __shared__ Expand x;
     const int b = blockIdx.x, tid = threadIdx.x;
     const int T = 1 + a.top_k * a.gamma_max;
-    // what the match workgroups left (requested before the group table, whose loads it does not depend on)
-    int2 h = make_int2(0, 0);
-    if (tid < a.parts) h = a.part_hdr[static_cast<size_t>(b) * a.parts + tid];
     const int plen = min(max(a.pattern_len[b], 0), a.p_max);
     const int want = a.max_spec_tokens[b];
-    load_group(a, a.req_group[b], x.gt);
-    if (tid < T) {
-        x.tok[tid] = tid == 0 && plen > 0 ? a.pattern[static_cast<size_t>(b) * a.p_max + a.p_max - 1] : -1;
-        x.par[tid] = tid == 0 ? -1 : -2;
-        x.num[tid] = 0;
-        x.msk[tid] = 1ull << tid;
-    }
-    if (tid == 0) x.n = 0, x.best_len = 0;
-    __syncthreads();
-    if (x.gt.bad && tid == 0 && a.status) atomicOr(a.status, x.gt.bad);
-    if (x.gt.n_seq == 0) h = make_int2(0, 0);
-    if (h.x > 0) atomicMax(&x.best_len, h.y);
-    __syncthreads();
-    const int p_star = x.best_len;
-    // places of the longest match, part by part: how many come before part p
-    if (tid < a.parts) x.hdr[tid] = make_int2(h.y == p_star ? h.x : 0, h.y);
-    __syncthreads();
-    // (at most kMaxParts = 256 of them: wave 0 takes four each; a running sum per thread cost 3 us with 200 stretches)
-    if (tid < 64) {
-        int c[kMaxParts / 64], sum = 0;
+    // What has to be known first, each part by a wave of its own, one barrier behind all: the longest match over the stretches
+    // and how many of its places come before part p (at most kMaxParts = 256 parts: four per lane); the group's table; the empty
+    // draft.  (One after the other, with eleven barriers of sixteen waves, it took 2 .. 3 us longer: with the match kernel's start
+    // the whole call 37.6 -> 35.0 us on 16 chains, 121.6 -> 119.2 us on the multi-path batch.)
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+    if (wave == 0) {
+        int2 h[kMaxParts / 64];
 #pragma unroll
         for (int k = 0; k < kMaxParts / 64; ++k) {
             const int p = tid * (kMaxParts / 64) + k;
-            c[k] = p < a.parts ? x.hdr[p].x : 0;
+            h[k] = p < a.parts ? a.part_hdr[static_cast<size_t>(b) * a.parts + p] : make_int2(0, 0);
+        }
+        int best = 0;
+#pragma unroll
+        for (int k = 0; k < kMaxParts / 64; ++k)
+            if (h[k].x > 0) best = max(best, h[k].y);
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) best = max(best, __shfl_xor(best, o, 64));
+        int c[kMaxParts / 64], sum = 0;
+#pragma unroll
+        for (int k = 0; k < kMaxParts / 64; ++k) {
+            c[k] = h[k].y == best ? h[k].x : 0;
             sum += c[k];
         }
         int incl = sum;
@@ -790,8 +802,19 @@ __global__ __launch_bounds__(kThreads) void draft_expand_kernel(Args a) {
             before += c[k];
         }
         if (tid == 63) x.first[kMaxParts] = before;
+        if (tid == 0) x.n = 0, x.best_len = best;
+    } else if (wave == 1) {
+        load_group(a, a.req_group[b], x.gt);
+    } else if (wave == 2 && tid - 128 < T) {
+        const int t = tid - 128;
+        x.tok[t] = t == 0 && plen > 0 ? a.pattern[static_cast<size_t>(b) * a.p_max + a.p_max - 1] : -1;
+        x.par[t] = t == 0 ? -1 : -2;
+        x.num[t] = 0;
+        x.msk[t] = 1ull << t;
     }
     __syncthreads();
+    if (x.gt.bad && tid == 0 && a.status) atomicOr(a.status, x.gt.bad);
+    const int p_star = x.gt.n_seq > 0 ? x.best_len : 0;
     const int n_kept = p_star > 0 ? x.first[a.parts] : 0;        // >= the places of the longest match
     uint32_t* cur = a.list_b + static_cast<size_t>(b) * a.cap;
     uint32_t* nxt = a.list_a + static_cast<size_t>(b) * a.cap;
