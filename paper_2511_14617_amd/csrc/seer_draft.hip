@@ -230,7 +230,7 @@ __global__ __launch_bounds__(kMatchThreads) void draft_match_kernel(Args a, int 
             const int halo0 = max(t0 - kMaxPattern, 0);            // first flat position the tile needs
             if (tid < n_seq && sh.gt.flat[tid] <= halo0 && halo0 < sh.gt.flat[tid + 1]) sh.first_seq = tid;
             __syncthreads();                                        // also: the previous tile is no longer read
-            // Loads: for every sequence that reaches into the tile, each thread requests its 16 places (four
+            // Loads: for every sequence that reaches into the tile, each thread requests its 8 places (two
             // quads) and one token of the run before the tile, all from addresses clamped into the pool, then
             // keeps those that belong to the sequence.
             int tok[4 * kQuads];
