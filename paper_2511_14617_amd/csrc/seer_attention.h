@@ -111,9 +111,13 @@ inline int gqa_waves_per_block(int rows_per_block) { return gqa_block_uses_helpe
 // The tiled kernel for the other head sizes (seer_attention_tile.hip): any page size, separate K and V pools, two LDS stages
 // of one K and one V tile, row blocks of as many waves as a workgroup holds.
 inline bool tile_shape(int Dqk, int Dv) { return (Dqk == 64 && Dv == 64) || (Dqk == 256 && Dv == 256) || (Dqk == 192 && Dv == 128); }
-// The workspace of these shapes is laid out by the shape alone, also for calls that force the general kernel (it walks whatever
-// stretches it finds): a plan is reused by calls whose flags differ.
+// Every workspace is laid out, and every plan made, by the shape alone, also for calls that force the general kernel (it
+// walks whatever stretches it finds): a plan is reused by calls whose flags differ.
 inline bool tile_layout(const seer_attn_params& p) { return tile_shape(p.Dqk, p.Dv) && !p.kv_shared_latent; }
+inline bool gqa_layout(const seer_attn_params& p) { return p.Dqk == 128 && p.Dv == 128 && gqa_page_size_ok(p.page_size) && !p.kv_shared_latent; }
+inline bool mla_layout(const seer_attn_params& p) {
+    return p.Dqk == 576 && p.Dv == 512 && p.page_size >= 32 && gqa_page_size_ok(p.page_size) && p.kv_shared_latent;
+}
 inline bool tile_supports(const seer_attn_params& p) { return tile_layout(p) && !(p.flags & SEER_ATTN_GENERAL_KERNEL); }
 constexpr int tile_stage_kb(int Dqk, int Dv) { return 32 * 2 * (Dqk + Dv) / 1024; }
 constexpr int tile_waves_per_simd(int Dqk) { return Dqk == 64 ? 3 : (Dqk == 256 ? 1 : 2); }
@@ -133,9 +137,7 @@ inline int resident_wgs_per_cu(const seer_attn_params& p) {
         const int n = by_waves < by_lds ? by_waves : by_lds;
         return n < 1 ? 1 : (n > 8 ? 8 : n);
     }
-    const bool tiled = p.Dqk == 128 && p.Dv == 128 && gqa_page_size_ok(p.page_size) && !p.kv_shared_latent &&
-                       !(p.flags & SEER_ATTN_GENERAL_KERNEL);
-    if (!tiled) return 4;
+    if (!gqa_layout(p)) return 4;
     const int waves = gqa_waves_per_block(gqa_rows_per_block((p.Hq / p.Hkv) * p.T));   // one wave per 32 query rows
     const int by_waves = 8 / waves;                       // 2 waves per SIMD, 4 SIMDs
     const int depth = gqa_pipe_depth(waves);
@@ -153,19 +155,15 @@ inline WorkspaceLayout workspace_layout(const seer_attn_params& p) {
         w.wgs_per_head = p.B;
         w.max_items = p.B;
     } else {
-        const bool mla_tiled = p.Dqk == 576 && p.Dv == 512 && p.page_size >= 32 && gqa_page_size_ok(p.page_size) && p.kv_shared_latent &&
-                               !(p.flags & SEER_ATTN_GENERAL_KERNEL);
-        if (mla_tiled) {
+        if (mla_layout(p)) {
             // one 4-wave workgroup per CU; a request's rows are cut into blocks of 128, and the
             // row-block workgroups of one stretch are launched as a group on one XCD (groups of 8 stretches)
             const int row_blocks = ((p.Hq / p.Hkv) * p.T + 127) / 128;
             w.wgs_per_head = 8 * (kNumCU / (8 * row_blocks * p.Hkv));
             if (w.wgs_per_head < 1) w.wgs_per_head = kNumCU / (row_blocks * p.Hkv);
         } else {
-            const bool tiled = p.Dqk == 128 && p.Dv == 128 && gqa_page_size_ok(p.page_size) && !p.kv_shared_latent &&
-                               !(p.flags & SEER_ATTN_GENERAL_KERNEL);
             const int rows = (p.Hq / p.Hkv) * p.T;
-            const int row_blocks = tiled ? gqa_row_blocks(rows) : (tile_layout(p) ? tile_row_blocks(rows, p.Dqk) : 1);
+            const int row_blocks = gqa_layout(p) ? gqa_row_blocks(rows) : (tile_layout(p) ? tile_row_blocks(rows, p.Dqk) : 1);
             w.wgs_per_head = kNumCU * resident_wgs_per_cu(p) / (p.Hkv * row_blocks);
             if (w.wgs_per_head > kMaxWgsPerHead) w.wgs_per_head = kMaxWgsPerHead;
         }

@@ -729,7 +729,7 @@ int run_verify_attention(void* out, const void* q, const void* k_pages, const vo
     a.scale_log2 = p->scale * seer::kLog2e;
 
     const bool tiled_ok = !(p->flags & SEER_ATTN_GENERAL_KERNEL);
-    a.min_tiles = tile_kernel || (tiled_ok && seer::gqa128_supports(a)) ? seer::kMinTiles : seer::kMinTilesLatent;
+    a.min_tiles = seer::tile_layout(*p) || seer::gqa_layout(*p) ? seer::kMinTiles : seer::kMinTilesLatent;
 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     // the plan depends on the shape and on ctx_len only: the layers of one step can share it

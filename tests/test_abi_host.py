@@ -79,6 +79,23 @@ def test_workspace_sizes(lib):
     assert binding.seer_accept_workspace(4, 65, 10) == 0
 
 
+@pytest.mark.parametrize("shape", [
+    dict(Hq=32, Hkv=8, T=9), dict(Hq=32, Hkv=8, T=17), dict(Hq=32, Hkv=8, T=33, page_size=64), dict(Hq=32, Hkv=2, T=33),
+    dict(Hq=128, Hkv=1, Dqk=576, Dv=512, page_size=64, kv_shared_latent=1), dict(Hq=16, Hkv=1, Dqk=576, Dv=512, page_size=16, kv_shared_latent=1),
+    dict(Dqk=64, Dv=64, T=33), dict(Dqk=256, Dv=256), dict(Dqk=192, Dv=128), dict(page_size=24)], ids=lambda s: "-".join("%s%d" % x for x in s.items()))
+@pytest.mark.parametrize("max_splits", [0, 1, 7])
+def test_the_layout_of_a_workspace_does_not_depend_on_flags(lib, shape, max_splits):
+    """A plan may be reused by a call with other flags: both have to find it at the same places."""
+    from paper_2511_14617_amd import binding as b
+
+    def layout(flags):
+        p = _params(**shape, max_splits=max_splits, flags=flags)
+        return b.seer_verify_attention_workspace(p), lib.seer_verify_attention_shared_tiles_offset(ctypes.byref(p))
+
+    for flags in (b.SEER_ATTN_GENERAL_KERNEL, b.SEER_ATTN_FIXED_SPLIT, b.SEER_ATTN_GENERAL_KERNEL | b.SEER_ATTN_REUSE_PLAN):
+        assert layout(flags) == layout(0)
+
+
 def test_attention_argument_errors_before_any_launch(lib):
     from paper_2511_14617_amd import binding as b
     call = lib.seer_verify_attention

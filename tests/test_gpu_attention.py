@@ -316,6 +316,25 @@ def test_layers_of_one_step_share_the_plan(case):
     assert_attention_close(reused, _oracle(inp2), case + " with a shared plan")
 
 
+@pytest.mark.parametrize("case", ["chain_T17", "tree_T33", "rows528_G16_T33", "mla_latent"])
+@pytest.mark.parametrize("max_splits", [0, 1])
+def test_a_plan_serves_calls_whose_flags_differ(case, max_splits):
+    """The tiled kernels and the general one run on each other's plans."""
+    from paper_2511_14617_amd import binding
+    cfg, kw = CASES[case]
+    inp = W.make_attention_inputs(cfg, values="peaked", **kw)
+    d = attention_device_inputs(inp)
+    p = binding.attn_params(d["q"], d["k_pages"], d["v_pages"], d["block_table"], inp.scale, Dv=cfg.Dv, max_splits=max_splits)
+    ws = torch.empty(binding.seer_verify_attention_workspace(p), dtype=torch.uint8, device="cuda")
+    ref, ref_abs = _oracle(inp), _oracle_abs(inp)
+    for plan, use in ((0, binding.SEER_ATTN_GENERAL_KERNEL), (binding.SEER_ATTN_GENERAL_KERNEL, 0)):
+        for flags in (plan, use | binding.SEER_ATTN_REUSE_PLAN):
+            out = binding.seer_verify_attention(d["q"], d["k_pages"], d["v_pages"], d["block_table"], d["ctx_len"], d["tree_mask"],
+                                                inp.scale, Dv=cfg.Dv, max_splits=max_splits, workspace=ws, flags=flags)
+        assert_attention_close(out, ref, "%s, plan of flags %d, run with %d" % (case, plan, use), hardened=True, ref_abs=ref_abs)
+        assert binding.seer_verify_attention_status(ws) == 0
+
+
 def _random_shape(rng):
     """A seeded random small workload: group width, slots, tree or chain, page size, context mix."""
     G = int(rng.choice([1, 2, 4, 5, 8, 16]))
