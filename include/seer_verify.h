@@ -91,7 +91,8 @@ typedef struct seer_attn_params {
  * once per layer with the same ctx_len: the first layer plans, the others pass this flag (saves a ~5 us
  * kernel and its launch per call).  The caller guarantees that the previous call on this workspace had the same
  * parameters (flags apart) and that ctx_len and block_table are unchanged; if not, the output is
- * undefined (every access still stays in bounds).  The status word then accumulates over the calls. */
+ * undefined (every access still stays in bounds; a workspace without a plan for this B and split leaves
+ * `out` as it is).  The status word then accumulates over the calls. */
 #define SEER_ATTN_REUSE_PLAN 8
 
 /* Supported shapes: (Dqk, Dv) in {(64,64), (128,128), (256,256), (192,128),

@@ -38,13 +38,18 @@ namespace seer {
 // other W) gives equal stretches; SEER_ATTN_FIXED_SPLIT always does.
 struct PlanHeader {
     uint32_t status;     // bit 0: bad ctx_len somewhere; bit 1: page id out of range
-    int32_t balanced;      // 1: stretches; 0: one workgroup per request (max_splits == 1), slot = request
-    int32_t total_tiles;   // tiles per KV head over all requests
+    int32_t plan_b, plan_w;  // the batch and the split the tables are for (see plan_b_word, plan_w_word)
     uint32_t fb_magic;     // kFeedbackMagic once the speed history below the header is meaningful
     int32_t fb_w;          // W it was recorded for
 };
 constexpr uint32_t kFeedbackMagic = 0x5ee2fb01u;
 constexpr int kMaxWgsPerHead = 1024;   // 256 CUs x 4 resident workgroups, one KV head
+
+// A call that reuses a plan reads tables that it did not write itself.  They index by request and by stretch and nothing else
+// steers an unchecked access, so tables made for the same number of requests and the same stretches keep every access in
+// bounds whatever else differs; the kernels compare these two words of the header first and do nothing if they differ.
+inline int32_t plan_b_word(int B) { return B ^ 0x2d35c0de; }
+inline int32_t plan_w_word(int W, bool balanced) { return balanced ? W : -W; }
 
 // A stretch as its workgroups need it, in one 16-byte load: the request in which it starts (-1: nothing to do), its tiles
 // on the line, and that request's first tile (with it the first page ids can be requested beside the request's other words
@@ -204,7 +209,8 @@ struct AttnArgs {
     uint32_t* fb_tiles;         // [wgs_per_head] sum over KV heads of the tiles it streamed
     float* fb_speed;            // [wgs_per_head] smoothed tiles per tick (owned by the plan kernel)
     int32_t fixed_split;        // 1: equal stretches, no history read or written
-    int32_t balanced;           // 0: one workgroup per request (max_splits == 1), no history either
+    int32_t balanced;           // 0: one workgroup per request (max_splits == 1), slot = request, no history either
+    int32_t plan_b, plan_w;     // what the header has to hold (see plan_b_word)
     int32_t min_tiles;          // tiles of a stretch, at least (see kMinTiles)
     int32_t stream_only;        // 1: the tiled D = 128 kernel only streams its tiles (diagnostic)
     int32_t stream_partials;    // 1: the tiled D = 128 kernel writes its partial results with non-temporal stores
@@ -215,10 +221,18 @@ struct AttnArgs {
     float scale_log2;           // scale * log2(e): scores are kept in base-2 units
 };
 
-// A stretch's record, moved to scalar registers (one load; see uniform_load).
-__device__ __forceinline__ StretchRec uniform_stretch(const StretchRec* r) {
-    const int4 v = *reinterpret_cast<const int4*>(r);
-    return {__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y), __builtin_amdgcn_readfirstlane(v.z),
+// Does the workspace hold a plan for this call's batch and split?
+__device__ __forceinline__ bool has_plan(const AttnArgs& a) {
+    const int32_t b = a.header->plan_b, w = a.header->plan_w;
+    return __builtin_amdgcn_readfirstlane(b) == a.plan_b && __builtin_amdgcn_readfirstlane(w) == a.plan_w;
+}
+
+// The record of stretch wg, moved to scalar registers (one load, requested together with the header's words; see uniform_load);
+// nothing to do where there is no plan.
+__device__ __forceinline__ StretchRec uniform_stretch(const AttnArgs& a, int wg) {
+    const int4 v = *reinterpret_cast<const int4*>(a.stretch + wg);
+    const bool planned = has_plan(a);
+    return {planned ? __builtin_amdgcn_readfirstlane(v.x) : -1, __builtin_amdgcn_readfirstlane(v.y), __builtin_amdgcn_readfirstlane(v.z),
             __builtin_amdgcn_readfirstlane(v.w)};
 }
 

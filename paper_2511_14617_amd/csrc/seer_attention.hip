@@ -37,6 +37,7 @@ struct PlanArgs {
     const int32_t* ctx_len;
     const int32_t* block_table;
     int B, T, max_ctx, wgs_per_head, max_splits, fixed_split, max_pages, page_size, min_tiles;
+    int32_t plan_b, plan_w;
     PlanHeader* header;
     ReqSlots* req_slots;
     int32_t* tile_off;
@@ -297,8 +298,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs p) {
     }
     if (tid == 0) {
         p.header->status = any_bad ? 1u : 0u;
-        p.header->balanced = balanced ? 1 : 0;
-        p.header->total_tiles = total;
+        p.header->plan_b = p.plan_b;
+        p.header->plan_w = p.plan_w;
         if (history) {
             p.header->fb_magic = kFeedbackMagic;
             p.header->fb_w = W;
@@ -319,6 +320,8 @@ hipError_t launch_plan(const AttnArgs& a, const WorkspaceLayout& w, hipStream_t 
     p.max_ctx = max_ctx_ll > 0x7fffffffLL - kPlanTile ? 0x7fffffff - kPlanTile : static_cast<int>(max_ctx_ll);
     p.wgs_per_head = w.wgs_per_head;
     p.max_splits = w.max_splits;
+    p.plan_b = a.plan_b;
+    p.plan_w = a.plan_w;
     p.header = a.header;
     p.req_slots = const_cast<ReqSlots*>(a.req_slots);
     p.tile_off = const_cast<int32_t*>(a.tile_off);
@@ -347,13 +350,13 @@ template <int DQK, int DV>
 __global__ __launch_bounds__(kGenThreads) void attn_general_kernel(AttnArgs a) {
     constexpr int NQ = (DQK + 127) / 128;  // bf16 pairs per lane
     constexpr int NV = (DV + 127) / 128;
-    const StretchRec rec = a.stretch[blockIdx.x];
+    const StretchRec rec = uniform_stretch(a, blockIdx.x);
     const int hq = blockIdx.y, t = blockIdx.z;
     const int kvh = hq / a.G;
     __shared__ float s_m[kGenWaves], s_l[kGenWaves];
     __shared__ float s_acc[kGenWaves][DV];
   int g = rec.tile_begin;
-  for (int b = rec.b; b >= 0 && b < a.B && g < rec.tile_end; ++b) {
+  for (int b = rec.b; b >= 0 && g < rec.tile_end; ++b) {
     const int t_lo = a.tile_off[b], t_hi = a.tile_off[b + 1];
     if (t_hi == t_lo) continue;
     const int n = a.ctx_len[b];
@@ -539,6 +542,7 @@ __global__ __launch_bounds__(kCombineThreads) void combine_kernel(AttnArgs a, in
     __shared__ PartSum s_part[kCombineThreads];
     const int b = blockIdx.x / blocks_per_request;
     const ReqSlots slots = a.req_slots[b];
+    if (!has_plan(a)) return;
     const int per_b = a.T * a.Hq;
     const int tid = threadIdx.x;
     const int r = ((blockIdx.x - b * blocks_per_request) * kCombineThreads + tid) >> (log2_per_row + log2_slices);
@@ -702,6 +706,8 @@ int run_verify_attention(void* out, const void* q, const void* k_pages, const vo
     a.tile_off = reinterpret_cast<const int32_t*>(ws + w.off_tiles);
     a.stretch = reinterpret_cast<const seer::StretchRec*>(ws + w.off_stretch);
     a.balanced = w.max_splits > 1 ? 1 : 0;
+    a.plan_b = seer::plan_b_word(p->B);
+    a.plan_w = seer::plan_w_word(w.wgs_per_head, w.max_splits > 1);
     a.shared_tiles = reinterpret_cast<const int32_t*>(ws + w.off_shared);
     a.fb_time = reinterpret_cast<uint32_t*>(ws + w.off_fb);
     a.fb_tiles = a.fb_time + (w.wgs_per_head + 1);

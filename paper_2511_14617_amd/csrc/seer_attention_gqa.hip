@@ -545,7 +545,7 @@ __device__ __forceinline__ void run(const AttnArgs& a, unsigned char* lds) {
     const bool has_left = wave < 2 || wave >= 6;       // one wave per SIMD; its 16-token half of its set's tile:
     const int half = wave & 1;
 
-    const StretchRec rec = uniform_stretch(a.stretch + wg);
+    const StretchRec rec = uniform_stretch(a, wg);
     int b = rec.b;
     if (b < 0) return;
     const int slot_bias = a.balanced ? wg : 0;
@@ -899,7 +899,7 @@ void attn_gqa128_kernel(AttnArgs a) {
     const int l16 = lane >> 4;
     const int p16 = lane & 15;
 
-    const StretchRec rec = uniform_stretch(a.stretch + wg);
+    const StretchRec rec = uniform_stretch(a, wg);
     int b = rec.b;
     if (b < 0) return;
     const int slot_bias = a.balanced ? wg : 0;

@@ -304,7 +304,7 @@ void attn_mla_kernel(AttnArgs a, int row_blocks) {
     const int wg = (slot / row_blocks) * 8 + xcd;
     const int rb = slot % row_blocks;
     if (wg >= a.wgs_per_head) return;
-    const StretchRec rec = uniform_stretch(a.stretch + wg);
+    const StretchRec rec = uniform_stretch(a, wg);
     int b = rec.b;
     if (b < 0) return;
     const int slot_bias = a.balanced ? wg : 0;

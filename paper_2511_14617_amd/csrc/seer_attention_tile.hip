@@ -109,7 +109,7 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int ln = lane & 31, lg = lane >> 5, l16 = lane >> 4, p16 = lane & 15;
 
-    const StretchRec rec = uniform_stretch(a.stretch + wg);
+    const StretchRec rec = uniform_stretch(a, wg);
     int b = rec.b;
     if (b < 0) return;
     const int slot_bias = a.balanced ? wg : 0;

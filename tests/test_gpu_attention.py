@@ -335,6 +335,31 @@ def test_a_plan_serves_calls_whose_flags_differ(case, max_splits):
         assert binding.seer_verify_attention_status(ws) == 0
 
 
+@pytest.mark.parametrize("case", ["chain_T9_multi_split", "tree_T33", "mla_latent", "mha_d64", "general"])
+def test_reuse_without_a_plan_for_the_call_writes_nothing(case):
+    """A workspace that holds none, or the plan of another batch or split: no kernel may follow its tables."""
+    from paper_2511_14617_amd import binding
+    cfg, kw = (CASES["tiny_chain"][0].scaled(page_size=24), {}) if case == "general" else CASES[case]
+    inp = W.make_attention_inputs(cfg, **kw)
+    d = attention_device_inputs(inp)
+
+    def call(B, ws, flags, max_splits=0):
+        out = torch.full((B, cfg.T, cfg.Hq, cfg.Dv), 7.0, dtype=torch.bfloat16, device="cuda")
+        return binding.seer_verify_attention(d["q"][:B], d["k_pages"], d["v_pages"], d["block_table"][:B], d["ctx_len"][:B],
+                                             None if d["tree_mask"] is None else d["tree_mask"][:B], inp.scale, Dv=cfg.Dv,
+                                             max_splits=max_splits, workspace=ws, flags=flags, out=out)
+    p = binding.attn_params(d["q"], d["k_pages"], d["v_pages"], d["block_table"], inp.scale, Dv=cfg.Dv)
+    n = binding.seer_verify_attention_workspace(p)
+    reuse = binding.SEER_ATTN_REUSE_PLAN
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    for ws in (torch.zeros(n, dtype=torch.uint8, device="cuda"), torch.randint(0, 256, (n,), dtype=torch.uint8, device="cuda", generator=gen)):
+        assert bool((call(cfg.B, ws, reuse) == 7.0).all())
+    call(cfg.B, ws, 0)
+    assert bool((call(cfg.B - 1, ws, reuse) == 7.0).all())               # fewer requests than the plan is for
+    assert bool((call(cfg.B, ws, reuse, max_splits=1) == 7.0).all())     # one workgroup per request instead of stretches
+    assert not bool((call(cfg.B, ws, reuse) == 7.0).any())
+
+
 def _random_shape(rng):
     """A seeded random small workload: group width, slots, tree or chain, page size, context mix."""
     G = int(rng.choice([1, 2, 4, 5, 8, 16]))
