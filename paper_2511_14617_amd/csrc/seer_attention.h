@@ -103,7 +103,7 @@ constexpr size_t kStreamPartialsBelow = size_t{64} << 20;
 // the first find the tiles in that XCD's L2).
 inline bool gqa_page_size_ok(int P) { return P >= 16 && P <= 1024 && (P & (P - 1)) == 0; }
 inline int gqa_row_blocks(int rows) { return (rows + 255) / 256; }
-// A row block of 129 .. 144 rows is served by two sets of four waves on alternate tiles, four of which
+// A row block of 129 .. 144 rows is served, where pieces are long, by two sets of four waves on alternate tiles, four of which
 // share the leftover rows (see the kernel), instead of by a fifth wave; such a block keeps its exact row count.
 inline bool gqa_block_uses_helpers(int rows_per_block) { return rows_per_block > 128 && rows_per_block <= 144; }
 inline int gqa_rows_per_block(int rows) {

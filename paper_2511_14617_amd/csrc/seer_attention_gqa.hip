@@ -380,6 +380,15 @@ __device__ __forceinline__ void fused_step(int k_off, int v_off, const int (&k_r
 // tile beside a software-pipelined main wave).  Not kept: the helpers half a step behind the main waves (the second copy
 // of the step spills, and a reload waits for the tile loads in flight).
 // ---------------------------------------------------------------------------------------------------
+
+// Pairs pay from this many tiles per piece on, five waves of the ordinary kernel are faster below: a short piece leaves half of
+// its last pair idle, cannot fill the two pairs in flight and pays for the merge of the states like a long one.  Measured,
+// whole call, five waves | pairs, by average tiles per piece: 3 tiles (44 requests of 80 tokens, two row blocks) 68.4 | 89.9 us, 10
+// (128 of 500) 118.2 | 124.3, 18 (44 of 1000) 112.1 | 120.6, 28 (44 of 1500) 96.5 | 105.5, 35 (128 of 1400) 227.7 | 224.5, 39 (128 of
+// 1500) 245.2 | 238.9, 77 (128 of 3000) 426.6 | 401.5.  Decided per stretch from its own pieces, so a batch of long and short
+// requests uses both.
+constexpr int kPairsFromTiles = 28;
+
 namespace pairs {
 
 constexpr int kWaves = 8, kSlots = 3;
@@ -530,14 +539,8 @@ __device__ __forceinline__ void softmax_pv(int v, f32x16& s, f32x16 (&acc)[4], f
 }
 
 template <bool STREAM, bool STREAM_PARTIALS>
-__device__ __forceinline__ void run(const AttnArgs& a, unsigned char* lds) {
+__device__ __forceinline__ void run(const AttnArgs& a, unsigned char* lds, int kvh, int rb, int wg, const StretchRec& rec) {
     constexpr int NT = kWaves * kWave;
-    int rest = blockIdx.x >> 3;                       // (the grid's layout: see the kernel below)
-    const int kvh = rest % a.Hkv;
-    rest /= a.Hkv;
-    const int rb = rest % a.row_blocks;
-    const int wg = (rest / a.row_blocks) * 8 + (blockIdx.x & 7);
-    if (wg >= a.wgs_per_head) return;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int ln = lane & 31, lg = lane >> 5, l16 = lane >> 4, p16 = lane & 15;
@@ -545,9 +548,7 @@ __device__ __forceinline__ void run(const AttnArgs& a, unsigned char* lds) {
     const bool has_left = wave < 2 || wave >= 6;       // one wave per SIMD; its 16-token half of its set's tile:
     const int half = wave & 1;
 
-    const StretchRec rec = uniform_stretch(a, wg);
     int b = rec.b;
-    if (b < 0) return;
     const int slot_bias = a.balanced ? wg : 0;
     int g = rec.tile_begin;
     const int g_end = rec.tile_end;
@@ -861,15 +862,12 @@ __device__ __forceinline__ void for_each_index(F& f, std::integer_sequence<int, 
 // system allows for exactly this access pattern and launch shape: the ceiling the kernel's
 // bytes-per-second should be read against.  It writes "saw nothing" partials, so the output is zero.
 // STREAM_PARTIALS: the partial results leave with non-temporal stores (see kStreamPartialsBelow).
-// NH: 0, or 4 helper waves that double the four main ones (see `pairs` above).
+// NH: 0, or the three further waves that make five row waves into four main and four helper waves (see `pairs` above) in
+// stretches whose pieces are long (kPairsFromTiles).
 template <int NW, int D, bool STREAM, bool STREAM_PARTIALS, int NH = 0>
 __global__ __launch_bounds__((NW + NH) * kWave) __attribute__((amdgpu_waves_per_eu(NW + NH == 1 ? 1 : 2, 2)))
 void attn_gqa128_kernel(AttnArgs a) {
-    if constexpr (NH > 0) {
-        static_assert(NW == 4 && NH == 4 && D == 2, "four main and four helper waves");
-        __shared__ __attribute__((aligned(1024))) unsigned char pair_lds[pairs::kLdsBytes];
-        pairs::run<STREAM, STREAM_PARTIALS>(a, pair_lds);
-    } else {
+    static_assert(NH == 0 || NW + NH == pairs::kWaves, "pairs need eight waves");
     constexpr int NT = NW * kWave;
     constexpr int NSLOT = D + 1;                    // slots in the K ring and in the V ring
     constexpr int NL = Loaders<NW>::kCount;        // waves that issue loads (the others have nothing to wait for)
@@ -878,7 +876,8 @@ void attn_gqa128_kernel(AttnArgs a) {
     constexpr int REM = 8 % NL;                     // loaders below this index load CEIL blocks, the others FLOOR
     static_assert(D >= 1 && (D - 1) * 2 * CEIL < 64, "vmcnt range");
 
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * NSLOT * kKBytes];   // K ring, then V ring
+    // K ring, then V ring (pairs have a layout of their own)
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[NH > 0 && pairs::kLdsBytes > 2 * NSLOT * kKBytes ? pairs::kLdsBytes : 2 * NSLOT * kKBytes];
     constexpr int kVRing = NSLOT * kKBytes;
 
     // Workgroup ids are dealt round-robin to the 8 XCDs and dispatched in id order.  The grid is laid
@@ -901,7 +900,23 @@ void attn_gqa128_kernel(AttnArgs a) {
 
     const StretchRec rec = uniform_stretch(a, wg);
     int b = rec.b;
-    if (b < 0) return;
+    if constexpr (NH > 0) {
+        // the pieces of this stretch: its requests up to the one the next stretch starts in (without it, if it starts with it)
+        const StretchRec next = uniform_stretch(a, min(wg + 1, a.wgs_per_head - 1));
+        if (b < 0) return;
+        int pieces = 1;
+        if (a.balanced) {
+            const int last = wg + 1 == a.wgs_per_head || next.b < 0 ? a.B - 1 : next.b - (next.req_begin == next.tile_begin ? 1 : 0);
+            pieces = max(1, last - b + 1);
+        }
+        if (rec.tile_end - rec.tile_begin >= kPairsFromTiles * pieces) {
+            pairs::run<STREAM, STREAM_PARTIALS>(a, lds, kvh, rb, wg, rec);
+            return;
+        }
+        if (wave >= NW) return;                     // (barriers wait for the waves that are left)
+    } else {
+        if (b < 0) return;
+    }
     const int slot_bias = a.balanced ? wg : 0;
     int g = rec.tile_begin;
     const int g_end = rec.tile_end;
@@ -1327,7 +1342,6 @@ void attn_gqa128_kernel(AttnArgs a) {
         atomicAdd(a.fb_time + wg, static_cast<uint32_t>(ticks > 0xffffffu ? 0xffffffu : ticks));
         atomicAdd(a.fb_tiles + wg, static_cast<uint32_t>(g_end - g_first));
     }
-    }  // NH == 0
 }
 
 bool gqa128_supports(const AttnArgs& a) {
@@ -1335,20 +1349,17 @@ bool gqa128_supports(const AttnArgs& a) {
            a.v_pages != nullptr && a.Hkv <= 65535;
 }
 
-// The helper shape: two steps' tiles in flight (see pairs).
-constexpr int kHelperDepth = 2;
-
 hipError_t launch_gqa128(const AttnArgs& a, hipStream_t stream) {
     const int nw = a.rows_per_block / 32;
     const dim3 grid(static_cast<unsigned>((a.wgs_per_head + 7) / 8) * 8u * static_cast<unsigned>(a.Hkv) *
                     static_cast<unsigned>(a.row_blocks));
-    // four main waves and four helpers instead of five waves: 129 .. 144 query rows in a row block
+    // 129 .. 144 query rows in a row block: five waves, or four main waves and four helpers
     if (gqa_block_uses_helpers(a.rows_per_block)) {
         const dim3 block(8 * kWave);
-        if (a.stream_only && a.stream_partials) hipLaunchKernelGGL((attn_gqa128_kernel<4, kHelperDepth, true, true, 4>), grid, block, 0, stream, a);
-        else if (a.stream_only) hipLaunchKernelGGL((attn_gqa128_kernel<4, kHelperDepth, true, false, 4>), grid, block, 0, stream, a);
-        else if (a.stream_partials) hipLaunchKernelGGL((attn_gqa128_kernel<4, kHelperDepth, false, true, 4>), grid, block, 0, stream, a);
-        else hipLaunchKernelGGL((attn_gqa128_kernel<4, kHelperDepth, false, false, 4>), grid, block, 0, stream, a);
+        if (a.stream_only && a.stream_partials) hipLaunchKernelGGL((attn_gqa128_kernel<5, gqa_pipe_depth(5), true, true, 3>), grid, block, 0, stream, a);
+        else if (a.stream_only) hipLaunchKernelGGL((attn_gqa128_kernel<5, gqa_pipe_depth(5), true, false, 3>), grid, block, 0, stream, a);
+        else if (a.stream_partials) hipLaunchKernelGGL((attn_gqa128_kernel<5, gqa_pipe_depth(5), false, true, 3>), grid, block, 0, stream, a);
+        else hipLaunchKernelGGL((attn_gqa128_kernel<5, gqa_pipe_depth(5), false, false, 3>), grid, block, 0, stream, a);
         return hipGetLastError();
     }
     switch (nw) {

@@ -316,6 +316,23 @@ def test_layers_of_one_step_share_the_plan(case):
     assert_attention_close(reused, _oracle(inp2), case + " with a shared plan")
 
 
+# 129 .. 144 rows per block: stretches with pieces of 28 tiles and more on average go to pairs of tiles, others to five waves.
+# Lengths on both sides of that, with even and odd tile counts, full and ragged last tiles, and the shortest possible.
+PAIR_LENGTHS = (43, 864, 865, 896, 897, 928, 1500, 60)
+
+
+@pytest.mark.parametrize("rows", ["129_chain", "132_tree", "144_chain", "265_two_blocks", "132_tree_page128"])
+@pytest.mark.parametrize("max_splits", [1, 2, 0])
+def test_parity_around_the_rule_for_pairs_of_tiles(rows, max_splits):
+    shape = {"129_chain": dict(Hq=6, Hkv=2, T=43), "132_tree": dict(Hq=8, Hkv=2, T=33, tree=(4, 8)), "144_chain": dict(Hq=32, Hkv=2, T=9),
+             "265_two_blocks": dict(Hq=5, Hkv=1, T=53), "132_tree_page128": dict(Hq=8, Hkv=2, T=33, tree=(4, 8), page_size=128)}[rows]
+    lengths = tuple(max(n, shape["T"]) for n in PAIR_LENGTHS)
+    cfg = W.CONFIGS[2].scaled(**{**dict(B=len(lengths), group_size=4, ctx=("fixed", lengths), shared_prefix=0, tree=None), **shape})
+    inp = W.make_attention_inputs(cfg, values="peaked", max_pages_per_seq=-(-max(lengths) // cfg.page_size))
+    out = _gpu(inp, max_splits=max_splits)
+    assert_attention_close(out, _oracle(inp), "pairs %s splits %d" % (rows, max_splits), hardened=True, ref_abs=_oracle_abs(inp))
+
+
 @pytest.mark.parametrize("case", ["chain_T17", "tree_T33", "rows528_G16_T33", "mla_latent"])
 @pytest.mark.parametrize("max_splits", [0, 1])
 def test_a_plan_serves_calls_whose_flags_differ(case, max_splits):
