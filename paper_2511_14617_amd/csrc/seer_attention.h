@@ -48,8 +48,8 @@ constexpr int kMaxWgsPerHead = 1024;   // 256 CUs x 4 resident workgroups, one K
 // A call that reuses a plan reads tables that it did not write itself.  They index by request and by stretch and nothing else
 // steers an unchecked access, so tables made for the same number of requests and the same stretches keep every access in
 // bounds whatever else differs; the kernels compare these two words of the header first and do nothing if they differ.
-inline int32_t plan_b_word(int B) { return B ^ 0x2d35c0de; }
-inline int32_t plan_w_word(int W, bool balanced) { return balanced ? W : -W; }
+__host__ __device__ inline int32_t plan_b_word(int B) { return B ^ 0x2d35c0de; }
+__host__ __device__ inline int32_t plan_w_word(int W, bool balanced) { return balanced ? W : -W; }
 
 // A stretch as its workgroups need it, in one 16-byte load: the request in which it starts (-1: nothing to do), its tiles
 // on the line, and that request's first tile (with it the first page ids can be requested beside the request's other words
@@ -210,7 +210,6 @@ struct AttnArgs {
     float* fb_speed;            // [wgs_per_head] smoothed tiles per tick (owned by the plan kernel)
     int32_t fixed_split;        // 1: equal stretches, no history read or written
     int32_t balanced;           // 0: one workgroup per request (max_splits == 1), slot = request, no history either
-    int32_t plan_b, plan_w;     // what the header has to hold (see plan_b_word)
     int32_t min_tiles;          // tiles of a stretch, at least (see kMinTiles)
     int32_t stream_only;        // 1: the tiled D = 128 kernel only streams its tiles (diagnostic)
     int32_t stream_partials;    // 1: the tiled D = 128 kernel writes its partial results with non-temporal stores
@@ -224,7 +223,8 @@ struct AttnArgs {
 // Does the workspace hold a plan for this call's batch and split?
 __device__ __forceinline__ bool has_plan(const AttnArgs& a) {
     const int32_t b = a.header->plan_b, w = a.header->plan_w;
-    return __builtin_amdgcn_readfirstlane(b) == a.plan_b && __builtin_amdgcn_readfirstlane(w) == a.plan_w;
+    return __builtin_amdgcn_readfirstlane(b) == plan_b_word(a.B) &&
+           __builtin_amdgcn_readfirstlane(w) == plan_w_word(a.wgs_per_head, a.balanced != 0);
 }
 
 // The record of stretch wg, moved to scalar registers (one load, requested together with the header's words; see uniform_load);

@@ -37,7 +37,6 @@ struct PlanArgs {
     const int32_t* ctx_len;
     const int32_t* block_table;
     int B, T, max_ctx, wgs_per_head, max_splits, fixed_split, max_pages, page_size, min_tiles;
-    int32_t plan_b, plan_w;
     PlanHeader* header;
     ReqSlots* req_slots;
     int32_t* tile_off;
@@ -298,8 +297,8 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs p) {
     }
     if (tid == 0) {
         p.header->status = any_bad ? 1u : 0u;
-        p.header->plan_b = p.plan_b;
-        p.header->plan_w = p.plan_w;
+        p.header->plan_b = plan_b_word(p.B);
+        p.header->plan_w = plan_w_word(W, balanced);
         if (history) {
             p.header->fb_magic = kFeedbackMagic;
             p.header->fb_w = W;
@@ -320,8 +319,6 @@ hipError_t launch_plan(const AttnArgs& a, const WorkspaceLayout& w, hipStream_t 
     p.max_ctx = max_ctx_ll > 0x7fffffffLL - kPlanTile ? 0x7fffffff - kPlanTile : static_cast<int>(max_ctx_ll);
     p.wgs_per_head = w.wgs_per_head;
     p.max_splits = w.max_splits;
-    p.plan_b = a.plan_b;
-    p.plan_w = a.plan_w;
     p.header = a.header;
     p.req_slots = const_cast<ReqSlots*>(a.req_slots);
     p.tile_off = const_cast<int32_t*>(a.tile_off);
@@ -706,8 +703,6 @@ int run_verify_attention(void* out, const void* q, const void* k_pages, const vo
     a.tile_off = reinterpret_cast<const int32_t*>(ws + w.off_tiles);
     a.stretch = reinterpret_cast<const seer::StretchRec*>(ws + w.off_stretch);
     a.balanced = w.max_splits > 1 ? 1 : 0;
-    a.plan_b = seer::plan_b_word(p->B);
-    a.plan_w = seer::plan_w_word(w.wgs_per_head, w.max_splits > 1);
     a.shared_tiles = reinterpret_cast<const int32_t*>(ws + w.off_shared);
     a.fb_time = reinterpret_cast<uint32_t*>(ws + w.off_fb);
     a.fb_tiles = a.fb_time + (w.wgs_per_head + 1);
