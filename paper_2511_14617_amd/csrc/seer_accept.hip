@@ -34,15 +34,23 @@ namespace seer {
 constexpr int kArgmaxThreads = 256;
 // Floats per workgroup: 16 x 16-byte loads per lane, 8 where the launch would otherwise leave the chip without eight
 // workgroups per CU.  Measured on V = 152 064, 16 384 against 8192 floats: greedy 52 vs 54 us for 576 rows, 364 vs 374 us
-// for 4224 rows.
+// for 4224 rows.  The sampled scan runs the generator for every load of a chunk, in the row or not, so its chunks are no longer
+// than rows need: two loads for rows of up to 2048 (8192 rows of 1024 logits: 84 us with sixteen loads, 50 with eight, 28 with two).
+// Its scalar form has no loads to keep in flight, only a loop, and is faster with more workgroups (1056 rows of 50 257 logits:
+// 145 us with 16 384 floats each, 118 with 8192).
 constexpr int kChunkLarge = 16384;
 constexpr int kChunkSmall = 8192;
+constexpr int kChunkShortRow = 2048;
 constexpr int kFullLaunch = 2048;
 
 __host__ __device__ inline int accept_num_chunks(int V, int chunk) { return (V + chunk - 1) / chunk; }
 // the workspace holds the finer of the two partitions
 __host__ __device__ inline int accept_max_chunks(int V) { return accept_num_chunks(V, kChunkSmall); }
-inline int accept_chunk(int64_t rows, int V) { return rows * accept_num_chunks(V, kChunkLarge) >= kFullLaunch ? kChunkLarge : kChunkSmall; }
+inline int accept_chunk(int64_t rows, int V, bool sampled, bool vec4) {
+    if (sampled && vec4 && V <= kChunkShortRow) return kChunkShortRow;
+    if (sampled && (!vec4 || V <= kChunkSmall)) return kChunkSmall;
+    return rows * accept_num_chunks(V, kChunkLarge) >= kFullLaunch ? kChunkLarge : kChunkSmall;
+}
 
 // (a, ia) beats (b, ib) iff a > b, or a == b and ia < ib.
 __device__ __forceinline__ void take_better(float& v, int& i, float ov, int oi) {
@@ -347,22 +355,24 @@ static int launch_accept(const float* logits, const int32_t* draft_tokens, const
                          int32_t T, int32_t V, bool sampled, SampleArgs sa, int32_t* accepted_len,
                          int32_t* accepted_path, int32_t* bonus_token, int32_t* target_token, void* scratch,
                          size_t capacity, hipStream_t stream) {
-    const int chunk = accept_chunk(static_cast<int64_t>(B) * T, V);
+    const bool vec4 = (V % 4 == 0) && (reinterpret_cast<uintptr_t>(logits) % 16 == 0);
+    const int chunk = accept_chunk(static_cast<int64_t>(B) * T, V, sampled, vec4);
     const int n_chunks = accept_num_chunks(V, chunk);
     float* part_val = static_cast<float*>(scratch);
     int* part_idx = reinterpret_cast<int*>(part_val + capacity);
-    const bool vec4 = (V % 4 == 0) && (reinterpret_cast<uintptr_t>(logits) % 16 == 0);
     const dim3 grid(static_cast<unsigned>(static_cast<size_t>(B) * T * n_chunks));
     const dim3 block(kArgmaxThreads);
-#define SEER_SCAN(VEC4, SAMPLED)                                                                                        \
-    if (chunk == kChunkLarge)                                                                                           \
-        hipLaunchKernelGGL((argmax_chunks<VEC4, SAMPLED, kChunkLarge>), grid, block, 0, stream, logits, V, n_chunks, part_val, part_idx, sa); \
-    else                                                                                                                \
-        hipLaunchKernelGGL((argmax_chunks<VEC4, SAMPLED, kChunkSmall>), grid, block, 0, stream, logits, V, n_chunks, part_val, part_idx, sa)
-    if (vec4 && sampled) { SEER_SCAN(true, true); }
-    else if (vec4) { SEER_SCAN(true, false); }
-    else if (sampled) { SEER_SCAN(false, true); }
-    else { SEER_SCAN(false, false); }
+#define SEER_SCAN(VEC4, SAMPLED, CHUNK)                                                                                       \
+    if (vec4 == VEC4 && sampled == SAMPLED && chunk == CHUNK)                                                                 \
+        hipLaunchKernelGGL((argmax_chunks<VEC4, SAMPLED, CHUNK>), grid, block, 0, stream, logits, V, n_chunks, part_val, part_idx, sa);
+    SEER_SCAN(true, true, kChunkLarge)
+    SEER_SCAN(true, true, kChunkSmall)
+    SEER_SCAN(true, true, kChunkShortRow)
+    SEER_SCAN(true, false, kChunkLarge)
+    SEER_SCAN(true, false, kChunkSmall)
+    SEER_SCAN(false, true, kChunkSmall)
+    SEER_SCAN(false, false, kChunkLarge)
+    SEER_SCAN(false, false, kChunkSmall)
 #undef SEER_SCAN
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return static_cast<int>(err);

@@ -250,6 +250,25 @@ def test_sampled_and_greedy_scans_of_large_batches(V):
         assert np.array_equal(g.cpu().numpy(), w)
 
 
+@pytest.mark.parametrize("V", [4, 1024, 2044, 2048, 2052, 8192, 8196, 1027])
+def test_sampled_scan_of_many_short_rows(V):
+    """Rows at the edges of the chunk lengths that the sampled scan chooses from by the row's length, in batches of more than
+    2048 rows: the last load full and ragged, winners at both ends, equal logits, rows of nothing but -inf, very large ones."""
+    rng = np.random.default_rng(V)
+    B, T = 100, 21
+    logits = rng.standard_normal((B, T, V)).astype(np.float32)
+    logits[::4, :, V - 1] += 14.0
+    logits[1::4, :, 0] += 14.0
+    logits[2::4, 3, :] = 0.25
+    logits[3::4, 4, :] = -np.inf
+    logits[3::4, 5, V // 2] = 3.0e5
+    parent = W.chain_parent(B, T)
+    draft = rng.integers(0, V, size=(B, T)).astype(np.int32)
+    drawn = oracle.argmax_sampled(logits, 0.8, 13)
+    draft[:, 1:] = np.where(rng.random((B, T - 1)) < 0.8, drawn[:, :-1], draft[:, 1:])
+    _check_sampled(logits, draft, parent, 0.8, 13)
+
+
 @pytest.mark.parametrize("dims,Hkv,page", [((128, 128), 8, 16), ((256, 256), 5, 32), ((64, 64), 16, 7)])
 def test_commit_moves_the_heads_of_long_paths_in_batches(dims, Hkv, page):
     """Two paths of 30 nodes: the rows of all heads are more than a workgroup holds at once; the second path is accepted to
