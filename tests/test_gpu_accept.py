@@ -109,3 +109,23 @@ def test_gamma_zero_and_empty_batch():
     e = binding.seer_accept(torch.zeros((0, 3, 10), device="cuda"), torch.zeros((0, 3), dtype=torch.int32,
                                                                                device="cuda"), None)
     assert e[0].numel() == 0
+
+
+@pytest.mark.parametrize("T", [1, 2, 16, 17, 33, 48, 49, 64])
+@pytest.mark.parametrize("V", [700, 40000])
+def test_walk_at_every_workgroup_size(T, V):
+    """The walk's workgroup follows slots x lanes per slot: one to four waves, one chunk and several."""
+    from paper_2511_14617_amd import binding
+    rng = np.random.default_rng(T * V)
+    B = 9
+    logits = rng.standard_normal((B, T, V)).astype(np.float32)
+    parent = W.chain_parent(B, T)
+    target = logits.argmax(axis=2).astype(np.int32)
+    draft = rng.integers(0, V, size=(B, T)).astype(np.int32)
+    draft[:, 1:] = np.where(rng.random((B, T - 1)) < 0.9, target[:, :-1], draft[:, 1:])
+    draft[0, 1:] = target[0, :-1]                             # accepted to the end
+    dev = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    got = binding.seer_accept(dev(logits), dev(draft), dev(parent))
+    for g, w in zip(got, oracle.verify_accept(logits, draft, parent)):
+        assert np.array_equal(g.cpu().numpy(), w)
+    assert int(got[0][0]) == T - 1
