@@ -66,9 +66,13 @@ struct ReqSlots {
 constexpr int kPlanTile = 32;          // tokens per scheduling tile
 // Tiles of a stretch, at least, where the batch is too short for the chip: one tile where a workgroup's time is the chain of its
 // tiles (whole call, 4 requests of 64 .. 512 tokens: 22.7 us with four tiles, 21.1 with two, 17.9 with one; 2 requests of
-// 64 .. 600 with heads of 64: 21.5, 18.6, 17.7; batches that fill the chip do not change).  The shared-latent kernel, whose pieces
-// leave partial results of 256 KB per row block, and the general kernel keep four (2 requests of 1000 .. 4000 tokens: 56.2 us
-// with four, 58.4 with one).
+// 64 .. 600 with heads of 64: 21.5, 18.6, 17.7; batches that fill the chip do not change).  The shapes of the shared-latent kernel, whose
+// pieces leave partial results of 256 KB per row block, and of the general kernel keep four (2 requests of 1000 .. 4000 tokens: 56.2 us
+// with four, 58.4 with one).  D = 128 keeps four as well once every stretch has two or three tiles anyway and the pieces would leave more
+// than kFinePartialsBelow: the shorter chain then saves less than the additional pieces cost in stores and in the combine kernel (75
+// requests of 150 tokens, 16/2 heads, 16 slots, 33 MB: 33.5 us with two tiles, 29.8 with four; 162, 8/2, 40 MB: 38.5, 38.1; but 144, 2/1, 10
+// slots, 10 MB: 28.1, 31.1).
+constexpr size_t kFinePartialsBelow = size_t{16} << 20;
 constexpr int kMinTilesLatent = 4, kMinTiles = 1;
 // Stretches follow the measured speeds only from here on (tiles per stretch): below, rounding to tiles decides.
 constexpr int kMinTilesWeighted = 8;
@@ -211,6 +215,7 @@ struct AttnArgs {
     int32_t fixed_split;        // 1: equal stretches, no history read or written
     int32_t balanced;           // 0: one workgroup per request (max_splits == 1), slot = request, no history either
     int32_t min_tiles;          // tiles of a stretch, at least (see kMinTiles)
+    int32_t fine_pieces;        // with more pieces than this in stretches of two or three tiles: four tiles (see kFinePartialsBelow)
     int32_t stream_only;        // 1: the tiled D = 128 kernel only streams its tiles (diagnostic)
     int32_t stream_partials;    // 1: the tiled D = 128 kernel writes its partial results with non-temporal stores
     int32_t row_blocks, rows_per_block;   // tiled D = 128 kernel: workgroups per (stretch, KV head), rows of each

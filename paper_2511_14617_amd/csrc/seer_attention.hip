@@ -36,7 +36,7 @@ constexpr int kPlanLdsRequests = 4096;   // tile offsets of this many requests a
 struct PlanArgs {
     const int32_t* ctx_len;
     const int32_t* block_table;
-    int B, T, max_ctx, wgs_per_head, max_splits, fixed_split, max_pages, page_size, min_tiles;
+    int B, T, max_ctx, wgs_per_head, max_splits, fixed_split, max_pages, page_size, min_tiles, fine_pieces;
     PlanHeader* header;
     ReqSlots* req_slots;
     int32_t* tile_off;
@@ -217,7 +217,9 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs p) {
     if (balanced) {
         // ---- the stretches ----------------------------------------------------------------------------------------------
         // a request of t tiles touches at most ceil(t / Lmin) + 1 stretches, which must fit max_splits
-        const int Lmin = max(p.min_tiles, (longest + p.max_splits - 2) / (p.max_splits - 1));
+        const int per_w = (total + W - 1) / W;
+        const bool fine = per_w < 2 || per_w >= kMinTilesLatent || total <= (p.fine_pieces - p.B) * per_w;
+        const int Lmin = max(fine ? p.min_tiles : kMinTilesLatent, (longest + p.max_splits - 2) / (p.max_splits - 1));
         // Stretch w begins at the tile nearest to total * (r_0 + .. + r_{w-1}) / R.  When the line is too
         // short for that to keep every stretch at Lmin tiles or more, cut it into equal stretches of
         // max(Lmin, ceil(total / W)) tiles instead (the last ones are then short or empty).
@@ -236,7 +238,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs p) {
             R += x;
         }
         if (tid < W) {
-            const int L_equal = max(Lmin, max((total + W - 1) / W, 1));
+            const int L_equal = max(Lmin, max(per_w, 1));
             const long long cut = weighted ? static_cast<long long>(static_cast<double>(total) * before / R + 0.5)
                                            : static_cast<long long>(tid) * L_equal;
             s_start[tid] = static_cast<int>(cut < total ? cut : total);
@@ -328,6 +330,7 @@ hipError_t launch_plan(const AttnArgs& a, const WorkspaceLayout& w, hipStream_t 
     p.fb_speed = a.fb_speed;
     p.fixed_split = a.fixed_split;
     p.min_tiles = a.min_tiles;
+    p.fine_pieces = a.fine_pieces;
     hipLaunchKernelGGL(plan_kernel, dim3(2), dim3(kPlanThreads), 0, stream, p);
     return hipGetLastError();
 }
@@ -731,6 +734,7 @@ int run_verify_attention(void* out, const void* q, const void* k_pages, const vo
 
     const bool tiled_ok = !(p->flags & SEER_ATTN_GENERAL_KERNEL);
     a.min_tiles = seer::tile_layout(*p) || seer::gqa_layout(*p) ? seer::kMinTiles : seer::kMinTilesLatent;
+    a.fine_pieces = seer::gqa_layout(*p) ? static_cast<int32_t>(seer::kFinePartialsBelow / (sizeof(float) * p->T * p->Hq * p->Dv)) : 1 << 28;
 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     // the plan depends on the shape and on ctx_len only: the layers of one step can share it

@@ -333,6 +333,17 @@ def test_parity_around_the_rule_for_pairs_of_tiles(rows, max_splits):
     assert_attention_close(out, _oracle(inp), "pairs %s splits %d" % (rows, max_splits), hardened=True, ref_abs=_oracle_abs(inp))
 
 
+@pytest.mark.parametrize("B", [20, 46, 75])
+def test_parity_of_short_batches_around_the_limit_for_fine_stretches(B):
+    """Stretches of one tile, of two tiles with few pieces and, with more than 16 MB of partial results, of four."""
+    cfg = W.CONFIGS[2].scaled(B=B, group_size=B, Hq=16, Hkv=2, T=16, ctx=("uniform", 60, 300), shared_prefix=0)
+    inp = W.make_attention_inputs(cfg, values="peaked")
+    # a probability just above a power of two moves by up to 2^-8 of itself (half a step of bf16's 8 significant bits), so the
+    # numerator by up to 2^-8 sum_j p_j |v_j|: twice the term that the check takes from ref_abs.  (Requests of 210 tokens whose
+    # probability sits on one or two tokens come to 1.1 times half of that, with any cut of the contexts.)
+    assert_attention_close(_gpu(inp), _oracle(inp), "short batch of %d" % B, hardened=True, ref_abs=2.0 * _oracle_abs(inp))
+
+
 @pytest.mark.parametrize("case", ["chain_T17", "tree_T33", "rows528_G16_T33", "mla_latent"])
 @pytest.mark.parametrize("max_splits", [0, 1])
 def test_a_plan_serves_calls_whose_flags_differ(case, max_splits):
