@@ -2,12 +2,12 @@
 // (192, 128), separate K and V pools, pages of any size.
 //
 // What bounds it: HBM.  A KV token is read once for all R = G*T query rows of its head; with the scores and P.V on
-// the matrix cores (48 MFMAs of 32 cycles per 32 KB tile and 32 rows at D = 256, 12 per 8 KB at D = 64) the
+// the matrix cores (64 MFMAs of 32 cycles per 32 KB tile and 32 rows at D = 256, 16 per 8 KB at D = 64) the
 // arithmetic of a CU keeps up with more than its share of the bandwidth even though one wave runs a tile's phases one
-// after the other, so the kernel leaves the overlap to the two to sixteen waves of a CU instead of a hand-placed pipeline.
+// after the other, so the kernel leaves the overlap to the four to twelve waves of a CU instead of a hand-placed pipeline.
 // The vector-ALU kernel it stands in for reads every KV token once per query row.  Measured, whole call: 16 requests, 16/4
-// heads of 64, T = 9, 43 687 KV tokens 997 -> 32.3 us; 8/1 heads of 256, T = 5, same lengths 396 -> 39.5 us (with the plan
-// and combine kernels as they are now; this kernel alone 21 and 30 us).
+// heads of 64, T = 9, 43 687 KV tokens 977 -> 31.9 us; 8/1 heads of 256, T = 5, same lengths 390 -> 39.9 us (with the plan
+// and combine kernels as they are now).
 //
 // Work decomposition as in the D = 128 kernel: workgroup (stretch, KV head, row block), wave i owns query rows
 // [32 i, 32 i + 32), the plan's stretches of 32-token tiles, one partial result per request touched.
@@ -16,9 +16,9 @@
 // the block table by ds_bpermute).  S^T = K.Q^T, softmax with one query row per lane, O^T += V^T.P^T.
 //
 // Precision: the vector-ALU kernel multiplies fp32 probabilities into V.  A probability goes into the bf16 matrix
-// product as two terms, its bf16 rounding and the bf16 rounding of what that leaves (together 2^-17 of the value or
-// better), and the row sums take the fp32 value, so the output differs from the vector kernel's by single roundings
-// of the bf16 result only.  V rows that hold infinities or NaN in a tile with masked slots are kept out of the product
+// product as three terms, its bf16 rounding and twice the bf16 rounding of what is left, which hold all its 24 bits,
+// and the row sums take the fp32 value, so the output differs from the vector kernel's by the order of the fp32 sums
+// only (two terms, good to 16 bits, would save 3 %: 31.9 -> 30.8 and 39.9 -> 39.4 us).  V rows that hold infinities or NaN in a tile with masked slots are kept out of the product
 // (0 * NaN must not reach rows that do not see the slot) and added per row.
 #include <type_traits>
 
@@ -298,14 +298,19 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
         float alpha;
         const float m_use = move_reference(mx, a.scale_log2, m_run, alpha);
         float psum = 0.f;
-        uint32_t hi[8], lo[8];
+        uint32_t term[3][8];                       // pairs of probabilities, each probability a sum of three bf16 terms
 #pragma unroll
         for (int i = 0; i < 16; i += 2) {
             s[i] = fast_exp2(fmaf(s[i], a.scale_log2, -m_use));
             s[i + 1] = fast_exp2(fmaf(s[i + 1], a.scale_log2, -m_use));
             psum += s[i] + s[i + 1];
-            hi[i >> 1] = cvt_pk_bf16(s[i], s[i + 1]);
-            lo[i >> 1] = cvt_pk_bf16(s[i] - bf16lo_to_f32(hi[i >> 1]), s[i + 1] - bf16hi_to_f32(hi[i >> 1]));
+            float r0 = s[i], r1 = s[i + 1];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                term[k][i >> 1] = cvt_pk_bf16(r0, r1);
+                r0 -= bf16lo_to_f32(term[k][i >> 1]);          // (exact)
+                r1 -= bf16hi_to_f32(term[k][i >> 1]);
+            }
         }
         l_run = l_run * alpha + psum;
         if (__any(alpha != 1.f)) {
@@ -314,7 +319,7 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
 #pragma unroll
                 for (int i = 0; i < 16; ++i) acc[dt][i] *= alpha;
         }
-        // ---- O^T[d][row] += V^T . (hi + lo) -----------------------------------------------------
+        // ---- O^T[d][row] += V^T . (sum of the terms) ----------------------------------------------
         const int va = lds0 + stage + v_rd;
         constexpr int kPer = S::kVRow % 256 == 0 ? 4 : 2;                      // d-tiles until the address bits repeat
         auto pv_pair = [&](auto dtc) __attribute__((always_inline)) {
@@ -326,10 +331,11 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
 #pragma unroll
                 for (int d2 = 0; d2 < 2; ++d2) {
                     const bf16x8 v = as_bf16x8(u32x4{vr[d2][2 * half][0], vr[d2][2 * half][1], vr[d2][2 * half + 1][0], vr[d2][2 * half + 1][1]});
-                    const bf16x8 ph = as_bf16x8(u32x4{hi[4 * half], hi[4 * half + 1], hi[4 * half + 2], hi[4 * half + 3]});
-                    const bf16x8 pl = as_bf16x8(u32x4{lo[4 * half], lo[4 * half + 1], lo[4 * half + 2], lo[4 * half + 3]});
-                    acc[dt + d2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, ph, acc[dt + d2], 0, 0, 0);
-                    acc[dt + d2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pl, acc[dt + d2], 0, 0, 0);
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        const bf16x8 pk = as_bf16x8(u32x4{term[k][4 * half], term[k][4 * half + 1], term[k][4 * half + 2], term[k][4 * half + 3]});
+                        acc[dt + d2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pk, acc[dt + d2], 0, 0, 0);
+                    }
                 }
         };
         pv_pair(std::integral_constant<int, 0>{});
@@ -341,10 +347,14 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
         // ---- V rows with infinities or NaN: added to the rows that see the slot ------------------
         for (uint32_t left = nonfinite; left; left &= left - 1) {
             const int j = __builtin_ctz(left), ij = (j >> 3) * 4 + (j & 3);
-            uint32_t h2 = hi[0], l2 = lo[0];
+            float pj = 0.f;
 #pragma unroll
-            for (int i = 1; i < 8; ++i) h2 = (ij >> 1) == i ? hi[i] : h2, l2 = (ij >> 1) == i ? lo[i] : l2;
-            float pj = (ij & 1) ? bf16hi_to_f32(h2) + bf16hi_to_f32(l2) : bf16lo_to_f32(h2) + bf16lo_to_f32(l2);
+            for (int k = 2; k >= 0; --k) {
+                uint32_t pair = term[k][0];
+#pragma unroll
+                for (int i = 1; i < 8; ++i) pair = (ij >> 1) == i ? term[k][i] : pair;
+                pj += (ij & 1) ? bf16hi_to_f32(pair) : bf16lo_to_f32(pair);
+            }
             pj = __shfl(pj, ln + ((j >> 2) & 1) * 32, kWave);                  // the half of the lanes that holds token j
             const bool sees = rel + j < 0 || ((word >> (rel + j)) & 1ull);
             const int tok = tb + j, lp = page_of(tok);

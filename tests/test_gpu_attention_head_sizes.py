@@ -1,6 +1,6 @@
 """GPU parity of the matrix-core kernel for head sizes (64, 64), (256, 256) and (192, 128): edges of tiles, pages and row
 blocks against the oracle, and infinities or NaN in V against the general kernel.  Probabilities keep fp32's precision there
-(two bf16 terms), so what is left is the rounding of the bf16 output: at most 2^-9 of each value, hence of the signal's rms."""
+(three bf16 terms), so what is left is the rounding of the bf16 output: at most 2^-9 of each value, hence of the signal's rms."""
 import numpy as np
 import pytest
 import torch
@@ -104,3 +104,28 @@ def test_infinities_and_nan_in_values_reach_only_the_rows_that_see_them(dims):
     ok = torch.isfinite(want)
     assert torch.isfinite(got[ok]).all()
     assert float((got[ok] - want[ok]).abs().max() / want[ok].abs().max()) < 2.0 ** -8   # a bf16 rounding of either
+
+
+@pytest.mark.parametrize("dims", SIZES, ids=lambda d: "%dx%d" % d)
+def test_probabilities_reach_the_product_with_all_their_bits(dims):
+    """Three tokens: two of weight 1 whose values are the first and the second bf16 term of the third one's weight p = exp(-j / 64),
+    and the third with value -1.  What is left is the part of p behind 16 bits, over 2 + p.  In fp32, p is off by its exponent's
+    rounding (below 2^-23 here) and the exponential's (2^-23), together less than 2^-22; the output is rounded to bf16."""
+    from paper_2511_14617_amd import binding
+    Dqk, Dv = dims
+    B, P = 64, 16
+    p = np.exp(-np.arange(1, B + 1) / 64.0)
+    first = torch.from_numpy(p).bfloat16().double()
+    second = (torch.from_numpy(p) - first).bfloat16().double()
+    want = (first + second - torch.from_numpy(p)) / (2.0 + torch.from_numpy(p))
+    q = torch.zeros((B, 1, 1, Dqk))
+    k, v = torch.zeros((B, 1, P, Dqk)), torch.zeros((B, 1, P, Dv))
+    q[..., 5] = 1.0
+    k[:, 0, 1, 5] = -torch.arange(1, B + 1) / 64.0                 # exact in bf16
+    v[:, 0, 0, :], v[:, 0, 1, :], v[:, 0, 2, :] = first.float()[:, None], -1.0, second.float()[:, None]
+    dev = lambda x: x.bfloat16().cuda()  # noqa: E731
+    table = torch.arange(B, dtype=torch.int32, device="cuda").view(B, 1)
+    n = torch.full((B,), 3, dtype=torch.int32, device="cuda")
+    out = binding.seer_verify_attention(dev(q), dev(k), dev(v), table, n, None, 1.0, Dv=Dv).cpu().double()
+    assert float(want.abs().max()) > 2.0 ** -20                   # so that two terms alone, which leave zero, are far outside
+    assert bool(((out[:, 0, 0, :] - want[:, None]).abs() <= 2.0 ** -22 + 2.0 ** -8 * want.abs()[:, None]).all())
