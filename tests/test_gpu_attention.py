@@ -523,3 +523,28 @@ def test_shared_latent_equals_explicit_value_pool():
     assert_attention_close(shared, ref, "shared latent", hardened=True, ref_abs=ref_abs)
     assert_attention_close(explicit, ref, "explicit value pool", hardened=True, ref_abs=ref_abs)
     assert float((shared.float() - explicit.float()).abs().max()) <= 0.05
+
+
+@pytest.mark.parametrize("B", [1024, 1025, 4096, 4100])
+@pytest.mark.parametrize("max_splits", [0, 1, 3])
+def test_plan_of_batches_beyond_its_thread_and_lds_tables(B, max_splits):
+    """More requests than the plan has threads (several per thread), than it keeps offsets of in LDS, and, one workgroup per
+    request, more stretches than threads; requests without a tile (unusable lengths) at the borders and in between."""
+    from paper_2511_14617_amd import binding
+    cfg = W.CONFIGS[1].scaled(B=B, group_size=4, Hq=2, Hkv=1, Dqk=64, Dv=64, T=1, ctx=("uniform", 1, 70), shared_prefix=0)
+    inp = W.make_attention_inputs(cfg, values="peaked")
+    ref = _oracle(inp)
+    bad = [0, 1, B // 2, B // 2 + 1, B - 1]
+    unusable = [0, -5, inp.block_table.shape[1] * cfg.page_size + 1, 0, 2 ** 31 - 1]
+    d = attention_device_inputs(inp)
+    n = d["ctx_len"].clone()
+    n[torch.tensor(bad, device="cuda")] = torch.tensor(unusable, dtype=torch.int32, device="cuda")
+    ref[bad] = 0.0
+    p = binding.attn_params(d["q"], d["k_pages"], d["v_pages"], d["block_table"], inp.scale, Dv=64, max_splits=max_splits)
+    ws = torch.empty(binding.seer_verify_attention_workspace(p), dtype=torch.uint8, device="cuda")
+    for _ in range(2):                                        # the second call plans with the first one's speed history
+        out = binding.seer_verify_attention(d["q"], d["k_pages"], d["v_pages"], d["block_table"], n, d["tree_mask"], inp.scale, Dv=64,
+                                            max_splits=max_splits, workspace=ws)
+        assert_attention_close(out, ref, "batch of %d, splits %d" % (B, max_splits), hardened=True)
+        assert bool((out[bad] == 0).all())
+        assert binding.seer_verify_attention_status(ws) == 1
