@@ -120,13 +120,6 @@ __device__ __forceinline__ void for_each_index(F&& f, std::integer_sequence<int,
     (f(std::integral_constant<int, I>{}), ...);
 }
 
-// max over the two lanes that share a query row (lane and lane ^ 32): see the D = 128 kernel
-__device__ __forceinline__ float max_across_halves(float x) {
-    float a = x, b = x;
-    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
-    return fmaxf(a, b);
-}
-
 // A wave issues in order, and an MFMA holds the matrix core for 32 cycles: whatever else a step has
 // to issue (operand reads from LDS, the softmax arithmetic) only runs in the shadow of the MFMAs
 // if it sits BETWEEN them, one MFMA at a time.  Both phases below are written that way: after
@@ -504,7 +497,7 @@ void attn_mla_kernel(AttnArgs a, int row_blocks) {
             mx_part = fmaxf(mx_part, sc[15]);
             SEER_MLA_PIN(mx_part);
         } else if constexpr (part == 2) {
-            mx_part = mla::max_across_halves(mx_part) * a.scale_log2;
+            mx_part = max_across_halves(mx_part) * a.scale_log2;
             SEER_MLA_PIN(mx_part);
         } else {
             const float m_new = (mx_part > m_run + 8.f) ? mx_part : m_run;
