@@ -71,8 +71,8 @@ constexpr int kPlanTile = 32;          // tokens per scheduling tile
 // with four, 58.4 with one).  D = 128 keeps four as well once every stretch has two or three tiles anyway and the pieces would leave more
 // than kFinePartialsBelow: the shorter chain then saves less than the additional pieces cost in stores and in the combine kernel (75
 // requests of 150 tokens, 16/2 heads, 16 slots, 33 MB: 33.5 us with two tiles, 29.8 with four; 162, 8/2, 40 MB: 38.5, 38.1; but 144, 2/1, 10
-// slots, 10 MB: 28.1, 31.1).
-constexpr size_t kFinePartialsBelow = size_t{16} << 20;
+// slots, 10 MB: 28.1, 31.1; 3 of 10 000 .. 20 000, 8/1, 9 slots, 19 MB: 27.7, 28.9).
+constexpr size_t kFinePartialsBelow = size_t{24} << 20;
 constexpr int kMinTilesLatent = 4, kMinTiles = 1;
 // Stretches follow the measured speeds only from here on (tiles per stretch): below, rounding to tiles decides.
 constexpr int kMinTilesWeighted = 8;

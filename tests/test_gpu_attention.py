@@ -335,7 +335,7 @@ def test_parity_around_the_rule_for_pairs_of_tiles(rows, max_splits):
 
 @pytest.mark.parametrize("B", [20, 46, 75])
 def test_parity_of_short_batches_around_the_limit_for_fine_stretches(B):
-    """Stretches of one tile, of two tiles with few pieces and, with more than 16 MB of partial results, of four."""
+    """Stretches of one tile, of two tiles with few pieces and, with more than 24 MB of partial results, of four."""
     cfg = W.CONFIGS[2].scaled(B=B, group_size=B, Hq=16, Hkv=2, T=16, ctx=("uniform", 60, 300), shared_prefix=0)
     inp = W.make_attention_inputs(cfg, values="peaked")
     # a probability just above a power of two moves by up to 2^-8 of itself (half a step of bf16's 8 significant bits), so the
