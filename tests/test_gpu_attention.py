@@ -50,8 +50,8 @@ CASES = {
     "rows168_G8_T21": (W.CONFIGS[2].scaled(B=3, group_size=3, Hq=16, Hkv=2, T=21, ctx=("uniform", 300, 1500)), {}),
     "rows224_G8_T28": (W.CONFIGS[2].scaled(B=2, group_size=2, Hq=16, Hkv=2, T=28, ctx=("uniform", 200, 1200)), {}),
     "rows256_G8_T32": (W.CONFIGS[2].scaled(B=2, group_size=2, Hq=8, Hkv=1, T=32, ctx=("uniform", 200, 1200)), {}),
-    # 129 .. 144 rows per KV head: four main waves plus four helper waves that share the leftover rows tile by tile
-    # (pieces shorter than four tiles leave some helpers without a tile; ragged tails; chain and tree masks)
+    # 129 .. 144 rows per KV head: five waves where the pieces of a stretch are short, as here in most stretches, pairs of tiles on
+    # two sets of four waves where they are long (test_parity_around_the_rule_for_pairs_of_tiles)
     "rows129_G3_T43": (W.CONFIGS[2].scaled(B=4, group_size=4, Hq=6, Hkv=2, T=43, ctx=("uniform", 43, 1500), shared_prefix=0), {}),
     "rows144_G16_T9": (W.CONFIGS[2].scaled(B=5, group_size=5, Hq=32, Hkv=2, T=9, ctx=("uniform", 9, 2500), shared_prefix=64), {}),
     "rows132_tree_short": (W.CONFIGS[5].scaled(B=9, group_size=3, ctx=("uniform", 33, 140), shared_prefix=0),
@@ -64,7 +64,7 @@ CASES = {
                                                shared_prefix=256), {}),
     "tp8_share_72b_tree": (W.CONFIGS[5].scaled(B=16, group_size=16, Hq=8, Hkv=1, ctx=("uniform", 100, 1500),
                                               shared_prefix=256), {"dedup_fraction": 0.3}),
-    # 265 rows per KV head: two row blocks of 133 and 132 rows, each four main waves plus four helper waves
+    # 265 rows per KV head: two row blocks of 133 and 132 rows
     "rows265_two_helper_blocks": (W.CONFIGS[2].scaled(B=3, group_size=3, Hq=5, Hkv=1, T=53, ctx=("uniform", 53, 1500),
                                                      shared_prefix=64), {}),
     # more than 256 query rows per KV head: the tiled kernel cuts them into row blocks (528 rows -> 3 blocks)
