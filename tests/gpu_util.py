@@ -55,9 +55,10 @@ def check_attention_values(got: np.ndarray, ref: np.ndarray, what: str = "", har
     """|got - ref| <= ATOL + RTOL*|ref| elementwise on fp64 arrays (all outputs, or sampled rows).
 
     `ref_abs` (hardened inputs only) names a STATED DEVIATION from that bar, not a part of it: the kernels
-    round the probabilities to bf16 before the P.V matrix product (relative error <= 2^-9 each), which can
-    move the numerator by up to 2^-9 * sum_j p_j |v_j| = 2^-9 * ref_abs.  Where ref_abs is given, an element
-    may exceed the plain bound by at most that term, at most 0.1 % of the elements may do so, and how far
+    round the probabilities to bf16 before the P.V matrix product (by 2^-9 to 2^-8 of each), which can
+    move the numerator by up to 2^-8 * sum_j p_j |v_j| = 2^-8 * ref_abs where one token carries the weight, and by
+    less than half of that on the inputs used here.  Where ref_abs is given, an element
+    may exceed the plain bound by at most 2^-9 * ref_abs, at most 0.1 % of the elements may do so, and how far
     and how many is printed and recorded (see MARGINS) for every comparison.
     """
     assert got.shape == ref.shape, (got.shape, ref.shape)
