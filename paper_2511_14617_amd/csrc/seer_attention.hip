@@ -350,17 +350,21 @@ template <int DQK, int DV>
 __global__ __launch_bounds__(kGenThreads) void attn_general_kernel(AttnArgs a) {
     constexpr int NQ = (DQK + 127) / 128;  // bf16 pairs per lane
     constexpr int NV = (DV + 127) / 128;
+    if (static_cast<int>(blockIdx.x) >= a.wgs_per_head) return;       // (padding of the grid, see launch_general)
     const StretchRec rec = uniform_stretch(a, blockIdx.x);
     const int hq = blockIdx.y, t = blockIdx.z;
     const int kvh = hq / a.G;
     __shared__ float s_m[kGenWaves], s_l[kGenWaves];
     __shared__ float s_acc[kGenWaves][DV];
+  const long long table_tok = static_cast<long long>(a.max_pages) * a.P;      // tokens that a row of the block table reaches
+  const int max_tok = static_cast<int>(table_tok < 0x7fffffffLL ? table_tok : 0x7fffffffLL);
   int g = rec.tile_begin;
   for (int b = rec.b; b >= 0 && g < rec.tile_end; ++b) {
     const int t_lo = a.tile_off[b], t_hi = a.tile_off[b + 1];
     if (t_hi == t_lo) continue;
     const int n = a.ctx_len[b];
-    const int piece_begin = (g - t_lo) * kPlanTile, piece_end = min(n, (min(rec.tile_end, t_hi) - t_lo) * kPlanTile);
+    const int piece_begin = (g - t_lo) * kPlanTile;
+    const int piece_end = min(min(n, (min(rec.tile_end, t_hi) - t_lo) * kPlanTile), max_tok);   // (max_tok: n of a reused plan may be any)
     g = t_hi;
     const int item_idx = b + (a.balanced ? static_cast<int>(blockIdx.x) : 0);
     const int n0 = n - a.T;
@@ -391,7 +395,7 @@ __global__ __launch_bounds__(kGenThreads) void attn_general_kernel(AttnArgs a) {
     for (int j = piece_begin + wave; j < piece_end; j += kGenWaves) {
         const bool visible = (j < n0) || ((word >> (j - n0)) & 1ull);
         if (!visible) continue;  // uniform across the wave
-        int page = table[min(j / a.P, a.max_pages - 1)];
+        int page = table[j / a.P];
         if (page < 0 || page >= a.num_pages) {
             bad_page = true;
             page = min(max(page, 0), a.num_pages - 1);
@@ -469,7 +473,11 @@ bool general_supports(int Dqk, int Dv) {
 }
 
 hipError_t launch_general(const AttnArgs& a, hipStream_t stream) {
-    const dim3 grid(a.wgs_per_head, a.Hq, a.T), block(kGenThreads);
+    // Of a short batch only the first few stretches hold work, for every head and slot: with a row of workgroups per (head, slot) that
+    // is a multiple of 256 they would land on the same few CUs of each XCD row after row (2 requests of 4000 tokens, 17 slots, eight heads:
+    // 217 us, 187 with rows of an odd multiple of 8; 16 of 1000, 9 slots, sixteen heads: 519, 480).
+    const int row = a.wgs_per_head < 64 ? a.wgs_per_head : ((a.wgs_per_head + 7) / 8 | 1) * 8;
+    const dim3 grid(row, a.Hq, a.T), block(kGenThreads);
 #define SEER_GEN_CASE(DQK_, DV_)                                                                   \
     if (a.Dqk == DQK_ && a.Dv == DV_) {                                                            \
         hipLaunchKernelGGL((attn_general_kernel<DQK_, DV_>), grid, block, 0, stream, a);           \

@@ -316,6 +316,16 @@ def test_layers_of_one_step_share_the_plan(case):
     assert_attention_close(reused, _oracle(inp2), case + " with a shared plan")
 
 
+@pytest.mark.parametrize("Hkv", [1, 3, 8, 16, 40])
+def test_general_kernel_at_every_width_of_its_grid(Hkv):
+    """1024, 341, 128, 64 and 25 stretches: rows of workgroups with padding behind the last stretch and without, a batch that
+    fills few of them and one with more requests than stretches."""
+    for B, ctx in ((2, ("uniform", 100, 900)), (70, ("uniform", 3, 60))):
+        cfg = W.CONFIGS[1].scaled(B=B, group_size=B, Hq=2 * Hkv, Hkv=Hkv, T=3, page_size=24, ctx=ctx, shared_prefix=0)
+        inp = W.make_attention_inputs(cfg, values="peaked")
+        assert_attention_close(_gpu(inp), _oracle(inp), "general, %d KV heads, %d requests" % (Hkv, B), hardened=True)
+
+
 # 129 .. 144 rows per block: stretches with pieces of 28 tiles and more on average go to pairs of tiles, others to five waves.
 # Lengths on both sides of that, with even and odd tile counts, full and ragged last tiles, and the shortest possible.
 PAIR_LENGTHS = (43, 864, 865, 896, 897, 928, 1500, 60)
