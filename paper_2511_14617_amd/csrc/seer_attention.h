@@ -34,7 +34,8 @@ namespace seer {
 // adds its tiles and its duration (constant 100 MHz clock) to two counters of
 // its stretch index in the workspace, and the next call's plan cuts the line in
 // proportion to the smoothed tiles-per-time of each index (clamped to
-// [3/4, 4/3] of the mean).  A workspace that holds no valid history (first use,
+// [3/4, 4/3] of the mean).  The sums of these rates that a cut needs are made at the end of a call that plans,
+// by a workgroup of the combine kernel.  A workspace that holds no valid history (first use,
 // other W) gives equal stretches; SEER_ATTN_FIXED_SPLIT always does.
 struct PlanHeader {
     uint32_t status;     // bit 0: bad ctx_len somewhere; bit 1: page id out of range
@@ -58,10 +59,16 @@ struct StretchRec {
     int32_t b, tile_begin, tile_end, req_begin;
 };
 
-// The partial slots of a request.
+// The partial slots of a request, first .. last (none: last < first).
 struct ReqSlots {
-    int32_t first, count;
+    int32_t first, last;
 };
+
+// Up to this many requests the tiled D = 128 kernel and the kernel for the other head sizes plan for themselves (seer_plan.h):
+// one per lane of a wave.  Whole call with the plan kernel | without: 4 requests of 64 .. 512 tokens 16.9 | 13.8 us, 16 requests with heads of
+// 64 32.1 | 27.4, of 256 39.6 | 35.5, 64 requests on one KV head 57.4 | 53.8, on eight 236.9 | 232.5.  (Not all of the plan kernel's 5.5 us:
+// the partition kernel begins 1.8 us later, most of it the fetch of the additional code.)
+constexpr int kSelfPlanRequests = 64;
 
 constexpr int kPlanTile = 32;          // tokens per scheduling tile
 // Tiles of a stretch, at least, where the batch is too short for the chip: one tile where a workgroup's time is the chain of its
@@ -83,7 +90,8 @@ struct WorkspaceLayout {
     int max_items;
     int wgs_per_head;    // W (balanced mode) or B (one workgroup per request)
     int max_splits;
-    size_t off_header, off_slots, off_tiles, off_stretch, off_shared, off_fb, off_ml, off_acc, total;
+    int row_blocks;
+    size_t off_header, off_slots, off_tiles, off_stretch, off_shared, off_fb, off_flags, off_ml, off_acc, total;
 };
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -128,6 +136,10 @@ inline bool mla_layout(const seer_attn_params& p) {
     return p.Dqk == 576 && p.Dv == 512 && p.page_size >= 32 && gqa_page_size_ok(p.page_size) && p.kv_shared_latent;
 }
 inline bool tile_supports(const seer_attn_params& p) { return tile_layout(p) && !(p.flags & SEER_ATTN_GENERAL_KERNEL); }
+// (also a matter of the shape alone; calls that force the general kernel or reuse a plan do not use it)
+inline bool self_plan_layout(const seer_attn_params& p) {
+    return p.B <= kSelfPlanRequests && p.max_splits != 1 && (gqa_layout(p) || tile_layout(p));
+}
 constexpr int tile_stage_kb(int Dqk, int Dv) { return 32 * 2 * (Dqk + Dv) / 1024; }
 constexpr int tile_waves_per_simd(int Dqk) { return Dqk == 64 ? 3 : (Dqk == 256 ? 1 : 2); }
 constexpr int tile_max_waves(int Dqk) { return Dqk == 256 ? 4 : 8; }     // per workgroup
@@ -160,6 +172,8 @@ inline int resident_wgs_per_cu(const seer_attn_params& p) {
 inline WorkspaceLayout workspace_layout(const seer_attn_params& p) {
     WorkspaceLayout w{};
     w.max_splits = p.max_splits > 0 ? p.max_splits : kDefaultMaxSplits;
+    const int rows_per_head = (p.Hq / p.Hkv) * p.T;
+    w.row_blocks = gqa_layout(p) ? gqa_row_blocks(rows_per_head) : (tile_layout(p) ? tile_row_blocks(rows_per_head, p.Dqk) : 1);
     if (w.max_splits == 1) {
         w.wgs_per_head = p.B;
         w.max_items = p.B;
@@ -171,9 +185,7 @@ inline WorkspaceLayout workspace_layout(const seer_attn_params& p) {
             w.wgs_per_head = 8 * (kNumCU / (8 * row_blocks * p.Hkv));
             if (w.wgs_per_head < 1) w.wgs_per_head = kNumCU / (row_blocks * p.Hkv);
         } else {
-            const int rows = (p.Hq / p.Hkv) * p.T;
-            const int row_blocks = gqa_layout(p) ? gqa_row_blocks(rows) : (tile_layout(p) ? tile_row_blocks(rows, p.Dqk) : 1);
-            w.wgs_per_head = kNumCU * resident_wgs_per_cu(p) / (p.Hkv * row_blocks);
+            w.wgs_per_head = kNumCU * resident_wgs_per_cu(p) / (p.Hkv * w.row_blocks);
             if (w.wgs_per_head > kMaxWgsPerHead) w.wgs_per_head = kMaxWgsPerHead;
         }
         if (w.wgs_per_head < 1) w.wgs_per_head = 1;
@@ -188,12 +200,17 @@ inline WorkspaceLayout workspace_layout(const seer_attn_params& p) {
     const size_t per_w = sizeof(int32_t) * (static_cast<size_t>(w.wgs_per_head) + 1);
     w.off_stretch = align_up(w.off_tiles + per_b, 256);
     w.off_shared = align_up(w.off_stretch + sizeof(StretchRec) * w.wgs_per_head, 256);
-    w.off_fb = align_up(w.off_shared + per_b, 256);               // time[W], tiles[W], smoothed speed[W]
-    w.off_ml = align_up(w.off_fb + 3 * per_w, 256);
+    w.off_fb = align_up(w.off_shared + per_b, 256);               // time[W], tiles[W], smoothed speed[W], shares of the rates[W]
+    w.off_flags = align_up(w.off_fb + 4 * per_w, 256);            // one byte per wave of the partition kernel's grid
+    const bool self_plans = self_plan_layout(p);
+    w.off_ml = align_up(w.off_flags + (self_plans ? size_t{8} * w.wgs_per_head * p.Hkv * w.row_blocks : 0), 256);
     w.off_acc = align_up(w.off_ml + 2 * sizeof(float) * rows, 256);
     w.total = align_up(w.off_acc + sizeof(float) * rows * p.Dv, 256);
     return w;
 }
+
+// floor(2^32 / d), or the largest number below 2^32 (see divide() in seer_plan.h).
+inline uint32_t reciprocal(uint32_t d) { return d > 1 ? static_cast<uint32_t>((uint64_t{1} << 32) / d) : 0xffffffffu; }
 
 // Everything a kernel needs, by value.
 struct AttnArgs {
@@ -211,7 +228,14 @@ struct AttnArgs {
     const int32_t* shared_tiles;  // [B] leading tiles of each request whose pages a neighbouring request maps too
     uint32_t* fb_time;          // [wgs_per_head] sum over KV heads of the workgroup's duration, 10 ns ticks
     uint32_t* fb_tiles;         // [wgs_per_head] sum over KV heads of the tiles it streamed
-    float* fb_speed;            // [wgs_per_head] smoothed tiles per tick (owned by the plan kernel)
+    float* fb_speed;            // [wgs_per_head] smoothed tiles per tick
+    uint32_t* fb_before;        // [wgs_per_head] share of the rates in front of a stretch index, in units of 2^-32
+    uint8_t* page_flags;        // [wgs_per_head][Hkv][row_blocks][8] see publish_stretch
+    int32_t self_plan;          // 1: the partition kernel plans for itself
+    int32_t plan_waves;         // waves of a workgroup of the partition kernel
+    int32_t reuse_plan;         // 1: the tables of an earlier call
+    int32_t max_splits, max_ctx;   // most pieces of a request; most tokens that a row of the block table holds
+    uint32_t inv_wgs, inv_splits;   // reciprocal() of wgs_per_head and of max_splits - 1
     int32_t fixed_split;        // 1: equal stretches, no history read or written
     int32_t balanced;           // 0: one workgroup per request (max_splits == 1), slot = request, no history either
     int32_t min_tiles;          // tiles of a stretch, at least (see kMinTiles)
@@ -241,7 +265,7 @@ __device__ __forceinline__ StretchRec uniform_stretch(const AttnArgs& a, int wg)
             __builtin_amdgcn_readfirstlane(v.w)};
 }
 
-hipError_t launch_plan(const AttnArgs& a, const WorkspaceLayout& w, hipStream_t stream);
+hipError_t launch_plan(const AttnArgs& a, hipStream_t stream);
 hipError_t launch_general(const AttnArgs& a, hipStream_t stream);   // any supported shape
 hipError_t launch_combine(const AttnArgs& a, hipStream_t stream);
 bool general_supports(int Dqk, int Dv);

@@ -14,17 +14,19 @@
 #include <stdio.h>
 
 #include "seer_device.h"
+#include "seer_plan.h"
 
 namespace seer {
 
 // ---------------------------------------------------------------------------
 // Plan: one workgroup turns ctx_len[B] into the tile line, the stretch of every
-// partition workgroup and the partial slots of every request; a second one,
-// beside it, compares neighbouring block-table rows (plan_shared_pages).
+// partition workgroup and the partial slots of every request; further ones,
+// beside it, compare neighbouring block-table rows (plan_shared_pages).  (Most calls of up to
+// kSelfPlanRequests requests do without it: seer_plan.h.)
 //
-// The kernel is one dependent chain in front of every planned call, so it is
-// written for the length of that chain: all global loads (lengths, header, speed
-// history) are requested at once, one request and one stretch per thread, two
+// The kernel is one dependent chain in front of every call that needs it, so it is
+// written for the length of that chain: all global loads (lengths, header, shares of
+// the speeds) are requested at once, one request and one stretch per thread, two
 // exchanges between the waves for all sums and scans, and searches in LDS
 // instead of walks over a request's pieces.  With 256 threads, four exchanges and
 // walks it took 8.6 .. 12.5 us of every call, now 4.8 .. 5.8 (4 to 64 requests).
@@ -33,61 +35,26 @@ constexpr int kPlanThreads = 1024;
 constexpr int kPlanWaves = kPlanThreads / kWave;
 constexpr int kPlanLdsRequests = 4096;   // tile offsets of this many requests are searched in LDS, of more in global memory
 
-struct PlanArgs {
-    const int32_t* ctx_len;
-    const int32_t* block_table;
-    int B, T, max_ctx, wgs_per_head, max_splits, fixed_split, max_pages, page_size, min_tiles, fine_pieces;
-    PlanHeader* header;
-    ReqSlots* req_slots;
-    int32_t* tile_off;
-    StretchRec* stretch;
-    int32_t* shared_tiles;
-    uint32_t* fb_time;
-    uint32_t* fb_tiles;
-    float* fb_speed;
-};
-
-// Inclusive sum over the lanes of a wave through DPP: shifts by 1, 2, 4, 8 inside rows of 16 lanes, then the last lane of a
-// row to the row behind it and of the lower half to the upper (lanes without a source add zero).
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ int dpp_take(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, ROW_MASK, 0xf, true); }
-__device__ __forceinline__ int wave_incl_scan(int v) {
-    v += dpp_take<0x111, 0xf>(v);
-    v += dpp_take<0x112, 0xf>(v);
-    v += dpp_take<0x114, 0xf>(v);
-    v += dpp_take<0x118, 0xf>(v);
-    v += dpp_take<0x142, 0xa>(v);
-    v += dpp_take<0x143, 0xc>(v);
-    return v;
-}
-__device__ __forceinline__ float wave_incl_scan(float v) {
-    auto step = [&](int x) { v += __int_as_float(x); };
-    step(dpp_take<0x111, 0xf>(__float_as_int(v)));
-    step(dpp_take<0x112, 0xf>(__float_as_int(v)));
-    step(dpp_take<0x114, 0xf>(__float_as_int(v)));
-    step(dpp_take<0x118, 0xf>(__float_as_int(v)));
-    step(dpp_take<0x142, 0xa>(__float_as_int(v)));
-    step(dpp_take<0x143, 0xc>(__float_as_int(v)));
-    return v;
-}
-__device__ __forceinline__ int last_lane(int v) { return __builtin_amdgcn_readlane(v, kWave - 1); }
-__device__ __forceinline__ float last_lane(float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), kWave - 1)); }
-
-// The plan's second workgroup.  Leading pages that a request has in common with the request before or after it
+// The plan's further workgroups.  Leading pages that a request has in common with the request before or after it
 // (the prompt that the rollouts of a group share sits in the same physical pages): the partition kernel loads such
 // tiles with the cache policy that keeps them, so that the repeats are served by the memory-side cache.  This is a
 // hint only, results do not depend on it, so the length of the common run is found by probing instead of comparing
 // every entry: sixteen entries at doubling distances, then sixteen evenly spaced ones between the last equal probe
 // and the first unequal one (two dependent rounds of loads; exact for runs of up to 32 pages, else short by less
-// than a sixteenth of the run if the tables are equal up to a point and differ behind it).  It runs beside the
-// first workgroup, which needs about as long for the tile line and the stretches.
-__device__ __forceinline__ void plan_shared_pages(const PlanArgs& p) {
-    for (int b = threadIdx.x; b < p.B; b += kPlanThreads) {
+// than a sixteenth of the run if the tables are equal up to a point and differ behind it).  They run beside the
+// first workgroup, which needs about as long for the tile line and the stretches.  A thread's probes lie in 128 cache lines
+// of their own, so a workgroup takes a few requests only (one for all 64 of the tensor-parallel batch: its combine kernel, in which
+// they run where the partition kernel plans for itself, took 0.8 us longer than without them).
+constexpr int kSharedRequests = 8;
+inline int shared_pages_wgs(int B) { return (B + kSharedRequests - 1) / kSharedRequests; }
+__device__ __forceinline__ void plan_shared_pages(const AttnArgs& p, int wg) {
+    const int b = wg * kSharedRequests + static_cast<int>(threadIdx.x);
+    if (threadIdx.x < kSharedRequests && b < p.B) {
         const int n = p.ctx_len[b];
         int best = 0;
         if (n >= p.T && n <= p.max_ctx) {
             const int32_t* mine = p.block_table + static_cast<size_t>(b) * p.max_pages;
-            const int pages = (n + p.page_size - 1) / p.page_size;
+            const int pages = (n + p.P - 1) / p.P;
             int m[2] = {0, 0};                 // entries that can be compared with the neighbour
             const int32_t* other[2] = {mine, mine};
 #pragma unroll
@@ -96,7 +63,7 @@ __device__ __forceinline__ void plan_shared_pages(const PlanArgs& p) {
                 if (nb < 0 || nb >= p.B) continue;
                 const int nn = p.ctx_len[nb];
                 if (nn < p.T || nn > p.max_ctx) continue;
-                m[s] = min(pages, (nn + p.page_size - 1) / p.page_size);
+                m[s] = min(pages, (nn + p.P - 1) / p.P);
                 other[s] = p.block_table + static_cast<size_t>(nb) * p.max_pages;
             }
             uint32_t eq[2] = {0u, 0u};        // bit k: probe k found equal entries
@@ -128,68 +95,56 @@ __device__ __forceinline__ void plan_shared_pages(const PlanArgs& p) {
 #pragma unroll
             for (int s = 0; s < 2; ++s) best = max(best, min(lo[s] + __builtin_ctz(~eq[s]) * step[s], hi[s]));
         }
-        p.shared_tiles[b] = static_cast<int>(static_cast<long long>(best) * p.page_size / kPlanTile);
+        const_cast<int32_t*>(p.shared_tiles)[b] = static_cast<int>(static_cast<long long>(best) * p.P / kPlanTile);
     }
 }
 
-__global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs p) {
-    if (blockIdx.x == 1) {
-        plan_shared_pages(p);
+__global__ __launch_bounds__(kPlanThreads) void plan_kernel(AttnArgs p) {
+    if (blockIdx.x > 0) {
+        plan_shared_pages(p, blockIdx.x - 1);
         return;
     }
     __shared__ int s_tiles[kPlanWaves], s_longest[kPlanWaves];       // per wave
-    __shared__ float s_speed[kPlanWaves], s_known[kPlanWaves], s_rate[kPlanWaves];
     __shared__ int s_start[kMaxWgsPerHead + 1];
     __shared__ int s_off[kPlanLdsRequests + 1];
+    int32_t* const tile_off = const_cast<int32_t*>(p.tile_off);
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     const int W = p.wgs_per_head;
-    const bool balanced = p.max_splits > 1, history = balanced && !p.fixed_split;
+    const bool balanced = p.balanced != 0, history = balanced && !p.fixed_split;
     const bool in_lds = p.B <= kPlanLdsRequests;
 
     // ---- everything this thread reads from global memory: its run of requests (one each up to 1024), its stretch -----
     const int per = (p.B + kPlanThreads - 1) / kPlanThreads;
     const int b0 = min(p.B, tid * per), b1 = min(p.B, b0 + per);
     const int n_first = b0 < b1 ? p.ctx_len[b0] : 0;
-    uint32_t magic = 0u, ticks = 0u, streamed = 0u;
-    int fb_w = 0;
-    float est = 0.f;
+    uint32_t before = equal_before(p, tid);
     if (history) {
-        magic = p.header->fb_magic, fb_w = p.header->fb_w;
-        if (tid < W) est = p.fb_speed[tid], ticks = p.fb_time[tid], streamed = p.fb_tiles[tid];
+        const uint32_t magic = p.header->fb_magic;
+        const int w = p.header->fb_w;
+        const uint32_t f = p.fb_before[min(tid, W)];
+        if (magic == kFeedbackMagic && w == W) before = f;
     }
-    auto tiles_of = [&](int n) -> int { return n < p.T || n > p.max_ctx ? 0 : (n + kPlanTile - 1) / kPlanTile; };
+    auto tiles = [&](int n) -> int { return tiles_of(n, p.T, p.max_ctx); };
     auto length = [&](int b) -> int { return b == b0 ? n_first : p.ctx_len[b]; };
 
-    // ---- sums inside the wave: tiles of its requests, speeds of its stretches -------------------------------------------
+    // ---- sums inside the wave: tiles of its requests --------------------------------------------------------------------
     int cnt = 0, mx = 0;
     bool bad = false;
     for (int b = b0; b < b1; ++b) {
-        const int n = length(b), t = tiles_of(n);
+        const int n = length(b), t = tiles(n);
         bad |= n < p.T || n > p.max_ctx;                 // flagged, gets a zero output
         cnt += t;
         mx = max(mx, t);
     }
-    // relative speed of each stretch index from the history in the workspace (unknown: 0, also whatever a stale one held)
-    if (!(magic == kFeedbackMagic && fb_w == W)) est = 0.f, ticks = 0u;
-    if (ticks > 0u && streamed > 0u) {
-        const float meas = static_cast<float>(streamed) / static_cast<float>(ticks);
-        est = est > 0.f ? 0.5f * est + 0.5f * meas : meas;
-    }
-    if (!(est > 0.f) || !(est < 1e30f)) est = 0.f;
     const int incl = wave_incl_scan(cnt);
     const int wave_bad = __any(bad) ? 1 : 0;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) mx = max(mx, __shfl_xor(mx, o, kWave));
-    const float sum = last_lane(wave_incl_scan(est)), known = last_lane(wave_incl_scan(est > 0.f ? 1.f : 0.f));
+    mx = wave_max_in_last_lane(mx);
     if (lane == kWave - 1) {
         s_tiles[wave] = incl;
         s_longest[wave] = mx * 2 + wave_bad;
-        s_speed[wave] = sum;
-        s_known[wave] = known;
     }
     __syncthreads();
     int total = 0, my_off = incl - cnt, longest = 0;
-    float speed_sum = 0.f, speed_known = 0.f;
     int any_bad = 0;
 #pragma unroll
     for (int w = 0; w < kPlanWaves; ++w) {
@@ -198,56 +153,24 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs p) {
         total += t;
         longest = max(longest, l >> 1);
         any_bad |= l & 1;
-        speed_sum += s_speed[w];
-        speed_known += s_known[w];
     }
     {
         int off = my_off;
         for (int b = b0; b < b1; ++b) {
-            p.tile_off[b] = off;
+            tile_off[b] = off;
             if (in_lds) s_off[b] = off;
-            off += tiles_of(length(b));
+            off += tiles(length(b));
         }
         if (tid == 0) {
-            p.tile_off[p.B] = total;
+            tile_off[p.B] = total;
             if (in_lds) s_off[p.B] = total;
         }
     }
 
     if (balanced) {
         // ---- the stretches ----------------------------------------------------------------------------------------------
-        // a request of t tiles touches at most ceil(t / Lmin) + 1 stretches, which must fit max_splits
-        const int per_w = (total + W - 1) / W;
-        const bool fine = per_w < 2 || per_w >= kMinTilesLatent || total <= (p.fine_pieces - p.B) * per_w;
-        const int Lmin = max(fine ? p.min_tiles : kMinTilesLatent, (longest + p.max_splits - 2) / (p.max_splits - 1));
-        // Stretch w begins at the tile nearest to total * (r_0 + .. + r_{w-1}) / R.  When the line is too
-        // short for that to keep every stretch at Lmin tiles or more, cut it into equal stretches of
-        // max(Lmin, ceil(total / W)) tiles instead (the last ones are then short or empty).
-        const bool weighted = static_cast<long long>(total) >= static_cast<long long>(max(2 * Lmin, kMinTilesWeighted)) * W;
-        const float mean = speed_known > 0.f ? speed_sum / speed_known : 1.f;
-        float rate = 0.f;
-        if (tid < W) rate = fminf(fmaxf((weighted && est > 0.f) ? est / mean : 1.f, 0.75f), 4.f / 3.f);
-        const float rate_incl = wave_incl_scan(rate);
-        if (lane == kWave - 1) s_rate[wave] = rate_incl;
-        __syncthreads();
-        float before = rate_incl - rate, R = 0.f;
-#pragma unroll
-        for (int w = 0; w < kPlanWaves; ++w) {
-            const float x = s_rate[w];
-            if (w < wave) before += x;
-            R += x;
-        }
-        if (tid < W) {
-            const int L_equal = max(Lmin, max(per_w, 1));
-            const long long cut = weighted ? static_cast<long long>(static_cast<double>(total) * before / R + 0.5)
-                                           : static_cast<long long>(tid) * L_equal;
-            s_start[tid] = static_cast<int>(cut < total ? cut : total);
-            if (history) {
-                p.fb_speed[tid] = est;
-                p.fb_time[tid] = 0u;
-                p.fb_tiles[tid] = 0u;
-            }
-        }
+        const Cut cut = cut_of(p, total, longest);
+        if (tid < W) s_start[tid] = cut_begin(cut, tid, before);
         if (tid == 0) s_start[W] = total;
     }
     __syncthreads();
@@ -255,7 +178,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs p) {
     // ---- per stretch: where it starts ------------------------------------------------------------------------------------
     for (int w = tid; w < W; w += kPlanThreads) {
         StretchRec r;
-        auto off = [&](int b) -> int { return in_lds ? s_off[b] : p.tile_off[b]; };
+        auto off = [&](int b) -> int { return in_lds ? s_off[b] : tile_off[b]; };
         if (balanced) {
             r.tile_begin = s_start[w], r.tile_end = s_start[w + 1];
             r.b = -1, r.req_begin = 0;
@@ -273,7 +196,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs p) {
             r.req_begin = r.tile_begin;
             r.b = r.tile_begin < r.tile_end ? w : -1;
         }
-        p.stretch[w] = r;
+        const_cast<StretchRec*>(p.stretch)[w] = r;
     }
     // ---- per request: its partial slots ----------------------------------------------------------------------------------
     // stretch that holds tile x (x < total): the last one that starts at or before it
@@ -287,51 +210,25 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(PlanArgs p) {
     };
     int lo = my_off;
     for (int b = b0; b < b1; ++b) {
-        const int hi = lo + tiles_of(length(b));
-        ReqSlots s{0, 0};
+        const int hi = lo + tiles(length(b));
+        ReqSlots s{0, -1};
         if (hi > lo) {
             const int first = balanced ? stretch_of(lo) : 0;
             s.first = first + b;
-            s.count = balanced ? stretch_of(hi - 1) - first + 1 : 1;
+            s.last = (balanced ? stretch_of(hi - 1) : 0) + b;
         }
-        p.req_slots[b] = s;
+        const_cast<ReqSlots*>(p.req_slots)[b] = s;
         lo = hi;
     }
     if (tid == 0) {
         p.header->status = any_bad ? 1u : 0u;
         p.header->plan_b = plan_b_word(p.B);
         p.header->plan_w = plan_w_word(W, balanced);
-        if (history) {
-            p.header->fb_magic = kFeedbackMagic;
-            p.header->fb_w = W;
-        }
     }
 }
 
-hipError_t launch_plan(const AttnArgs& a, const WorkspaceLayout& w, hipStream_t stream) {
-    const long long max_ctx_ll = static_cast<long long>(a.max_pages) * a.P;
-    PlanArgs p;
-    p.ctx_len = a.ctx_len;
-    p.block_table = a.block_table;
-    p.max_pages = a.max_pages;
-    p.page_size = a.P;
-    p.shared_tiles = const_cast<int32_t*>(a.shared_tiles);
-    p.B = a.B;
-    p.T = a.T;
-    p.max_ctx = max_ctx_ll > 0x7fffffffLL - kPlanTile ? 0x7fffffff - kPlanTile : static_cast<int>(max_ctx_ll);
-    p.wgs_per_head = w.wgs_per_head;
-    p.max_splits = w.max_splits;
-    p.header = a.header;
-    p.req_slots = const_cast<ReqSlots*>(a.req_slots);
-    p.tile_off = const_cast<int32_t*>(a.tile_off);
-    p.stretch = const_cast<StretchRec*>(a.stretch);
-    p.fb_time = a.fb_time;
-    p.fb_tiles = a.fb_tiles;
-    p.fb_speed = a.fb_speed;
-    p.fixed_split = a.fixed_split;
-    p.min_tiles = a.min_tiles;
-    p.fine_pieces = a.fine_pieces;
-    hipLaunchKernelGGL(plan_kernel, dim3(2), dim3(kPlanThreads), 0, stream, p);
+hipError_t launch_plan(const AttnArgs& a, hipStream_t stream) {
+    hipLaunchKernelGGL(plan_kernel, dim3(1 + shared_pages_wgs(a.B)), dim3(kPlanThreads), 0, stream, a);
     return hipGetLastError();
 }
 
@@ -546,19 +443,118 @@ __device__ __forceinline__ void add_pieces(PartSum& s, const float2* ml, const f
     }
 }
 
-__global__ __launch_bounds__(kCombineThreads) void combine_kernel(AttnArgs a, int blocks_per_request, int log2_slices, int log2_per_row) {
+// What a call that plans leaves for the calls after it, by a workgroup of the combine kernel beside its others: the rates
+// of the stretch indices from the partition kernel's measurements (in front of the partition kernel this was part of the plan
+// kernel's chain), and, where the partition kernel planned for itself, the status word.
+__device__ __forceinline__ void finish_call(const AttnArgs& a) {
+    constexpr int kPer = kMaxWgsPerHead / kCombineThreads, kWaves = kCombineThreads / kWave;
+    __shared__ float s_speed[kWaves], s_known[kWaves], s_rate[kWaves];
+    __shared__ int s_status;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave, W = a.wgs_per_head;
+    const bool history = a.balanced && !a.fixed_split;
+    if (tid == 0) s_status = 0;
+    float est[kPer];
+    float sum = 0.f, known = 0.f;
+    if (history) {
+        const bool valid = a.header->fb_magic == kFeedbackMagic && a.header->fb_w == W;
+        uint32_t ticks[kPer], streamed[kPer];
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int w = min(tid * kPer + k, W - 1);
+            est[k] = a.fb_speed[w], ticks[k] = a.fb_time[w], streamed[k] = a.fb_tiles[w];
+        }
+        // relative speed of each stretch index (unknown: 0, also whatever a stale one held)
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            if (!valid) est[k] = 0.f, ticks[k] = 0u;
+            if (ticks[k] > 0u && streamed[k] > 0u) {
+                const float meas = static_cast<float>(streamed[k]) / static_cast<float>(ticks[k]);
+                est[k] = est[k] > 0.f ? 0.5f * est[k] + 0.5f * meas : meas;
+            }
+            if (!(est[k] > 0.f) || !(est[k] < 1e30f) || tid * kPer + k >= W) est[k] = 0.f;
+            sum += est[k];
+            known += est[k] > 0.f ? 1.f : 0.f;
+        }
+        sum = last_lane(wave_incl_scan(sum)), known = last_lane(wave_incl_scan(known));
+        if (lane == 0) s_speed[wave] = sum, s_known[wave] = known;
+    }
+    bool bad_len = false, bad_page = false;
+    if (a.self_plan) {
+        if (tid < a.B) {
+            const int n = a.ctx_len[tid];
+            bad_len = n < a.T || n > a.max_ctx;
+        }
+        const int count = W * a.Hkv * a.row_blocks, waves = a.plan_waves;
+        const uint64_t mask = waves >= 8 ? ~0ull : (1ull << (8 * waves)) - 1;
+        uint64_t any = 0;
+#pragma unroll 8
+        for (int i = tid; i < count; i += kCombineThreads) any |= reinterpret_cast<const uint64_t*>(a.page_flags)[i] & mask;
+        bad_page = any != 0;
+    }
+    __syncthreads();
+    const int found = (__any(bad_len) ? 1 : 0) | (__any(bad_page) ? 2 : 0);
+    if (found && lane == 0) atomicOr(&s_status, found);
+    float rate[kPer], mine = 0.f, incl = 0.f;
+    if (history) {
+        sum = known = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) sum += s_speed[w], known += s_known[w];
+        const float mean = known > 0.f ? sum / known : 1.f;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            rate[k] = tid * kPer + k >= W ? 0.f : fminf(fmaxf(est[k] > 0.f ? est[k] / mean : 1.f, 0.75f), 4.f / 3.f);
+            mine += rate[k];
+        }
+        incl = wave_incl_scan(mine);
+        if (lane == kWave - 1) s_rate[wave] = incl;
+    }
+    __syncthreads();
+    if (history) {
+        float before = incl - mine, all = 0.f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            if (w < wave) before += s_rate[w];
+            all += s_rate[w];
+        }
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int w = tid * kPer + k;
+            if (w < W) {
+                a.fb_before[w] = static_cast<uint32_t>(fminf(before / all, 0.99999994f) * 4294967296.f);
+                before += rate[k];
+                a.fb_speed[w] = est[k];
+                a.fb_time[w] = 0u, a.fb_tiles[w] = 0u;
+            }
+        }
+    }
+    if (tid == 0) {
+        if (history) a.header->fb_magic = kFeedbackMagic, a.header->fb_w = W;
+        if (a.self_plan) a.header->status = static_cast<uint32_t>(s_status);
+    }
+}
+
+// (five waves per SIMD: the extra workgroups' code must not cost the others theirs)
+__global__ __launch_bounds__(kCombineThreads) __attribute__((amdgpu_waves_per_eu(5))) void combine_kernel(AttnArgs a, int blocks_per_request, int log2_slices, int log2_per_row,
+                                                                  int extra) {
     __shared__ PartSum s_part[kCombineThreads];
-    const int b = blockIdx.x / blocks_per_request;
+    // the first workgroups (none in a call that reuses a plan): what is left for later calls
+    if (static_cast<int>(blockIdx.x) < extra) {
+        if (blockIdx.x == 0) finish_call(a);
+        else plan_shared_pages(a, blockIdx.x - 1);
+        return;
+    }
+    const int block = static_cast<int>(blockIdx.x) - extra;
+    const int b = block / blocks_per_request;
     const ReqSlots slots = a.req_slots[b];
     if (!has_plan(a)) return;
     const int per_b = a.T * a.Hq;
     const int tid = threadIdx.x;
-    const int r = ((blockIdx.x - b * blocks_per_request) * kCombineThreads + tid) >> (log2_per_row + log2_slices);
+    const int r = ((block - b * blocks_per_request) * kCombineThreads + tid) >> (log2_per_row + log2_slices);
     const int slice = (tid >> log2_per_row) & ((1 << log2_slices) - 1);
     const int d = (tid & ((1 << log2_per_row) - 1)) << 2;
     const bool row_ok = r < per_b;
     PartSum s{kNegInf, 0.f, f32x4{0.f, 0.f, 0.f, 0.f}};
-    int left = row_ok ? (slots.count - slice + (1 << log2_slices) - 1) >> log2_slices : 0;   // pieces of this slice
+    int left = row_ok ? (slots.last - slots.first - slice + (1 << log2_slices)) >> log2_slices : 0;   // pieces of this slice
     if (left > 0) {
         const size_t at = static_cast<size_t>(slots.first + slice) * per_b + r;
         const float2* ml = reinterpret_cast<const float2*>(a.part_ml) + at;
@@ -611,8 +607,9 @@ hipError_t launch_combine(const AttnArgs& a, hipStream_t stream) {
     const int log2_slices = combine_slices_log2(a, log2_per_row);
     const long long threads = static_cast<long long>(a.T) * a.Hq << (log2_per_row + log2_slices);
     const int per_request = static_cast<int>((threads + kCombineThreads - 1) / kCombineThreads);
-    hipLaunchKernelGGL(combine_kernel, dim3(static_cast<unsigned>(per_request) * static_cast<unsigned>(a.B)), dim3(kCombineThreads), 0,
-                       stream, a, per_request, log2_slices, log2_per_row);
+    const int extra = a.self_plan ? 1 + shared_pages_wgs(a.B) : (!a.reuse_plan && a.balanced && !a.fixed_split ? 1 : 0);
+    hipLaunchKernelGGL(combine_kernel, dim3(static_cast<unsigned>(per_request) * static_cast<unsigned>(a.B) + extra), dim3(kCombineThreads),
+                       0, stream, a, per_request, log2_slices, log2_per_row, extra);
     return hipGetLastError();
 }
 
@@ -718,6 +715,15 @@ int run_verify_attention(void* out, const void* q, const void* k_pages, const vo
     a.fb_time = reinterpret_cast<uint32_t*>(ws + w.off_fb);
     a.fb_tiles = a.fb_time + (w.wgs_per_head + 1);
     a.fb_speed = reinterpret_cast<float*>(a.fb_tiles + (w.wgs_per_head + 1));
+    a.fb_before = reinterpret_cast<uint32_t*>(a.fb_speed + (w.wgs_per_head + 1));
+    a.inv_wgs = seer::reciprocal(w.wgs_per_head);
+    a.inv_splits = seer::reciprocal(w.max_splits - 1);
+    a.page_flags = reinterpret_cast<uint8_t*>(ws + w.off_flags);
+    a.max_splits = w.max_splits;
+    const long long max_ctx = static_cast<long long>(p->max_pages_per_seq) * p->page_size;
+    a.max_ctx = max_ctx > 0x7fffffffLL - seer::kPlanTile ? 0x7fffffff - seer::kPlanTile : static_cast<int>(max_ctx);
+    a.reuse_plan = (p->flags & SEER_ATTN_REUSE_PLAN) ? 1 : 0;
+    a.self_plan = seer::self_plan_layout(*p) && !(p->flags & (SEER_ATTN_GENERAL_KERNEL | SEER_ATTN_REUSE_PLAN | SEER_ATTN_STREAM_ONLY)) ? 1 : 0;
     a.fixed_split = (p->flags & SEER_ATTN_FIXED_SPLIT) ? 1 : 0;
     a.stream_only = (p->flags & SEER_ATTN_STREAM_ONLY) ? 1 : 0;
     a.stream_partials = (w.total - w.off_acc) < seer::kStreamPartialsBelow ? 1 : 0;
@@ -725,6 +731,7 @@ int run_verify_attention(void* out, const void* q, const void* k_pages, const vo
     const int rows = (p->Hq / p->Hkv) * p->T;
     a.row_blocks = tile_kernel ? seer::tile_row_blocks(rows, p->Dqk) : seer::gqa_row_blocks(rows);
     a.rows_per_block = tile_kernel ? seer::tile_rows_per_block(rows, p->Dqk) : seer::gqa_rows_per_block(rows);
+    a.plan_waves = tile_kernel || !seer::gqa_block_uses_helpers(a.rows_per_block) ? a.rows_per_block / 32 : 8;
     a.part_ml = reinterpret_cast<float*>(ws + w.off_ml);
     a.part_acc = reinterpret_cast<float*>(ws + w.off_acc);
     a.B = p->B;
@@ -746,7 +753,7 @@ int run_verify_attention(void* out, const void* q, const void* k_pages, const vo
 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     // the plan depends on the shape and on ctx_len only: the layers of one step can share it
-    hipError_t err = (p->flags & SEER_ATTN_REUSE_PLAN) ? hipSuccess : seer::launch_plan(a, w, stream);
+    hipError_t err = a.reuse_plan || a.self_plan ? hipSuccess : seer::launch_plan(a, stream);
     if (err != hipSuccess) return static_cast<int>(err);
     if (ev_begin && (err = hipEventRecord(ev_begin, stream)) != hipSuccess) return static_cast<int>(err);
     if (tiled_ok && seer::gqa128_supports(a)) err = seer::launch_gqa128(a, stream);

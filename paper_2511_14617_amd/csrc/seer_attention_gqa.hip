@@ -53,6 +53,7 @@
 
 #include "seer_attention.h"
 #include "seer_device.h"
+#include "seer_plan.h"
 #include "seer_tile.h"
 
 namespace seer {
@@ -538,8 +539,8 @@ __device__ __forceinline__ void softmax_pv(int v, f32x16& s, f32x16 (&acc)[4], f
                                                           acc[dt], 0, 0, 0);
 }
 
-template <bool STREAM, bool STREAM_PARTIALS>
-__device__ __forceinline__ void run(const AttnArgs& a, unsigned char* lds, int kvh, int rb, int wg, const StretchRec& rec) {
+template <bool STREAM, bool STREAM_PARTIALS, bool SELF>
+__device__ __forceinline__ void run(const AttnArgs& a, unsigned char* lds, const int* line, int kvh, int rb, int wg, const StretchRec& rec) {
     constexpr int NT = kWaves * kWave;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -583,19 +584,21 @@ __device__ __forceinline__ void run(const AttnArgs& a, unsigned char* lds, int k
     auto first_pages = [&](int bb, int page0) __attribute__((always_inline)) -> int {
         return (a.block_table + static_cast<size_t>(min(bb, a.B - 1)) * a.max_pages)[min(page0 + lane, a.max_pages - 1)];
     };
-    int pw = piece_words(b);
+    int pw = SELF ? 0 : piece_words(b);
     int page_ahead = ((g - rec.req_begin) * kTile) >> page_shift;       // (see the kernel below)
     int pg_ahead = first_pages(b, page_ahead);
     const int g_first = g;
 
   for (; g < g_end; ++b) {
+    if (SELF) pw = line_words(line, b);
     const int t_lo = __builtin_amdgcn_readlane(pw, 0), t_hi = __builtin_amdgcn_readlane(pw, 1);
     const int item_idx = b + slot_bias;
     const int n = __builtin_amdgcn_readlane(pw, 2);
-    const int shared_tiles = __builtin_amdgcn_readlane(pw, 3);
+    int shared_tiles = __builtin_amdgcn_readlane(pw, 3);
     const int pg_first = pg_ahead;
     const int page_first = page_ahead;
-    pw = piece_words(b + 1);
+    if (SELF) shared_tiles = t_hi > t_lo ? page_first * a.P / kTile + shared_tiles_from(a, b, page_first, pg_first) : 0;
+    else pw = piece_words(b + 1);
     pg_ahead = first_pages(b + 1, 0);
     page_ahead = 0;
     if (t_hi == t_lo) continue;
@@ -842,7 +845,8 @@ __device__ __forceinline__ void run(const AttnArgs& a, unsigned char* lds, int k
         }
     }
   }  // pieces of the stretch
-    if (bad_page && lane == 0) atomicOr(&a.header->status, 2u);
+    if constexpr (SELF) publish_stretch(a, line, rec, wg, kvh, rb, wave, bad_page);
+    else if (bad_page && lane == 0) atomicOr(&a.header->status, 2u);
     if (a.balanced && !a.fixed_split && tid == 0) {
         const uint64_t ticks = __builtin_amdgcn_s_memrealtime() - clock_begin;
         atomicAdd(a.fb_time + wg, static_cast<uint32_t>(ticks > 0xffffffu ? 0xffffffu : ticks));
@@ -864,7 +868,9 @@ __device__ __forceinline__ void for_each_index(F& f, std::integer_sequence<int, 
 // STREAM_PARTIALS: the partial results leave with non-temporal stores (see kStreamPartialsBelow).
 // NH: 0, or the three further waves that make five row waves into four main and four helper waves (see `pairs` above) in
 // stretches whose pieces are long (kPairsFromTiles).
-template <int NW, int D, bool STREAM, bool STREAM_PARTIALS, int NH = 0>
+// SELF: every wave finds its stretch itself (seer_plan.h) instead of reading it from the plan kernel's tables.  (A template
+// parameter: with both ways in one kernel the multi-path batch, which needs the tables, took 0.8 % longer through spilled scalars.)
+template <int NW, int D, bool STREAM, bool STREAM_PARTIALS, int NH = 0, bool SELF = false>
 __global__ __launch_bounds__((NW + NH) * kWave) __attribute__((amdgpu_waves_per_eu(NW + NH == 1 ? 1 : 2, 2)))
 void attn_gqa128_kernel(AttnArgs a) {
     static_assert(NH == 0 || NW + NH == pairs::kWaves, "pairs need eight waves");
@@ -878,6 +884,7 @@ void attn_gqa128_kernel(AttnArgs a) {
 
     // K ring, then V ring (pairs have a layout of their own)
     __shared__ __attribute__((aligned(1024))) unsigned char lds[NH > 0 && pairs::kLdsBytes > 2 * NSLOT * kKBytes ? pairs::kLdsBytes : 2 * NSLOT * kKBytes];
+    __shared__ int s_line[kLineWords];              // (see plan_stretch)
     constexpr int kVRing = NSLOT * kKBytes;
 
     // Workgroup ids are dealt round-robin to the 8 XCDs and dispatched in id order.  The grid is laid
@@ -898,22 +905,36 @@ void attn_gqa128_kernel(AttnArgs a) {
     const int l16 = lane >> 4;
     const int p16 = lane & 15;
 
-    const StretchRec rec = uniform_stretch(a, wg);
+    StretchRec rec;
+    int pieces = 1;
+    if (SELF) {
+        const SelfPlan own = plan_stretch(a, s_line, wg);
+        rec = own.rec, pieces = own.pieces;
+        if (rec.b < 0) {
+            publish_stretch(a, s_line, rec, wg, kvh, rb, wave, false);
+            return;
+        }
+    } else {
+        rec = uniform_stretch(a, wg);
+    }
     int b = rec.b;
     if constexpr (NH > 0) {
         // the pieces of this stretch: its requests up to the one the next stretch starts in (without it, if it starts with it)
-        const StretchRec next = uniform_stretch(a, min(wg + 1, a.wgs_per_head - 1));
+        StretchRec next{-1, 0, 0, 0};
+        if (!SELF) next = uniform_stretch(a, min(wg + 1, a.wgs_per_head - 1));
         if (b < 0) return;
-        int pieces = 1;
-        if (a.balanced) {
+        if (a.balanced && !SELF) {
             const int last = wg + 1 == a.wgs_per_head || next.b < 0 ? a.B - 1 : next.b - (next.req_begin == next.tile_begin ? 1 : 0);
             pieces = max(1, last - b + 1);
         }
         if (rec.tile_end - rec.tile_begin >= kPairsFromTiles * pieces) {
-            pairs::run<STREAM, STREAM_PARTIALS>(a, lds, kvh, rb, wg, rec);
+            pairs::run<STREAM, STREAM_PARTIALS, SELF>(a, lds, s_line, kvh, rb, wg, rec);
             return;
         }
-        if (wave >= NW) return;                     // (barriers wait for the waves that are left)
+        if (wave >= NW) {                           // (barriers wait for the waves that are left)
+            if constexpr (SELF) publish_stretch(a, s_line, rec, wg, kvh, rb, wave, false);
+            return;
+        }
     } else {
         if (b < 0) return;
     }
@@ -961,20 +982,22 @@ void attn_gqa128_kernel(AttnArgs a) {
     auto first_pages = [&](int bb, int page0) __attribute__((always_inline)) -> int {
         return (a.block_table + static_cast<size_t>(min(bb, a.B - 1)) * a.max_pages)[min(page0 + lane, a.max_pages - 1)];
     };
-    int pw = piece_words(b);
+    int pw = SELF ? 0 : piece_words(b);
     // 64 page ids of request b from page page_ahead on, where its next piece starts (a stretch starts inside a request, every
     // other piece at its request's first page)
     int page_ahead = ((g - rec.req_begin) * kTile) >> page_shift;
     int pg_ahead = first_pages(b, page_ahead);
 
   for (; g < g_end; ++b) {
+    if (SELF) pw = line_words(s_line, b);
     const int t_lo = __builtin_amdgcn_readlane(pw, 0), t_hi = __builtin_amdgcn_readlane(pw, 1);
     const int item_idx = b + slot_bias;
     const int n = __builtin_amdgcn_readlane(pw, 2);
-    const int shared_tiles = __builtin_amdgcn_readlane(pw, 3);
+    int shared_tiles = __builtin_amdgcn_readlane(pw, 3);
     const int pg_first = pg_ahead;
     const int page_first = page_ahead;
-    pw = piece_words(b + 1);          // in flight while this piece is worked on
+    if (SELF) shared_tiles = t_hi > t_lo ? page_first * a.P / kTile + shared_tiles_from(a, b, page_first, pg_first) : 0;
+    else pw = piece_words(b + 1);          // in flight while this piece is worked on
     pg_ahead = first_pages(b + 1, 0);
     page_ahead = 0;
     if (t_hi == t_lo) continue;
@@ -1335,7 +1358,8 @@ void attn_gqa128_kernel(AttnArgs a) {
             }
     }
   }  // pieces of the stretch
-    if (bad_page && lane == 0) atomicOr(&a.header->status, 2u);
+    if constexpr (SELF) publish_stretch(a, s_line, rec, wg, kvh, rb, wave, bad_page);
+    else if (bad_page && lane == 0) atomicOr(&a.header->status, 2u);
     // speed history for the next call's plan: tiles streamed and time taken, by stretch index
     if (a.balanced && !a.fixed_split && tid == 0) {
         const uint64_t ticks = __builtin_amdgcn_s_memrealtime() - clock_begin;
@@ -1353,38 +1377,34 @@ hipError_t launch_gqa128(const AttnArgs& a, hipStream_t stream) {
     const int nw = a.rows_per_block / 32;
     const dim3 grid(static_cast<unsigned>((a.wgs_per_head + 7) / 8) * 8u * static_cast<unsigned>(a.Hkv) *
                     static_cast<unsigned>(a.row_blocks));
+    const dim3 block((gqa_block_uses_helpers(a.rows_per_block) ? 8 : nw) * kWave);
+#define SEER_GQA_LAUNCH(NW_, NH_)                                                                                       \
+    do {                                                                                                              \
+        constexpr int D_ = gqa_pipe_depth(NW_);                                                                       \
+        if (a.stream_only && a.stream_partials) hipLaunchKernelGGL((attn_gqa128_kernel<NW_, D_, true, true, NH_>), grid, block, 0, stream, a);   \
+        else if (a.stream_only) hipLaunchKernelGGL((attn_gqa128_kernel<NW_, D_, true, false, NH_>), grid, block, 0, stream, a);                  \
+        else if (a.self_plan && a.stream_partials) hipLaunchKernelGGL((attn_gqa128_kernel<NW_, D_, false, true, NH_, true>), grid, block, 0, stream, a); \
+        else if (a.self_plan) hipLaunchKernelGGL((attn_gqa128_kernel<NW_, D_, false, false, NH_, true>), grid, block, 0, stream, a);             \
+        else if (a.stream_partials) hipLaunchKernelGGL((attn_gqa128_kernel<NW_, D_, false, true, NH_>), grid, block, 0, stream, a);              \
+        else hipLaunchKernelGGL((attn_gqa128_kernel<NW_, D_, false, false, NH_>), grid, block, 0, stream, a);                                    \
+    } while (0)
     // 129 .. 144 query rows in a row block: five waves, or four main waves and four helpers
     if (gqa_block_uses_helpers(a.rows_per_block)) {
-        const dim3 block(8 * kWave);
-        if (a.stream_only && a.stream_partials) hipLaunchKernelGGL((attn_gqa128_kernel<5, gqa_pipe_depth(5), true, true, 3>), grid, block, 0, stream, a);
-        else if (a.stream_only) hipLaunchKernelGGL((attn_gqa128_kernel<5, gqa_pipe_depth(5), true, false, 3>), grid, block, 0, stream, a);
-        else if (a.stream_partials) hipLaunchKernelGGL((attn_gqa128_kernel<5, gqa_pipe_depth(5), false, true, 3>), grid, block, 0, stream, a);
-        else hipLaunchKernelGGL((attn_gqa128_kernel<5, gqa_pipe_depth(5), false, false, 3>), grid, block, 0, stream, a);
+        SEER_GQA_LAUNCH(5, 3);
         return hipGetLastError();
     }
     switch (nw) {
-#define SEER_GQA_LAUNCH(NW_, STREAM_, PARTIALS_)                                                               \
-    hipLaunchKernelGGL((attn_gqa128_kernel<NW_, gqa_pipe_depth(NW_), STREAM_, PARTIALS_>), grid, dim3(NW_ * kWave), 0, \
-                       stream, a)
-#define SEER_GQA_CASE(NW_)                                                                                     \
-    case NW_:                                                                                                  \
-        if (a.stream_only && a.stream_partials) SEER_GQA_LAUNCH(NW_, true, true);                              \
-        else if (a.stream_only) SEER_GQA_LAUNCH(NW_, true, false);                                             \
-        else if (a.stream_partials) SEER_GQA_LAUNCH(NW_, false, true);                                         \
-        else SEER_GQA_LAUNCH(NW_, false, false);                                                               \
-        break;
-        SEER_GQA_CASE(1)
-        SEER_GQA_CASE(2)
-        SEER_GQA_CASE(3)
-        SEER_GQA_CASE(4)
-        SEER_GQA_CASE(5)
-        SEER_GQA_CASE(6)
-        SEER_GQA_CASE(7)
-        SEER_GQA_CASE(8)
-#undef SEER_GQA_CASE
-#undef SEER_GQA_LAUNCH
+        case 1: SEER_GQA_LAUNCH(1, 0); break;
+        case 2: SEER_GQA_LAUNCH(2, 0); break;
+        case 3: SEER_GQA_LAUNCH(3, 0); break;
+        case 4: SEER_GQA_LAUNCH(4, 0); break;
+        case 5: SEER_GQA_LAUNCH(5, 0); break;
+        case 6: SEER_GQA_LAUNCH(6, 0); break;
+        case 7: SEER_GQA_LAUNCH(7, 0); break;
+        case 8: SEER_GQA_LAUNCH(8, 0); break;
         default: return hipErrorInvalidValue;
     }
+#undef SEER_GQA_LAUNCH
     return hipGetLastError();
 }
 

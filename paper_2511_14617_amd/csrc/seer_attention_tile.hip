@@ -24,6 +24,7 @@
 
 #include "seer_attention.h"
 #include "seer_device.h"
+#include "seer_plan.h"
 #include "seer_tile.h"
 
 namespace seer {
@@ -89,13 +90,15 @@ __device__ __forceinline__ void read_v2(u32x2 (&vr)[2][4], int a0, int a1) {
 // One wave per 32 query rows.  Registers: 64-wide heads leave room for three waves per SIMD, (192, 128) for two; at D = 256
 // Q^T and O^T alone take 192, so one wave has a SIMD to itself (with 256 registers 40 of them would be spilled, and a
 // spill's reload waits for the tile loads in flight).
-template <int DQK, int DV>
+// SELF: every wave finds its stretch itself (seer_plan.h) instead of reading it from the plan kernel's tables.
+template <int DQK, int DV, bool SELF>
 __global__ __launch_bounds__(tile_max_waves(DQK) * kWave) __attribute__((amdgpu_waves_per_eu(tile_waves_per_simd(DQK))))
 void attn_tile_kernel(AttnArgs a, int n_waves) {
     using namespace tile;
     using S = Shape<DQK, DV>;
     // two stages of K tile, V tile; then two words: the scanned tile's tokens with infinities or NaN, "take the piece again"
     __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * S::kStage + 16];
+    __shared__ int s_line[kLineWords];              // (see plan_stretch)
     volatile uint32_t* s_nonfinite = reinterpret_cast<volatile uint32_t*>(lds + 2 * S::kStage);
     volatile uint32_t* s_again = s_nonfinite + 1;
 
@@ -109,7 +112,16 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int ln = lane & 31, lg = lane >> 5, l16 = lane >> 4, p16 = lane & 15;
 
-    const StretchRec rec = uniform_stretch(a, wg);
+    StretchRec rec;
+    if (SELF) {
+        rec = plan_stretch(a, s_line, wg).rec;
+        if (rec.b < 0) {
+            publish_stretch(a, s_line, rec, wg, kvh, rb, wave, false);
+            return;
+        }
+    } else {
+        rec = uniform_stretch(a, wg);
+    }
     int b = rec.b;
     if (b < 0) return;
     const int slot_bias = a.balanced ? wg : 0;
@@ -142,12 +154,13 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
     int words = 0, pages = 0;
     auto request = [&](int req, int first_page) __attribute__((always_inline)) {
         req = min(req, a.B - 1);
-        words = *(lane < 2 ? a.tile_off + req + lane : a.ctx_len + req);
+        if (!SELF) words = *(lane < 2 ? a.tile_off + req + lane : a.ctx_len + req);
         pages = a.block_table[static_cast<size_t>(req) * a.max_pages + min(first_page + lane, a.max_pages - 1)];
     };
     request(b, page_of((g - rec.req_begin) * kTile));
 
   for (; g < g_end; ++b) {
+    if (SELF) words = line_words(s_line, b);
     const int t_lo = __builtin_amdgcn_readlane(words, 0), t_hi = __builtin_amdgcn_readlane(words, 1);
     if (t_hi == t_lo) {
         request(b + 1, 0);
@@ -406,7 +419,8 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
                     f32x4{acc[dt][i4 * 4], acc[dt][i4 * 4 + 1], acc[dt][i4 * 4 + 2], acc[dt][i4 * 4 + 3]};
     }
   }  // pieces of the stretch
-    if (bad_page && lane == 0) atomicOr(&a.header->status, 2u);
+    if constexpr (SELF) publish_stretch(a, s_line, rec, wg, kvh, rb, wave, bad_page);
+    else if (bad_page && lane == 0) atomicOr(&a.header->status, 2u);
     // speed history for the next call's plan (see the D = 128 kernel)
     if (a.balanced && !a.fixed_split && tid == 0) {
         const uint64_t ticks = __builtin_amdgcn_s_memrealtime() - clock_begin;
@@ -421,7 +435,8 @@ hipError_t launch_tile(const AttnArgs& a, hipStream_t stream) {
                     static_cast<unsigned>(a.row_blocks));
 #define SEER_TILE_CASE(DQK_, DV_)                                                                                      \
     if (a.Dqk == DQK_ && a.Dv == DV_) {                                                                                \
-        hipLaunchKernelGGL((attn_tile_kernel<DQK_, DV_>), grid, dim3(nw * kWave), 0, stream, a, nw);           \
+        if (a.self_plan) hipLaunchKernelGGL((attn_tile_kernel<DQK_, DV_, true>), grid, dim3(nw * kWave), 0, stream, a, nw);      \
+        else hipLaunchKernelGGL((attn_tile_kernel<DQK_, DV_, false>), grid, dim3(nw * kWave), 0, stream, a, nw);                 \
         return hipGetLastError();                                                                                      \
     }
     SEER_TILE_CASE(64, 64)

@@ -1,0 +1,187 @@
+// The split of a call into stretches, as the plan kernel and the partition kernels that plan for themselves compute it.
+#pragma once
+#include "seer_attention.h"
+#include "seer_device.h"
+
+namespace seer {
+
+// Inclusive sum over the lanes of a wave through DPP: shifts by 1, 2, 4, 8 inside rows of 16 lanes, then the last lane of a
+// row to the row behind it and of the lower half to the upper (lanes without a source add zero).
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ int dpp_take(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, ROW_MASK, 0xf, true); }
+__device__ __forceinline__ int wave_incl_scan(int v) {
+    v += dpp_take<0x111, 0xf>(v);
+    v += dpp_take<0x112, 0xf>(v);
+    v += dpp_take<0x114, 0xf>(v);
+    v += dpp_take<0x118, 0xf>(v);
+    v += dpp_take<0x142, 0xa>(v);
+    v += dpp_take<0x143, 0xc>(v);
+    return v;
+}
+__device__ __forceinline__ float wave_incl_scan(float v) {
+    auto step = [&](int x) { v += __int_as_float(x); };
+    step(dpp_take<0x111, 0xf>(__float_as_int(v)));
+    step(dpp_take<0x112, 0xf>(__float_as_int(v)));
+    step(dpp_take<0x114, 0xf>(__float_as_int(v)));
+    step(dpp_take<0x118, 0xf>(__float_as_int(v)));
+    step(dpp_take<0x142, 0xa>(__float_as_int(v)));
+    step(dpp_take<0x143, 0xc>(__float_as_int(v)));
+    return v;
+}
+// Maximum of non-negative values over the wave, in its last lane (lanes without a source count as zero).
+__device__ __forceinline__ int wave_max_in_last_lane(int v) {
+    v = max(v, dpp_take<0x111, 0xf>(v));
+    v = max(v, dpp_take<0x112, 0xf>(v));
+    v = max(v, dpp_take<0x114, 0xf>(v));
+    v = max(v, dpp_take<0x118, 0xf>(v));
+    v = max(v, dpp_take<0x142, 0xa>(v));
+    v = max(v, dpp_take<0x143, 0xc>(v));
+    return v;
+}
+__device__ __forceinline__ int last_lane(int v) { return __builtin_amdgcn_readlane(v, kWave - 1); }
+__device__ __forceinline__ float last_lane(float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), kWave - 1)); }
+
+// Tiles of a request of n tokens (a length outside [T, max_ctx] is flagged and gets a zero output).
+__device__ __forceinline__ int tiles_of(int n, int T, int max_ctx) { return n < T || n > max_ctx ? 0 : (n + kPlanTile - 1) / kPlanTile; }
+
+// x / d for 0 <= x < 2^31 and 1 <= d, with inv = reciprocal(d).  (A division by a number in a register is some thirty
+// instructions, and every workgroup begins with two; the code itself has to be fetched, too.)
+__device__ __forceinline__ int divide(int x, int d, uint32_t inv) {
+    int q = static_cast<int>(__umulhi(static_cast<uint32_t>(x), inv));       // the quotient or one less
+    return x - q * d >= d ? q + 1 : q;
+}
+
+// How a line of `total` tiles, whose longest request has `longest`, is cut into W stretches.
+struct Cut {
+    int total, W, equal;      // tiles of the line, stretches, tiles of a stretch where all are alike
+    bool weighted;            // the line is long enough for stretches that follow the measured speeds
+};
+__device__ __forceinline__ Cut cut_of(const AttnArgs& a, int total, int longest) {
+    const int W = a.wgs_per_head;
+    // a request of t tiles touches at most ceil(t / Lmin) + 1 stretches, which must fit max_splits
+    const int per_w = divide(total + W - 1, W, a.inv_wgs);
+    const bool fine = per_w < 2 || per_w >= kMinTilesLatent || total <= static_cast<long long>(a.fine_pieces - a.B) * per_w;
+    const int Lmin = max(fine ? a.min_tiles : kMinTilesLatent, divide(longest + a.max_splits - 2, a.max_splits - 1, a.inv_splits));
+    // Stretch w begins at the tile nearest to total * (r_0 + .. + r_{w-1}) / R.  When the line is too
+    // short for that to keep every stretch at Lmin tiles or more, cut it into equal stretches of
+    // max(Lmin, ceil(total / W)) tiles instead (the last ones are then short or empty).
+    return {total, W, max(Lmin, max(per_w, 1)), total >= static_cast<long long>(max(2 * Lmin, kMinTilesWeighted)) * W};
+}
+// First tile of stretch w; before = (r_0 + .. + r_{w-1}) / R in units of 2^-32 (looked at only where the cut is weighted).
+__device__ __forceinline__ int cut_begin(const Cut& c, int w, uint32_t before) {
+    if (w >= c.W) return c.total;
+    const uint64_t at = c.weighted ? (static_cast<uint64_t>(static_cast<uint32_t>(c.total)) * before + (1u << 31)) >> 32
+                                   : static_cast<uint64_t>(w) * static_cast<uint32_t>(c.equal);
+    return static_cast<int>(at < static_cast<uint64_t>(c.total) ? at : c.total);
+}
+// The same where no speeds are known: w / W.
+__device__ __forceinline__ uint32_t equal_before(const AttnArgs& a, int w) { return static_cast<uint32_t>(w) * a.inv_wgs; }
+
+// ---------------------------------------------------------------------------
+// A partition kernel's own plan.  A batch of up to kSelfPlanRequests requests has its lengths in one register of a wave, so
+// every wave finds its stretch by itself: lengths and speeds in one round of loads, a scan over the lanes, one ballot.
+// That takes the place of the load of the stretch's record; the plan kernel and its launch, 5.3 .. 5.8 us in front of
+// every call, are not needed.  The tables that the combine kernel and calls which reuse the plan read are written by the workgroups
+// of the first KV head and row block, each its own part.  (Larger batches would need several requests per lane and keep the kernel.)
+// ---------------------------------------------------------------------------
+constexpr int kLineWords = 2 * kSelfPlanRequests + 2;      // LDS: (first tile, tokens) per request, then (all tiles, -)
+
+struct SelfPlan {
+    StretchRec rec;
+    int pieces;               // requests that the stretch touches
+};
+__device__ __forceinline__ SelfPlan plan_stretch(const AttnArgs& a, int* line, int wg) {
+    const int lane = static_cast<int>(threadIdx.x) & (kWave - 1), W = a.wgs_per_head;
+    const int n = lane < a.B ? a.ctx_len[lane] : 0;
+    uint32_t before = equal_before(a, wg), behind = equal_before(a, wg + 1);
+    if (!a.fixed_split) {
+        const uint32_t magic = a.header->fb_magic;
+        const int w = a.header->fb_w;
+        const uint32_t f0 = a.fb_before[wg], f1 = a.fb_before[wg + 1];        // (one more than there are stretches: in the layout)
+        if (magic == kFeedbackMagic && w == W) before = f0, behind = f1;
+    }
+    const int t = lane < a.B ? tiles_of(n, a.T, a.max_ctx) : 0;
+    const int incl = wave_incl_scan(t), off = incl - t;
+    const int total = last_lane(incl), longest = last_lane(wave_max_in_last_lane(t));
+    const Cut cut = cut_of(a, total, longest);
+    const int begin = __builtin_amdgcn_readfirstlane(cut_begin(cut, wg, before));
+    const int end = __builtin_amdgcn_readfirstlane(cut_begin(cut, wg + 1, behind));
+    // every wave writes the same words and reads them behind its own writes
+    line[2 * lane] = off, line[2 * lane + 1] = n;
+    if (lane == 0) line[2 * kSelfPlanRequests] = total;
+    SelfPlan r{{-1, begin, end, 0}, 1};
+    if (begin < end) {                          // the last request that starts at or before the first tile
+        r.rec.b = max(__popcll(__ballot(lane < a.B && off <= begin)) - 1, 0);
+        r.rec.req_begin = __builtin_amdgcn_readlane(off, r.rec.b);
+        r.pieces = __popcll(__ballot(t > 0 && off < end && incl > begin));
+    }
+    return r;
+}
+
+// At a wave's end (stores in front of its loads would have to be waited for with them): whether it met a page id outside the
+// pool, one byte per wave of the grid (the status word cannot collect these: nothing in front of the kernel clears it); and by
+// one workgroup per stretch that stretch's part of the tables.
+__device__ __forceinline__ void publish_stretch(const AttnArgs& a, const int* line, const StretchRec& rec, int wg, int kvh, int rb, int wave,
+                                                bool bad_page) {
+    const int lane = static_cast<int>(threadIdx.x) & (kWave - 1);
+    const bool any_bad = __any(bad_page);
+    if (lane == 0) a.page_flags[((static_cast<size_t>(wg) * a.Hkv + kvh) * a.row_blocks + rb) * 8 + wave] = any_bad ? 1 : 0;
+    if (kvh != 0 || rb != 0 || wave != 0) return;
+    if (lane == 0) *const_cast<int4*>(reinterpret_cast<const int4*>(a.stretch + wg)) = make_int4(rec.b, rec.tile_begin, rec.tile_end, rec.req_begin);
+    if (lane < a.B) {
+        const int off = line[2 * lane], t = tiles_of(line[2 * lane + 1], a.T, a.max_ctx), last = off + t - 1;
+        ReqSlots* slots = const_cast<ReqSlots*>(a.req_slots) + lane;
+        if (t > 0 && off >= rec.tile_begin && off < rec.tile_end) slots->first = wg + lane;
+        if (t > 0 && last >= rec.tile_begin && last < rec.tile_end) slots->last = wg + lane;
+        if (wg == 0) {
+            if (t == 0) *slots = ReqSlots{0, -1};
+            const_cast<int32_t*>(a.tile_off)[lane] = off;
+        }
+    }
+    if (wg == 0 && lane == 0) {
+        const_cast<int32_t*>(a.tile_off)[a.B] = line[2 * kSelfPlanRequests];
+        a.header->plan_b = plan_b_word(a.B);
+        a.header->plan_w = plan_w_word(a.wgs_per_head, true);
+    }
+}
+
+// What a piece needs of request b: lanes 0, 1, 2 get its first tile, the first tile behind it, its tokens.  (Read and wait in one
+// block: the compiler would put a wait for all tile loads in front of a read of its own.)
+__device__ __forceinline__ int line_words(const int* line, int b) {
+    const int lane = static_cast<int>(threadIdx.x) & (kWave - 1);
+    const int word = 2 * b + (lane == 1 ? 2 : (lane == 2 ? 1 : 0));
+    const int at = static_cast<int>(reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) int*)(line))) + 4 * word;
+    int v;
+    asm volatile("ds_read_b32 %0, %1\n"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(v)
+                 : "v"(at)
+                 : "memory");
+    return v;
+}
+
+// Leading tiles, from page `first` of request b on, whose pages a neighbouring request maps too; `mine` is lane l's entry
+// first + l of the request's row.  What shared_tiles says, found from the rows themselves, for the windows at hand (64 pages
+// a round, while all of them are shared).  A hint like that table: entries behind a neighbour's end may be anything.
+__device__ __forceinline__ int shared_tiles_from(const AttnArgs& a, int b, int first, int mine) {
+    const int lane = static_cast<int>(threadIdx.x) & (kWave - 1);
+    const int32_t* row = a.block_table + static_cast<size_t>(b) * a.max_pages;
+    bool up = b > 0, down = b + 1 < a.B;
+    int pages = 0;
+    for (int base = first; base < a.max_pages; base += kWave) {
+        const int i = min(base + lane, a.max_pages - 1);
+        if (base > first) mine = row[i];
+        const int above = up ? row[i - static_cast<ptrdiff_t>(a.max_pages)] : 0, below = down ? row[i + static_cast<ptrdiff_t>(a.max_pages)] : 0;
+        const uint64_t same_up = up ? __ballot(mine == above) : 0, same_down = down ? __ballot(mine == below) : 0;
+        up = same_up == ~0ull, down = same_down == ~0ull;
+        if (up || down) {
+            pages += kWave;
+            continue;
+        }
+        pages += max(__builtin_ctzll(~same_up), __builtin_ctzll(~same_down));
+        break;
+    }
+    return static_cast<int>(static_cast<long long>(pages) * a.P / kPlanTile);
+}
+
+}  // namespace seer

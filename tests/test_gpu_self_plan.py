@@ -1,0 +1,50 @@
+"""Batches of up to 64 requests, whose partition kernel plans for itself: its tables against the plan kernel's."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2511_14617_amd import workloads as W
+from paper_2511_14617_amd.device_inputs import attention_device_inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("heads", [(8, 2, 128, 16), (36, 2, 128, 32), (40, 1, 128, 64), (4, 2, 64, 20), (4, 1, 256, 16)])
+@pytest.mark.parametrize("B,hi", [(1, 9), (3, 300), (63, 40), (64, 700), (65, 700), (9, 9000)])
+@pytest.mark.parametrize("max_splits", [0, 2])
+def test_tables_equal_the_plan_kernels(heads, B, hi, max_splits):
+    """A call that forces the general kernel plans with the plan kernel, whatever its batch: after one of either kind the
+    workspace holds the same slots, offsets, stretches and shared tiles, for batches on both sides of the limit, lines shorter
+    and longer than the stretches, and requests with unusable lengths; and a call reuses them with equal results."""
+    from paper_2511_14617_amd import binding
+    Hq, Hkv, D, P = heads
+    cfg = W.CONFIGS[2].scaled(B=B, group_size=3, Hq=Hq, Hkv=Hkv, T=4, Dqk=D, Dv=D, page_size=P, ctx=("uniform", 4, hi),
+                              shared_prefix=2 * P if hi > 3 * P else 0)
+    inp = W.make_attention_inputs(cfg)
+    if B > 2:
+        inp.ctx_len[B // 2] = 3                                   # fewer tokens than slots
+        inp.ctx_len[B - 1] = inp.block_table.shape[1] * P + 1     # more than the table holds
+    d = attention_device_inputs(inp)
+    p = binding.attn_params(d["q"], d["k_pages"], d["v_pages"], d["block_table"], inp.scale, Dv=D, max_splits=max_splits)
+    n = binding.seer_verify_attention_workspace(p)
+    end = binding.load_library().seer_verify_attention_shared_tiles_offset(p) + 4 * B
+
+    def call(ws, flags):
+        return binding.seer_verify_attention(d["q"], d["k_pages"], d["v_pages"], d["block_table"], d["ctx_len"], None, inp.scale,
+                                             Dv=D, max_splits=max_splits, workspace=ws, flags=flags).clone()
+    fixed = binding.SEER_ATTN_FIXED_SPLIT
+    one, other = (torch.zeros(n, dtype=torch.uint8, device="cuda") for _ in range(2))
+    own = call(one, fixed)
+    call(other, fixed | binding.SEER_ATTN_GENERAL_KERNEL)
+    assert torch.equal(one[256:end], other[256:end])
+    status = 1 if B > 2 else 0
+    assert binding.seer_verify_attention_status(one) == binding.seer_verify_attention_status(other) == status
+    # the same cut, planned by either kernel: the same sums in the same order
+    for ws in (one, other):
+        assert torch.equal(call(ws, fixed | binding.SEER_ATTN_REUSE_PLAN).view(torch.int16), own.view(torch.int16))
+    # lengths that change from call to call, with the speeds of the calls before
+    for k in range(3):
+        d["ctx_len"].copy_(torch.from_numpy(np.roll(inp.ctx_len, k)).cuda().clamp_(max=int(inp.ctx_len.min()) if k == 2 else 1 << 30))
+        call(one, 0)
+        torch.cuda.synchronize()
+        assert binding.seer_verify_attention_status(one) == (1 if B > 2 else 0)
