@@ -846,7 +846,7 @@ __device__ __forceinline__ void run(const AttnArgs& a, unsigned char* lds, const
     }
   }  // pieces of the stretch
     if constexpr (SELF) publish_stretch(a, line, rec, wg, kvh, rb, wave, bad_page);
-    else if (bad_page && lane == 0) atomicOr(&a.header->status, 2u);
+    else if (__any(bad_page) && lane == 0) atomicOr(&a.header->status, 2u);
     if (a.balanced && !a.fixed_split && tid == 0) {
         const uint64_t ticks = __builtin_amdgcn_s_memrealtime() - clock_begin;
         atomicAdd(a.fb_time + wg, static_cast<uint32_t>(ticks > 0xffffffu ? 0xffffffu : ticks));
@@ -1359,7 +1359,7 @@ void attn_gqa128_kernel(AttnArgs a) {
     }
   }  // pieces of the stretch
     if constexpr (SELF) publish_stretch(a, s_line, rec, wg, kvh, rb, wave, bad_page);
-    else if (bad_page && lane == 0) atomicOr(&a.header->status, 2u);
+    else if (__any(bad_page) && lane == 0) atomicOr(&a.header->status, 2u);
     // speed history for the next call's plan: tiles streamed and time taken, by stretch index
     if (a.balanced && !a.fixed_split && tid == 0) {
         const uint64_t ticks = __builtin_amdgcn_s_memrealtime() - clock_begin;

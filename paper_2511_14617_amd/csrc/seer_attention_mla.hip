@@ -638,7 +638,7 @@ void attn_mla_kernel(AttnArgs a, int row_blocks) {
             }
     }
   }
-    if (bad_page && lane == 0) atomicOr(&a.header->status, 2u);
+    if (__any(bad_page) && lane == 0) atomicOr(&a.header->status, 2u);
 }
 
 bool mla_supports(const AttnArgs& a) {

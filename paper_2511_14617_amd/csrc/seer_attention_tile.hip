@@ -420,7 +420,7 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
     }
   }  // pieces of the stretch
     if constexpr (SELF) publish_stretch(a, s_line, rec, wg, kvh, rb, wave, bad_page);
-    else if (bad_page && lane == 0) atomicOr(&a.header->status, 2u);
+    else if (__any(bad_page) && lane == 0) atomicOr(&a.header->status, 2u);
     // speed history for the next call's plan (see the D = 128 kernel)
     if (a.balanced && !a.fixed_split && tid == 0) {
         const uint64_t ticks = __builtin_amdgcn_s_memrealtime() - clock_begin;

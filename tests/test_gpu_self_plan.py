@@ -48,3 +48,29 @@ def test_tables_equal_the_plan_kernels(heads, B, hi, max_splits):
         call(one, 0)
         torch.cuda.synchronize()
         assert binding.seer_verify_attention_status(one) == (1 if B > 2 else 0)
+
+
+@pytest.mark.parametrize("B", [3, 70])
+@pytest.mark.parametrize("shape", [(128, 128, 2, 16), (64, 64, 2, 16), (576, 512, 1, 32)])
+def test_a_page_id_outside_the_pool_is_reported_wherever_it_is(B, shape):
+    """Bit 1 of the status word, by batches that plan for themselves and by others; cleared by the next good call.  The
+    kernels clamp such an id to the pool."""
+    from paper_2511_14617_amd import binding
+    Dqk, Dv, Hkv, P = shape
+    cfg = W.CONFIGS[2].scaled(B=B, group_size=B, Hq=4 * Hkv, Hkv=Hkv, T=3, Dqk=Dqk, Dv=Dv, page_size=P, ctx=("uniform", 7 * P, 9 * P),
+                              shared_prefix=0, shared_latent=Dqk == 576)
+    inp = W.make_attention_inputs(cfg)
+    d = attention_device_inputs(inp)
+    p = binding.attn_params(d["q"], d["k_pages"], d["v_pages"], d["block_table"], inp.scale, Dv=Dv)
+    ws = torch.zeros(binding.seer_verify_attention_workspace(p), dtype=torch.uint8, device="cuda")
+    for page, value, want in ((5, cfg_pages(d), 2), (0, None, 0), (6, -1, 2), (1, None, 0)):
+        table = d["block_table"].clone()
+        if value is not None:
+            table[B - 2, page] = value
+        binding.seer_verify_attention(d["q"], d["k_pages"], d["v_pages"], table, d["ctx_len"], None, inp.scale, Dv=Dv, workspace=ws)
+        torch.cuda.synchronize()
+        assert binding.seer_verify_attention_status(ws) == want, (page, value)
+
+
+def cfg_pages(d):
+    return int(d["k_pages"].shape[0])
