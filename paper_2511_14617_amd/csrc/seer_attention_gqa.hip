@@ -587,6 +587,8 @@ __device__ __forceinline__ void run(const AttnArgs& a, unsigned char* lds, const
     int pw = SELF ? 0 : piece_words(b);
     int page_ahead = ((g - rec.req_begin) * kTile) >> page_shift;       // (see the kernel below)
     int pg_ahead = first_pages(b, page_ahead);
+    int run_ahead = 0;                                 // SELF: how many of those a neighbouring request maps too
+    if constexpr (SELF) run_ahead = shared_run(a, b, pg_ahead, neighbour_rows(a, b, page_ahead));
     const int g_first = g;
 
   for (; g < g_end; ++b) {
@@ -597,11 +599,20 @@ __device__ __forceinline__ void run(const AttnArgs& a, unsigned char* lds, const
     int shared_tiles = __builtin_amdgcn_readlane(pw, 3);
     const int pg_first = pg_ahead;
     const int page_first = page_ahead;
-    if (SELF) shared_tiles = t_hi > t_lo ? page_first * a.P / kTile + shared_tiles_from(a, b, page_first, pg_first) : 0;
-    else pw = piece_words(b + 1);
+    NeighbourRows next_rows{0, 0};
+    if constexpr (SELF) {
+        if (run_ahead == kWave && t_hi > t_lo) run_ahead += shared_run_behind(a, b, page_first + kWave);
+        shared_tiles = static_cast<int>(static_cast<long long>(page_first + run_ahead) * a.P / kTile);
+        next_rows = neighbour_rows(a, b + 1, 0);
+    } else {
+        pw = piece_words(b + 1);
+    }
     pg_ahead = first_pages(b + 1, 0);
     page_ahead = 0;
-    if (t_hi == t_lo) continue;
+    if (t_hi == t_lo) {
+        if constexpr (SELF) run_ahead = shared_run(a, b + 1, pg_ahead, next_rows);
+        continue;
+    }
     const int tok_begin = (g - t_lo) * kTile;
     const int tok_end = min(n, (min(g_end, t_hi) - t_lo) * kTile);
     g = t_hi;
@@ -713,6 +724,10 @@ __device__ __forceinline__ void run(const AttnArgs& a, unsigned char* lds, const
         }
         asm volatile("" : "+v"(word), "+v"(word2));
         if (a.T < 64) word &= (1ull << a.T) - 1, word2 &= (1ull << a.T) - 1;
+        if constexpr (SELF) {                          // (the next request's rows, requested in front of these, are there too)
+            asm volatile("" : "+v"(pg_ahead), "+v"(next_rows.above), "+v"(next_rows.below));
+            run_ahead = shared_run(a, b + 1, pg_ahead, next_rows);
+        }
     }
     f32x16 acc[4];
 #pragma unroll
@@ -987,6 +1002,8 @@ void attn_gqa128_kernel(AttnArgs a) {
     // other piece at its request's first page)
     int page_ahead = ((g - rec.req_begin) * kTile) >> page_shift;
     int pg_ahead = first_pages(b, page_ahead);
+    int run_ahead = 0;                                 // SELF: how many of those a neighbouring request maps too
+    if constexpr (SELF) run_ahead = shared_run(a, b, pg_ahead, neighbour_rows(a, b, page_ahead));
 
   for (; g < g_end; ++b) {
     if (SELF) pw = line_words(s_line, b);
@@ -996,11 +1013,20 @@ void attn_gqa128_kernel(AttnArgs a) {
     int shared_tiles = __builtin_amdgcn_readlane(pw, 3);
     const int pg_first = pg_ahead;
     const int page_first = page_ahead;
-    if (SELF) shared_tiles = t_hi > t_lo ? page_first * a.P / kTile + shared_tiles_from(a, b, page_first, pg_first) : 0;
-    else pw = piece_words(b + 1);          // in flight while this piece is worked on
+    NeighbourRows next_rows{0, 0};
+    if constexpr (SELF) {
+        if (run_ahead == kWave && t_hi > t_lo) run_ahead += shared_run_behind(a, b, page_first + kWave);
+        shared_tiles = static_cast<int>(static_cast<long long>(page_first + run_ahead) * a.P / kTile);
+        next_rows = neighbour_rows(a, b + 1, 0);
+    } else {
+        pw = piece_words(b + 1);          // in flight while this piece is worked on
+    }
     pg_ahead = first_pages(b + 1, 0);
     page_ahead = 0;
-    if (t_hi == t_lo) continue;
+    if (t_hi == t_lo) {
+        if constexpr (SELF) run_ahead = shared_run(a, b + 1, pg_ahead, next_rows);
+        continue;
+    }
     const int tok_begin = (g - t_lo) * kTile;
     const int tok_end = min(n, (min(g_end, t_hi) - t_lo) * kTile);
     g = t_hi;
@@ -1146,6 +1172,10 @@ void attn_gqa128_kernel(AttnArgs a) {
         asm volatile("" : "+v"(w_lo), "+v"(w_hi));
         word = (static_cast<uint64_t>(w_hi) << 32) | w_lo;
         if (a.T < 64) word &= (1ull << a.T) - 1;
+        if constexpr (SELF) {                          // (the next request's rows, requested in front of these, are there too)
+            asm volatile("" : "+v"(pg_ahead), "+v"(next_rows.above), "+v"(next_rows.below));
+            run_ahead = shared_run(a, b + 1, pg_ahead, next_rows);
+        }
     }
 
     f32x16 s_a, s_b;

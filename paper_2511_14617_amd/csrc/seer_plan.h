@@ -160,28 +160,32 @@ __device__ __forceinline__ int line_words(const int* line, int b) {
     return v;
 }
 
-// Leading tiles, from page `first` of request b on, whose pages a neighbouring request maps too; `mine` is lane l's entry
-// first + l of the request's row.  What shared_tiles says, found from the rows themselves, for the windows at hand (64 pages
-// a round, while all of them are shared).  A hint like that table: entries behind a neighbour's end may be anything.
-__device__ __forceinline__ int shared_tiles_from(const AttnArgs& a, int b, int first, int mine) {
+// Pages, from page `first` of request b on, that a neighbouring request maps too: what shared_tiles says, found from the rows
+// themselves, 64 pages at a time.  A hint like that table (entries behind a neighbour's end may be anything).
+struct NeighbourRows {
+    int above, below;         // lane l: entry first + l of the requests in front and behind
+};
+__device__ __forceinline__ NeighbourRows neighbour_rows(const AttnArgs& a, int b, int first) {
     const int lane = static_cast<int>(threadIdx.x) & (kWave - 1);
-    const int32_t* row = a.block_table + static_cast<size_t>(b) * a.max_pages;
-    bool up = b > 0, down = b + 1 < a.B;
+    const int32_t* col = a.block_table + min(first + lane, a.max_pages - 1);
+    return {col[static_cast<size_t>(max(min(b, a.B) - 1, 0)) * a.max_pages], col[static_cast<size_t>(min(b + 1, a.B - 1)) * a.max_pages]};
+}
+// mine: lane l's entry first + l of request b
+__device__ __forceinline__ int shared_run(const AttnArgs& a, int b, int mine, const NeighbourRows& rows) {
+    const uint64_t up = b > 0 ? ~__ballot(mine == rows.above) : ~0ull, down = b + 1 < a.B ? ~__ballot(mine == rows.below) : ~0ull;
+    return up == 0 || down == 0 ? kWave : max(__builtin_ctzll(up), __builtin_ctzll(down));
+}
+// The run behind a window that is shared throughout.
+__device__ __forceinline__ int shared_run_behind(const AttnArgs& a, int b, int first) {
+    const int lane = static_cast<int>(threadIdx.x) & (kWave - 1);
     int pages = 0;
     for (int base = first; base < a.max_pages; base += kWave) {
-        const int i = min(base + lane, a.max_pages - 1);
-        if (base > first) mine = row[i];
-        const int above = up ? row[i - static_cast<ptrdiff_t>(a.max_pages)] : 0, below = down ? row[i + static_cast<ptrdiff_t>(a.max_pages)] : 0;
-        const uint64_t same_up = up ? __ballot(mine == above) : 0, same_down = down ? __ballot(mine == below) : 0;
-        up = same_up == ~0ull, down = same_down == ~0ull;
-        if (up || down) {
-            pages += kWave;
-            continue;
-        }
-        pages += max(__builtin_ctzll(~same_up), __builtin_ctzll(~same_down));
-        break;
+        const int mine = a.block_table[static_cast<size_t>(b) * a.max_pages + min(base + lane, a.max_pages - 1)];
+        const int run = shared_run(a, b, mine, neighbour_rows(a, b, base));
+        pages += run;
+        if (run < kWave) break;
     }
-    return static_cast<int>(static_cast<long long>(pages) * a.P / kPlanTile);
+    return pages;
 }
 
 }  // namespace seer
