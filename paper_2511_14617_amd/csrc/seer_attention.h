@@ -64,7 +64,7 @@ struct ReqSlots {
     int32_t first, last;
 };
 
-// Up to this many requests the tiled D = 128 kernel and the kernel for the other head sizes plan for themselves (seer_plan.h):
+// Up to this many requests the tiled kernels plan for themselves (seer_plan.h):
 // one per lane of a wave.  Whole call with the plan kernel | without: 4 requests of 64 .. 512 tokens 16.9 | 13.8 us, 16 requests with heads of
 // 64 32.1 | 27.4, of 256 39.6 | 35.5, 64 requests on one KV head 57.4 | 53.8, on eight 236.9 | 232.5.  (Not all of the plan kernel's 5.5 us:
 // the partition kernel begins 1.8 us later, most of it the fetch of the additional code.)
@@ -138,7 +138,7 @@ inline bool mla_layout(const seer_attn_params& p) {
 inline bool tile_supports(const seer_attn_params& p) { return tile_layout(p) && !(p.flags & SEER_ATTN_GENERAL_KERNEL); }
 // (also a matter of the shape alone; calls that force the general kernel or reuse a plan do not use it)
 inline bool self_plan_layout(const seer_attn_params& p) {
-    return p.B <= kSelfPlanRequests && p.max_splits != 1 && (gqa_layout(p) || tile_layout(p));
+    return p.B <= kSelfPlanRequests && p.max_splits != 1 && (gqa_layout(p) || tile_layout(p) || mla_layout(p));
 }
 constexpr int tile_stage_kb(int Dqk, int Dv) { return 32 * 2 * (Dqk + Dv) / 1024; }
 constexpr int tile_waves_per_simd(int Dqk) { return Dqk == 64 ? 3 : (Dqk == 256 ? 1 : 2); }
@@ -173,7 +173,7 @@ inline WorkspaceLayout workspace_layout(const seer_attn_params& p) {
     WorkspaceLayout w{};
     w.max_splits = p.max_splits > 0 ? p.max_splits : kDefaultMaxSplits;
     const int rows_per_head = (p.Hq / p.Hkv) * p.T;
-    w.row_blocks = gqa_layout(p) ? gqa_row_blocks(rows_per_head) : (tile_layout(p) ? tile_row_blocks(rows_per_head, p.Dqk) : 1);
+    w.row_blocks = mla_layout(p) ? (rows_per_head + 127) / 128 : gqa_layout(p) ? gqa_row_blocks(rows_per_head) : (tile_layout(p) ? tile_row_blocks(rows_per_head, p.Dqk) : 1);
     if (w.max_splits == 1) {
         w.wgs_per_head = p.B;
         w.max_items = p.B;
@@ -181,9 +181,8 @@ inline WorkspaceLayout workspace_layout(const seer_attn_params& p) {
         if (mla_layout(p)) {
             // one 4-wave workgroup per CU; a request's rows are cut into blocks of 128, and the
             // row-block workgroups of one stretch are launched as a group on one XCD (groups of 8 stretches)
-            const int row_blocks = ((p.Hq / p.Hkv) * p.T + 127) / 128;
-            w.wgs_per_head = 8 * (kNumCU / (8 * row_blocks * p.Hkv));
-            if (w.wgs_per_head < 1) w.wgs_per_head = kNumCU / (row_blocks * p.Hkv);
+            w.wgs_per_head = 8 * (kNumCU / (8 * w.row_blocks * p.Hkv));
+            if (w.wgs_per_head < 1) w.wgs_per_head = kNumCU / (w.row_blocks * p.Hkv);
         } else {
             w.wgs_per_head = kNumCU * resident_wgs_per_cu(p) / (p.Hkv * w.row_blocks);
             if (w.wgs_per_head > kMaxWgsPerHead) w.wgs_per_head = kMaxWgsPerHead;

@@ -729,9 +729,9 @@ int run_verify_attention(void* out, const void* q, const void* k_pages, const vo
     a.stream_partials = (w.total - w.off_acc) < seer::kStreamPartialsBelow ? 1 : 0;
     const bool tile_kernel = seer::tile_supports(*p);
     const int rows = (p->Hq / p->Hkv) * p->T;
-    a.row_blocks = tile_kernel ? seer::tile_row_blocks(rows, p->Dqk) : seer::gqa_row_blocks(rows);
+    a.row_blocks = w.row_blocks;
     a.rows_per_block = tile_kernel ? seer::tile_rows_per_block(rows, p->Dqk) : seer::gqa_rows_per_block(rows);
-    a.plan_waves = tile_kernel || !seer::gqa_block_uses_helpers(a.rows_per_block) ? a.rows_per_block / 32 : 8;
+    a.plan_waves = seer::mla_layout(*p) ? 4 : tile_kernel || !seer::gqa_block_uses_helpers(a.rows_per_block) ? a.rows_per_block / 32 : 8;
     a.part_ml = reinterpret_cast<float*>(ws + w.off_ml);
     a.part_acc = reinterpret_cast<float*>(ws + w.off_acc);
     a.B = p->B;

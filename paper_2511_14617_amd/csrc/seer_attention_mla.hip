@@ -33,6 +33,7 @@
 
 #include "seer_attention.h"
 #include "seer_device.h"
+#include "seer_plan.h"
 #include "seer_tile.h"
 
 namespace seer {
@@ -272,6 +273,8 @@ __device__ __forceinline__ void phase_b(const int (&va)[4], u32x2 (&vr)[kVAhead]
 
 }  // namespace mla
 
+// SELF: every wave finds its stretch itself (seer_plan.h) instead of reading it from the plan kernel's tables.
+template <bool SELF>
 __global__ __launch_bounds__(mla::kWaves* kWave) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void attn_mla_kernel(AttnArgs a, int row_blocks) {
     using namespace mla;
@@ -282,6 +285,8 @@ void attn_mla_kernel(AttnArgs a, int row_blocks) {
     // writes and re-reads only its own 16 bytes).  A separate array, so that the compiler can tell these
     // accesses apart from the tile stages that the direct-to-LDS loads write.
     __shared__ __attribute__((aligned(16))) u32x4 q_tail[kWaves][kQLdsSteps][kWave];
+
+    __shared__ int s_line[kLineWords];              // (see plan_stretch)
 
     const int kvh = blockIdx.y;
     const int tid = threadIdx.x;
@@ -297,7 +302,16 @@ void attn_mla_kernel(AttnArgs a, int row_blocks) {
     const int wg = (slot / row_blocks) * 8 + xcd;
     const int rb = slot % row_blocks;
     if (wg >= a.wgs_per_head) return;
-    const StretchRec rec = uniform_stretch(a, wg);
+    StretchRec rec;
+    if (SELF) {
+        rec = plan_stretch(a, s_line, wg).rec;
+        if (rec.b < 0) {
+            publish_stretch(a, s_line, rec, wg, kvh, rb, wave, false);
+            return;
+        }
+    } else {
+        rec = uniform_stretch(a, wg);
+    }
     int b = rec.b;
     if (b < 0) return;
     const int slot_bias = a.balanced ? wg : 0;
@@ -334,10 +348,12 @@ void attn_mla_kernel(AttnArgs a, int row_blocks) {
     }
 
   for (; g < g_end; ++b) {
-    const int t_lo = uniform_load(a.tile_off + b), t_hi = uniform_load(a.tile_off + b + 1);
+    const int words = SELF ? line_words(s_line, b) : 0;
+    const int t_lo = SELF ? __builtin_amdgcn_readlane(words, 0) : uniform_load(a.tile_off + b);
+    const int t_hi = SELF ? __builtin_amdgcn_readlane(words, 1) : uniform_load(a.tile_off + b + 1);
     if (t_hi == t_lo) continue;
     const int item_idx = b + slot_bias;
-    const int n = uniform_load(a.ctx_len + b);
+    const int n = SELF ? __builtin_amdgcn_readlane(words, 2) : uniform_load(a.ctx_len + b);
     const int tok_begin = (g - t_lo) * kTile;
     const int tok_end = min(n, (min(g_end, t_hi) - t_lo) * kTile);
     g = t_hi;
@@ -638,7 +654,8 @@ void attn_mla_kernel(AttnArgs a, int row_blocks) {
             }
     }
   }
-    if (__any(bad_page) && lane == 0) atomicOr(&a.header->status, 2u);
+    if constexpr (SELF) publish_stretch(a, s_line, rec, wg, kvh, rb, wave, bad_page);
+    else if (__any(bad_page) && lane == 0) atomicOr(&a.header->status, 2u);
 }
 
 bool mla_supports(const AttnArgs& a) {
@@ -650,7 +667,8 @@ hipError_t launch_mla(const AttnArgs& a, hipStream_t stream) {
     const int row_blocks = (a.G * a.T + mla::kRowsPerWg - 1) / mla::kRowsPerWg;
     const unsigned groups = (a.wgs_per_head + 7) / 8;
     const dim3 grid(8u * groups * row_blocks, a.Hkv);
-    hipLaunchKernelGGL(attn_mla_kernel, grid, dim3(mla::kWaves * kWave), 0, stream, a, row_blocks);
+    if (a.self_plan) hipLaunchKernelGGL(attn_mla_kernel<true>, grid, dim3(mla::kWaves * kWave), 0, stream, a, row_blocks);
+    else hipLaunchKernelGGL(attn_mla_kernel<false>, grid, dim3(mla::kWaves * kWave), 0, stream, a, row_blocks);
     return hipGetLastError();
 }
 

@@ -9,7 +9,8 @@ from paper_2511_14617_amd.device_inputs import attention_device_inputs
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("heads", [(8, 2, 128, 16), (36, 2, 128, 32), (40, 1, 128, 64), (4, 2, 64, 20), (4, 1, 256, 16)])
+@pytest.mark.parametrize("heads", [(8, 2, 128, 16), (36, 2, 128, 32), (40, 1, 128, 64), (4, 2, 64, 20), (4, 1, 256, 16), (16, 1, 576, 32),
+                                   (64, 1, 576, 64)])
 @pytest.mark.parametrize("B,hi", [(1, 9), (3, 300), (63, 40), (64, 700), (65, 700), (9, 9000)])
 @pytest.mark.parametrize("max_splits", [0, 2])
 def test_tables_equal_the_plan_kernels(heads, B, hi, max_splits):
@@ -18,20 +19,20 @@ def test_tables_equal_the_plan_kernels(heads, B, hi, max_splits):
     and longer than the stretches, and requests with unusable lengths; and a call reuses them with equal results."""
     from paper_2511_14617_amd import binding
     Hq, Hkv, D, P = heads
-    cfg = W.CONFIGS[2].scaled(B=B, group_size=3, Hq=Hq, Hkv=Hkv, T=4, Dqk=D, Dv=D, page_size=P, ctx=("uniform", 4, hi),
+    cfg = W.CONFIGS[2].scaled(B=B, group_size=3, Hq=Hq, Hkv=Hkv, T=4, Dqk=D, Dv=512 if D == 576 else D, page_size=P, ctx=("uniform", 4, hi), shared_latent=D == 576,
                               shared_prefix=2 * P if hi > 3 * P else 0)
     inp = W.make_attention_inputs(cfg)
     if B > 2:
         inp.ctx_len[B // 2] = 3                                   # fewer tokens than slots
         inp.ctx_len[B - 1] = inp.block_table.shape[1] * P + 1     # more than the table holds
     d = attention_device_inputs(inp)
-    p = binding.attn_params(d["q"], d["k_pages"], d["v_pages"], d["block_table"], inp.scale, Dv=D, max_splits=max_splits)
+    p = binding.attn_params(d["q"], d["k_pages"], d["v_pages"], d["block_table"], inp.scale, Dv=cfg.Dv, max_splits=max_splits)
     n = binding.seer_verify_attention_workspace(p)
     end = binding.load_library().seer_verify_attention_shared_tiles_offset(p) + 4 * B
 
     def call(ws, flags):
         return binding.seer_verify_attention(d["q"], d["k_pages"], d["v_pages"], d["block_table"], d["ctx_len"], None, inp.scale,
-                                             Dv=D, max_splits=max_splits, workspace=ws, flags=flags).clone()
+                                             Dv=cfg.Dv, max_splits=max_splits, workspace=ws, flags=flags).clone()
     fixed = binding.SEER_ATTN_FIXED_SPLIT
     one, other = (torch.zeros(n, dtype=torch.uint8, device="cuda") for _ in range(2))
     own = call(one, fixed)
