@@ -89,7 +89,7 @@ typedef struct seer_attn_params {
 /* flags: use the plan that the previous call on this workspace computed instead of planning again.  How the
  * KV stream is cut depends on the shape parameters and on ctx_len only, and a model calls this function
  * once per layer with the same ctx_len: the first layer plans, the others pass this flag (saves a ~5 us
- * kernel and its launch per call).  The caller guarantees that the previous call on this workspace had the same
+ * kernel and its launch per call, or 2 us of it in batches of up to 64 requests).  The caller guarantees that the previous call on this workspace had the same
  * parameters (flags apart) and that ctx_len and block_table are unchanged; if not, the output is
  * undefined (every access still stays in bounds; a workspace without a plan for this B and split leaves
  * `out` as it is).  The status word then accumulates over the calls. */

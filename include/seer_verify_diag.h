@@ -24,7 +24,7 @@ extern "C" {
  * hipEvent_t (passed as void*) on the stream immediately before and after the
  * partition kernel -- the kernel that streams the KV pages and dominates the
  * call -- so that its duration can be read with hipEventElapsedTime without a
- * profiler.  The plan kernel runs before event_begin, the combine after
+ * profiler.  The plan kernel, where the call needs one, runs before event_begin, the combine after
  * event_end.  Results are identical to seer_verify_attention.
  */
 SEER_API int seer_verify_attention_timed(void* out, const void* q, const void* k_pages, const void* v_pages,

@@ -66,7 +66,8 @@ struct ReqSlots {
 
 // Up to this many requests the tiled kernels plan for themselves (seer_plan.h):
 // one per lane of a wave.  Whole call with the plan kernel | without: 4 requests of 64 .. 512 tokens 16.9 | 13.8 us, 16 requests with heads of
-// 64 32.1 | 27.4, of 256 39.6 | 35.5, 64 requests on one KV head 57.4 | 53.8, on eight 236.9 | 232.5.  (Not all of the plan kernel's 5.5 us:
+// 64 32.1 | 27.4, of 256 39.6 | 35.5, 64 requests on one KV head 57.4 | 53.8, on eight 236.9 | 232.5; shared
+// latent, two requests, 33.7 | 30.0.  (Not all of the plan kernel's 5.5 us:
 // the partition kernel begins 1.8 us later, most of it the fetch of the additional code.)
 constexpr int kSelfPlanRequests = 64;
 
@@ -173,7 +174,9 @@ inline WorkspaceLayout workspace_layout(const seer_attn_params& p) {
     WorkspaceLayout w{};
     w.max_splits = p.max_splits > 0 ? p.max_splits : kDefaultMaxSplits;
     const int rows_per_head = (p.Hq / p.Hkv) * p.T;
-    w.row_blocks = mla_layout(p) ? (rows_per_head + 127) / 128 : gqa_layout(p) ? gqa_row_blocks(rows_per_head) : (tile_layout(p) ? tile_row_blocks(rows_per_head, p.Dqk) : 1);
+    w.row_blocks = gqa_layout(p) ? gqa_row_blocks(rows_per_head) : 1;
+    if (mla_layout(p)) w.row_blocks = (rows_per_head + 127) / 128;
+    else if (tile_layout(p)) w.row_blocks = tile_row_blocks(rows_per_head, p.Dqk);
     if (w.max_splits == 1) {
         w.wgs_per_head = p.B;
         w.max_items = p.B;
@@ -241,7 +244,7 @@ struct AttnArgs {
     int32_t fine_pieces;        // with more pieces than this in stretches of two or three tiles: four tiles (see kFinePartialsBelow)
     int32_t stream_only;        // 1: the tiled D = 128 kernel only streams its tiles (diagnostic)
     int32_t stream_partials;    // 1: the tiled D = 128 kernel writes its partial results with non-temporal stores
-    int32_t row_blocks, rows_per_block;   // tiled D = 128 kernel: workgroups per (stretch, KV head), rows of each
+    int32_t row_blocks, rows_per_block;   // tiled kernels: workgroups per (stretch, KV head); rows of each (D = 128 and the other head sizes)
     float* part_ml;             // [max_items][T][Hq][2]  (running max in log2 units, sum)
     float* part_acc;            // [max_items][T][Hq][Dv] unnormalised
     int32_t B, T, Hq, Hkv, G, Dqk, Dv, P, num_pages, max_pages, wgs_per_head;
