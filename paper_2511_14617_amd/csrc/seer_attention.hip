@@ -20,8 +20,8 @@ namespace seer {
 
 // ---------------------------------------------------------------------------
 // Plan: one workgroup turns ctx_len[B] into the tile line, the stretch of every
-// partition workgroup and the partial slots of every request; further ones,
-// beside it, compare neighbouring block-table rows (plan_shared_pages).  (Most calls of up to
+// partition workgroup and the partial slots of every request; a second one,
+// beside it, compares neighbouring block-table rows (plan_shared_pages).  (Most calls of up to
 // kSelfPlanRequests requests do without it: seer_plan.h.)
 //
 // The kernel is one dependent chain in front of every call that needs it, so it is
@@ -29,27 +29,23 @@ namespace seer {
 // the speeds) are requested at once, one request and one stretch per thread, two
 // exchanges between the waves for all sums and scans, and searches in LDS
 // instead of walks over a request's pieces.  With 256 threads, four exchanges and
-// walks it took 8.6 .. 12.5 us of every call, now 4.8 .. 5.8 (4 to 64 requests).
+// walks it took 8.6 .. 12.5 us of every call; 4.9 with 75 to 110 requests (5.6 while it also smoothed the speeds).
 // ---------------------------------------------------------------------------
 constexpr int kPlanThreads = 1024;
 constexpr int kPlanWaves = kPlanThreads / kWave;
 constexpr int kPlanLdsRequests = 4096;   // tile offsets of this many requests are searched in LDS, of more in global memory
 
-// The plan's further workgroups.  Leading pages that a request has in common with the request before or after it
+// The plan's second workgroup.  Leading pages that a request has in common with the request before or after it
 // (the prompt that the rollouts of a group share sits in the same physical pages): the partition kernel loads such
 // tiles with the cache policy that keeps them, so that the repeats are served by the memory-side cache.  This is a
 // hint only, results do not depend on it, so the length of the common run is found by probing instead of comparing
 // every entry: sixteen entries at doubling distances, then sixteen evenly spaced ones between the last equal probe
 // and the first unequal one (two dependent rounds of loads; exact for runs of up to 32 pages, else short by less
-// than a sixteenth of the run if the tables are equal up to a point and differ behind it).  They run beside the
-// first workgroup, which needs about as long for the tile line and the stretches.  A thread's probes lie in 128 cache lines
-// of their own, so a workgroup takes a few requests only (one for all 64 of the tensor-parallel batch: its combine kernel, in which
-// they run where the partition kernel plans for itself, took 0.8 us longer than without them).
-constexpr int kSharedRequests = 8;
-inline int shared_pages_wgs(int B) { return (B + kSharedRequests - 1) / kSharedRequests; }
-__device__ __forceinline__ void plan_shared_pages(const AttnArgs& p, int wg) {
-    const int b = wg * kSharedRequests + static_cast<int>(threadIdx.x);
-    if (threadIdx.x < kSharedRequests && b < p.B) {
+// than a sixteenth of the run if the tables are equal up to a point and differ behind it).  It runs beside the
+// first workgroup, which needs about as long for the tile line and the stretches.  (Spread over workgroups of eight requests
+// the plan kernel takes longer, calls of 75 to 110 requests 1.8 .. 2.7 us: workgroups of sixteen waves are slow to start.)
+__device__ __forceinline__ void plan_shared_pages(const AttnArgs& p, int b_begin, int b_end, int threads) {
+    for (int b = b_begin + static_cast<int>(threadIdx.x); b < b_end; b += threads) {
         const int n = p.ctx_len[b];
         int best = 0;
         if (n >= p.T && n <= p.max_ctx) {
@@ -100,8 +96,8 @@ __device__ __forceinline__ void plan_shared_pages(const AttnArgs& p, int wg) {
 }
 
 __global__ __launch_bounds__(kPlanThreads) void plan_kernel(AttnArgs p) {
-    if (blockIdx.x > 0) {
-        plan_shared_pages(p, blockIdx.x - 1);
+    if (blockIdx.x == 1) {
+        plan_shared_pages(p, 0, p.B, kPlanThreads);
         return;
     }
     __shared__ int s_tiles[kPlanWaves], s_longest[kPlanWaves];       // per wave
@@ -228,7 +224,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(AttnArgs p) {
 }
 
 hipError_t launch_plan(const AttnArgs& a, hipStream_t stream) {
-    hipLaunchKernelGGL(plan_kernel, dim3(1 + shared_pages_wgs(a.B)), dim3(kPlanThreads), 0, stream, a);
+    hipLaunchKernelGGL(plan_kernel, dim3(2), dim3(kPlanThreads), 0, stream, a);
     return hipGetLastError();
 }
 
@@ -443,6 +439,11 @@ __device__ __forceinline__ void add_pieces(PartSum& s, const float2* ml, const f
     }
 }
 
+// Requests whose shared pages one workgroup of the combine kernel counts: a thread's probes lie in 128 cache lines of their own (all 64
+// requests of the tensor-parallel batch in one workgroup: 0.8 us of the call).
+constexpr int kSharedRequests = 8;
+inline int shared_pages_wgs(int B) { return (B + kSharedRequests - 1) / kSharedRequests; }
+
 // What a call that plans leaves for the calls after it, by a workgroup of the combine kernel beside its others: the rates
 // of the stretch indices from the partition kernel's measurements (in front of the partition kernel this was part of the plan
 // kernel's chain), and, where the partition kernel planned for itself, the status word.
@@ -540,7 +541,7 @@ __global__ __launch_bounds__(kCombineThreads) __attribute__((amdgpu_waves_per_eu
     // the first workgroups (none in a call that reuses a plan): what is left for later calls
     if (static_cast<int>(blockIdx.x) < extra) {
         if (blockIdx.x == 0) finish_call(a);
-        else plan_shared_pages(a, blockIdx.x - 1);
+        else plan_shared_pages(a, (blockIdx.x - 1) * kSharedRequests, min(static_cast<int>(blockIdx.x) * kSharedRequests, a.B), kCombineThreads);
         return;
     }
     const int block = static_cast<int>(blockIdx.x) - extra;
@@ -724,7 +725,8 @@ int run_verify_attention(void* out, const void* q, const void* k_pages, const vo
     a.max_ctx = max_ctx > 0x7fffffffLL - seer::kPlanTile ? 0x7fffffff - seer::kPlanTile : static_cast<int>(max_ctx);
     a.reuse_plan = (p->flags & SEER_ATTN_REUSE_PLAN) ? 1 : 0;
     a.self_plan = seer::self_plan_layout(*p) && !(p->flags & (SEER_ATTN_GENERAL_KERNEL | SEER_ATTN_REUSE_PLAN | SEER_ATTN_STREAM_ONLY)) ? 1 : 0;
-    a.fixed_split = (p->flags & SEER_ATTN_FIXED_SPLIT) ? 1 : 0;
+    // (the shared-latent kernel records no speeds: nothing to keep a history of)
+    a.fixed_split = (p->flags & SEER_ATTN_FIXED_SPLIT) || seer::mla_layout(*p) ? 1 : 0;
     a.stream_only = (p->flags & SEER_ATTN_STREAM_ONLY) ? 1 : 0;
     a.stream_partials = (w.total - w.off_acc) < seer::kStreamPartialsBelow ? 1 : 0;
     const bool tile_kernel = seer::tile_supports(*p);
