@@ -80,8 +80,9 @@ typedef struct seer_attn_params {
 /* flags: run the general kernel even where a tiled one exists (for cross-checks). */
 #define SEER_ATTN_GENERAL_KERNEL 1
 /* flags: cut the KV stream into equal stretches.  By default the library sizes each workgroup's
- * stretch by that workgroup slot's measured speed in earlier calls ON THE SAME WORKSPACE (a few
- * hundred bytes of history kept in it; any contents are valid, unusable ones mean equal stretches).
+ * stretch by that workgroup slot's measured speed in earlier calls ON THE SAME WORKSPACE (16 KB of
+ * history behind its header, at the same place for every shape and batch; any contents are valid,
+ * unusable ones mean equal stretches).
  * The result is the same up to the rounding order of the partial sums; with this flag the cut, and
  * therefore the result, does not depend on earlier calls. */
 #define SEER_ATTN_FIXED_SPLIT 2

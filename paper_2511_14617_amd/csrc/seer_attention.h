@@ -35,8 +35,10 @@ namespace seer {
 // its stretch index in the workspace, and the next call's plan cuts the line in
 // proportion to the smoothed tiles-per-time of each index (clamped to
 // [3/4, 4/3] of the mean).  The sums of these rates that a cut needs are made at the end of a call that plans,
-// by a workgroup of the combine kernel.  A workspace that holds no valid history (first use,
-// other W) gives equal stretches; SEER_ATTN_FIXED_SPLIT always does.
+// by a workgroup of the combine kernel.  The history lies at one place and has one size in every layout, so that no
+// other part of a workspace ever comes to lie there and it outlives a change of the batch.  A workspace that holds no
+// valid history (first use, other W, sums that no rates can have: share_ok in seer_plan.h) gives equal stretches;
+// SEER_ATTN_FIXED_SPLIT always does.
 struct PlanHeader {
     uint32_t status;     // bit 0: bad ctx_len somewhere; bit 1: page id out of range
     int32_t plan_b, plan_w;  // the batch and the split the tables are for (see plan_b_word, plan_w_word)
@@ -45,6 +47,7 @@ struct PlanHeader {
 };
 constexpr uint32_t kFeedbackMagic = 0x5ee2fb01u;
 constexpr int kMaxWgsPerHead = 1024;   // 256 CUs x 4 resident workgroups, one KV head
+constexpr int kHistoryStride = kMaxWgsPerHead + 4;     // words from one array of the history to the next (16-byte loads of five words)
 
 // A call that reuses a plan reads tables that it did not write itself.  They index by request and by stretch and nothing else
 // steers an unchecked access, so tables made for the same number of requests and the same stretches keep every access in
@@ -92,7 +95,7 @@ struct WorkspaceLayout {
     int wgs_per_head;    // W (balanced mode) or B (one workgroup per request)
     int max_splits;
     int row_blocks;
-    size_t off_header, off_slots, off_tiles, off_stretch, off_shared, off_fb, off_flags, off_ml, off_acc, total;
+    size_t off_header, off_fb, off_slots, off_tiles, off_stretch, off_shared, off_flags, off_ml, off_acc, total;
 };
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -197,13 +200,12 @@ inline WorkspaceLayout workspace_layout(const seer_attn_params& p) {
     const size_t rows = static_cast<size_t>(w.max_items) * p.T * p.Hq;
     const size_t per_b = sizeof(int32_t) * (static_cast<size_t>(p.B) + 1);
     w.off_header = 0;
-    w.off_slots = 256;
+    w.off_fb = 256;                    // time[W], tiles[W], smoothed speed[W], shares of the rates[W], whatever the shape
+    w.off_slots = align_up(w.off_fb + 4 * sizeof(uint32_t) * kHistoryStride, 256);
     w.off_tiles = align_up(w.off_slots + sizeof(ReqSlots) * p.B, 256);
-    const size_t per_w = sizeof(int32_t) * (static_cast<size_t>(w.wgs_per_head) + 1);
     w.off_stretch = align_up(w.off_tiles + per_b, 256);
     w.off_shared = align_up(w.off_stretch + sizeof(StretchRec) * w.wgs_per_head, 256);
-    w.off_fb = align_up(w.off_shared + per_b, 256);               // time[W], tiles[W], smoothed speed[W], shares of the rates[W]
-    w.off_flags = align_up(w.off_fb + 4 * per_w, 256);            // one byte per wave of the partition kernel's grid
+    w.off_flags = align_up(w.off_shared + per_b, 256);            // one byte per wave of the partition kernel's grid
     const bool self_plans = self_plan_layout(p);
     w.off_ml = align_up(w.off_flags + (self_plans ? size_t{8} * w.wgs_per_head * p.Hkv * w.row_blocks : 0), 256);
     w.off_acc = align_up(w.off_ml + 2 * sizeof(float) * rows, 256);
@@ -238,7 +240,7 @@ struct AttnArgs {
     int32_t reuse_plan;         // 1: the tables of an earlier call
     int32_t max_splits, max_ctx;   // most pieces of a request; most tokens that a row of the block table holds
     uint32_t inv_wgs, inv_splits;   // reciprocal() of wgs_per_head and of max_splits - 1
-    int32_t fixed_split;        // 1: equal stretches, no history read or written
+    int32_t fixed_split;        // 1: equal stretches, no history read or written (also where there is one stretch only)
     int32_t balanced;           // 0: one workgroup per request (max_splits == 1), slot = request, no history either
     int32_t min_tiles;          // tiles of a stretch, at least (see kMinTiles)
     int32_t fine_pieces;        // with more pieces than this in stretches of two or three tiles: four tiles (see kFinePartialsBelow)

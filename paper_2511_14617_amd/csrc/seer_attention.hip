@@ -113,12 +113,14 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(AttnArgs p) {
     const int per = (p.B + kPlanThreads - 1) / kPlanThreads;
     const int b0 = min(p.B, tid * per), b1 = min(p.B, b0 + per);
     const int n_first = b0 < b1 ? p.ctx_len[b0] : 0;
-    uint32_t before = equal_before(p, tid);
+    uint32_t before = equal_before(p, tid), recorded = 0u;
+    bool usable = false;                                 // the history, as far as this thread's stretch goes
     if (history) {
         const uint32_t magic = p.header->fb_magic;
         const int w = p.header->fb_w;
-        const uint32_t f = p.fb_before[min(tid, W)];
-        if (magic == kFeedbackMagic && w == W) before = f;
+        recorded = p.fb_before[min(tid, W)];
+        const uint32_t behind = p.fb_before[min(tid, W) + 1];
+        usable = magic == kFeedbackMagic && w == W && share_ok(p, tid, recorded, behind);
     }
     auto tiles = [&](int n) -> int { return tiles_of(n, p.T, p.max_ctx); };
     auto length = [&](int b) -> int { return b == b0 ? n_first : p.ctx_len[b]; };
@@ -134,22 +136,25 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(AttnArgs p) {
     }
     const int incl = wave_incl_scan(cnt);
     const int wave_bad = __any(bad) ? 1 : 0;
+    const bool wave_usable = __all(usable);
     mx = wave_max_in_last_lane(mx);
     if (lane == kWave - 1) {
         s_tiles[wave] = incl;
-        s_longest[wave] = mx * 2 + wave_bad;
+        s_longest[wave] = mx * 4 + (wave_usable ? 2 : 0) + wave_bad;
     }
     __syncthreads();
     int total = 0, my_off = incl - cnt, longest = 0;
-    int any_bad = 0;
+    int any_bad = 0, all_usable = 2;
 #pragma unroll
     for (int w = 0; w < kPlanWaves; ++w) {
         const int t = s_tiles[w], l = s_longest[w];
         if (w < wave) my_off += t;
         total += t;
-        longest = max(longest, l >> 1);
+        longest = max(longest, l >> 2);
         any_bad |= l & 1;
+        all_usable &= l & 2;
     }
+    if (all_usable) before = recorded;
     {
         int off = my_off;
         for (int b = b0; b < b1; ++b) {
@@ -714,9 +719,9 @@ int run_verify_attention(void* out, const void* q, const void* k_pages, const vo
     a.balanced = w.max_splits > 1 ? 1 : 0;
     a.shared_tiles = reinterpret_cast<const int32_t*>(ws + w.off_shared);
     a.fb_time = reinterpret_cast<uint32_t*>(ws + w.off_fb);
-    a.fb_tiles = a.fb_time + (w.wgs_per_head + 1);
-    a.fb_speed = reinterpret_cast<float*>(a.fb_tiles + (w.wgs_per_head + 1));
-    a.fb_before = reinterpret_cast<uint32_t*>(a.fb_speed + (w.wgs_per_head + 1));
+    a.fb_tiles = a.fb_time + seer::kHistoryStride;
+    a.fb_speed = reinterpret_cast<float*>(a.fb_tiles + seer::kHistoryStride);
+    a.fb_before = reinterpret_cast<uint32_t*>(a.fb_speed + seer::kHistoryStride);
     a.inv_wgs = seer::reciprocal(w.wgs_per_head);
     a.inv_splits = seer::reciprocal(w.max_splits - 1);
     a.page_flags = reinterpret_cast<uint8_t*>(ws + w.off_flags);
@@ -725,8 +730,8 @@ int run_verify_attention(void* out, const void* q, const void* k_pages, const vo
     a.max_ctx = max_ctx > 0x7fffffffLL - seer::kPlanTile ? 0x7fffffff - seer::kPlanTile : static_cast<int>(max_ctx);
     a.reuse_plan = (p->flags & SEER_ATTN_REUSE_PLAN) ? 1 : 0;
     a.self_plan = seer::self_plan_layout(*p) && !(p->flags & (SEER_ATTN_GENERAL_KERNEL | SEER_ATTN_REUSE_PLAN | SEER_ATTN_STREAM_ONLY)) ? 1 : 0;
-    // (the shared-latent kernel records no speeds: nothing to keep a history of)
-    a.fixed_split = (p->flags & SEER_ATTN_FIXED_SPLIT) || seer::mla_layout(*p) ? 1 : 0;
+    // (the shared-latent kernel records no speeds, and a single stretch is the whole line: nothing to keep a history of)
+    a.fixed_split = (p->flags & SEER_ATTN_FIXED_SPLIT) || seer::mla_layout(*p) || w.wgs_per_head == 1 ? 1 : 0;
     a.stream_only = (p->flags & SEER_ATTN_STREAM_ONLY) ? 1 : 0;
     a.stream_partials = (w.total - w.off_acc) < seer::kStreamPartialsBelow ? 1 : 0;
     const bool tile_kernel = seer::tile_supports(*p);

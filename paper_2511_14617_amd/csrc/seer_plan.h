@@ -46,8 +46,8 @@ __device__ __forceinline__ int tiles_of(int n, int T, int max_ctx) { return n < 
 
 // x / d for 0 <= x < 2^31 and 1 <= d, with inv = reciprocal(d).  (A division by a number in a register is some thirty
 // instructions, and every workgroup begins with two; the code itself has to be fetched, too.)
-__device__ __forceinline__ int divide(int x, int d, uint32_t inv) {
-    int q = static_cast<int>(__umulhi(static_cast<uint32_t>(x), inv));       // the quotient or one less
+__host__ __device__ __forceinline__ int divide(int x, int d, uint32_t inv) {
+    int q = static_cast<int>((static_cast<uint64_t>(static_cast<uint32_t>(x)) * inv) >> 32);       // the quotient or one less
     return x - q * d >= d ? q + 1 : q;
 }
 
@@ -56,7 +56,7 @@ struct Cut {
     int total, W, equal;      // tiles of the line, stretches, tiles of a stretch where all are alike
     bool weighted;            // the line is long enough for stretches that follow the measured speeds
 };
-__device__ __forceinline__ Cut cut_of(const AttnArgs& a, int total, int longest) {
+__host__ __device__ __forceinline__ Cut cut_of(const AttnArgs& a, int total, int longest) {
     const int W = a.wgs_per_head;
     // a request of t tiles touches at most ceil(t / Lmin) + 1 stretches, which must fit max_splits
     const int per_w = divide(total + W - 1, W, a.inv_wgs);
@@ -68,14 +68,26 @@ __device__ __forceinline__ Cut cut_of(const AttnArgs& a, int total, int longest)
     return {total, W, max(Lmin, max(per_w, 1)), total >= static_cast<long long>(max(2 * Lmin, kMinTilesWeighted)) * W};
 }
 // First tile of stretch w; before = (r_0 + .. + r_{w-1}) / R in units of 2^-32 (looked at only where the cut is weighted).
-__device__ __forceinline__ int cut_begin(const Cut& c, int w, uint32_t before) {
+__host__ __device__ __forceinline__ int cut_begin(const Cut& c, int w, uint32_t before) {
     if (w >= c.W) return c.total;
     const uint64_t at = c.weighted ? (static_cast<uint64_t>(static_cast<uint32_t>(c.total)) * before + (1u << 31)) >> 32
                                    : static_cast<uint64_t>(w) * static_cast<uint32_t>(c.equal);
     return static_cast<int>(at < static_cast<uint64_t>(c.total) ? at : c.total);
 }
 // The same where no speeds are known: w / W.
-__device__ __forceinline__ uint32_t equal_before(const AttnArgs& a, int w) { return static_cast<uint32_t>(w) * a.inv_wgs; }
+__host__ __device__ __forceinline__ uint32_t equal_before(const AttnArgs& a, int w) { return static_cast<uint32_t>(w) * a.inv_wgs; }
+
+// Can words w and w + 1 of the recorded shares belong to a cut?  The first share has nothing in front of it, the last ends with
+// the line, and rates between 3/4 and 4/3 make a share of 9/16 to 16/9 of an equal one; taken from 1/2 to 15/8 here.  W differences of at most
+// 15/8 of 2^32 / W each, modulo 2^32, can only add up to 2^32 - 1 without a wrap: where all W pass, the shares rise from 0, the stretches
+// cover the line once, and every one has a part of it that is a share's, whatever bytes the workspace held.  (Looked at in full by every
+// wave that cuts: a mark beside the sums says who wrote them, not what has become of them since.)  (W >= 2)
+__host__ __device__ __forceinline__ bool share_ok(const AttnArgs& a, int w, uint32_t here, uint32_t behind) {
+    if (w >= a.wgs_per_head) return true;
+    if (w + 1 == a.wgs_per_head) behind = 0xffffffffu;
+    const uint32_t equal = a.inv_wgs;
+    return (w > 0 || here == 0) && behind - here - equal / 2 <= equal + equal / 4 + equal / 8;
+}
 
 // ---------------------------------------------------------------------------
 // A partition kernel's own plan.  A batch of up to kSelfPlanRequests requests has its lengths in one register of a wave, so
@@ -93,17 +105,38 @@ struct SelfPlan {
 __device__ __forceinline__ SelfPlan plan_stretch(const AttnArgs& a, int* line, int wg) {
     const int lane = static_cast<int>(threadIdx.x) & (kWave - 1), W = a.wgs_per_head;
     const int n = lane < a.B ? a.ctx_len[lane] : 0;
-    uint32_t before = equal_before(a, wg), behind = equal_before(a, wg + 1);
+    // the history: this stretch's two words, and eight words per lane to see whether all of them can be used
+    struct Shares {
+        u32x4 x, y;
+        uint32_t next;
+    };
+    auto shares = [&](int i) __attribute__((always_inline)) -> Shares {          // i <= kMaxWgsPerHead - 8
+        return {*reinterpret_cast<const u32x4*>(a.fb_before + i), *reinterpret_cast<const u32x4*>(a.fb_before + i + 4), a.fb_before[i + 8]};
+    };
+    static_assert(kMaxWgsPerHead % (8 * kWave) == 0 && kHistoryStride > kMaxWgsPerHead, "shares() stays inside the array");
+    Shares s{};
+    uint32_t f0 = 0u, f1 = 0u;
+    bool usable = false;
     if (!a.fixed_split) {
-        const uint32_t magic = a.header->fb_magic;
-        const int w = a.header->fb_w;
-        const uint32_t f0 = a.fb_before[wg], f1 = a.fb_before[wg + 1];        // (one more than there are stretches: in the layout)
-        if (magic == kFeedbackMagic && w == W) before = f0, behind = f1;
+        usable = a.header->fb_magic == kFeedbackMagic && a.header->fb_w == W;
+        f0 = a.fb_before[wg], f1 = a.fb_before[wg + 1];
+        s = shares(8 * lane);
     }
     const int t = lane < a.B ? tiles_of(n, a.T, a.max_ctx) : 0;
     const int incl = wave_incl_scan(t), off = incl - t;
     const int total = last_lane(incl), longest = last_lane(wave_max_in_last_lane(t));
     const Cut cut = cut_of(a, total, longest);
+    uint32_t before = equal_before(a, wg), behind = equal_before(a, wg + 1);
+    if (!a.fixed_split && cut.weighted) {
+        for (int i = 8 * lane;; s = shares(i)) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                usable &= share_ok(a, i + k, k < 4 ? s.x[k & 3] : s.y[k & 3], k < 3 ? s.x[(k + 1) & 3] : (k < 7 ? s.y[(k + 1) & 3] : s.next));
+            i += 8 * kWave;
+            if (i >= W) break;
+        }
+        if (__all(usable)) before = f0, behind = f1;
+    }
     const int begin = __builtin_amdgcn_readfirstlane(cut_begin(cut, wg, before));
     const int end = __builtin_amdgcn_readfirstlane(cut_begin(cut, wg + 1, behind));
     // every wave writes the same words and reads them behind its own writes
@@ -120,7 +153,8 @@ __device__ __forceinline__ SelfPlan plan_stretch(const AttnArgs& a, int* line, i
 
 // At a wave's end (stores in front of its loads would have to be waited for with them): whether it met a page id outside the
 // pool, one byte per wave of the grid (the status word cannot collect these: nothing in front of the kernel clears it); and by
-// one workgroup per stretch that stretch's part of the tables.
+// one workgroup per stretch that stretch's part of the tables.  (The stretches cover the line once, whatever the history held, so
+// every request with tiles gets both words of its slots.)
 __device__ __forceinline__ void publish_stretch(const AttnArgs& a, const int* line, const StretchRec& rec, int wg, int kvh, int rb, int wave,
                                                 bool bad_page) {
     const int lane = static_cast<int>(threadIdx.x) & (kWave - 1);

@@ -1,0 +1,102 @@
+"""The speed history that a workspace carries from call to call: a loop changes its batch on one workspace, other calls use it
+in between, and it may hold anything before its first use.  Every output is compared with a 64-bit reference, every cut with
+the line that it has to cover."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import assert_attention_close
+
+pytestmark = pytest.mark.gpu
+
+PAGE, PAGES = 32, 192
+# name: Hq, Hkv, Dqk, T, tokens of a request; lines of eight tiles and more for every stretch from 32 requests on
+SHAPES = {"one_wave": (8, 8, 128, 2, (1100, 1900)), "four_waves": (32, 8, 128, 27, (550, 900)), "pairs": (32, 8, 128, 33, (300, 700)),
+          "head64": (32, 32, 64, 2, (520, 900))}
+
+
+class Batch:
+    """Requests over a small pool, and what their outputs are; the first B of them are a batch of their own."""
+
+    def __init__(self, B, Hq, Hkv, D, T, tokens, Dv=None, seed=3):
+        gen = torch.Generator(device="cuda").manual_seed(seed)
+        rng = np.random.default_rng(seed)
+        self.Dv, self.scale, self.T = Dv or D, D ** -0.5, T
+        normal = lambda *shape: torch.randn(shape, dtype=torch.bfloat16, device="cuda", generator=gen)  # noqa: E731
+        self.q, self.k = normal(B, T, Hq, D), normal(PAGES, Hkv, PAGE, D)
+        self.v = None if Dv else normal(PAGES, Hkv, PAGE, D)
+        self.lengths = rng.integers(*tokens, size=B)
+        self.ctx = torch.from_numpy(self.lengths.astype(np.int32)).cuda()
+        self.table = torch.from_numpy(rng.integers(0, PAGES, size=(B, -(-tokens[1] // PAGE))).astype(np.int32)).cuda()
+
+    def reference(self):
+        B, T, Hq, D = self.q.shape
+        Hkv = self.k.shape[1]
+        out = torch.zeros((B, T, Hkv, Hq // Hkv, self.Dv), dtype=torch.float64, device="cuda")
+        for b, n in enumerate(self.lengths.tolist()):
+            pages = self.table[b, : -(-n // PAGE)].long()
+            k = self.k[pages].transpose(0, 1).reshape(Hkv, -1, D)[:, :n].double()
+            v = k[..., : self.Dv] if self.v is None else self.v[pages].transpose(0, 1).reshape(Hkv, -1, self.Dv)[:, :n].double()
+            hidden = torch.arange(n, device="cuda")[None, :] > torch.arange(n - T, n, device="cuda")[:, None]
+            for h in range(Hkv):
+                q = self.q[b, :, h * (Hq // Hkv):(h + 1) * (Hq // Hkv)].double()
+                for g in range(q.shape[1]):
+                    s = (q[:, g].contiguous() @ k[h].T.contiguous()) * self.scale
+                    out[b, :, h, g] = torch.softmax(s.masked_fill_(hidden, -np.inf), dim=1) @ v[h]
+        return out.view(B, T, Hq, self.Dv).cpu().numpy()
+
+    def params(self, B, max_splits=0):
+        from paper_2511_14617_amd import binding
+        return binding.attn_params(self.q[:B], self.k, self.v, self.table[:B], self.scale, Dv=self.Dv, max_splits=max_splits)
+
+    def call(self, B, ws, flags=0, max_splits=0):
+        from paper_2511_14617_amd import binding
+        return binding.seer_verify_attention(self.q[:B], self.k, self.v, self.table[:B], self.ctx[:B], None, self.scale, Dv=self.Dv,
+                                             max_splits=max_splits, workspace=ws, flags=flags)
+
+
+def workspace(*params):
+    from paper_2511_14617_amd import binding
+    return torch.zeros(max(binding.seer_verify_attention_workspace(p) for p in params), dtype=torch.uint8, device="cuda")
+
+
+def stretches(ws, p):
+    """(first tile, first tile behind it) of every stretch, from the records that the last plan left in front of the shared tiles."""
+    from paper_2511_14617_amd import binding
+    W = int(ws[8:12].view(torch.int32))
+    begin = binding.load_library().seer_verify_attention_shared_tiles_offset(p) - (16 * W + 255) // 256 * 256
+    return ws[begin:begin + 16 * W].view(torch.int32).view(W, 4)[:, 1:3].cpu().numpy()
+
+
+def assert_cut(ws, p, lengths):
+    """The line is covered once, in order, and no stretch has more than twice its share (nobody works for all the others)."""
+    cut, total = stretches(ws, p), int(np.sum(-(-lengths // 32)))
+    assert total >= 8 * len(cut), "the test wants lines that follow the measured speeds"
+    assert cut[0, 0] == 0 and cut[-1, 1] == total and (cut[1:, 0] == cut[:-1, 1]).all() and (cut[:, 0] <= cut[:, 1]).all()
+    assert (cut[:, 1] - cut[:, 0]).max() <= 2 * total / len(cut) + 2
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_a_workspace_may_serve_other_batches_and_hold_anything(shape):
+    from paper_2511_14617_amd import binding
+    Hq, Hkv, D, T, tokens = SHAPES[shape]
+    most = Batch(100, Hq, Hkv, D, T, tokens)
+    latent = Batch(2, 16, 1, 576, 2, (600, 900), Dv=512)
+    ref, ref_latent = most.reference(), latent.reference()
+    ws = workspace(most.params(100), most.params(64, max_splits=1), latent.params(2))
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    steps = [64, 48, 32, 48, 100, 65, 64, "fixed", 64, 63, "whole requests", 63, "latent", 33, 32, "other bytes", 64, "other bytes", 32, "other bytes", 100, 100]
+    for k, step in enumerate(steps):
+        print(shape, k, step, flush=True)
+        if step == "latent":
+            assert_attention_close(latent.call(2, ws), ref_latent, "latent")
+        elif step == "fixed":
+            assert_attention_close(most.call(48, ws, binding.SEER_ATTN_FIXED_SPLIT), ref[:48], "fixed split")
+        elif step == "whole requests":
+            assert_attention_close(most.call(64, ws, max_splits=1), ref[:64], "whole requests")
+        elif step == "other bytes":                       # behind the header, which still says that there is a history
+            ws[256:] = torch.randint(0, 256, (len(ws) - 256,), dtype=torch.uint8, device="cuda", generator=gen)
+        else:
+            assert_attention_close(most.call(step, ws), ref[:step], "%s, call %d, batch of %d" % (shape, k, step))
+            assert binding.seer_verify_attention_status(ws) == 0
+            assert_cut(ws, most.params(step), most.lengths[:step])
