@@ -32,7 +32,8 @@ namespace seer {
 // workgroups with the same stretch index w, one per KV head, share XCD and
 // dispatch round), and stable from call to call.  So every partition workgroup
 // adds its tiles and its duration (constant 100 MHz clock) to two counters of
-// its stretch index in the workspace, and the next call's plan cuts the line in
+// its stretch index in the workspace (where a call that plans for itself finds no history, and nothing has cleared counters, one
+// workgroup of a stretch index sets them), and the next call's plan cuts the line in
 // proportion to the smoothed tiles-per-time of each index (clamped to
 // [3/4, 4/3] of the mean).  The sums of these rates that a cut needs are made at the end of a call that plans,
 // by a workgroup of the combine kernel.  The history lies at one place and has one size in every layout, so that no

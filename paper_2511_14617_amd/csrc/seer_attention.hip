@@ -114,14 +114,17 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(AttnArgs p) {
     const int b0 = min(p.B, tid * per), b1 = min(p.B, b0 + per);
     const int n_first = b0 < b1 ? p.ctx_len[b0] : 0;
     uint32_t before = equal_before(p, tid), recorded = 0u;
-    bool usable = false;                                 // the history, as far as this thread's stretch goes
+    bool marked = true, usable = false;                  // is there a history; can it be used, as far as this thread's stretch goes
     if (history) {
         const uint32_t magic = p.header->fb_magic;
         const int w = p.header->fb_w;
         recorded = p.fb_before[min(tid, W)];
         const uint32_t behind = p.fb_before[min(tid, W) + 1];
-        usable = magic == kFeedbackMagic && w == W && share_ok(p, tid, recorded, behind);
+        marked = magic == kFeedbackMagic && w == W;
+        usable = marked && share_ok(p, tid, recorded, behind);
     }
+    // a new one begins with this call's measurements
+    if (!marked && tid < W) p.fb_time[tid] = 0u, p.fb_tiles[tid] = 0u, p.fb_speed[tid] = 0.f;
     auto tiles = [&](int n) -> int { return tiles_of(n, p.T, p.max_ctx); };
     auto length = [&](int b) -> int { return b == b0 ? n_first : p.ctx_len[b]; };
 
@@ -225,6 +228,7 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(AttnArgs p) {
         p.header->status = any_bad ? 1u : 0u;
         p.header->plan_b = plan_b_word(p.B);
         p.header->plan_w = plan_w_word(W, balanced);
+        if (!marked) p.header->fb_magic = kFeedbackMagic, p.header->fb_w = W;
     }
 }
 
@@ -469,10 +473,10 @@ __device__ __forceinline__ void finish_call(const AttnArgs& a) {
             const int w = min(tid * kPer + k, W - 1);
             est[k] = a.fb_speed[w], ticks[k] = a.fb_time[w], streamed[k] = a.fb_tiles[w];
         }
-        // relative speed of each stretch index (unknown: 0, also whatever a stale one held)
+        // relative speed of each stretch index (unknown: 0, also whatever a stale one held; the counters are this call's)
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
-            if (!valid) est[k] = 0.f, ticks[k] = 0u;
+            if (!valid) est[k] = 0.f;
             if (ticks[k] > 0u && streamed[k] > 0u) {
                 const float meas = static_cast<float>(streamed[k]) / static_cast<float>(ticks[k]);
                 est[k] = est[k] > 0.f ? 0.5f * est[k] + 0.5f * meas : meas;

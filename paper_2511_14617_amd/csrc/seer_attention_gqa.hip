@@ -540,7 +540,8 @@ __device__ __forceinline__ void softmax_pv(int v, f32x16& s, f32x16 (&acc)[4], f
 }
 
 template <bool STREAM, bool STREAM_PARTIALS, bool SELF>
-__device__ __forceinline__ void run(const AttnArgs& a, unsigned char* lds, const int* line, int kvh, int rb, int wg, const StretchRec& rec) {
+__device__ __forceinline__ void run(const AttnArgs& a, unsigned char* lds, const int* line, int kvh, int rb, int wg, const StretchRec& rec,
+                                    bool new_history) {
     constexpr int NT = kWaves * kWave;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -862,11 +863,8 @@ __device__ __forceinline__ void run(const AttnArgs& a, unsigned char* lds, const
   }  // pieces of the stretch
     if constexpr (SELF) publish_stretch(a, line, rec, wg, kvh, rb, wave, bad_page);
     else if (__any(bad_page) && lane == 0) atomicOr(&a.header->status, 2u);
-    if (a.balanced && !a.fixed_split && tid == 0) {
-        const uint64_t ticks = __builtin_amdgcn_s_memrealtime() - clock_begin;
-        atomicAdd(a.fb_time + wg, static_cast<uint32_t>(ticks > 0xffffffu ? 0xffffffu : ticks));
-        atomicAdd(a.fb_tiles + wg, static_cast<uint32_t>(g_end - g_first));
-    }
+    if (a.balanced && !a.fixed_split && tid == 0)
+        record_speed(a, wg, kvh, rb, __builtin_amdgcn_s_memrealtime() - clock_begin, g_end - g_first, new_history);
 }
 
 }  // namespace pairs
@@ -922,11 +920,13 @@ void attn_gqa128_kernel(AttnArgs a) {
 
     StretchRec rec;
     int pieces = 1;
+    bool new_history = false;
     if (SELF) {
         const SelfPlan own = plan_stretch(a, s_line, wg);
-        rec = own.rec, pieces = own.pieces;
+        rec = own.rec, pieces = own.pieces, new_history = own.new_history;
         if (rec.b < 0) {
             publish_stretch(a, s_line, rec, wg, kvh, rb, wave, false);
+            if (new_history && tid == 0) record_speed(a, wg, kvh, rb, 0, 0, true);
             return;
         }
     } else {
@@ -943,7 +943,7 @@ void attn_gqa128_kernel(AttnArgs a) {
             pieces = max(1, last - b + 1);
         }
         if (rec.tile_end - rec.tile_begin >= kPairsFromTiles * pieces) {
-            pairs::run<STREAM, STREAM_PARTIALS, SELF>(a, lds, s_line, kvh, rb, wg, rec);
+            pairs::run<STREAM, STREAM_PARTIALS, SELF>(a, lds, s_line, kvh, rb, wg, rec, new_history);
             return;
         }
         if (wave >= NW) {                           // (barriers wait for the waves that are left)
@@ -1391,11 +1391,8 @@ void attn_gqa128_kernel(AttnArgs a) {
     if constexpr (SELF) publish_stretch(a, s_line, rec, wg, kvh, rb, wave, bad_page);
     else if (__any(bad_page) && lane == 0) atomicOr(&a.header->status, 2u);
     // speed history for the next call's plan: tiles streamed and time taken, by stretch index
-    if (a.balanced && !a.fixed_split && tid == 0) {
-        const uint64_t ticks = __builtin_amdgcn_s_memrealtime() - clock_begin;
-        atomicAdd(a.fb_time + wg, static_cast<uint32_t>(ticks > 0xffffffu ? 0xffffffu : ticks));
-        atomicAdd(a.fb_tiles + wg, static_cast<uint32_t>(g_end - g_first));
-    }
+    if (a.balanced && !a.fixed_split && tid == 0)
+        record_speed(a, wg, kvh, rb, __builtin_amdgcn_s_memrealtime() - clock_begin, g_end - g_first, new_history);
 }
 
 bool gqa128_supports(const AttnArgs& a) {

@@ -113,10 +113,13 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
     const int ln = lane & 31, lg = lane >> 5, l16 = lane >> 4, p16 = lane & 15;
 
     StretchRec rec;
+    bool new_history = false;
     if (SELF) {
-        rec = plan_stretch(a, s_line, wg).rec;
+        const SelfPlan own = plan_stretch(a, s_line, wg);
+        rec = own.rec, new_history = own.new_history;
         if (rec.b < 0) {
             publish_stretch(a, s_line, rec, wg, kvh, rb, wave, false);
+            if (new_history && tid == 0) record_speed(a, wg, kvh, rb, 0, 0, true);
             return;
         }
     } else {
@@ -422,11 +425,8 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
     if constexpr (SELF) publish_stretch(a, s_line, rec, wg, kvh, rb, wave, bad_page);
     else if (__any(bad_page) && lane == 0) atomicOr(&a.header->status, 2u);
     // speed history for the next call's plan (see the D = 128 kernel)
-    if (a.balanced && !a.fixed_split && tid == 0) {
-        const uint64_t ticks = __builtin_amdgcn_s_memrealtime() - clock_begin;
-        atomicAdd(a.fb_time + wg, static_cast<uint32_t>(ticks > 0xffffffu ? 0xffffffu : ticks));
-        atomicAdd(a.fb_tiles + wg, static_cast<uint32_t>(g_end - g_first));
-    }
+    if (a.balanced && !a.fixed_split && tid == 0)
+        record_speed(a, wg, kvh, rb, __builtin_amdgcn_s_memrealtime() - clock_begin, g_end - g_first, new_history);
 }
 
 hipError_t launch_tile(const AttnArgs& a, hipStream_t stream) {

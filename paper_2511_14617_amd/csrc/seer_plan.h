@@ -101,6 +101,7 @@ constexpr int kLineWords = 2 * kSelfPlanRequests + 2;      // LDS: (first tile, 
 struct SelfPlan {
     StretchRec rec;
     int pieces;               // requests that the stretch touches
+    bool new_history;         // the workspace holds none: this call begins it (see record_speed)
 };
 __device__ __forceinline__ SelfPlan plan_stretch(const AttnArgs& a, int* line, int wg) {
     const int lane = static_cast<int>(threadIdx.x) & (kWave - 1), W = a.wgs_per_head;
@@ -116,9 +117,9 @@ __device__ __forceinline__ SelfPlan plan_stretch(const AttnArgs& a, int* line, i
     static_assert(kMaxWgsPerHead % (8 * kWave) == 0 && kHistoryStride > kMaxWgsPerHead, "shares() stays inside the array");
     Shares s{};
     uint32_t f0 = 0u, f1 = 0u;
-    bool usable = false;
+    bool usable = false, marked = true;
     if (!a.fixed_split) {
-        usable = a.header->fb_magic == kFeedbackMagic && a.header->fb_w == W;
+        usable = marked = a.header->fb_magic == kFeedbackMagic && a.header->fb_w == W;
         f0 = a.fb_before[wg], f1 = a.fb_before[wg + 1];
         s = shares(8 * lane);
     }
@@ -142,7 +143,7 @@ __device__ __forceinline__ SelfPlan plan_stretch(const AttnArgs& a, int* line, i
     // every wave writes the same words and reads them behind its own writes
     line[2 * lane] = off, line[2 * lane + 1] = n;
     if (lane == 0) line[2 * kSelfPlanRequests] = total;
-    SelfPlan r{{-1, begin, end, 0}, 1};
+    SelfPlan r{{-1, begin, end, 0}, 1, !marked};
     if (begin < end) {                          // the last request that starts at or before the first tile
         r.rec.b = max(__popcll(__ballot(lane < a.B && off <= begin)) - 1, 0);
         r.rec.req_begin = __builtin_amdgcn_readlane(off, r.rec.b);
@@ -176,6 +177,20 @@ __device__ __forceinline__ void publish_stretch(const AttnArgs& a, const int* li
         const_cast<int32_t*>(a.tile_off)[a.B] = line[2 * kSelfPlanRequests];
         a.header->plan_b = plan_b_word(a.B);
         a.header->plan_w = plan_w_word(a.wgs_per_head, true);
+    }
+}
+
+// At the end of a workgroup that had tiles, or of one without in a call that plans for itself, by one thread: its part of the speed history.
+// set: the counters hold anything (a call that plans for itself, with nothing in front of it that could clear them, has found no
+// history): the workgroup of the first KV head and row block sets them.
+__device__ __forceinline__ void record_speed(const AttnArgs& a, int wg, int kvh, int rb, uint64_t ticks, int tiles, bool set) {
+    const uint32_t t = static_cast<uint32_t>(ticks > 0xffffffu ? 0xffffffu : ticks);
+    if (!set) {
+        atomicAdd(a.fb_time + wg, t);
+        atomicAdd(a.fb_tiles + wg, static_cast<uint32_t>(tiles));
+    } else if (kvh == 0 && rb == 0) {
+        a.fb_time[wg] = t;
+        a.fb_tiles[wg] = static_cast<uint32_t>(tiles);
     }
 }
 

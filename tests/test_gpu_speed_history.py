@@ -100,3 +100,26 @@ def test_a_workspace_may_serve_other_batches_and_hold_anything(shape):
             assert_attention_close(most.call(step, ws), ref[:step], "%s, call %d, batch of %d" % (shape, k, step))
             assert binding.seer_verify_attention_status(ws) == 0
             assert_cut(ws, most.params(step), most.lengths[:step])
+
+
+@pytest.mark.parametrize("shape,B", [("one_wave", 64), ("one_wave", 100), ("pairs", 40), ("head64", 64), ("head64", 100)])
+@pytest.mark.parametrize("first_bytes", [0, 0xA5])
+def test_the_second_call_follows_the_speeds_of_the_first(shape, B, first_bytes):
+    """On a new workspace, whichever kernel plans; and a batch of another size follows them at once."""
+    Hq, Hkv, D, T, tokens = SHAPES[shape]
+    most = Batch(B, Hq, Hkv, D, T, tokens)
+    p = most.params(B)
+    ws = workspace(p)
+    ws.fill_(first_bytes)
+
+    def equal(cut):
+        W, total = len(cut), int(cut[-1, 1])
+        return bool((cut[:, 0] == (np.arange(W) * total + W // 2) // W).all())
+    most.call(B, ws)
+    assert equal(stretches(ws, p))
+    most.call(B, ws)
+    assert not equal(stretches(ws, p))
+    less = B - 5
+    most.call(less, ws)
+    assert not equal(stretches(ws, most.params(less)))
+    assert_cut(ws, most.params(less), most.lengths[:less])
