@@ -602,7 +602,8 @@ __device__ __forceinline__ void run(const AttnArgs& a, unsigned char* lds, const
     const int page_first = page_ahead;
     NeighbourRows next_rows{0, 0};
     if constexpr (SELF) {
-        if (run_ahead == kWave && t_hi > t_lo) run_ahead += shared_run_behind(a, b, page_first + kWave);
+        if (run_ahead == kWave && t_hi > t_lo)
+            run_ahead += shared_run_behind(a, b, page_first + kWave, (min(n, (min(g_end, t_hi) - t_lo) * kTile) - 1) >> page_shift);
         shared_tiles = static_cast<int>(static_cast<long long>(page_first + run_ahead) * a.P / kTile);
         next_rows = neighbour_rows(a, b + 1, 0);
     } else {
@@ -1015,7 +1016,8 @@ void attn_gqa128_kernel(AttnArgs a) {
     const int page_first = page_ahead;
     NeighbourRows next_rows{0, 0};
     if constexpr (SELF) {
-        if (run_ahead == kWave && t_hi > t_lo) run_ahead += shared_run_behind(a, b, page_first + kWave);
+        if (run_ahead == kWave && t_hi > t_lo)
+            run_ahead += shared_run_behind(a, b, page_first + kWave, (min(n, (min(g_end, t_hi) - t_lo) * kTile) - 1) >> page_shift);
         shared_tiles = static_cast<int>(static_cast<long long>(page_first + run_ahead) * a.P / kTile);
         next_rows = neighbour_rows(a, b + 1, 0);
     } else {

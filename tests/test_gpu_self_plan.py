@@ -75,3 +75,29 @@ def test_a_page_id_outside_the_pool_is_reported_wherever_it_is(B, shape):
 
 def cfg_pages(d):
     return int(d["k_pages"].shape[0])
+
+
+@pytest.mark.parametrize("heads", [(4, 2, 4), (32, 8, 33), (8, 1, 2)])
+@pytest.mark.parametrize("common", [63, 64, 65, 130, 700])
+def test_long_common_prompts_only_change_how_pages_are_read(heads, common):
+    """Prompts of more pages than a wave looks at in one window, beginnings and ends of pieces inside them, rows that stay equal
+    behind a request's end: the same bits as from copies of the pages that no request shares."""
+    from paper_2511_14617_amd import binding
+    (Hq, Hkv, T), D, P, B = heads, 128, 16, 5
+    gen = torch.Generator(device="cuda").manual_seed(common)
+    lengths = [common * P + 3, common * P + 200, common * P // 2 + T, common * P + 1000, common * P + 40]
+    pages = max(-(-n // P) for n in lengths) + 70
+    table = torch.zeros((B, pages), dtype=torch.int32)
+    table[:] = torch.randperm(pages, generator=torch.Generator().manual_seed(1)).int()
+    for b in range(B):
+        if b != 2:                                       # (request 2 ends inside the prompt)
+            table[b, common:] = torch.arange(pages - common) + pages * (1 + b)
+    pool = pages * (B + 1)
+    k, v = (torch.randn((pool, Hkv, P, D), dtype=torch.bfloat16, device="cuda", generator=gen) for _ in range(2))
+    own = torch.arange(B * pages, dtype=torch.int32).view(B, pages).cuda()
+    src = table.cuda().view(-1).long()
+    q = torch.randn((B, T, Hq, D), dtype=torch.bfloat16, device="cuda", generator=gen)
+    ctx = torch.tensor(lengths, dtype=torch.int32, device="cuda")
+    outs = [binding.seer_verify_attention(q, kk, vv, t, ctx, None, D ** -0.5, flags=binding.SEER_ATTN_FIXED_SPLIT).view(torch.int16)
+            for kk, vv, t in ((k, v, table.cuda()), (k[src].contiguous(), v[src].contiguous(), own))]
+    assert torch.equal(*outs)
