@@ -100,7 +100,7 @@ constexpr int kLineWords = 2 * kSelfPlanRequests + 2;      // LDS: (first tile, 
 
 struct SelfPlan {
     StretchRec rec;
-    int pieces;               // requests that the stretch touches
+    int pieces;               // requests from the stretch's first to its last, those without tiles included (as the tables give it)
     bool new_history;         // the workspace holds none: this call begins it (see record_speed)
 };
 __device__ __forceinline__ SelfPlan plan_stretch(const AttnArgs& a, int* line, int wg) {
@@ -147,7 +147,12 @@ __device__ __forceinline__ SelfPlan plan_stretch(const AttnArgs& a, int* line, i
     if (begin < end) {                          // the last request that starts at or before the first tile
         r.rec.b = max(__popcll(__ballot(lane < a.B && off <= begin)) - 1, 0);
         r.rec.req_begin = __builtin_amdgcn_readlane(off, r.rec.b);
-        r.pieces = __popcll(__ballot(t > 0 && off < end && incl > begin));
+        int last = a.B - 1;
+        if (end < total) {                      // the request that the next stretch starts in, if it does not start with it
+            last = __popcll(__ballot(lane < a.B && off <= end)) - 1;
+            if (__builtin_amdgcn_readlane(off, last) == end) --last;
+        }
+        r.pieces = max(1, last - r.rec.b + 1);
     }
     return r;
 }

@@ -101,3 +101,21 @@ def test_long_common_prompts_only_change_how_pages_are_read(heads, common):
     outs = [binding.seer_verify_attention(q, kk, vv, t, ctx, None, D ** -0.5, flags=binding.SEER_ATTN_FIXED_SPLIT).view(torch.int16)
             for kk, vv, t in ((k, v, table.cuda()), (k[src].contiguous(), v[src].contiguous(), own))]
     assert torch.equal(*outs)
+
+
+@pytest.mark.parametrize("tiles", [(630, 0, 1290), (630, 0, 1290, 0, 0), (600, 0, 0, 1320), (0, 0, 1920), (0, 540, 0, 2, 0, 1378)])
+def test_reused_plans_with_unusable_lengths_give_the_same_bits(tiles):
+    """129 .. 144 rows of a KV head, where a stretch takes pairs of tiles or five waves by the number of its pieces: both kinds of
+    call count requests without tiles alike (60 tiles a stretch, between twice and three times the least for pairs)."""
+    from paper_2511_14617_amd import binding
+    B, T, Hq, Hkv, D, P, pool = len(tiles), 33, 32, 8, 128, 32, 64
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    q = torch.randn((B, T, Hq, D), dtype=torch.bfloat16, device="cuda", generator=gen)
+    k, v = (torch.randn((pool, Hkv, P, D), dtype=torch.bfloat16, device="cuda", generator=gen) for _ in range(2))
+    table = torch.randint(0, pool, (B, max(tiles)), dtype=torch.int32, device="cuda", generator=gen)
+    ctx = torch.tensor([32 * t for t in tiles], dtype=torch.int32, device="cuda")
+    p = binding.attn_params(q, k, v, table, D ** -0.5)
+    ws = torch.zeros(binding.seer_verify_attention_workspace(p), dtype=torch.uint8, device="cuda")
+    own, reused = (binding.seer_verify_attention(q, k, v, table, ctx, None, D ** -0.5, workspace=ws, flags=flags).view(torch.int16).clone()
+                   for flags in (binding.SEER_ATTN_FIXED_SPLIT, binding.SEER_ATTN_FIXED_SPLIT | binding.SEER_ATTN_REUSE_PLAN))
+    assert torch.equal(own, reused)
