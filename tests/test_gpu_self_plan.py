@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 import torch
 
+from gpu_util import ATOL, RTOL
 from paper_2511_14617_amd import workloads as W
 from paper_2511_14617_amd.device_inputs import attention_device_inputs
 
@@ -43,11 +44,12 @@ def test_tables_equal_the_plan_kernels(heads, B, hi, max_splits):
     # the same cut, planned by either kernel: the same sums in the same order
     for ws in (one, other):
         assert torch.equal(call(ws, fixed | binding.SEER_ATTN_REUSE_PLAN).view(torch.int16), own.view(torch.int16))
-    # lengths that change from call to call, with the speeds of the calls before
+    # lengths that change from call to call on one workspace (lines too short to follow the speeds: test_gpu_speed_history.py has others);
+    # either call is within the bar of the oracle, so they are within twice the bar of one another
     for k in range(3):
         d["ctx_len"].copy_(torch.from_numpy(np.roll(inp.ctx_len, k)).cuda().clamp_(max=int(inp.ctx_len.min()) if k == 2 else 1 << 30))
-        call(one, 0)
-        torch.cuda.synchronize()
+        out, want = call(one, 0).double(), call(torch.zeros_like(one), fixed | binding.SEER_ATTN_GENERAL_KERNEL).double()
+        assert bool(((out - want).abs() <= 2 * (ATOL + RTOL * want.abs())).all())
         assert binding.seer_verify_attention_status(one) == (1 if B > 2 else 0)
 
 

@@ -123,3 +123,30 @@ def test_the_second_call_follows_the_speeds_of_the_first(shape, B, first_bytes):
     most.call(less, ws)
     assert not equal(stretches(ws, most.params(less)))
     assert_cut(ws, most.params(less), most.lengths[:less])
+
+
+@pytest.mark.parametrize("shape,B", [("one_wave", 64), ("four_waves", 40), ("pairs", 40), ("head64", 64)])
+def test_both_kinds_of_plan_cut_alike_by_the_same_speeds(shape, B):
+    """On copies of a workspace with a history, a batch with unusable lengths in it: once the partition kernel plans for itself,
+    once the plan kernel plans (it does for the general kernel).  The same stretches, and the same bits from calls that reuse them."""
+    from paper_2511_14617_amd import binding
+    Hq, Hkv, D, T, tokens = SHAPES[shape]
+    most = Batch(B, Hq, Hkv, D, T, tokens)
+    p, ref = most.params(B), most.reference()
+    bad = [1, B // 2, B // 2 + 1, B - 1]
+    most.lengths[bad] = T - 1
+    most.ctx[bad] = T - 1
+    ref[bad] = 0.0
+    one = workspace(p)
+    for k in range(3):
+        assert_attention_close(most.call(B, one), ref, "%s, call %d" % (shape, k))
+        other = one.clone()
+        assert_attention_close(most.call(B, one), ref, "%s, its own plan" % shape)
+        most.call(B, other, binding.SEER_ATTN_GENERAL_KERNEL)
+        cut = stretches(one, p)
+        assert np.array_equal(cut, stretches(other, p))
+        lengths = np.where(most.lengths < T, 0, most.lengths)
+        assert_cut(one, p, lengths)
+        assert not (np.diff(cut[:-1, 0]) == cut[0, 1]).all()
+        a, b = (most.call(B, ws, binding.SEER_ATTN_REUSE_PLAN).view(torch.int16).clone() for ws in (one, other))
+        assert torch.equal(a, b)
