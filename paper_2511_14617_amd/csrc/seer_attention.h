@@ -69,9 +69,9 @@ struct ReqSlots {
 };
 
 // Up to this many requests the tiled kernels plan for themselves (seer_plan.h):
-// one per lane of a wave.  Whole call with the plan kernel | without: 4 requests of 64 .. 512 tokens 16.9 | 13.8 us, 16 requests with heads of
-// 64 32.1 | 27.4, of 256 39.6 | 35.5, 64 requests on one KV head 57.4 | 53.8, on eight 236.9 | 232.5; shared
-// latent, two requests, 33.7 | 30.0.  (Not all of the plan kernel's 5.5 us:
+// one per lane of a wave.  Whole call with the plan kernel | without: 4 requests of 64 .. 512 tokens 16.9 | 14.1 us, 16 requests with heads of
+// 64 31.9 | 27.6, of 256 40.0 | 36.0, 64 requests on one KV head 57.1 | 53.5, on eight 237.3 | 233.3; shared
+// latent, two requests, 33.7 | 30.0.  (0.2 .. 0.5 us of the second figures is the look at the whole history, share_ok.)  (Not all of the plan kernel's 5.5 us:
 // the partition kernel begins 1.8 us later, most of it the fetch of the additional code.)
 constexpr int kSelfPlanRequests = 64;
 
