@@ -90,7 +90,8 @@ typedef struct seer_attn_params {
 /* flags: use the plan that the previous call on this workspace computed instead of planning again.  How the
  * KV stream is cut depends on the shape parameters and on ctx_len only, and a model calls this function
  * once per layer with the same ctx_len: the first layer plans, the others pass this flag (saves a ~5 us
- * kernel and its launch per call, or 2 us of it in batches of up to 64 requests).  The caller guarantees that the previous call on this workspace had the same
+ * kernel and its launch per call, or 2 us of it in batches of up to 64 requests; calls on short block tables,
+ * which take whole requests, need no plan, and only look whether there is one).  The caller guarantees that the previous call on this workspace had the same
  * parameters (flags apart) and that ctx_len and block_table are unchanged; if not, the output is
  * undefined (every access still stays in bounds; a workspace without a plan for this B and split leaves
  * `out` as it is).  The status word then accumulates over the calls. */
@@ -147,8 +148,9 @@ SEER_API int seer_verify_attention(void* out, const void* q, const void* k_pages
                           size_t workspace_bytes, void* hip_stream);
 
 /* Name of the partition kernel (the kernel that streams the KV pages) a call with these params launches,
- * e.g. "attn_gqa128_kernel<2,1>" (waves per workgroup, tiles in flight); NULL on invalid params.
- * Static text, host-only. */
+ * e.g. "attn_gqa128_kernel<2,1>" (waves per workgroup, tiles in flight); NULL on invalid params.  Where the
+ * block table holds short contexts only and the call takes whole requests instead, the name goes on with
+ * "; takes whole requests: " and that kernel's.  Static text, host-only. */
 SEER_API const char* seer_verify_attention_kernel(const seer_attn_params* p);
 
 /* Bytes of device scratch seer_accept needs; 0 on invalid sizes.  Host-only. */

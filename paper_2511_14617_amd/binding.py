@@ -153,7 +153,8 @@ def seer_verify_attention_workspace(params: SeerAttnParams) -> int:
 
 
 def seer_verify_attention_kernel(params: SeerAttnParams) -> Optional[str]:
-    """Name of the partition kernel a call with these params launches (None on invalid params)."""
+    """Name of the partition kernel a call with these params launches, and of the kernel that takes whole requests where it does
+    (None on invalid params)."""
     name = load_library().seer_verify_attention_kernel(ctypes.byref(params))
     return None if name is None else name.decode()
 

@@ -154,6 +154,18 @@ inline int tile_rows_per_block(int rows, int Dqk) {
     return ((rows + nb - 1) / nb + 31) / 32 * 32;
 }
 
+// Requests taken whole, one workgroup per 32 query rows of a KV head (seer_attention_short.hip): the waves of such a workgroup, and
+// whether a call is one.  The block table's width is what the host knows of the lengths.
+constexpr int kShortTilesPerWave = 16;
+constexpr int kShortTableEntries = 16384;      // page ids that one workgroup looks through for the status word
+inline int short_tiles(const seer_attn_params& p) {
+    const long long t = (static_cast<long long>(p.max_pages_per_seq) * p.page_size + 31) / 32;
+    return t > 1 << 20 ? 1 << 20 : static_cast<int>(t);
+}
+inline int short_waves(const seer_attn_params& p) { return p.Dqk == 256 || short_tiles(p) <= 4 ? 4 : (p.Dqk == 192 ? 7 : 8); }
+inline int short_tiles_per_wave(const seer_attn_params& p) { return (short_tiles(p) + short_waves(p) - 1) / short_waves(p); }
+bool short_call(const seer_attn_params& p);
+
 // Workgroups of the partition kernel that one CU holds at once, by kernel shape.
 inline int resident_wgs_per_cu(const seer_attn_params& p) {
     if (tile_layout(p)) {
@@ -245,6 +257,8 @@ struct AttnArgs {
     int32_t balanced;           // 0: one workgroup per request (max_splits == 1), slot = request, no history either
     int32_t min_tiles;          // tiles of a stretch, at least (see kMinTiles)
     int32_t fine_pieces;        // with more pieces than this in stretches of two or three tiles: four tiles (see kFinePartialsBelow)
+    int32_t short_waves, short_tiles_per_wave;   // requests taken whole: waves of a workgroup, tiles of a wave at most
+    uint32_t inv_pages;         // reciprocal() of max_pages
     int32_t stream_only;        // 1: the tiled D = 128 kernel only streams its tiles (diagnostic)
     int32_t stream_partials;    // 1: the tiled D = 128 kernel writes its partial results with non-temporal stores
     int32_t row_blocks, rows_per_block;   // tiled kernels: workgroups per (stretch, KV head); rows of each (D = 128 and the other head sizes)
@@ -278,6 +292,7 @@ bool gqa128_supports(const AttnArgs& a);                            // D = 128, 
 hipError_t launch_gqa128(const AttnArgs& a, hipStream_t stream);
 bool mla_supports(const AttnArgs& a);                               // shared latent 576/512, pages of 32..1024 tokens
 hipError_t launch_mla(const AttnArgs& a, hipStream_t stream);
+hipError_t launch_short(const AttnArgs& a, hipStream_t stream);     // calls of short_call
 hipError_t launch_tile(const AttnArgs& a, hipStream_t stream);      // shapes of tile_supports
 
 }  // namespace seer

@@ -14,7 +14,7 @@
 #include <stdio.h>
 
 #include "seer_device.h"
-#include "seer_plan.h"
+#include "seer_plan_tables.h"
 
 namespace seer {
 
@@ -32,204 +32,33 @@ namespace seer {
 // walks it took 8.6 .. 12.5 us of every call; 4.9 with 75 to 110 requests (5.6 while it also smoothed the speeds).
 // ---------------------------------------------------------------------------
 constexpr int kPlanThreads = 1024;
-constexpr int kPlanWaves = kPlanThreads / kWave;
-constexpr int kPlanLdsRequests = 4096;   // tile offsets of this many requests are searched in LDS, of more in global memory
-
-// The plan's second workgroup.  Leading pages that a request has in common with the request before or after it
-// (the prompt that the rollouts of a group share sits in the same physical pages): the partition kernel loads such
-// tiles with the cache policy that keeps them, so that the repeats are served by the memory-side cache.  This is a
-// hint only, results do not depend on it, so the length of the common run is found by probing instead of comparing
-// every entry: sixteen entries at doubling distances, then sixteen evenly spaced ones between the last equal probe
-// and the first unequal one (two dependent rounds of loads; exact for runs of up to 32 pages, else short by less
-// than a sixteenth of the run if the tables are equal up to a point and differ behind it).  It runs beside the
-// first workgroup, which needs about as long for the tile line and the stretches.  (Spread over workgroups of eight requests
-// the plan kernel takes longer, calls of 75 to 110 requests 1.8 .. 2.7 us: workgroups of sixteen waves are slow to start.)
-__device__ __forceinline__ void plan_shared_pages(const AttnArgs& p, int b_begin, int b_end, int threads) {
-    for (int b = b_begin + static_cast<int>(threadIdx.x); b < b_end; b += threads) {
-        const int n = p.ctx_len[b];
-        int best = 0;
-        if (n >= p.T && n <= p.max_ctx) {
-            const int32_t* mine = p.block_table + static_cast<size_t>(b) * p.max_pages;
-            const int pages = (n + p.P - 1) / p.P;
-            int m[2] = {0, 0};                 // entries that can be compared with the neighbour
-            const int32_t* other[2] = {mine, mine};
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                const int nb = s ? b + 1 : b - 1;
-                if (nb < 0 || nb >= p.B) continue;
-                const int nn = p.ctx_len[nb];
-                if (nn < p.T || nn > p.max_ctx) continue;
-                m[s] = min(pages, (nn + p.P - 1) / p.P);
-                other[s] = p.block_table + static_cast<size_t>(nb) * p.max_pages;
-            }
-            uint32_t eq[2] = {0u, 0u};        // bit k: probe k found equal entries
-#pragma unroll
-            for (int s = 0; s < 2; ++s)
-#pragma unroll
-                for (int k = 0; k < 16; ++k) {
-                    const int i = (1 << k) - 1;
-                    const int ic = min(i, max(m[s] - 1, 0));
-                    eq[s] |= static_cast<uint32_t>((i < m[s]) & (mine[ic] == other[s][ic])) << k;
-                }
-            int lo[2], step[2], hi[2];
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                const int k = __builtin_ctz(~eq[s]);          // first probe that differs or lies outside (<= 16)
-                lo[s] = k ? (1 << (k - 1)) : 0;               // number of leading entries taken as equal
-                hi[s] = k ? min((1 << k) - 1, m[s]) : 0;      // entry hi differs or does not exist
-                step[s] = max(1, (hi[s] - lo[s] + 15) / 16);
-                eq[s] = 0u;
-            }
-#pragma unroll
-            for (int s = 0; s < 2; ++s)
-#pragma unroll
-                for (int j = 0; j < 16; ++j) {
-                    const int i = lo[s] + (j + 1) * step[s] - 1;
-                    const int ic = min(i, max(m[s] - 1, 0));
-                    eq[s] |= static_cast<uint32_t>((i < hi[s]) & (mine[ic] == other[s][ic])) << j;
-                }
-#pragma unroll
-            for (int s = 0; s < 2; ++s) best = max(best, min(lo[s] + __builtin_ctz(~eq[s]) * step[s], hi[s]));
-        }
-        const_cast<int32_t*>(p.shared_tiles)[b] = static_cast<int>(static_cast<long long>(best) * p.P / kPlanTile);
-    }
-}
 
 __global__ __launch_bounds__(kPlanThreads) void plan_kernel(AttnArgs p) {
-    if (blockIdx.x == 1) {
-        plan_shared_pages(p, 0, p.B, kPlanThreads);
-        return;
-    }
-    __shared__ int s_tiles[kPlanWaves], s_longest[kPlanWaves];       // per wave
-    __shared__ int s_start[kMaxWgsPerHead + 1];
-    __shared__ int s_off[kPlanLdsRequests + 1];
-    int32_t* const tile_off = const_cast<int32_t*>(p.tile_off);
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int W = p.wgs_per_head;
-    const bool balanced = p.balanced != 0, history = balanced && !p.fixed_split;
-    const bool in_lds = p.B <= kPlanLdsRequests;
+    __shared__ PlanLds<kPlanThreads> lds;
+    if (blockIdx.x == 1) plan_shared_pages(p, 0, p.B, kPlanThreads);
+    else plan_tables<kPlanThreads>(p, lds);
+}
 
-    // ---- everything this thread reads from global memory: its run of requests (one each up to 1024), its stretch -----
-    const int per = (p.B + kPlanThreads - 1) / kPlanThreads;
-    const int b0 = min(p.B, tid * per), b1 = min(p.B, b0 + per);
-    const int n_first = b0 < b1 ? p.ctx_len[b0] : 0;
-    uint32_t before = equal_before(p, tid), recorded = 0u;
-    bool marked = true, usable = false;                  // is there a history; can it be used, as far as this thread's stretch goes
-    if (history) {
-        const uint32_t magic = p.header->fb_magic;
-        const int w = p.header->fb_w;
-        recorded = p.fb_before[min(tid, W)];
-        const uint32_t behind = p.fb_before[min(tid, W) + 1];
-        marked = magic == kFeedbackMagic && w == W;
-        usable = marked && share_ok(p, tid, recorded, behind);
-    }
-    // a new one begins with this call's measurements
-    if (!marked && tid < W) p.fb_time[tid] = 0u, p.fb_tiles[tid] = 0u, p.fb_speed[tid] = 0.f;
-    auto tiles = [&](int n) -> int { return tiles_of(n, p.T, p.max_ctx); };
-    auto length = [&](int b) -> int { return b == b0 ? n_first : p.ctx_len[b]; };
-
-    // ---- sums inside the wave: tiles of its requests --------------------------------------------------------------------
-    int cnt = 0, mx = 0;
-    bool bad = false;
-    for (int b = b0; b < b1; ++b) {
-        const int n = length(b), t = tiles(n);
-        bad |= n < p.T || n > p.max_ctx;                 // flagged, gets a zero output
-        cnt += t;
-        mx = max(mx, t);
-    }
-    const int incl = wave_incl_scan(cnt);
-    const int wave_bad = __any(bad) ? 1 : 0;
-    const bool wave_usable = __all(usable);
-    mx = wave_max_in_last_lane(mx);
-    if (lane == kWave - 1) {
-        s_tiles[wave] = incl;
-        s_longest[wave] = mx * 4 + (wave_usable ? 2 : 0) + wave_bad;
-    }
-    __syncthreads();
-    int total = 0, my_off = incl - cnt, longest = 0;
-    int any_bad = 0, all_usable = 2;
-#pragma unroll
-    for (int w = 0; w < kPlanWaves; ++w) {
-        const int t = s_tiles[w], l = s_longest[w];
-        if (w < wave) my_off += t;
-        total += t;
-        longest = max(longest, l >> 2);
-        any_bad |= l & 1;
-        all_usable &= l & 2;
-    }
-    if (all_usable) before = recorded;
-    {
-        int off = my_off;
-        for (int b = b0; b < b1; ++b) {
-            tile_off[b] = off;
-            if (in_lds) s_off[b] = off;
-            off += tiles(length(b));
-        }
-        if (tid == 0) {
-            tile_off[p.B] = total;
-            if (in_lds) s_off[p.B] = total;
-        }
-    }
-
-    if (balanced) {
-        // ---- the stretches ----------------------------------------------------------------------------------------------
-        const Cut cut = cut_of(p, total, longest);
-        if (tid < W) s_start[tid] = cut_begin(cut, tid, before);
-        if (tid == 0) s_start[W] = total;
-    }
-    __syncthreads();
-
-    // ---- per stretch: where it starts ------------------------------------------------------------------------------------
-    for (int w = tid; w < W; w += kPlanThreads) {
-        StretchRec r;
-        auto off = [&](int b) -> int { return in_lds ? s_off[b] : tile_off[b]; };
-        if (balanced) {
-            r.tile_begin = s_start[w], r.tile_end = s_start[w + 1];
-            r.b = -1, r.req_begin = 0;
-            if (r.tile_begin < r.tile_end) {             // the last request that starts at or before the first tile
-                int lo = 0, hi = p.B - 1;
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (off(mid) <= r.tile_begin) lo = mid; else hi = mid - 1;
-                }
-                r.b = lo;
-                r.req_begin = off(lo);
-            }
-        } else {
-            r.tile_begin = off(w), r.tile_end = off(w + 1);
-            r.req_begin = r.tile_begin;
-            r.b = r.tile_begin < r.tile_end ? w : -1;
-        }
-        const_cast<StretchRec*>(p.stretch)[w] = r;
-    }
-    // ---- per request: its partial slots ----------------------------------------------------------------------------------
-    // stretch that holds tile x (x < total): the last one that starts at or before it
-    auto stretch_of = [&](int x) -> int {
-        int lo = 0, hi = W - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (s_start[mid] <= x) lo = mid; else hi = mid - 1;
-        }
-        return lo;
-    };
-    int lo = my_off;
-    for (int b = b0; b < b1; ++b) {
-        const int hi = lo + tiles(length(b));
-        ReqSlots s{0, -1};
-        if (hi > lo) {
-            const int first = balanced ? stretch_of(lo) : 0;
-            s.first = first + b;
-            s.last = (balanced ? stretch_of(hi - 1) : 0) + b;
-        }
-        const_cast<ReqSlots*>(p.req_slots)[b] = s;
-        lo = hi;
-    }
-    if (tid == 0) {
-        p.header->status = any_bad ? 1u : 0u;
-        p.header->plan_b = plan_b_word(p.B);
-        p.header->plan_w = plan_w_word(W, balanced);
-        if (!marked) p.header->fb_magic = kFeedbackMagic, p.header->fb_w = W;
-    }
+// Which calls take whole requests (seer_attention_short.hip).  Measured against the partition kernels over head sizes, tables of 64 .. 4096
+// tokens, 1 .. 128 requests, 1 .. 8 KV heads, 16 .. 96 rows (lengths from half the table on; whole calls, this kernel | the others):
+//   heads of 128 and 64: 8.0 .. 8.5 us | 14 .. 20 up to 512 tokens; a wave's further tiles cost 1.4 us each (heads of 64: 0.8), which many items
+//     hide and few do not, since the stretches of the others spread a long request over idle CUs: 2048 tokens, 8 items 18.9 | 14.8, 64 items
+//     21.9 | 27.8, 256 items 24.3 | 47.0; 4096 tokens, 64 items 36.6 | 33.6, 128 items 39.0 | 46.6.  Hence as many items as tiles beyond 1024
+//     tokens; and no more work than one round of workgroups or two takes: 256 tokens, 2048 items 64.8 | 63.6.
+//   192/128: 512 tokens, 8 items 15.0 | 15.4, 1024 tokens 64 items 23.4 | 26.2, 16 items 22.4 | 17.1, 64 tokens 1024 items 42.6 | 29.8.
+//   256 (four waves to 160 KB): 128 tokens 14.3 | 19.3; 512 tokens 96 items 28.4 | 34.3, 16 items 27.1 | 20.2; 384 items of 64 tokens 30.1 | 27.1.
+// More than 64 rows of heads of 128 share a tile's loads in the kernel of the longer contexts.
+bool short_call(const seer_attn_params& p) {
+    if (!(gqa_layout(p) || tile_layout(p)) || p.max_splits == 1 || (p.flags & (SEER_ATTN_GENERAL_KERNEL | SEER_ATTN_STREAM_ONLY))) return false;
+    const int rows = (p.Hq / p.Hkv) * p.T, tiles = short_tiles(p);
+    const long long items = static_cast<long long>(p.B) * p.Hkv * ((rows + 31) / 32);
+    if (rows > (p.Dqk == 128 ? 64 : 128) || short_tiles_per_wave(p) > kShortTilesPerWave ||
+        static_cast<long long>(p.B) * p.max_pages_per_seq > kShortTableEntries)
+        return false;
+    const int any = p.Dqk == 256 ? 4 : (p.Dqk == 192 ? 8 : 32);                 // tiles of any number of items
+    const int per_tile = p.Dqk == 256 ? 6 : (p.Dqk == 192 ? 2 : 1);             // items per tile beyond
+    const int most = p.Dqk == 256 ? 256 : (p.Dqk == 192 ? 512 : 1024);
+    return (tiles <= any || items >= static_cast<long long>(per_tile) * tiles) && items <= most && items * tiles <= (p.Dqk > 128 ? 8192 : 12288);
 }
 
 hipError_t launch_plan(const AttnArgs& a, hipStream_t stream) {
@@ -667,18 +496,25 @@ extern "C" const char* seer_verify_attention_kernel(const seer_attn_params* p) {
     const bool tiled_ok = !(p->flags & SEER_ATTN_GENERAL_KERNEL);
     if (tiled_ok && seer::gqa128_supports(a)) {
         struct Names {
-            char text[9][40];
+            char text[9][40], whole[3][80];
             Names() {
                 for (int nw = 1; nw <= 8; ++nw)
                     snprintf(text[nw], sizeof(text[nw]), "attn_gqa128_kernel<%d,%d>", nw, seer::gqa_pipe_depth(nw));
+                for (int nw = 1; nw <= 2; ++nw)                      // (no more than 64 rows)
+                    snprintf(whole[nw], sizeof(whole[nw]), "%s; takes whole requests: attn_short_kernel<128,128>", text[nw]);
             }
         };
         static const Names names;
         const int rows = (p->Hq / p->Hkv) * p->T;
         if (seer::gqa_block_uses_helpers(seer::gqa_rows_per_block(rows))) return "attn_gqa128_kernel<4,2,helpers=4>";
-        return names.text[seer::gqa_rows_per_block(rows) / 32];
+        const int waves = seer::gqa_rows_per_block(rows) / 32;
+        return seer::short_call(*p) ? names.whole[waves] : names.text[waves];
     }
     if (tiled_ok && seer::mla_supports(a)) return "attn_mla_kernel";
+    if (seer::short_call(*p))
+        return p->Dqk == 64 ? "attn_tile_kernel<64,64>; takes whole requests: attn_short_kernel<64,64>"
+             : p->Dqk == 256 ? "attn_tile_kernel<256,256>; takes whole requests: attn_short_kernel<256,256>"
+                             : "attn_tile_kernel<192,128>; takes whole requests: attn_short_kernel<192,128>";
     if (seer::tile_supports(*p))
         return p->Dqk == 64 ? "attn_tile_kernel<64,64>" : p->Dqk == 256 ? "attn_tile_kernel<256,256>" : "attn_tile_kernel<192,128>";
     if (p->Dqk == 64) return "attn_general_kernel<64,64>";
@@ -763,6 +599,16 @@ int run_verify_attention(void* out, const void* q, const void* k_pages, const vo
     a.fine_pieces = seer::gqa_layout(*p) ? static_cast<int32_t>(seer::kFinePartialsBelow / (sizeof(float) * p->T * p->Hq * p->Dv)) : 1 << 28;
 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    if (seer::short_call(*p)) {
+        a.short_waves = seer::short_waves(*p), a.short_tiles_per_wave = seer::short_tiles_per_wave(*p);
+        a.inv_pages = seer::reciprocal(p->max_pages_per_seq);
+        a.self_plan = 0, a.fixed_split = 1;      // (no stretches are timed: the speed history stays as it is)
+        hipError_t err = hipSuccess;
+        if (ev_begin && (err = hipEventRecord(ev_begin, stream)) != hipSuccess) return static_cast<int>(err);
+        if ((err = seer::launch_short(a, stream)) != hipSuccess) return static_cast<int>(err);
+        if (ev_end && (err = hipEventRecord(ev_end, stream)) != hipSuccess) return static_cast<int>(err);
+        return SEER_OK;
+    }
     // the plan depends on the shape and on ctx_len only: the layers of one step can share it
     hipError_t err = a.reuse_plan || a.self_plan ? hipSuccess : seer::launch_plan(a, stream);
     if (err != hipSuccess) return static_cast<int>(err);

@@ -28,64 +28,6 @@
 #include "seer_tile.h"
 
 namespace seer {
-namespace tile {
-
-constexpr int kTile = kPlanTile;
-
-template <int DQK, int DV>
-struct Shape {
-    static constexpr int kKRow = DQK * 2, kVRow = DV * 2;                    // bytes of a token's row
-    static constexpr int kKBytes = kTile * kKRow, kVBytes = kTile * kVRow;
-    static constexpr int kStage = kKBytes + kVBytes;
-    static constexpr int kKSteps = DQK / 16, kDTiles = DV / 32;
-    static_assert(kKRow % 128 == 0 && kVRow % 128 == 0 && kKBytes % 1024 == 0 && kVBytes % 1024 == 0, "");
-    static_assert(kStage == tile_stage_kb(DQK, DV) * 1024, "the host sizes the launch with the same number");
-};
-
-// LDS swizzles: 16-byte chunk c of row r is stored at chunk position c ^ f(r) of the row.  64 banks of 4 bytes are 16
-// chunks.  K (ds_read_b128, 16 rows at one chunk per quarter-wave): rows of 256 or 512 bytes all start at bank 0 and take
-// four bits of the row; rows of 128 or 384 bytes alternate between two halves of the banks and take three.
-// V (transposing read, 4 rows x 64 bytes per half-wave): the four rows must fall into different 64-byte groups.
-template <int ROW_BYTES>
-__device__ __forceinline__ int k_swz(int row) { return ROW_BYTES % 256 == 0 ? row & 15 : (row >> 1) & 7; }
-template <int ROW_BYTES>
-__device__ __forceinline__ int v_swz(int row) { return ROW_BYTES % 256 == 0 ? (row & 3) << 2 : ((row >> 1) & 1) << 2; }
-
-__device__ __forceinline__ int lds_addr(const unsigned char* p) {
-    return static_cast<int>(reinterpret_cast<uintptr_t>((const SEER_AS3 void*)(p)));
-}
-
-// Operand reads and their wait in one block (through the builtins the compiler would put a vmcnt(0) in front of them: it
-// cannot tell them apart from the tile loads in flight).
-__device__ __forceinline__ void read_k4(u32x4 (&kv)[4], int a0, int a1, int a2, int a3) {
-    asm volatile("ds_read_b128 %0, %4\n"
-                 "ds_read_b128 %1, %5\n"
-                 "ds_read_b128 %2, %6\n"
-                 "ds_read_b128 %3, %7\n"
-                 "s_waitcnt lgkmcnt(0)"
-                 : "=&v"(kv[0]), "=&v"(kv[1]), "=&v"(kv[2]), "=&v"(kv[3])
-                 : "v"(a0), "v"(a1), "v"(a2), "v"(a3)
-                 : "memory");
-}
-// V^T operands of two d-tiles (lane addresses a0, a1) for the tile's 32 tokens: vr[tile][token rows 0, 8, 16, 24].
-template <int OFF, int ROW8>
-__device__ __forceinline__ void read_v2(u32x2 (&vr)[2][4], int a0, int a1) {
-    asm volatile("ds_read_b64_tr_b16 %0, %8 offset:%10\n"
-                 "ds_read_b64_tr_b16 %1, %8 offset:%11\n"
-                 "ds_read_b64_tr_b16 %2, %8 offset:%12\n"
-                 "ds_read_b64_tr_b16 %3, %8 offset:%13\n"
-                 "ds_read_b64_tr_b16 %4, %9 offset:%10\n"
-                 "ds_read_b64_tr_b16 %5, %9 offset:%11\n"
-                 "ds_read_b64_tr_b16 %6, %9 offset:%12\n"
-                 "ds_read_b64_tr_b16 %7, %9 offset:%13\n"
-                 "s_waitcnt lgkmcnt(0)"
-                 : "=&v"(vr[0][0]), "=&v"(vr[0][1]), "=&v"(vr[0][2]), "=&v"(vr[0][3]), "=&v"(vr[1][0]),
-                   "=&v"(vr[1][1]), "=&v"(vr[1][2]), "=&v"(vr[1][3])
-                 : "v"(a0), "v"(a1), "n"(OFF), "n"(OFF + ROW8), "n"(OFF + 2 * ROW8), "n"(OFF + 3 * ROW8)
-                 : "memory");
-}
-
-}  // namespace tile
 
 // One wave per 32 query rows.  Registers: 64-wide heads leave room for three waves per SIMD, (192, 128) for two; at D = 256
 // Q^T and O^T alone take 192, so one wave has a SIMD to itself (with 256 registers 40 of them would be spilled, and a
@@ -96,6 +38,7 @@ __global__ __launch_bounds__(tile_max_waves(DQK) * kWave) __attribute__((amdgpu_
 void attn_tile_kernel(AttnArgs a, int n_waves) {
     using namespace tile;
     using S = Shape<DQK, DV>;
+    static_assert(S::kStage == tile_stage_kb(DQK, DV) * 1024 && kTile == kPlanTile, "the host sizes the launch with the same numbers");
     // two stages of K tile, V tile; then two words: the scanned tile's tokens with infinities or NaN, "take the piece again"
     __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * S::kStage + 16];
     __shared__ int s_line[kLineWords];              // (see plan_stretch)
@@ -110,7 +53,7 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
     if (wg >= a.wgs_per_head) return;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const int ln = lane & 31, lg = lane >> 5, l16 = lane >> 4, p16 = lane & 15;
+    const int ln = lane & 31, lg = lane >> 5;
 
     StretchRec rec;
     bool new_history = false;
@@ -141,14 +84,7 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
     const int page_shift = __builtin_ctz(static_cast<unsigned>(a.P));
     auto page_of = [&](int tok) __attribute__((always_inline)) -> int { return page_pow2 ? tok >> page_shift : tok / a.P; };
 
-    // operand addresses inside a stage: K chunk 2 kk + lg of row ln, V as the transposing read wants it (lane 4k + c of a
-    // 16-lane group points at token row k, columns 4c .. 4c + 3 of the group's 16)
-    constexpr int kXorBits = S::kKRow % 256 == 0 ? 4 : 3;                      // chunk bits the K swizzle touches
-    constexpr int kPerXor = 1 << (kXorBits - 1);                              // contraction steps until those bits repeat
-    const int k_rd = ln * S::kKRow + ((lg ^ k_swz<S::kKRow>(ln)) << 4);       // step kk: ^ (kk % kPerXor) << 5, + whole periods
-    const int v_k = p16 >> 2, v_c4 = p16 & 3;
-    const int v_rd = S::kKBytes + (lg * 4 + v_k) * S::kVRow + ((((l16 & 1) * 2 + (v_c4 >> 1)) ^ v_swz<S::kVRow>(v_k)) << 4) +
-                     (v_c4 & 1) * 8;                                           // d-tile dt: ^ (dt % n) << 6, + whole periods
+    const Operands<DQK, DV> operands;
 
     // A piece's start needs the request's first and last tile and its length (lanes 0, 1, 2 of `words`) and its first window of
     // page ids.  They are requested together, for the first piece right behind the stretch's record and for each further
@@ -264,14 +200,7 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
             if (tid == 0) *s_nonfinite = 0;
             __builtin_amdgcn_s_waitcnt(0xc07f);
             bare_barrier();
-            uint32_t found = 0;
-            for (int c = tid; c < S::kVBytes / 16; c += n_waves * kWave) {
-                const int row = c / (S::kVRow / 16);
-                const u32x4 x = *reinterpret_cast<const u32x4*>(vl + c * 16);
-#pragma unroll
-                for (int w = 0; w < 4; ++w)
-                    if ((x[w] & 0x7f80u) == 0x7f80u || (x[w] & 0x7f800000u) == 0x7f800000u) found |= 1u << row;
-            }
+            uint32_t found = tile_nonfinite<DQK, DV>(vl, tid, n_waves * kWave);
             if (tb + kTile > n) found &= (1u << (n - tb)) - 1;
             if (found) atomicOr(const_cast<uint32_t*>(s_nonfinite), found);
             __builtin_amdgcn_s_waitcnt(0xc07f);
@@ -279,118 +208,30 @@ void attn_tile_kernel(AttnArgs a, int n_waves) {
             nonfinite = __builtin_amdgcn_readfirstlane(*s_nonfinite);
             const uint32_t cleared = nonfinite | (tb + kTile > n ? ~((1u << (n - tb)) - 1) : 0u);
             if (cleared) {
-                for (int c = tid; c < S::kVBytes / 16; c += n_waves * kWave)
-                    if ((cleared >> (c / (S::kVRow / 16))) & 1u) *reinterpret_cast<u32x4*>(vl + c * 16) = u32x4{0u, 0u, 0u, 0u};
+                tile_clear_rows<DQK, DV>(vl, cleared, tid, n_waves * kWave);
                 __builtin_amdgcn_s_waitcnt(0xc07f);
             }
             bare_barrier();
         }
 
-        // ---- scores: S^T[token][row] ----------------------------------------------------------
-        f32x16 s;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) s[i] = 0.f;
-        const int ka = lds0 + stage + k_rd;
-#pragma unroll
-        for (int h = 0; h < S::kKSteps; h += 4) {
-            u32x4 kv[4];
-            auto at = [&](int kk) { return (ka ^ ((kk % kPerXor) << 5)) + kk / kPerXor * (kPerXor * 32); };
-            read_k4(kv, at(h), at(h + 1), at(h + 2), at(h + 3));
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kv[kk]), qreg[h + kk], s, 0, 0, 0);
-        }
-        // ---- softmax: register i holds token (i/4)*8 + lg*4 + i%4 of the tile, for this lane's row -----
-        if (rel > -kTile) {
-            uint32_t vis = rel >= 0 ? static_cast<uint32_t>(word >> rel)
-                                    : (static_cast<uint32_t>(word << (-rel)) | ((1u << (-rel)) - 1u));
-            vis >>= lg * 4;
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                if (!((vis >> ((i >> 2) * 8 + (i & 3))) & 1u)) s[i] = kNegInf;
-        }
-        float mx = s[0];
-#pragma unroll
-        for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
+        // ---- scores, softmax with one query row per lane, O^T += V^T . P^T --------------------------------
+        f32x16 s = tile_scores<DQK, DV>(lds0 + stage, operands, qreg);
+        if (rel > -kTile) tile_mask(s, word, rel);
         float alpha;
-        const float m_use = move_reference(mx, a.scale_log2, m_run, alpha);
-        float psum = 0.f;
-        uint32_t term[3][8];                       // pairs of probabilities, each probability a sum of three bf16 terms
-#pragma unroll
-        for (int i = 0; i < 16; i += 2) {
-            s[i] = fast_exp2(fmaf(s[i], a.scale_log2, -m_use));
-            s[i + 1] = fast_exp2(fmaf(s[i + 1], a.scale_log2, -m_use));
-            psum += s[i] + s[i + 1];
-            float r0 = s[i], r1 = s[i + 1];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                term[k][i >> 1] = cvt_pk_bf16(r0, r1);
-                r0 -= bf16lo_to_f32(term[k][i >> 1]);          // (exact)
-                r1 -= bf16hi_to_f32(term[k][i >> 1]);
-            }
-        }
-        l_run = l_run * alpha + psum;
+        uint32_t term[3][8];
+        tile_softmax<3>(s, a.scale_log2, m_run, m_run, l_run, alpha, term);
         if (__any(alpha != 1.f)) {
 #pragma unroll
             for (int dt = 0; dt < S::kDTiles; ++dt)
 #pragma unroll
                 for (int i = 0; i < 16; ++i) acc[dt][i] *= alpha;
         }
-        // ---- O^T[d][row] += V^T . (sum of the terms) ----------------------------------------------
-        const int va = lds0 + stage + v_rd;
-        constexpr int kPer = S::kVRow % 256 == 0 ? 4 : 2;                      // d-tiles until the address bits repeat
-        auto pv_pair = [&](auto dtc) __attribute__((always_inline)) {
-            constexpr int dt = decltype(dtc)::value;
-            u32x2 vr[2][4];
-            read_v2<dt / kPer * (kPer * 64), 8 * S::kVRow>(vr, va ^ ((dt % kPer) << 6), va ^ (((dt + 1) % kPer) << 6));
-#pragma unroll
-            for (int half = 0; half < 2; ++half)
-#pragma unroll
-                for (int d2 = 0; d2 < 2; ++d2) {
-                    const bf16x8 v = as_bf16x8(u32x4{vr[d2][2 * half][0], vr[d2][2 * half][1], vr[d2][2 * half + 1][0], vr[d2][2 * half + 1][1]});
-#pragma unroll
-                    for (int k = 0; k < 3; ++k) {
-                        const bf16x8 pk = as_bf16x8(u32x4{term[k][4 * half], term[k][4 * half + 1], term[k][4 * half + 2], term[k][4 * half + 3]});
-                        acc[dt + d2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pk, acc[dt + d2], 0, 0, 0);
-                    }
-                }
-        };
-        pv_pair(std::integral_constant<int, 0>{});
-        if constexpr (S::kDTiles >= 4) pv_pair(std::integral_constant<int, 2>{});
-        if constexpr (S::kDTiles >= 8) {
-            pv_pair(std::integral_constant<int, 4>{});
-            pv_pair(std::integral_constant<int, 6>{});
-        }
-        // ---- V rows with infinities or NaN: added to the rows that see the slot ------------------
-        for (uint32_t left = nonfinite; left; left &= left - 1) {
-            const int j = __builtin_ctz(left), ij = (j >> 3) * 4 + (j & 3);
-            float pj = 0.f;
-#pragma unroll
-            for (int k = 2; k >= 0; --k) {
-                uint32_t pair = term[k][0];
-#pragma unroll
-                for (int i = 1; i < 8; ++i) pair = (ij >> 1) == i ? term[k][i] : pair;
-                pj += (ij & 1) ? bf16hi_to_f32(pair) : bf16lo_to_f32(pair);
-            }
-            pj = __shfl(pj, ln + ((j >> 2) & 1) * 32, kWave);                  // the half of the lanes that holds token j
-            const bool sees = rel + j < 0 || ((word >> (rel + j)) & 1ull);
+        tile_pv<DQK, DV, 3>(lds0 + stage, operands, term, acc);
+        tile_add_rows<3>(nonfinite, term, word, rel, acc, [&](int j) __attribute__((always_inline)) -> const uint16_t* {
             const int tok = tb + j, lp = page_of(tok);
             const int pg = min(max(table[min(lp, a.max_pages - 1)], 0), a.num_pages - 1);
-            const uint16_t* vrow = reinterpret_cast<const uint16_t*>(vbase) +
-                                   ((static_cast<size_t>(pg) * a.Hkv + kvh) * a.P + (tok - lp * a.P)) * DV;
-#pragma unroll
-            for (int dt = 0; dt < S::kDTiles; ++dt)
-#pragma unroll
-                for (int i4 = 0; i4 < 4; ++i4) {
-                    const u32x2 v = *reinterpret_cast<const u32x2*>(vrow + dt * 32 + i4 * 8 + lg * 4);
-                    if (sees) {
-                        acc[dt][i4 * 4] = fmaf(pj, bf16lo_to_f32(v[0]), acc[dt][i4 * 4]);
-                        acc[dt][i4 * 4 + 1] = fmaf(pj, bf16hi_to_f32(v[0]), acc[dt][i4 * 4 + 1]);
-                        acc[dt][i4 * 4 + 2] = fmaf(pj, bf16lo_to_f32(v[1]), acc[dt][i4 * 4 + 2]);
-                        acc[dt][i4 * 4 + 3] = fmaf(pj, bf16hi_to_f32(v[1]), acc[dt][i4 * 4 + 3]);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);   // (one load at a time: all of them in flight would spill)
-                }
-        }
+            return reinterpret_cast<const uint16_t*>(vbase) + ((static_cast<size_t>(pg) * a.Hkv + kvh) * a.P + (tok - lp * a.P)) * DV;
+        });
     }
 
     float sum0 = 0.f;                               // NaN iff some accumulator is infinite or NaN
