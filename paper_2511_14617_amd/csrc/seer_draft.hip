@@ -34,6 +34,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "../../include/seer_verify.h"
 
 namespace seer {
@@ -57,8 +59,6 @@ constexpr int kTile = 4 * kQuads * kMatchThreads;   // tokens a match workgroup 
 constexpr int kTokensPerPart = kTile;     // target length of a stretch: one round
 constexpr int kSmall = 2048;              // up to this many places the expansion holds in registers
 constexpr int kAhead = 8;                 // levels whose tokens it fetches at a time
-constexpr int kRankAll = 32;              // up to this many candidates of a level are ranked against each other
-constexpr int kSolo = 256;                // at most this many live places: one wave finishes the search alone
 
 // A place = (sequence inside the group, offset of the token that follows the occurrence); while the
 // match is still being searched it also carries the match length.
@@ -94,6 +94,9 @@ struct Args {
     float min_confidence;
 };
 
+// What is the same in all lanes, where the compiler cannot know (words in LDS): in a scalar register, so that loops and
+// branches on it are scalar ones.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ int lane_id() { return static_cast<int>(threadIdx.x) & 63; }
 
 // Index for each lane whose `hit` is set, from a counter in LDS: one atomic per wave instead of one per lane.
@@ -355,51 +358,111 @@ __global__ __launch_bounds__(kMatchThreads) void draft_match_kernel(Args a, int 
 // ------------------------------------------------------------------------------------------------
 // Expand: beam search over the continuations of the longest match.
 // ------------------------------------------------------------------------------------------------
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        const uint64_t w = __shfl_xor(v, o, 64);
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+    auto step = [&](auto ctrl) __attribute__((always_inline)) {
+        const uint32_t w = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), decltype(ctrl)::value, 0xf, 0xf, false));
         v = w > v ? w : v;
-    }
-    return v;
+    };
+    step(std::integral_constant<int, 0x111>{}), step(std::integral_constant<int, 0x112>{});     // row_shr 1, 2, 4, 8
+    step(std::integral_constant<int, 0x114>{}), step(std::integral_constant<int, 0x118>{});
+    step(std::integral_constant<int, 0x142>{}), step(std::integral_constant<int, 0x143>{});     // row_bcast 15, 31
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), 63));
+}
+__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
+    const uint32_t hi = wave_max_u32(static_cast<uint32_t>(v >> 32));
+    const uint32_t lo = wave_max_u32(static_cast<uint32_t>(v >> 32) == hi ? static_cast<uint32_t>(v) : 0u);
+    return (static_cast<uint64_t>(hi) << 32) | lo;
+}
+__device__ __forceinline__ uint64_t lane_value(uint64_t v, int lane) {
+    return (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v >> 32), lane))) << 32) |
+           static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), lane));
+}
+__device__ __forceinline__ int wave_sum(int v) {
+    auto step = [&](auto ctrl, auto rows) __attribute__((always_inline)) {
+        v += __builtin_amdgcn_update_dpp(0, v, decltype(ctrl)::value, decltype(rows)::value, 0xf, false);
+    };
+    using std::integral_constant;
+    step(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{}), step(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{}), step(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{}), step(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});
+    return __builtin_amdgcn_readlane(v, 63);
 }
 
 struct Member {            // one beam member of the current level
     int base, n, slot;     // its places are list[base .. base + n) while the places live in global memory
 };
 
+// ---- up to kSmall places: the tokens that follow them, as strings in LDS, kAhead levels at a time ----
+//
+// What bounds the search is the chain of LDS round trips (some 130 clocks each) and of issued instructions of the request
+// with the most places: an LDS atomic costs about a clock per lane, and an instruction of sixteen waves sixteen clocks.
+// So as few strings as can be go through as little as can be:
+//   - the levels on which all strings agree are settled at once;
+//   - more than kFew places are reduced to distinct strings first (a phrase that recurs a thousand times goes on in a
+//     few dozen ways);
+//   - while more than a wave's worth of strings is left, a level counts its (member, token) pairs in a hash table
+//     and the beam drops the strings nobody goes on with (most of them, where strings part); up to kFew strings are
+//     four waves' work, up to twice as many eight waves', and the waves without work end;
+//   - up to 64 strings, one per lane, are searched by one wave in registers: the lanes that show what the first one left
+//     shows are one pair, found and counted with one ballot.
+// The expansion of 128 requests with four paths of eight, in a call whose request with the most places has 1477: 46.9 us
+// when each level was counted by the whole workgroup behind six barriers (7 .. 12 thousand clocks a level with sixteen waves,
+// 2 .. 3 thousand for one wave with up to 256 places), 29 now; whole calls over 16 draws of the histories 67 .. 254 us, 48 .. 73 now.
+// Not kept: comparing all strings with each other (n^2 / 64 wave steps of some 60 instructions) and a trie of all
+// levels in one table (strings that the beam drops at the next level are entered all the way down).
+constexpr int kSlots = 4096;              // of the table of a level's pairs, at most
+constexpr int kFew = 512;
+constexpr int kFewThreads = 256;
+constexpr int kPer = kSmall / kThreads;   // strings per thread, at most
+// Distinct strings stay distinct only as far as they are known: they are for the last kAhead levels, and cost what two
+// or three levels of the table do (two levels, 1207 places with 691 strings: whole call 37.8 us with them, 36.0 without).
+constexpr int kDistinctLevels = 3;
+constexpr int kManyPlaces = 1 << 16;      // (numbers of places in 16 bits)
+// More than kSmall places are given up after the first kThreads if as many in proportion would be this many distinct ones
+// (later places repeat more; 2761 places with 2034 strings: whole call 155 us without the strings, 68 with; 3787 with 3058: 91, given up late 98).
+constexpr int kHopeless = kSmall * 3 / 2;
+constexpr int kRankWave = 16;             // candidates of a level that are ranked one by one
+constexpr int kPeel = 4;                  // pairs that one wave takes one by one before it looks for the rest by hash
+constexpr int kMeetLog2 = 9;              // words it uses for that
+constexpr int kListed = 4;                // pairs of a longer list per lane and round
+constexpr uint64_t kNoPair = ~0ull;       // an entry: strings << 48 | places << 32 | rank of the member << 24 | token
+static_assert((4 << kMeetLog2) <= 2 * kSmall, "words in the list");
+static_assert(kSlots >= 2 * kSmall && kFew <= kPer * kFewThreads, "strings per table and thread");
+
 // What the expansion keeps in LDS.
 struct Expand {
     GroupTable gt;
-    uint32_t key[kTableSlots];
-    uint32_t cnt[kTableSlots];
-    uint64_t cand[kSmall];                 // candidates of a level: count << 32 | ~key
+    union {
+        struct {                           // while the places live in global memory: the pairs of a level
+            uint32_t key[kTableSlots];
+            uint32_t cnt[kTableSlots];
+        };
+        __attribute__((aligned(16))) int row[kSmall][kAhead];    // strings, while they change threads
+        struct {                           // while distinct strings are found among more than kSmall places
+            __attribute__((aligned(16))) int fresh[kThreads][kAhead];
+            __attribute__((aligned(16))) int kept[kSmall][kAhead];
+        };
+        __attribute__((aligned(16))) uint64_t pair[2][kSlots];   // the pairs of a level, and the next level's cleared table
+    };
+    uint32_t distinct[2 * kSmall];         // while distinct strings are found
+    int8_t rank[2][kSlots];                // of a pair among the level's picks, -1 = not picked
+    uint16_t id[kSmall], weight[kSmall];   // of the strings that change threads: a place that shows it, how many do,
+    int8_t member[kSmall];                 //   and the rank of the member it belongs to
+    __attribute__((aligned(16))) uint16_t list[kSmall];          // entries of the level's pairs (in one wave's search, the words of its hash)
+    int lead[kAhead], lead_member;         // the string that the others are compared with
+    int n_list[2], n_held, n_left, n_on, common;
     uint32_t place[kSmall];                // hand-over of places between the phases
     int8_t owner[kSmall];                  // rank of the member a place belongs to, -1 = dropped
     int first[kMaxParts + 1];              // places of the longest match before part p
     Member mem[kMaxTopK], next[kMaxTopK];  // members while the places live in global memory
-    int mem_slot[2][kMaxTopK];             // members while the places live in registers: slot and ancestor mask,
-    uint64_t mem_msk[2][kMaxTopK];         //   level d - 1 in buffer (d - 1) & 1
     uint64_t red[kThreads / 64];
-    uint64_t best[kMaxTopK];
     int ref[kMaxTopK], ref_cnt[kMaxTopK];  // the token all places of a member show, and how many show it
     uint64_t pick[kMaxTopK];               // chosen children: count << 32 | ~key, best first
     int fill[kMaxTopK];
     int tok[SEER_MAX_T], par[SEER_MAX_T], num[SEER_MAX_T];
     uint64_t msk[SEER_MAX_T];
-    int n, best_len, nmem, overflow, n_cand;
+    int n, best_len, nmem, overflow;
 };
-
-// Workgroup barrier, or (SOLO: wave 0 works alone) only an ordering point for the wave's own LDS traffic.
-template <bool SOLO>
-__device__ __forceinline__ void level_sync() {
-    if (SOLO) {
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    } else {
-        __syncthreads();
-    }
-}
 
 // count[key] += n in the hash table (open addressing, linear probing).
 __device__ __forceinline__ void hash_add(Expand& x, int table, int shift, uint32_t key, uint32_t n) {
@@ -473,290 +536,541 @@ __device__ __forceinline__ void emit_nodes(Expand& x, int d, int top_k, int n_pi
     }
 }
 
-// One level for the places a thread holds in registers (own[u] = rank of the member the place belongs to
-// or -1, t[u] = the token the place shows at this level or -1).  Counting in the LDS hash table, then the
-// candidates (one per distinct (member, token) pair, held by the thread that entered the pair) are ranked:
-// against each other if they are few, else by top_k rounds of a maximum.  The thread that holds the pick
-// of rank j writes draft node j of the level.  Returns the number of picks; n_alive = places they own.
-template <bool SOLO, int PER>
-__device__ __forceinline__ int reg_level(const Args& a, Expand& x, int d, float threshold, int n_mem, int (&own)[PER],
-                                         const int (&t)[PER], int& n_alive, int& chain_slot, uint64_t& chain_mask) {
-    const int me = SOLO ? lane_id() : static_cast<int>(threadIdx.x), stride = SOLO ? 64 : kThreads;
-    const uint64_t below = (1ull << lane_id()) - 1;
-    uint32_t k[PER];
-    bool act[PER];
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        act[u] = own[u] >= 0 && t[u] >= 0;       // else the sequence ends here, or the token cannot be proposed
-        k[u] = (static_cast<uint32_t>(own[u]) << 24) | static_cast<uint32_t>(t[u]);
-    }
-    uint64_t v[PER];
-#pragma unroll
-    for (int u = 0; u < PER; ++u) v[u] = 0;
-    // Inside a phrase that recurs, all places of a member show the same token: then there is nothing to
-    // count pair by pair.
-    // One wave, one member: ballots settle it without touching LDS (chain_slot < 0: the member's slot and
-    // ancestor mask are not in registers yet).
-    if (SOLO && n_mem == 1) {
-        int count = 0, ref = -1;
-        bool have = false;
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const uint64_t m = __ballot(act[u]);
-            count += __popcll(m);
-            if (!have && m != 0) {
-                ref = __builtin_amdgcn_readlane(t[u], __builtin_amdgcn_readfirstlane(__ffsll(static_cast<long long>(m)) - 1));
-                have = true;
-            }
-        }
-        if (!have) return 0;                                         // no place goes on
-        bool differ = false;
-#pragma unroll
-        for (int u = 0; u < PER; ++u) differ = differ || __ballot(act[u] && t[u] != ref) != 0;
-        if (!differ) {
-            if (static_cast<float>(count) < threshold) return 0;
-            const int from = (d - 1) & 1, slot = 1 + (d - 1) * a.top_k;
-            if (chain_slot < 0) chain_slot = x.mem_slot[from][0], chain_mask = x.mem_msk[from][0];
-            const uint64_t m = (1ull << slot) | chain_mask;
-            if (me == 0) {
-                x.tok[slot] = ref, x.par[slot] = chain_slot, x.num[slot] = count, x.msk[slot] = m;
-                x.mem_slot[from ^ 1][0] = slot, x.mem_msk[from ^ 1][0] = m;
-            }
-            chain_slot = slot, chain_mask = m;
-#pragma unroll
-            for (int u = 0; u < PER; ++u) own[u] = act[u] ? 0 : -1;
-            n_alive = count;
-            return 1;
-        }
-    }
-    chain_slot = -1;
-    // The whole workgroup, one member: every place writes its token as the member's reference (any one
-    // wins), and if all places agree with it the member itself is the candidate.
-    bool unanimous = false;
-    if (!SOLO && n_mem == 1) {                   // (several members are rarely all of one mind: not tried)
-        if (me < kMaxTopK) x.ref_cnt[me] = 0;
-        if (me == 0) x.n_cand = 0;
-#pragma unroll
-        for (int u = 0; u < PER; ++u)
-            if (act[u]) x.ref[own[u]] = t[u];
-        __syncthreads();
-        bool agree = true;
-#pragma unroll
-        for (int u = 0; u < PER; ++u)
-            if (act[u]) agree = agree && t[u] == x.ref[own[u]];
-        unanimous = __syncthreads_and(agree ? 1 : 0) != 0;
-    }
-    if (unanimous) {
-        for (int r = 0; r < n_mem; ++r) {
-            int c = 0;
-#pragma unroll
-            for (int u = 0; u < PER; ++u) c += __popcll(__ballot(act[u] && own[u] == r));
-            if (lane_id() == 0 && c) atomicAdd(&x.ref_cnt[r], c);
-        }
-        __syncthreads();
-        if (me < n_mem) {
-            const uint32_t c = static_cast<uint32_t>(x.ref_cnt[me]);
-            if (c > 0 && static_cast<float>(c) >= threshold)
-                v[0] = (static_cast<uint64_t>(c) << 32) |
-                       static_cast<uint32_t>(~((static_cast<uint32_t>(me) << 24) | static_cast<uint32_t>(x.ref[me])));
-        }
-    } else {
-        int table = 64;
-        while (table < kTableSlots && table < 2 * n_alive) table <<= 1;      // at most n_alive distinct keys
-        const int shift = 32 - __builtin_ctz(static_cast<unsigned>(table));
-        for (int s = me; s < table; s += stride) x.key[s] = kEmpty, x.cnt[s] = 0;
-        if (me < kMaxTopK) x.best[me] = 0;
-        if (me == 0) x.n_cand = 0;
-        level_sync<SOLO>();
-        uint32_t h[PER], old[PER];
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            h[u] = (k[u] * 2654435761u) >> shift;
-            old[u] = kEmpty;
-            if (act[u]) old[u] = atomicCAS(&x.key[h[u]], kEmpty, k[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            if (!act[u]) continue;
-            for (int probes = 0; old[u] != kEmpty && old[u] != k[u] && probes < table; ++probes) {
-                h[u] = (h[u] + 1) & (table - 1);
-                old[u] = atomicCAS(&x.key[h[u]], kEmpty, k[u]);
-            }
-            atomicAdd(&x.cnt[h[u]], 1u);
-        }
-        level_sync<SOLO>();
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            if (act[u] && old[u] == kEmpty) {                       // this thread entered the pair: it speaks for it
-                const uint32_t c = x.cnt[h[u]];
-                if (static_cast<float>(c) >= threshold) v[u] = (static_cast<uint64_t>(c) << 32) | static_cast<uint32_t>(~k[u]);
-            }
-        }
-    }
-    int wave_total = 0;
-#pragma unroll
-    for (int u = 0; u < PER; ++u) wave_total += __popcll(__ballot(v[u] != 0));
-    int base = 0;
-    if (!SOLO) {
-        if (lane_id() == 0 && wave_total) base = atomicAdd(&x.n_cand, wave_total);
-        base = __builtin_amdgcn_readfirstlane(base);
-    }
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        const uint64_t mask = __ballot(v[u] != 0);
-        if (v[u] != 0) x.cand[base + __popcll(mask & below)] = v[u];
-        base += __popcll(mask);
-    }
-    level_sync<SOLO>();
-    const int n_cand = SOLO ? base : x.n_cand;
-    const int n_pick = min(n_cand, a.top_k);
-    if (n_pick == 0) return 0;
-    const int from = (d - 1) & 1;
-    auto emit = [&](int rank, uint64_t val) {
-        const uint32_t key = ~static_cast<uint32_t>(val);
-        const int r = static_cast<int>(key >> 24), slot = 1 + (d - 1) * a.top_k + rank;
-        const int parent = x.mem_slot[from][r];
-        const uint64_t m = (1ull << slot) | x.mem_msk[from][r];
-        x.tok[slot] = static_cast<int>(key & 0xffffffu);
-        x.par[slot] = parent;
-        x.num[slot] = static_cast<int>(val >> 32);
-        x.msk[slot] = m;
-        x.mem_slot[from ^ 1][rank] = slot;
-        x.mem_msk[from ^ 1][rank] = m;
-        x.pick[rank] = val;
-    };
-    if (n_cand <= kRankAll) {
-        // few candidates: every holder counts how many of the others beat its own (reads in batches that
-        // do not wait for each other; entries past n_cand are stale and masked)
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            if (v[u] == 0) continue;
-            int rank = 0;
-            for (int j0 = 0; j0 < n_cand; j0 += 8) {
-                uint64_t other[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) other[j] = x.cand[j0 + j];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) rank += (j0 + j < n_cand && other[j] > v[u]) ? 1 : 0;
-            }
-            if (rank < a.top_k) emit(rank, v[u]);
-        }
-    } else {
-        for (int round = 0; round < n_pick; ++round) {
-            uint64_t mine = 0;
-#pragma unroll
-            for (int u = 0; u < PER; ++u) mine = v[u] > mine ? v[u] : mine;
-            if (mine != 0) atomicMax(reinterpret_cast<unsigned long long*>(&x.best[round]), static_cast<unsigned long long>(mine));
-            level_sync<SOLO>();
-            const uint64_t win = x.best[round];
-#pragma unroll
-            for (int u = 0; u < PER; ++u)
-                if (v[u] == win && win != 0) {
-                    emit(round, win);
-                    v[u] = 0;
-                }
-        }
-    }
-    level_sync<SOLO>();
-    int alive = 0;
-    int now[PER];
-#pragma unroll
-    for (int u = 0; u < PER; ++u) now[u] = -1;
-    uint64_t picks[kMaxTopK];
-#pragma unroll
-    for (int j = 0; j < kMaxTopK; ++j) picks[j] = j < n_pick ? x.pick[j] : 0;
-#pragma unroll
-    for (int j = 0; j < kMaxTopK; ++j) {
-        if (j >= n_pick) continue;
-        alive += static_cast<int>(picks[j] >> 32);
-#pragma unroll
-        for (int u = 0; u < PER; ++u)
-            if (act[u] && k[u] == ~static_cast<uint32_t>(picks[j])) now[u] = j;
-    }
-#pragma unroll
-    for (int u = 0; u < PER; ++u) own[u] = now[u];
-    n_alive = alive;
-    return n_pick;
+// Slot of the member of this rank at the level before d (the root in front of the first level).
+__device__ __forceinline__ int member_slot(int d, int top_k, int rank) { return d == 1 ? 0 : 1 + (d - 2) * top_k + rank; }
+
+// Draft node of rank `rank` at level d, for the pick `val` (count << 32 | ~key).
+__device__ __forceinline__ void put_node(Expand& x, int d, int top_k, int rank, uint64_t val) {
+    const uint32_t key = ~static_cast<uint32_t>(val);
+    const int slot = 1 + (d - 1) * top_k + rank, parent = member_slot(d, top_k, static_cast<int>(key >> 24));
+    x.tok[slot] = static_cast<int>(key & 0xffffffu);
+    x.par[slot] = parent;
+    x.num[slot] = static_cast<int>(val >> 32);
+    x.msk[slot] = (1ull << slot) | x.msk[parent];
 }
 
-// Levels d .. levels with the places in registers, PER per thread, taken from x.place / x.owner.  The next
-// kAhead tokens of every place are fetched at once, so that most levels run without touching global memory.
-// !SOLO: the whole workgroup, until at most kSolo places are alive; then the live places go back to
-// x.place / x.owner.  SOLO: wave 0 alone, no workgroup barriers.  Returns the next level (levels + 1 = finished).
-template <bool SOLO, int PER>
-__device__ __forceinline__ int reg_levels(const Args& a, Expand& x, int d, int levels, float threshold, int& n_places,
-                                          int& n_alive, int& n_mem) {
-    const int me = SOLO ? lane_id() : static_cast<int>(threadIdx.x), stride = SOLO ? 64 : kThreads;
-    uint32_t place[PER];
-    int own[PER];
-    int chain_slot = -1;                       // one member: its slot and ancestor mask, once they are in registers
-    uint64_t chain_mask = 0;
+// What a thread holds: strings (their words still to be searched in front, -1 behind their end), a place that shows
+// each, how many do, and the rank of the member it belongs to (-1: nobody goes on with it).
+struct Held {
+    int t[kPer][kAhead], id[kPer], w[kPer], member[kPer];
+};
+
+// The words of a place's string from level d on, at most L; -1 behind its end, or if the place belongs to nobody.
+__device__ __forceinline__ void fetch_string(const Args& a, const Expand& x, uint32_t place, bool on, int d, int L, int (&t)[kAhead]) {
+    const int j = place_seq(place), off = place_off(place) + d - 1;
+    const int have = on ? min(x.gt.len[j] - off, L) : 0;
+    const int at = have > 0 ? x.gt.start[j] + off : 0;           // (loads from clamped addresses do not wait for each other)
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        const int i = me + u * stride;
-        own[u] = i < n_places ? x.owner[i] : -1;
-        place[u] = i < n_places ? x.place[i] : 0u;
+    for (int l = 0; l < kAhead; ++l) t[l] = a.tokens[at + min(l, max(have - 1, 0))];
+#pragma unroll
+    for (int l = 0; l < kAhead; ++l) {
+        on = on && l < have && t[l] >= 0 && t[l] < a.vocab;      // (a token that cannot be proposed ends the string)
+        t[l] = on ? t[l] : -1;
     }
-    while (d <= levels && (SOLO || n_alive > kSolo)) {
-        int cont[PER][kAhead];
+}
+__device__ __forceinline__ void put_string(int* row, const int (&t)[kAhead]) {
+    static_assert(kAhead == 8, "two 16-byte words");
+    *reinterpret_cast<int4*>(row) = make_int4(t[0], t[1], t[2], t[3]);
+    *reinterpret_cast<int4*>(row + 4) = make_int4(t[4], t[5], t[6], t[7]);
+}
+__device__ __forceinline__ void get_string(const int* row, int (&t)[kAhead]) {
+    const int4 lo = *reinterpret_cast<const int4*>(row), hi = *reinterpret_cast<const int4*>(row + 4);
+    t[0] = lo.x, t[1] = lo.y, t[2] = lo.z, t[3] = lo.w, t[4] = hi.x, t[5] = hi.y, t[6] = hi.z, t[7] = hi.w;
+}
+__device__ __forceinline__ bool same_string(const int* row, const int (&t)[kAhead]) {
+    int other[kAhead];
+    get_string(row, other);
+    bool same = true;
 #pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int j = place_seq(place[u]), off = place_off(place[u]) + d - 1;
-            const int have = own[u] >= 0 ? min(x.gt.len[j] - off, levels - d + 1) : 0;
-            const int32_t* src = a.tokens + x.gt.start[j] + off;
+    for (int l = 0; l < kAhead; ++l) same = same && other[l] == t[l];
+    return same;
+}
+__device__ __forceinline__ uint32_t hash_string(int member, const int (&t)[kAhead]) {
+    uint32_t f = static_cast<uint32_t>(member);
 #pragma unroll
-            for (int l = 0; l < kAhead; ++l) {
-                int t = -1;
-                if (l < have) t = src[l];
-                cont[u][l] = t >= a.vocab ? -1 : t;
-            }
+    for (int l = 0; l < kAhead; ++l) f = (f ^ static_cast<uint32_t>(t[l])) * 0x9e3779b1u, f ^= f >> 15;
+    return f * 2654435761u;
+}
+
+__device__ __forceinline__ void drop_word(Held& h) {
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+#pragma unroll
+        for (int l = 0; l + 1 < kAhead; ++l) h.t[u][l] = h.t[u][l + 1];
+        h.t[u][kAhead - 1] = -1;
+    }
+}
+
+// One string stays for all places that show the same, with their number as its weight.
+__device__ __forceinline__ void distinct_strings(Expand& x, Held& h, int n, int threads) {
+    const int tid = static_cast<int>(threadIdx.x);
+    // a slot of the table: the string that entered it, and 1 << 16 for every place that shows it
+    int table = 2 * kFew;
+    while (table < 2 * n) table <<= 1;
+    const int shift = 32 - __builtin_ctz(static_cast<unsigned>(table));
+    for (int i = tid; i < table; i += threads) x.distinct[i] = kEmpty;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u)
+        if (h.member[u] >= 0) {
+            put_string(x.row[tid + u * threads], h.t[u]);
+            x.member[tid + u * threads] = static_cast<int8_t>(h.member[u]);
         }
-        // One copy of the level's code, whatever the level: the fetched tokens are picked out of the registers
-        // by compares (unrolled eight times the code would not stay in the instruction cache).
-        bool done = false;
-#pragma nounroll
-        for (int l = 0; l < kAhead && !done && d <= levels && (SOLO || n_alive > kSolo); ++l) {
-            int t[PER];
+    __syncthreads();
+    uint32_t at[kPer], old[kPer];
 #pragma unroll
-            for (int u = 0; u < PER; ++u) {
-                t[u] = cont[u][0];
+    for (int u = 0; u < kPer; ++u) {
+        at[u] = hash_string(h.member[u], h.t[u]) >> shift;
+        old[u] = kEmpty;
+        if (h.member[u] >= 0) old[u] = atomicCAS(&x.distinct[at[u]], kEmpty, (1u << 16) | static_cast<uint32_t>(tid + u * threads));
+    }
+    bool own[kPer];
 #pragma unroll
-                for (int i = 1; i < kAhead; ++i) t[u] = l == i ? cont[u][i] : t[u];
+    for (int u = 0; u < kPer; ++u) {
+        own[u] = h.member[u] >= 0;
+        if (!own[u]) continue;
+        for (int probes = 0; old[u] != kEmpty && probes < table; ++probes) {
+            const int j = static_cast<int>(old[u] & 0xffffu);
+            if (x.member[j] == h.member[u] && same_string(x.row[j], h.t[u])) {
+                atomicAdd(&x.distinct[at[u]], 1u << 16);
+                own[u] = false;
+                break;
             }
-            const int n_pick = reg_level<SOLO, PER>(a, x, d, threshold, n_mem, own, t, n_alive, chain_slot, chain_mask);
-            if (n_pick == 0) {
-                done = true;
-                d = levels + 1;
-            } else {
-                n_mem = n_pick;
-                ++d;
-            }
+            at[u] = (at[u] + 1) & (table - 1);
+            old[u] = atomicCAS(&x.distinct[at[u]], kEmpty, (1u << 16) | static_cast<uint32_t>(tid + u * threads));
         }
     }
-    if (!SOLO && d <= levels) {
-        // the live places go to wave 0
-        if (threadIdx.x == 0) x.n = 0;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        if (own[u]) h.w[u] = static_cast<int>(x.distinct[at[u]] >> 16);
+        h.member[u] = own[u] ? h.member[u] : -1;
+    }
+}
+
+// Threads that n strings are for, of those that are left.
+__device__ __forceinline__ int threads_for(int n, int threads) {
+    return n <= 64 ? 64 : min(threads, n <= kFew ? kFewThreads : (n <= 2 * kFew ? 2 * kFewThreads : kThreads));
+}
+
+// The strings that are left move to the first threads; the waves without any end.  Returns their number.
+__device__ __forceinline__ int pack_strings(Expand& x, Held& h, int& threads) {
+    const int tid = static_cast<int>(threadIdx.x);
+    if (tid == 0) x.n_held = 0;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int at = wave_append(&x.n_held, h.member[u] >= 0);
+        if (h.member[u] >= 0) {
+            put_string(x.row[at], h.t[u]);
+            x.id[at] = static_cast<uint16_t>(h.id[u]), x.weight[at] = static_cast<uint16_t>(h.w[u]);
+            x.member[at] = static_cast<int8_t>(h.member[u]);
+        }
+    }
+    __syncthreads();
+    const int n = uniform(x.n_held);
+    threads = threads_for(n, threads);
+    if (tid >= threads) __builtin_amdgcn_endpgm();
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int at = tid + u * threads;
+        h.member[u] = -1;
+        if (at >= n) continue;
+        get_string(x.row[at], h.t[u]);
+        h.id[u] = x.id[at], h.w[u] = x.weight[at], h.member[u] = x.member[at];
+    }
+    __syncthreads();                                             // the tables lie where the strings were
+    return n;
+}
+
+// The distinct strings, of at most kAhead words, of the n places on a list in global memory, which belong to the root: in
+// the first threads, which alone go on.  Returns their number; -1, with all threads, if there are more than kSmall.
+__device__ __forceinline__ int distinct_listed(const Args& a, Expand& x, const uint32_t* list, int n, int L, Held& h, int& threads) {
+    const int tid = static_cast<int>(threadIdx.x);
+    constexpr int kTable = 2 * kSmall, kShift = 32 - __builtin_ctz(static_cast<unsigned>(kTable));
+    // a slot of the table: 1 << 16 for every place that shows the string, which is x.fresh[slot] of this round
+    // or x.kept[slot - kThreads] of an earlier one
+    for (int i = tid; i < kTable; i += kThreads) x.distinct[i] = kEmpty;
+    if (tid == 0) x.n_held = 0;
+    __syncthreads();                                             // (the last level's list is written)
+    for (int i0 = 0; i0 < n; i0 += kThreads) {
+        const uint32_t place = list[min(i0 + tid, n - 1)];
+        int t[kAhead];
+        fetch_string(a, x, place, i0 + tid < n, 1, L, t);
+        bool own = t[0] >= 0;
+        if (own) put_string(x.fresh[tid], t);
         __syncthreads();
-        int wave_total = 0;
-#pragma unroll
-        for (int u = 0; u < PER; ++u) wave_total += __popcll(__ballot(own[u] >= 0));
-        int base = 0;
-        if (lane_id() == 0 && wave_total) base = atomicAdd(&x.n, wave_total);
-        base = __builtin_amdgcn_readfirstlane(base);
-        const uint64_t below = (1ull << lane_id()) - 1;
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const uint64_t mask = __ballot(own[u] >= 0);
-            if (own[u] >= 0) {
-                const int at = base + __popcll(mask & below);
-                x.place[at] = place[u], x.owner[at] = static_cast<int8_t>(own[u]);
+        const int so_far = uniform(x.n_held);
+        if (so_far > kSmall || (i0 == kThreads && so_far * n > kThreads * kHopeless)) return -1;
+        uint32_t at = hash_string(0, t) >> kShift;
+        if (own) {
+            const uint32_t enter = (1u << 16) | static_cast<uint32_t>(tid);
+            uint32_t old = atomicCAS(&x.distinct[at], kEmpty, enter);
+            for (int probes = 0; old != kEmpty && probes < kTable; ++probes) {
+                const int j = static_cast<int>(old & 0xffffu);
+                if (same_string(j < kThreads ? x.fresh[j] : x.kept[j - kThreads], t)) {
+                    atomicAdd(&x.distinct[at], 1u << 16);
+                    own = false;
+                    break;
+                }
+                at = (at + 1) & (kTable - 1);
+                old = atomicCAS(&x.distinct[at], kEmpty, enter);
             }
-            base += __popcll(mask);
         }
         __syncthreads();
-        n_places = x.n;
+        const int k = wave_append(&x.n_held, own);
+        if (own && k < kSmall) {
+            put_string(x.kept[k], t);
+            x.list[k] = static_cast<uint16_t>(at);
+            x.distinct[at] += static_cast<uint32_t>(kThreads + k - tid);
+        }
     }
-    return d;
+    __syncthreads();
+    const int n_str = uniform(x.n_held);
+    if (n_str > kSmall) return -1;
+    threads = threads_for(n_str, threads);
+    if (tid >= threads) __builtin_amdgcn_endpgm();
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int e = tid + u * threads;
+        h.id[u] = e, h.w[u] = 0, h.member[u] = -1;
+        if (e >= n_str) continue;
+        get_string(x.kept[e], h.t[u]);
+        h.w[u] = static_cast<int>(x.distinct[x.list[e]] >> 16), h.member[u] = 0;
+    }
+    __syncthreads();                                             // the tables lie where the strings were
+    return n_str;
+}
+
+// `n` places show the pair: its entry, and whether it was new.
+__device__ __forceinline__ int enter_pair(uint64_t* table, int slots, uint32_t pair, int n, bool* entered) {
+    const uint64_t count = (1ull << 48) | (static_cast<uint64_t>(static_cast<uint32_t>(n)) << 32);
+    int at = static_cast<int>((pair * 2654435761u) >> (32 - __builtin_ctz(static_cast<unsigned>(slots))));
+    for (int probes = 0; probes < slots; ++probes) {             // (fewer pairs than slots: it always ends before)
+        uint64_t word = table[at];
+        if (word == kNoPair) {
+            word = atomicCAS(reinterpret_cast<unsigned long long*>(&table[at]), kNoPair, pair | count);
+            if (word == kNoPair) {
+                *entered = true;
+                break;
+            }
+        }
+        if (static_cast<uint32_t>(word) == pair) {
+            atomicAdd(reinterpret_cast<unsigned long long*>(&table[at]), count);
+            break;
+        }
+        at = (at + 1) & (slots - 1);
+    }
+    return at;
+}
+
+// One wave: ranks of the up to 64 candidates (one per lane, 0 = none; all differ), kMaxTopK or more for the others.
+__device__ __forceinline__ int rank_lanes(uint64_t v, uint64_t mask, int n_pick) {
+    const int n_cand = __popcll(mask);
+    int rank = v != 0 ? 0 : kMaxTopK;
+    if (n_cand <= kRankWave) {
+        if (n_cand > 1)
+            for (uint64_t left = mask; left != 0; left &= left - 1)
+                rank += lane_value(v, __ffsll(static_cast<long long>(left)) - 1) > v ? 1 : 0;
+    } else {
+        uint64_t rest = v;
+        rank = kMaxTopK;
+        for (int round = 0; round < n_pick; ++round) {
+            const uint64_t best = wave_max_u64(rest);
+            if (rest == best) rank = round, rest = 0;
+        }
+    }
+    return rank;
+}
+
+// An entry of the table as a candidate of the beam: count << 32 | ~pair, 0 if fewer than `least` places show it.
+__device__ __forceinline__ uint64_t candidate(uint64_t word, int least) {
+    const uint32_t count = static_cast<uint32_t>(word >> 32) & 0xffffu;
+    return static_cast<int>(count) >= least ? (static_cast<uint64_t>(count) << 32) | static_cast<uint32_t>(~static_cast<uint32_t>(word)) : 0;
+}
+
+// One wave: the picks of level d among the level's pairs become draft nodes.  Returns the strings that go on.
+__device__ __forceinline__ int pick_listed(const Args& a, Expand& x, int buf, int d, int least) {
+    const int lane = lane_id(), n_pairs = uniform(x.n_list[buf]);
+    if (n_pairs <= 64) {
+        const int at = lane < n_pairs ? x.list[lane] : 0;
+        const uint64_t word = x.pair[buf][at];
+        const uint64_t v = lane < n_pairs ? candidate(word, least) : 0;
+        const uint64_t mask = __ballot(v != 0);
+        const int n_pick = min(__popcll(mask), a.top_k), rank = rank_lanes(v, mask, n_pick);
+        if (rank < n_pick) {
+            x.rank[buf][at] = static_cast<int8_t>(rank);
+            put_node(x, d, a.top_k, rank, v);
+        }
+        return wave_sum(rank < n_pick ? static_cast<int>(word >> 48) : 0);
+    }
+    // a longer list: lane j keeps the j-th best so far
+    uint64_t kept = 0;
+    int kept_at = 0, n_cand = 0;
+    for (int i0 = 0; i0 < n_pairs; i0 += kListed * 64) {
+        uint64_t v[kListed + 1];
+        int at[kListed + 1];
+#pragma unroll
+        for (int u = 0; u < kListed; ++u) at[u] = x.list[min(i0 + u * 64 + lane, n_pairs - 1)];
+#pragma unroll
+        for (int u = 0; u < kListed; ++u) {
+            v[u] = candidate(x.pair[buf][at[u]], least);
+            if (i0 + u * 64 + lane >= n_pairs) v[u] = 0;
+            n_cand += __popcll(__ballot(v[u] != 0));
+        }
+        v[kListed] = kept, at[kListed] = kept_at;
+        kept = 0;
+        const int rounds = min(n_cand, a.top_k);
+        for (int round = 0; round < rounds; ++round) {
+            uint64_t best = 0;
+            int of = 0;
+#pragma unroll
+            for (int u = 0; u <= kListed; ++u)
+                if (v[u] > best) best = v[u], of = at[u];
+            const uint64_t top = wave_max_u64(best);
+            of = __builtin_amdgcn_readlane(of, __ffsll(static_cast<long long>(__ballot(best == top))) - 1);
+#pragma unroll
+            for (int u = 0; u <= kListed; ++u)
+                if (v[u] == top) v[u] = 0;
+            if (lane == round) kept = top, kept_at = of;
+        }
+    }
+    const int n_pick = min(n_cand, a.top_k);
+    if (lane < n_pick) {
+        x.rank[buf][kept_at] = static_cast<int8_t>(lane);
+        put_node(x, d, a.top_k, lane, kept);
+    }
+    return wave_sum(lane < n_pick ? static_cast<int>(x.pair[buf][kept_at] >> 48) : 0);
+}
+
+__device__ __forceinline__ void clear_pairs(Expand& x, int buf, int slots, int from, int step) {
+    for (int i = 2 * from; i < slots; i += 2 * step)
+        *reinterpret_cast<ulonglong2*>(&x.pair[buf][i]) = make_ulonglong2(kNoPair, kNoPair);
+    if (from == 0) x.n_list[buf] = 0;
+}
+
+// Levels from d on, over the first words of the n strings, until no more than `most` strings are left or `levels` levels are
+// done; n = strings left, 0 if the search has ended.  Returns the levels done.
+__device__ __forceinline__ int count_levels(const Args& a, Expand& x, Held& h, int d, int levels, int threads, int least,
+                                            int most, int& n) {
+    const int tid = static_cast<int>(threadIdx.x);
+    int slots = 256, done = 0, buf = 0;
+    while (slots < kSlots && slots < 4 * n) slots <<= 1;
+    clear_pairs(x, 0, slots, tid, threads);
+    __syncthreads();
+    for (; done < levels && n > most; ++done, ++d, buf ^= 1) {
+        int at[kPer];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const bool go = h.member[u] >= 0 && h.t[u][0] >= 0;
+            bool entered = false;
+            at[u] = -1;
+            if (go)
+                at[u] = enter_pair(x.pair[buf], slots, (static_cast<uint32_t>(h.member[u]) << 24) | static_cast<uint32_t>(h.t[u][0]), h.w[u], &entered);
+            const int to = wave_append(&x.n_list[buf], entered);
+            if (entered) x.list[to] = static_cast<uint16_t>(at[u]), x.rank[buf][at[u]] = -1;
+        }
+        drop_word(h);
+        __syncthreads();
+        if (tid < 64) {
+            const int left = pick_listed(a, x, buf, d, least);
+            if (tid == 0) x.n_left = left;
+        } else {
+            clear_pairs(x, buf ^ 1, slots, tid - 64, threads - 64);
+        }
+        __syncthreads();
+        n = uniform(x.n_left);
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) h.member[u] = at[u] >= 0 ? x.rank[buf][at[u]] : -1;
+    }
+    return done;
+}
+
+// One wave, one string per lane: `levels` levels from d on; false if the search has ended.
+__device__ __forceinline__ bool search_lanes(const Args& a, Expand& x, Held& h, int d, int levels, int least) {
+    const int lane = lane_id(), w = h.w[0], top_k = a.top_k;
+    const bool single = __ballot(h.member[0] >= 0 && w > 1) == 0;
+    int member = h.member[0];
+    // lane r: the ancestors of the member of rank r
+    uint64_t ancestors = x.msk[lane < top_k ? member_slot(d, top_k, lane) : 0];
+    for (int p = 0; p < levels; ++p, ++d) {
+        const int token = h.t[0][0], slot0 = 1 + (d - 1) * top_k;
+        drop_word(h);
+        const bool go = member >= 0 && token >= 0;
+        const uint32_t pair = (static_cast<uint32_t>(member) << 24) | static_cast<uint32_t>(token);
+        const uint64_t all = __ballot(go);
+        if (all == 0) return false;
+        int lead = __ffsll(static_cast<long long>(all)) - 1;
+        uint32_t shown = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(pair), lead));
+        uint64_t same = __ballot(go && pair == shown);
+        if (same == all) {
+            // all show the same: nothing to rank
+            const int count = single ? __popcll(all) : wave_sum(go ? w : 0);
+            if (count < least) return false;
+            const int r = static_cast<int>(shown >> 24);
+            ancestors = (1ull << slot0) | lane_value(ancestors, r);
+            if (lane == 0)
+                x.tok[slot0] = static_cast<int>(shown & 0xffffffu), x.par[slot0] = member_slot(d, top_k, r), x.num[slot0] = count, x.msk[slot0] = ancestors;
+            member = go ? 0 : -1;
+            continue;
+        }
+        int v_hi = 0, v_lo = 0;
+        uint64_t left = all;
+        const auto settle = [&]() __attribute__((always_inline)) {          // the lanes that show what `lead` shows
+            const int count = single ? __popcll(same) : wave_sum((same >> lane) & 1 ? w : 0);
+            left &= ~same;
+            const int hi = count >= least ? count : 0;
+            v_hi = lane == lead ? hi : v_hi, v_lo = lane == lead ? static_cast<int>(~shown) : v_lo;
+        };
+        settle();
+        int peeled = 1;
+        while (left != 0) {
+            if (peeled < kPeel) {
+                lead = __ffsll(static_cast<long long>(left)) - 1;
+                shown = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(pair), lead));
+                same = __ballot(pair == shown) & left;
+                settle();
+                ++peeled;
+                continue;
+            }
+            // Many pairs: a lane that hashes to the same word as others and finds its own pair there counts with the
+            // one that wrote it.  (The next round takes those whose word another pair took.)
+            const bool open = (left >> lane) & 1;
+            uint32_t* const word = reinterpret_cast<uint32_t*>(x.list) + ((pair * 2654435761u) >> (32 - kMeetLog2));
+            uint32_t* const met = x.distinct;
+            met[lane] = 0;
+            if (open) *word = static_cast<uint32_t>(lane);
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const int at = open ? static_cast<int>(*word) : lane;
+            const bool joins = static_cast<uint32_t>(__shfl(static_cast<int>(pair), at, 64)) == pair && open;
+            if (joins) atomicAdd(&met[at], static_cast<uint32_t>(w));
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const int count = static_cast<int>(met[lane]);
+            if (count > 0) v_hi = count >= least ? count : 0, v_lo = static_cast<int>(~pair);
+            left &= ~__ballot(joins);
+            peeled = 0;
+        }
+        const uint64_t v = v_hi > 0 ? (static_cast<uint64_t>(static_cast<uint32_t>(v_hi)) << 32) | static_cast<uint32_t>(v_lo) : 0;
+        const uint64_t mask = __ballot(v_hi > 0);
+        const int n_pick = min(__popcll(mask), top_k);
+        if (n_pick == 0) return false;
+        const int rank = rank_lanes(v, mask, n_pick);
+        int now = -1, tok = 0, par = 0, num = 0;
+        uint64_t msk = 0;
+        for (int r = 0; r < n_pick; ++r) {
+            const int of = __ffsll(static_cast<long long>(__ballot(rank == r))) - 1;
+            const uint64_t pick = lane_value(v, of);
+            shown = ~static_cast<uint32_t>(pick);
+            const int up = static_cast<int>(shown >> 24);
+            const uint64_t m = (1ull << (slot0 + r)) | lane_value(ancestors, up);
+            now = go && pair == shown ? r : now;
+            const bool here = lane == r;
+            tok = here ? static_cast<int>(shown & 0xffffffu) : tok, par = here ? member_slot(d, top_k, up) : par;
+            num = here ? static_cast<int>(pick >> 32) : num, msk = here ? m : msk;
+        }
+        member = now;
+        if (lane < n_pick) x.tok[slot0 + lane] = tok, x.par[slot0 + lane] = par, x.num[slot0 + lane] = num, x.msk[slot0 + lane] = msk;
+        ancestors = msk;
+    }
+    h.member[0] = member;
+    return true;
+}
+
+// L levels from level d on, over the first L words of the n_str strings that `threads` threads hold; threads that are no
+// longer needed end.  True if the search has ended.
+__device__ __forceinline__ bool search_strings(const Args& a, Expand& x, Held& h, int d, int L, int least, int n_str, int& threads) {
+    const int tid = static_cast<int>(threadIdx.x);
+    int lvl = 0;
+    bool ended = n_str == 0;
+    if (n_str > 64) {
+        // the levels on which all strings agree, for one member
+        if (tid == 0) {
+#pragma unroll
+            for (int l = 0; l < kAhead; ++l) x.lead[l] = h.t[0][l];
+            x.lead_member = h.member[0], x.common = L, x.n_on = 0;
+        }
+        __syncthreads();
+        const int member = uniform(x.lead_member);
+        int all = member >= 0 ? L : 0, n_on = 0;
+#pragma unroll
+        for (int l = kAhead - 1; l >= 0; --l) {
+            const int lead = x.lead[l];
+            bool parts = lead < 0;
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) parts = parts || (h.member[u] >= 0 && (h.member[u] != member || h.t[u][l] != lead));
+            if (l < all && __ballot(parts) != 0) all = l;
+        }
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) n_on += h.member[u] >= 0 ? h.w[u] : 0;
+        n_on = wave_sum(n_on);
+        if (lane_id() == 0) {
+            atomicMin(&x.common, all);
+            atomicAdd(&x.n_on, n_on);
+        }
+        __syncthreads();
+        lvl = uniform(x.common);
+        if (lvl > 0) {
+            const int count = uniform(x.n_on);
+            if (count < least) ended = true;
+            if (!ended && tid == 0)
+                for (int l = 0; l < lvl; ++l)
+                    put_node(x, d + l, a.top_k, 0,
+                             (static_cast<uint64_t>(static_cast<uint32_t>(count)) << 32) |
+                                 static_cast<uint32_t>(~((static_cast<uint32_t>(l == 0 ? member : 0) << 24) | static_cast<uint32_t>(x.lead[l]))));
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) h.member[u] = min(h.member[u], 0);
+            for (int l = 0; l < lvl; ++l) drop_word(h);
+        }
+        while (!ended && lvl < L && n_str > 64) {
+            lvl += count_levels(a, x, h, d + lvl, L - lvl, threads, least, threads > kFewThreads ? kPer / 2 * threads : 64, n_str);
+            ended = n_str == 0;
+            if (!ended && lvl < L) n_str = pack_strings(x, h, threads);
+        }
+    }
+    if (!ended && lvl < L) ended = !search_lanes(a, x, h, d + lvl, L - lvl, least);
+    return ended;
+}
+
+// Levels d .. levels over the n places in x.place / x.owner, by the whole workgroup.
+__device__ __forceinline__ void search_places(const Args& a, Expand& x, int d, int levels, int least, int n) {
+    const int tid = static_cast<int>(threadIdx.x);
+    int threads = kThreads;
+    while (d <= levels) {
+        threads = threads_for(n, threads);
+        if (tid >= threads) __builtin_amdgcn_endpgm();
+        const int L = min(levels - d + 1, kAhead);
+        Held h;
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int i = tid + u * threads;
+            const uint32_t place = i < n ? x.place[i] : 0u;
+            const int own = i < n ? x.owner[i] : -1;
+            fetch_string(a, x, place, own >= 0, d, L, h.t[u]);
+            h.id[u] = i, h.w[u] = 1, h.member[u] = h.t[u][0] >= 0 ? own : -1;
+        }
+        int n_str = n;
+        if (n > kFew && d + L > levels && L >= kDistinctLevels) {
+            distinct_strings(x, h, n, threads);
+            n_str = pack_strings(x, h, threads);
+        }
+        const bool ended = search_strings(a, x, h, d, L, least, n_str, threads);
+        d += L;
+        if (ended || d > levels) break;
+        // the places that go on, in front (each string is one place: distinct strings are for the last round)
+        uint32_t place[kPer];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) place[u] = h.member[u] >= 0 ? x.place[h.id[u]] : 0u;
+        if (tid == 0) x.n_held = 0;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int at = wave_append(&x.n_held, h.member[u] >= 0);
+            if (h.member[u] >= 0) x.place[at] = place[u], x.owner[at] = static_cast<int8_t>(h.member[u]);
+        }
+        __syncthreads();
+        n = uniform(x.n_held);
+    }
 }
 
 __global__ __launch_bounds__(kThreads) void draft_expand_kernel(Args a) {
@@ -851,8 +1165,19 @@ __global__ __launch_bounds__(kThreads) void draft_expand_kernel(Args a) {
     __syncthreads();
 
     int d = 1;
+    const int least = uniform(static_cast<int>(ceilf(threshold)));       // (counts are below 2^24: the same test)
+    bool done = false;
+    if (!handed_over && n_root > kSmall && n_root < kManyPlaces && levels >= kDistinctLevels && levels <= kAhead) {
+        Held h;
+        int threads = kThreads;
+        const int n_str = distinct_listed(a, x, cur, uniform(n_root), uniform(levels), h, threads);
+        if (n_str >= 0) {
+            search_strings(a, x, h, 1, uniform(levels), least, n_str, threads);
+            done = true;
+        }
+    }
     // ---- places in global memory: as long as a level holds more than kSmall places ----
-    for (; d <= levels && !handed_over; ++d) {
+    for (; d <= levels && !handed_over && !done; ++d) {
         const int nmem = x.nmem;
         const int n_level = x.mem[nmem - 1].base + x.mem[nmem - 1].n;
         if (n_level <= kSmall) {
@@ -1022,19 +1347,10 @@ __global__ __launch_bounds__(kThreads) void draft_expand_kernel(Args a) {
         __syncthreads();
     }
 
-    // ---- few enough places: they move into registers; the whole workgroup works while many are alive,
-    //      then wave 0 finishes alone without barriers ----
-    if (handed_over && d <= levels) {
-        int n_places = min(x.mem[x.nmem - 1].base + x.mem[x.nmem - 1].n, kSmall);
-        int n_alive = n_places;
-        if (tid < x.nmem) {
-            x.mem_slot[(d - 1) & 1][tid] = x.mem[tid].slot;
-            x.mem_msk[(d - 1) & 1][tid] = x.msk[x.mem[tid].slot];
-        }
-        __syncthreads();
-        int n_mem = x.nmem;
-        if (n_alive > kSolo) d = reg_levels<false, kSmall / kThreads>(a, x, d, levels, threshold, n_places, n_alive, n_mem);
-        if (d <= levels && tid < 64) reg_levels<true, kSolo / 64>(a, x, d, levels, threshold, n_places, n_alive, n_mem);
+    // ---- few enough places: a trie ----
+    if (handed_over && !done && d <= levels) {
+        const int n_places = min(x.mem[x.nmem - 1].base + x.mem[x.nmem - 1].n, kSmall);
+        search_places(a, x, uniform(d), uniform(levels), least, uniform(n_places));
     }
     __syncthreads();
 
