@@ -55,6 +55,7 @@ constexpr int kReqWindow = 64;            // request ids a match workgroup looks
 // length grows with the tokens a thread holds, and the launch has workgroups to spare (whole call, 16 requests of 6 k tokens
 // 44.5 us with four, 37.7 with two, 36.4 with one; 128 requests, four paths: 126, 121, 125).
 constexpr int kQuads = 2;
+constexpr int kSet = 64 / (4 * kQuads);   // requests whose candidate places a thread notes at a time, a bit each
 constexpr int kTile = 4 * kQuads * kMatchThreads;   // tokens a match workgroup takes per round
 constexpr int kTokensPerPart = kTile;     // target length of a stretch: one round
 constexpr int kSmall = 2048;              // up to this many places the expansion holds in registers
@@ -274,76 +275,70 @@ __global__ __launch_bounds__(kMatchThreads) void draft_match_kernel(Args a, int 
             int prev_quad[kQuads];
 #pragma unroll
             for (int u = 0; u < kQuads; ++u) prev_quad[u] = sh.tile[kMaxPattern + 4 * tid + u * 4 * kMatchThreads - 1];
-            int4 info = sh.info[0], older = sh.older[0];
-            for (int r = 0; r < n_req; ++r) {
-                // A place counts only if at least `need` pattern tokens end there: with need >= 2 the token
-                // before it is tested too, in registers, which leaves few places to look at closely.
-                // (The next request's constants are requested before this one's are used.)
-                const int newest = info.x, second = info.y, plen = info.z;
-                const int p2 = older.x, p3 = older.y, p4 = older.z, p5 = older.w;
-                info = sh.info[r + 1], older = sh.older[r + 1];
-                if (plen < need) continue;
-                // first only whether any lane holds a candidate at all: two compares per place
-                bool any = false;
+            // Requests go in sets of kSet: first, which of the thread's places end a match of at least `need` tokens for which
+            // request, a bit each, from registers; then every lane that has such places takes one of them per round,
+            // whatever its request (round after round per request, most of them with a lane or two, the scan took 13.1 us
+            // for 16 requests in two groups and 18.2 for 128 in sixteen; now 11.6 and 16.0).
+            int4 info = sh.info[0];
+            for (int r0 = 0; r0 < n_req; r0 += kSet) {
+                uint64_t hits = 0;
+#pragma nounroll
+                for (int k = 0; k < min(kSet, n_req - r0); ++k) {
+                    // A place counts only if at least `need` pattern tokens end there: with need >= 2 the token
+                    // before it is tested too, in registers, which leaves few places to look at closely.
+                    // (The next request's constants are requested before this one's are used.)
+                    const int newest = info.x, second = info.y, plen = info.z;
+                    info = sh.info[r0 + k + 1];
+                    if (plen < need) continue;
+                    // first only whether any lane holds a candidate at all: two compares per place
+                    bool any = false;
 #pragma unroll
-                for (int c = 0; c < 4 * kQuads; ++c) {
-                    const int prev = (c & 3) ? tok[c - 1] : prev_quad[c >> 2];
-                    any |= (tok[c] == newest) & (!two | (prev == second));
-                }
-                if (__ballot(any) == 0) continue;
-                uint32_t hits = 0;
+                    for (int c = 0; c < 4 * kQuads; ++c) {
+                        const int prev = (c & 3) ? tok[c - 1] : prev_quad[c >> 2];
+                        any |= (tok[c] == newest) & (!two | (prev == second));
+                    }
+                    if (__ballot(any) == 0) continue;
+                    uint32_t set = 0;
 #pragma unroll
-                for (int c = 0; c < 4 * kQuads; ++c) {
-                    const int prev = (c & 3) ? tok[c - 1] : prev_quad[c >> 2];
-                    bool h = tok[c] == newest && ((inside >> c) & 1u) != 0;
-                    if (two) h = h && prev == second && ((has_prev >> c) & 1u) != 0;
-                    hits |= static_cast<uint32_t>(h) << c;
+                    for (int c = 0; c < 4 * kQuads; ++c) {
+                        const int prev = (c & 3) ? tok[c - 1] : prev_quad[c >> 2];
+                        bool h = tok[c] == newest && ((inside >> c) & 1u) != 0;
+                        if (two) h = h && prev == second && ((has_prev >> c) & 1u) != 0;
+                        set |= static_cast<uint32_t>(h) << c;
+                    }
+                    hits |= static_cast<uint64_t>(set) << (k * 4 * kQuads);
                 }
-                if (__ballot(hits != 0) == 0) continue;
-                uint32_t* out = a.list_a + static_cast<size_t>(sh.req[r]) * a.cap + static_cast<size_t>(part) * a.chunk;
-                int best = sh.best[r];
-                // every lane that has candidate places takes one of them per round
                 while (__ballot(hits != 0) != 0) {
-                    int m = 0, seq_of = 0, off = 0;
-                    if (hits != 0) {
-                        const int c = __builtin_ctz(hits);
-                        hits &= hits - 1;
-                        const int p = t0 + 4 * tid + (c >> 2) * 4 * kMatchThreads + (c & 3);
-                        int j = sh.first_seq;                              // the sequence that holds place p
-                        while (p >= sh.gt.flat[j + 1]) ++j;
-                        seq_of = j, off = p - sh.gt.flat[j];
-                        const int limit = min(plen, off + 1);             // not past the start of the sequence
-                        const int* at = &sh.tile[kMaxPattern + (p - t0)];
-                        // the five tokens before the place are requested together and compared in registers;
-                        // only a longer match goes on through LDS
-                        const int v1 = at[-1], v2 = at[-2], v3 = at[-3], v4 = at[-4], v5 = at[-5];
-                        m = 1;
-                        if (1 < limit && v1 == second) {
-                            m = 2;
-                            if (2 < limit && v2 == p2) {
-                                m = 3;
-                                if (3 < limit && v3 == p3) {
-                                    m = 4;
-                                    if (4 < limit && v4 == p4) {
-                                        m = 5;
-                                        if (5 < limit && v5 == p5) {
-                                            m = 6;
-                                            while (m < limit && at[-m] == sh.pat[r][a.p_max - 1 - m]) ++m;
-                                        }
-                                    }
-                                }
-                            }
-                        }
-                    }
+                    if (hits == 0) continue;
+                    const int bit = __builtin_ctzll(hits);
+                    hits &= hits - 1;
+                    const int r = r0 + bit / (4 * kQuads), c = bit & (4 * kQuads - 1);
+                    const int p = t0 + 4 * tid + (c >> 2) * 4 * kMatchThreads + (c & 3);
+                    const int4 mine = sh.info[r];
+                    const int4 older = sh.older[r];
+                    const int best = sh.best[r];
+                    int j = sh.first_seq;                              // the sequence that holds place p
+                    while (p >= sh.gt.flat[j + 1]) ++j;
+                    const int off = p - sh.gt.flat[j];
+                    const int limit = min(mine.z, off + 1);           // not past the start of the sequence
+                    const int* at = &sh.tile[kMaxPattern + (p - t0)];
+                    // the five tokens before the place are requested together and compared in registers;
+                    // only a longer match goes on through LDS
+                    const int v1 = at[-1], v2 = at[-2], v3 = at[-3], v4 = at[-4], v5 = at[-5];
+                    int m = 1;
+                    bool on = 1 < limit && v1 == mine.y;
+                    m += on ? 1 : 0, on = on && 2 < limit && v2 == older.x;
+                    m += on ? 1 : 0, on = on && 3 < limit && v3 == older.y;
+                    m += on ? 1 : 0, on = on && 4 < limit && v4 == older.z;
+                    m += on ? 1 : 0, on = on && 5 < limit && v5 == older.w;
+                    m += on ? 1 : 0;
+                    if (on)
+                        while (m < limit && at[-m] == sh.pat[r][a.p_max - 1 - m]) ++m;
                     // a shorter match than one already seen in this stretch can never win
-                    const bool keep = m >= best;
-                    if (__ballot(keep) == 0) continue;
-                    if (keep && m > best) {
-                        atomicMax(&sh.best[r], m);
-                        best = m;
-                    }
-                    const int slot = wave_append(&sh.kept[r], keep);
-                    if (keep) out[slot] = pack_place(seq_of, m, off + 1);
+                    if (m < best) continue;
+                    if (m > best) atomicMax(&sh.best[r], m);
+                    const int slot = atomicAdd(&sh.kept[r], 1);
+                    a.list_a[static_cast<size_t>(sh.req[r]) * a.cap + static_cast<size_t>(part) * a.chunk + slot] = pack_place(j, m, off + 1);
                 }
             }
             __syncthreads();                                        // sh.first_seq and the tile are free again
