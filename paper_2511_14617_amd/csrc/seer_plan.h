@@ -74,6 +74,12 @@ __host__ __device__ __forceinline__ int cut_begin(const Cut& c, int w, uint32_t 
                                    : static_cast<uint64_t>(w) * static_cast<uint32_t>(c.equal);
     return static_cast<int>(at < static_cast<uint64_t>(c.total) ? at : c.total);
 }
+// A short line (equal stretches) of up to kSelfPlanRequests requests is cut so that no stretch goes on into the next request, where
+// that takes no more than W stretches: stretch first + i of a request begins i * c.equal tiles into it.  A second piece costs its workgroup
+// more than a tile (query rows, a first tile to wait for, partial results of its own), and the call waits for the slowest: of 459 workgroups of
+// three tiles of 256-wide heads those with one piece were done after 18 .. 20 us, those with two after 28 (16 requests of 2730 tokens,
+// one KV head: 36.0 -> 32.3 us a call; 64-wide heads 27.9 -> 25.8).
+__host__ __device__ __forceinline__ int stretches_of(const Cut& c, int tiles) { return (tiles + c.equal - 1) / c.equal; }
 // The same where no speeds are known: w / W.
 __host__ __device__ __forceinline__ uint32_t equal_before(const AttnArgs& a, int w) { return static_cast<uint32_t>(w) * a.inv_wgs; }
 
@@ -138,8 +144,17 @@ __device__ __forceinline__ SelfPlan plan_stretch(const AttnArgs& a, int* line, i
         }
         if (__all(usable)) before = f0, behind = f1;
     }
-    const int begin = __builtin_amdgcn_readfirstlane(cut_begin(cut, wg, before));
-    const int end = __builtin_amdgcn_readfirstlane(cut_begin(cut, wg + 1, behind));
+    int begin, end;
+    const int own = cut.weighted ? 0 : stretches_of(cut, t), own_incl = cut.weighted ? 0 : wave_incl_scan(own);
+    if (!cut.weighted && last_lane(own_incl) <= W) {
+        const int first = own_incl - own, b = __popcll(__ballot(lane < a.B && first <= wg)) - 1;      // (the last one that starts at or before it)
+        const int at = min(wg - __builtin_amdgcn_readlane(first, b), __builtin_amdgcn_readlane(own, b)) * cut.equal, size = __builtin_amdgcn_readlane(t, b);
+        begin = __builtin_amdgcn_readlane(off, b) + min(at, size);
+        end = __builtin_amdgcn_readlane(off, b) + min(at + cut.equal, size);
+    } else {
+        begin = __builtin_amdgcn_readfirstlane(cut_begin(cut, wg, before));
+        end = __builtin_amdgcn_readfirstlane(cut_begin(cut, wg + 1, behind));
+    }
     // every wave writes the same words and reads them behind its own writes
     line[2 * lane] = off, line[2 * lane + 1] = n;
     if (lane == 0) line[2 * kSelfPlanRequests] = total;

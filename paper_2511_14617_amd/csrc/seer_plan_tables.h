@@ -72,6 +72,7 @@ template <int THREADS>
 struct PlanLds {
     int tiles[THREADS / kWave], longest[THREADS / kWave];       // per wave
     int start[kMaxWgsPerHead + 1];
+    int first[kSelfPlanRequests], used;          // first stretch of each request, where none goes on into the next; their number
     int off[kPlanLdsRequests + 1];
 };
 
@@ -154,7 +155,28 @@ __device__ __forceinline__ void plan_tables(const AttnArgs& p, PlanLds<THREADS>&
     if (balanced) {
         // ---- the stretches ----------------------------------------------------------------------------------------------
         const Cut cut = cut_of(p, total, longest);
-        for (int w = tid; w < W; w += THREADS) s_start[w] = cut_begin(cut, w, w == tid ? before : equal_before(p, w));
+        const bool short_line = !cut.weighted && p.B <= kSelfPlanRequests;
+        if (short_line) {
+            if (wave == 0) {                             // (one request per thread)
+                const int own = stretches_of(cut, cnt), incl_own = wave_incl_scan(own);
+                if (lane < p.B) lds.first[lane] = incl_own - own;
+                if (lane == kWave - 1) lds.used = incl_own;
+            }
+            __syncthreads();
+        }
+        if (short_line && lds.used <= W) {
+            for (int w = tid; w < W; w += THREADS) {
+                int lo = 0, hi = p.B - 1;                // the last request whose stretches start at or before w
+                while (lo < hi) {
+                    const int mid = (lo + hi + 1) >> 1;
+                    if (lds.first[mid] <= w) lo = mid; else hi = mid - 1;
+                }
+                const int size = s_off[lo + 1] - s_off[lo];
+                s_start[w] = s_off[lo] + min(min(w - lds.first[lo], stretches_of(cut, size)) * cut.equal, size);
+            }
+        } else {
+            for (int w = tid; w < W; w += THREADS) s_start[w] = cut_begin(cut, w, w == tid ? before : equal_before(p, w));
+        }
         if (tid == 0) s_start[W] = total;
     }
     __syncthreads();
