@@ -74,12 +74,16 @@ __host__ __device__ __forceinline__ int cut_begin(const Cut& c, int w, uint32_t 
                                    : static_cast<uint64_t>(w) * static_cast<uint32_t>(c.equal);
     return static_cast<int>(at < static_cast<uint64_t>(c.total) ? at : c.total);
 }
-// A short line (equal stretches) of up to kSelfPlanRequests requests is cut so that no stretch goes on into the next request, where
+// A short line (equal stretches) of up to kWholeRequests requests is cut so that no stretch goes on into the next request, where
 // that takes no more than W stretches: stretch first + i of a request begins i * c.equal tiles into it.  A second piece costs its workgroup
 // more than a tile (query rows, a first tile to wait for, partial results of its own), and the call waits for the slowest: of 459 workgroups of
 // three tiles of 256-wide heads those with one piece were done after 18 .. 20 us, those with two after 28 (16 requests of 2730 tokens,
-// one KV head: 36.0 -> 32.3 us a call; 64-wide heads 27.9 -> 25.8).
+// one KV head: 36.0 -> 32.3 us a call; 64-wide heads 27.9 -> 25.8; 75 of 150 tokens, D = 128, two KV heads, 30.7 -> 27.2).
+constexpr int kWholeRequests = 256;
+// (Where stretches of c.equal tiles are too many, stretches of one more are tried, if that is no more than a third: 80 requests of 64 .. 1500
+// tokens on 256-wide heads, four tiles cut across requests 46.0 us, five not 43.5; 60 of 64 .. 2000 41.2, 35.7.)
 __host__ __device__ __forceinline__ int stretches_of(const Cut& c, int tiles) { return (tiles + c.equal - 1) / c.equal; }
+__host__ __device__ __forceinline__ int longest_whole(const Cut& c) { return c.equal + (c.equal >= 3 ? 1 : 0); }
 // The same where no speeds are known: w / W.
 __host__ __device__ __forceinline__ uint32_t equal_before(const AttnArgs& a, int w) { return static_cast<uint32_t>(w) * a.inv_wgs; }
 
@@ -132,7 +136,7 @@ __device__ __forceinline__ SelfPlan plan_stretch(const AttnArgs& a, int* line, i
     const int t = lane < a.B ? tiles_of(n, a.T, a.max_ctx) : 0;
     const int incl = wave_incl_scan(t), off = incl - t;
     const int total = last_lane(incl), longest = last_lane(wave_max_in_last_lane(t));
-    const Cut cut = cut_of(a, total, longest);
+    Cut cut = cut_of(a, total, longest);
     uint32_t before = equal_before(a, wg), behind = equal_before(a, wg + 1);
     if (!a.fixed_split && cut.weighted) {
         for (int i = 8 * lane;; s = shares(i)) {
@@ -145,8 +149,17 @@ __device__ __forceinline__ SelfPlan plan_stretch(const AttnArgs& a, int* line, i
         if (__all(usable)) before = f0, behind = f1;
     }
     int begin, end;
-    const int own = cut.weighted ? 0 : stretches_of(cut, t), own_incl = cut.weighted ? 0 : wave_incl_scan(own);
-    if (!cut.weighted && last_lane(own_incl) <= W) {
+    int own = 0, own_incl = 0;
+    bool whole = false;
+    if (!cut.weighted && cut.equal > 1) {       // (single tiles end with their request anyway)
+        Cut tried = cut;
+        for (const int most = longest_whole(cut); tried.equal <= most && !whole; ++tried.equal) {
+            own = stretches_of(tried, t), own_incl = wave_incl_scan(own);
+            whole = last_lane(own_incl) <= W;
+            if (whole) cut.equal = tried.equal;
+        }
+    }
+    if (whole) {
         const int first = own_incl - own, b = __popcll(__ballot(lane < a.B && first <= wg)) - 1;      // (the last one that starts at or before it)
         const int at = min(wg - __builtin_amdgcn_readlane(first, b), __builtin_amdgcn_readlane(own, b)) * cut.equal, size = __builtin_amdgcn_readlane(t, b);
         begin = __builtin_amdgcn_readlane(off, b) + min(at, size);

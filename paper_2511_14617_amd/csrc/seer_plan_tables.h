@@ -72,7 +72,7 @@ template <int THREADS>
 struct PlanLds {
     int tiles[THREADS / kWave], longest[THREADS / kWave];       // per wave
     int start[kMaxWgsPerHead + 1];
-    int first[kSelfPlanRequests], used;          // first stretch of each request, where none goes on into the next; their number
+    int first[kWholeRequests], part[THREADS / kWave];      // first stretch of each request, where none goes on into the next; per wave
     int off[kPlanLdsRequests + 1];
 };
 
@@ -154,17 +154,29 @@ __device__ __forceinline__ void plan_tables(const AttnArgs& p, PlanLds<THREADS>&
 
     if (balanced) {
         // ---- the stretches ----------------------------------------------------------------------------------------------
-        const Cut cut = cut_of(p, total, longest);
-        const bool short_line = !cut.weighted && p.B <= kSelfPlanRequests;
+        Cut cut = cut_of(p, total, longest);
+        static_assert(kSelfPlanRequests <= kWholeRequests && kWholeRequests <= THREADS, "both planners cut alike; one request per thread");
+        const bool short_line = !cut.weighted && cut.equal > 1 && p.B <= kWholeRequests;
+        int used = W + 1;
         if (short_line) {
-            if (wave == 0) {                             // (one request per thread)
-                const int own = stretches_of(cut, cnt), incl_own = wave_incl_scan(own);
-                if (lane < p.B) lds.first[lane] = incl_own - own;
-                if (lane == kWave - 1) lds.used = incl_own;
+            Cut tried = cut;
+            for (const int most = longest_whole(cut); tried.equal <= most && used > W; ++tried.equal) {
+                const int own = stretches_of(tried, cnt), incl_own = wave_incl_scan(own);
+                if (lane == kWave - 1) lds.part[wave] = incl_own;
+                __syncthreads();
+                int in_front = incl_own - own;
+                used = 0;
+#pragma unroll
+                for (int w = 0; w < THREADS / kWave; ++w) {
+                    if (w < wave) in_front += lds.part[w];
+                    used += lds.part[w];
+                }
+                if (used <= W) cut.equal = tried.equal;
+                if (tid < p.B) lds.first[tid] = in_front;
+                __syncthreads();
             }
-            __syncthreads();
         }
-        if (short_line && lds.used <= W) {
+        if (used <= W) {
             for (int w = tid; w < W; w += THREADS) {
                 int lo = 0, hi = p.B - 1;                // the last request whose stretches start at or before w
                 while (lo < hi) {
