@@ -21,8 +21,8 @@
 //   draft_expand_kernel  grid (requests): takes the longest match over all stretches, gathers its
 //                        places, then searches level by level: the (member, next token) pairs of
 //                        the live places are counted, the top_k picked, the places reassigned.
-//                        Few places live in registers (one wave alone, or the whole workgroup),
-//                        many in two lists in global memory.
+//                        The places' next tokens are held as strings, equal ones as one where places
+//                        are many; more than that takes two lists in global memory.
 //
 // Counts are integers, the order of the beam is (count descending, parent rank ascending, token
 // ascending) and the confidence test is one fp32 product and one comparison, so the result is
@@ -402,7 +402,8 @@ struct Member {            // one beam member of the current level
 //     shows are one pair, found and counted with one ballot.
 // The expansion of 128 requests with four paths of eight, in a call whose request with the most places has 1477: 46.9 us
 // when each level was counted by the whole workgroup behind six barriers (7 .. 12 thousand clocks a level with sixteen waves,
-// 2 .. 3 thousand for one wave with up to 256 places), 29 now; whole calls over 16 draws of the histories 67 .. 254 us, 48 .. 73 now.
+// 2 .. 3 thousand for one wave with up to 256 places), 29 now; whole calls over 16 draws of the histories
+// 67 .. 254 us, 46 .. 79 now (2 .. 4 of it the match scan).
 // Not kept: comparing all strings with each other (n^2 / 64 wave steps of some 60 instructions) and a trie of all
 // levels in one table (strings that the beam drops at the next level are entered all the way down).
 constexpr int kSlots = 4096;              // of the table of a level's pairs, at most
