@@ -39,26 +39,39 @@ __global__ __launch_bounds__(kPlanThreads) void plan_kernel(AttnArgs p) {
     else plan_tables<kPlanThreads>(p, lds);
 }
 
-// Which calls take whole requests (seer_attention_short.hip).  Measured against the partition kernels over head sizes, tables of 64 .. 4096
-// tokens, 1 .. 128 requests, 1 .. 8 KV heads, 16 .. 96 rows (lengths from half the table on; whole calls, this kernel | the others):
-//   heads of 128 and 64: 8.0 .. 8.5 us | 14 .. 20 up to 512 tokens; a wave's further tiles cost 1.4 us each (heads of 64: 0.8), which many items
-//     hide and few do not, since the stretches of the others spread a long request over idle CUs: 2048 tokens, 8 items 18.9 | 14.8, 64 items
-//     21.9 | 27.8, 256 items 24.3 | 47.0; 4096 tokens, 64 items 36.6 | 33.6, 128 items 39.0 | 46.6.  Hence as many items as tiles beyond 1024
-//     tokens; and no more work than one round of workgroups or two takes: 256 tokens, 2048 items 64.8 | 63.6.
-//   192/128: 512 tokens, 8 items 15.0 | 15.4, 1024 tokens 64 items 23.4 | 26.2, 16 items 22.4 | 17.1, 64 tokens 1024 items 42.6 | 29.8.
-//   256 (four waves to 160 KB): 128 tokens 14.3 | 19.3; 512 tokens 96 items 28.4 | 34.3, 16 items 27.1 | 20.2; 384 items of 64 tokens 30.1 | 27.1.
+// Which calls take whole requests (seer_attention_short.hip).  The host knows the table's width and not the lengths, and a model has one call that
+// plans and many that reuse its plan: taken whole are the sizes where both kinds gain or stay level in the middle of all lengths, and where none
+// makes a call slower by more than two microseconds.  39 500 random calls (tables of 32 ..
+// 1536 tokens, 1 .. 1024 workgroups, 1 .. 128 rows, pages of 1 .. 64 tokens; all long, all short, any, or one long request among short ones), microseconds on the
+// device of this kernel minus those of the partition kernels: median, 95th of 100 and worst of the calls that plan | of those that reuse (the same
+// library against itself: 0, +0.2, +2.4 | 0, +0.2, +2.1).
+//   heads of 64    up to 4 tiles -7.3 -6.4 -3.8 | -4.8 -3.8 -0.8; 16 tiles, 512 workgroups -6.1 -4.1 -3.0 | -3.4 -1.4 +0.5; 24 tiles, 256 workgroups
+//                  -6.8 -2.9 -1.8 | -4.1 -0.3 +0.6; 32 tiles, 256 workgroups, up to 127 of them -3.2 -1.0 -0.8 | -1.1 +1.5 +1.7, more -11.0 -4.0 -1.9 | -7.5 -1.3 +1.0
+//          not     more tiles -7.7 -0.7 +1.2 | -4.8 +1.7 +3.3; more workgroups -9.9 -0.6 +1.1 | -2.4 +3.4 +4.4
+//   heads of 128   up to 4 tiles -8.1 -7.0 -5.3 | -4.9 -3.6 +0.3; 8 tiles, 512 workgroups -6.7 -5.1 -3.0 | -3.5 -2.2 +1.2; 16 tiles, 256 workgroups
+//                  -5.1 -3.5 -2.8 | -2.2 -0.5 -0.3; 24 tiles, 256 workgroups, up to 31 of them -2.4 -1.5 -1.4 | +0.2 +1.3 +1.4, more -9.1 -3.1 -1.6 | -5.5 -0.3 +1.3
+//          not     25 .. 32 tiles -10.1 -0.6 +0.4 | -6.0 +2.3 +3.1: a request of many tiles keeps its workgroup while others idle, and the partition
+//                  kernels' stretches spread it (one as long as the table among short ones: 2048 tokens +6.6, 3072 +12.9); more workgroups, a second
+//                  round of them, -11.2 -3.7 -1.7 | -4.3 +1.0 +4.0
+//   192/128        up to 4 tiles, 256 workgroups -5.9 -4.3 -3.3 | -3.0 -1.3 -0.2; 8 tiles, 128 .. 256 workgroups -8.4 -4.2 -1.2 | -4.8 -1.4 +1.9
+//          not     more workgroups -2.5 +1.7 +2.2 | +2.9 +5.4 +5.9; fewer of 5 .. 8 tiles -3.4 -1.1 -0.4 | -0.5 +2.1 +2.6; more tiles -6.2 +1.0 +2.2 | -2.8 +4.0 +8.1
+//   256            up to 4 tiles, 256 workgroups: up to 32 rows -6.5 -4.6 -2.4 | -3.1 -1.2 +0.8, more rows from 65 workgroups on -6.1 -4.1 -2.9 | -2.8 -0.8 0.0
+//          not     fewer of more rows, which share a tile's loads there, -3.6 -2.0 -0.7 | -0.1 +1.5 +2.6; 5 .. 8 tiles -8.4 -3.3 -0.2 | -4.9 -0.1 +3.4
 // More than 64 rows of heads of 128 share a tile's loads in the kernel of the longer contexts.
 bool short_call(const seer_attn_params& p) {
     if (!(gqa_layout(p) || tile_layout(p)) || p.max_splits == 1 || (p.flags & (SEER_ATTN_GENERAL_KERNEL | SEER_ATTN_STREAM_ONLY))) return false;
     const int rows = (p.Hq / p.Hkv) * p.T, tiles = short_tiles(p);
-    const long long items = static_cast<long long>(p.B) * p.Hkv * ((rows + 31) / 32);
-    if (rows > (p.Dqk == 128 ? 64 : 128) || short_tiles_per_wave(p) > kShortTilesPerWave ||
-        static_cast<long long>(p.B) * p.max_pages_per_seq > kShortTableEntries)
-        return false;
-    const int any = p.Dqk == 256 ? 4 : (p.Dqk == 192 ? 8 : 32);                 // tiles of any number of items
-    const int per_tile = p.Dqk == 256 ? 6 : (p.Dqk == 192 ? 2 : 1);             // items per tile beyond
-    const int most = p.Dqk == 256 ? 256 : (p.Dqk == 192 ? 512 : 1024);
-    return (tiles <= any || items >= static_cast<long long>(per_tile) * tiles) && items <= most && items * tiles <= (p.Dqk > 128 ? 8192 : 12288);
+    if (rows > (p.Dqk == 128 ? 64 : 128) || static_cast<long long>(p.B) * p.max_pages_per_seq > kShortTableEntries) return false;
+    struct Range {
+        int Dqk, tiles, from, to;                   // tables of up to so many tiles: workgroups
+    };
+    static constexpr Range kRanges[] = {{64, 4, 1, 1024}, {64, 16, 1, 512}, {64, 32, 1, 256},
+                                        {128, 4, 1, 1024}, {128, 8, 1, 512}, {128, 24, 1, 256},
+                                        {192, 4, 1, 256}, {192, 8, 128, 256}, {256, 4, 1, 256}};
+    const long long wgs = short_workgroups(p);
+    for (const Range& r : kRanges)
+        if (p.Dqk == r.Dqk && tiles <= r.tiles) return wgs >= (p.Dqk == 256 && rows > 32 ? 65 : r.from) && wgs <= r.to;
+    return false;
 }
 
 hipError_t launch_plan(const AttnArgs& a, hipStream_t stream) {
@@ -600,7 +613,7 @@ int run_verify_attention(void* out, const void* q, const void* k_pages, const vo
 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (seer::short_call(*p)) {
-        a.short_waves = seer::short_waves(*p), a.short_tiles_per_wave = seer::short_tiles_per_wave(*p);
+        a.short_waves = seer::short_waves(p->Dqk, seer::short_tiles(*p));
         a.inv_pages = seer::reciprocal(p->max_pages_per_seq);
         a.self_plan = 0, a.fixed_split = 1;      // (no stretches are timed: the speed history stays as it is)
         hipError_t err = hipSuccess;

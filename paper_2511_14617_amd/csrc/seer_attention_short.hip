@@ -5,11 +5,14 @@
 // What bounds it: the length of its chain (launch, page ids, one tile's loads after the other, the merge), not a roofline.  The
 // partition kernels cut a short batch into stretches of a tile or two to fill the chip; what they save in tiles per workgroup
 // they spend on partial results and on the combine kernel behind them.  Here a tile belongs to one wave from its loads to its
-// product, in LDS of that wave's own, so there is no barrier until the merge; the K rows of the wave's next tile are requested
-// behind the scores, the V rows behind the product, and with four or eight waves to a workgroup a CU has eight tiles in flight.
+// product, in LDS of that wave's own, so there is no barrier until the merge; the K rows of a wave's next tile are requested
+// behind the scores, the V rows behind the product.  A CU holds twelve tiles of heads of 64 (three workgroups of four waves; eight
+// where a workgroup has eight), eight of heads of 128, seven or four of 192/128 (one workgroup of as many waves), four of heads of 256.
 //
 // The workgroups in front of the grid leave what a call leaves in its workspace: the plan's tables (calls that reuse the plan, with
-// whatever kernel, find them) and the status word.  They run beside the others and are done before them.
+// whatever kernel, find them) and the status word.  They run beside the others and are done before them in batches of up to 128 requests and
+// 8000 table entries (at the median, a call that plans takes no longer than one that reuses its plan); beyond, the call waits for them
+// (193 .. 256 requests up to 8.7 us; more up to 18), and is still ahead of one with a plan kernel in front.
 #include "seer_attention.h"
 #include "seer_device.h"
 #include "seer_plan_tables.h"
@@ -19,9 +22,6 @@ namespace seer {
 namespace shortctx {
 
 using namespace tile;
-
-template <int DQK, int DV>
-constexpr int kWavesMost = DQK == 256 ? 4 : (DQK == 192 ? 7 : 8);     // 160 KB hold this many tiles
 
 // Page ids outside the pool, among the entries that the requests' lengths reach: kBatch entries per thread and round, all of a
 // round requested at once.
@@ -51,8 +51,9 @@ struct TableCheck {
 
 }  // namespace shortctx
 
-// TERMS: bf16 terms of a probability in the matrix product, as in the kernel that takes the shape's longer contexts.
-template <int DQK, int DV, int TERMS, int NW>
+// TERMS: bf16 terms of a probability in the matrix product, as in the kernel that takes the shape's longer contexts.  NW waves, each with up
+// to TILES tiles.
+template <int DQK, int DV, int TERMS, int NW, int TILES>
 __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(DQK > 128 && NW == 4 ? 1 : 2))) void attn_short_kernel(AttnArgs a, int extra) {
     using namespace shortctx;
     using S = Shape<DQK, DV>;
@@ -97,17 +98,14 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(DQK 
     const int page_shift = __builtin_ctz(static_cast<unsigned>(a.P));
     auto page_of = [&](int tok) __attribute__((always_inline)) -> int { return page_pow2 ? tok >> page_shift : tok / a.P; };
 
-    // ---- requested together: the length, the page ids of all tiles of this wave (tile i of it is tile wave + i * NW of the request; each
+    // ---- requested together: the length, the page ids of the tiles of this wave (tile i of it is tile wave + i * NW of the request; each
     //      lane the page of its own token, the lower lanes of even tiles, the upper ones of odd tiles), its query row and mask -------
     const int n = uniform_load(a.ctx_len + b);
-    constexpr int kPairs = kShortTilesPerWave / 2;
-    const int pairs = (a.short_tiles_per_wave + 1) / 2;
+    constexpr int kPairs = (TILES + 1) / 2;
+    auto own_tok = [&](int j) __attribute__((always_inline)) -> int { return (wave + (TILES > 1 ? (2 * j + lg) * NW : 0)) * kTile + ln; };
     int row_of[kPairs];                            // page id, then row index in the pool, of this lane's token
 #pragma unroll
-    for (int j = 0; j < kPairs; ++j) row_of[j] = 0;
-#pragma unroll
-    for (int j = 0; j < kPairs; ++j)
-        if (j < pairs) row_of[j] = table[min(page_of((wave + (2 * j + lg) * NW) * kTile + ln), a.max_pages - 1)];
+    for (int j = 0; j < kPairs; ++j) row_of[j] = table[min(page_of(own_tok(j)), a.max_pages - 1)];
     const int r = rb * 32 + ln;
     const bool row_ok = r < a.G * a.T;
     const int t = row_ok ? r / a.G : 0;
@@ -128,22 +126,20 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(DQK 
     const int mine = wave < n_tiles ? (n_tiles - 1 - wave) / NW + 1 : 0;
     const int n0 = n - a.T;
 #pragma unroll
-    for (int j = 0; j < kPairs; ++j)
-        if (j < pairs) {
-            const int tok = (wave + (2 * j + lg) * NW) * kTile + ln;
-            const int pg = min(max(row_of[j], 0), a.num_pages - 1);
-            // (of 128 bytes or more each: 32 bits reach past the memory of the GPU)
-            row_of[j] = static_cast<int>((static_cast<uint32_t>(pg) * a.Hkv + kvh) * static_cast<uint32_t>(a.P) + (tok - page_of(tok) * a.P));
-        }
+    for (int j = 0; j < kPairs; ++j) {
+        const int tok = own_tok(j), pg = min(max(row_of[j], 0), a.num_pages - 1);
+        // (of 128 bytes or more each: 32 bits reach past the memory of the GPU)
+        row_of[j] = static_cast<int>((static_cast<uint32_t>(pg) * a.Hkv + kvh) * static_cast<uint32_t>(a.P) + (tok - page_of(tok) * a.P));
+    }
     // the row index in the pool of token `of` of this wave's tile i, for every lane
     auto pool_row = [&](int i, int of) __attribute__((always_inline)) -> uint32_t {
-        int v = 0;
+        int v = row_of[0];
 #pragma unroll
-        for (int j = 0; j < kPairs; ++j) {
+        for (int j = 1; j < kPairs; ++j) {
             const int x = row_of[j];
             v = (i >> 1) == j ? x : v;
         }
-        return __builtin_amdgcn_ds_bpermute((of + (i & 1) * 32) << 2, v);
+        return __builtin_amdgcn_ds_bpermute((of + (TILES > 1 ? (i & 1) * 32 : 0)) << 2, v);
     };
 
     unsigned char* const stage = lds + wave * S::kStage;
@@ -200,7 +196,7 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(DQK 
         }
         for (int i = 0; i < mine; ++i) {
             const int tb = (wave + i * NW) * kTile, rel = tb - n0;      // uniform; a tile with masked slots has rel > -32
-            const bool more = i + 1 < mine;
+            const bool more = TILES > 1 && i + 1 < mine;
             wait_vmcnt<kVLoads>();                 // this tile's K rows (its V rows are behind them)
             __builtin_amdgcn_sched_barrier(0);
             f32x16 s = tile_scores<DQK, DV>(at, operands, qreg);
@@ -309,19 +305,22 @@ hipError_t launch_short(const AttnArgs& a, hipStream_t stream) {
     const int rows = a.G * a.T, row_blocks = (rows + 31) / 32;
     auto launch = [&](auto* kernel, int waves) {
         const int extra = a.reuse_plan ? 0 : 1 + (a.B + waves * kWave - 1) / (waves * kWave);
-        const unsigned grid = static_cast<unsigned>((a.B * a.Hkv + 7) / 8) * 8u * row_blocks + extra;
+        const unsigned grid = static_cast<unsigned>((a.B * a.Hkv + 7) / 8) * 8u * row_blocks + extra;      // (short_workgroups())
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(waves * kWave), 0, stream, a, extra);
         return hipGetLastError();
     };
-#define SEER_SHORT_CASE(DQK_, DV_, TERMS_)                                                                                    \
-    if (a.Dqk == DQK_ && a.Dv == DV_) {                                                                                       \
-        constexpr int kMost = shortctx::kWavesMost<DQK_, DV_>;                                                                \
-        return a.short_waves <= 4 ? launch(&attn_short_kernel<DQK_, DV_, TERMS_, 4>, 4) : launch(&attn_short_kernel<DQK_, DV_, TERMS_, kMost>, kMost); \
+#define SEER_SHORT_CASE(DQK_, DV_, TERMS_, NW_, TILES_)                                                          \
+    if (a.Dqk == DQK_ && a.Dv == DV_ && a.short_waves == NW_) {                                                  \
+        static_assert(short_most_tiles(DQK_, NW_) <= NW_ * TILES_, "short_call() lets no longer tables in");     \
+        return launch(&attn_short_kernel<DQK_, DV_, TERMS_, NW_, TILES_>, NW_);                                  \
     }
-    SEER_SHORT_CASE(128, 128, 1)
-    SEER_SHORT_CASE(64, 64, 3)
-    SEER_SHORT_CASE(256, 256, 3)
-    SEER_SHORT_CASE(192, 128, 3)
+    SEER_SHORT_CASE(128, 128, 1, 4, 1)
+    SEER_SHORT_CASE(128, 128, 1, 8, 3)
+    SEER_SHORT_CASE(64, 64, 3, 4, 1)
+    SEER_SHORT_CASE(64, 64, 3, 8, 4)
+    SEER_SHORT_CASE(256, 256, 3, 4, 1)
+    SEER_SHORT_CASE(192, 128, 3, 4, 1)
+    SEER_SHORT_CASE(192, 128, 3, 7, 2)
 #undef SEER_SHORT_CASE
     return hipErrorInvalidValue;
 }

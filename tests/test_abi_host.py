@@ -283,3 +283,20 @@ def test_kernel_name_follows_the_dispatch(lib):
     assert name(_params(flags=binding.SEER_ATTN_GENERAL_KERNEL)) == "attn_general_kernel<128,128>"
     assert name(_params(page_size=24)) == "attn_general_kernel<128,128>"
     assert name(_params(T=65)) is None
+
+
+@pytest.mark.parametrize("whole,dims,tokens,B,heads,T", [
+    # (tables whose lengths can make a call slower when its requests are taken whole, measured: one long request among short ones, later layers)
+    (False, (128, 128), 2048, 12, (16, 8), 4), (False, (128, 128), 3072, 12, (16, 8), 4), (False, (128, 128), 1024, 18, (16, 8), 8),
+    (False, (128, 128), 256, 64, (16, 8), 24), (False, (128, 128), 512, 39, (16, 8), 4), (False, (64, 64), 2048, 12, (16, 8), 4), (False, (64, 64), 256, 64, (16, 8), 24),
+    (False, (64, 64), 1536, 8, (16, 8), 4), (False, (192, 128), 512, 8, (8, 2), 12), (False, (192, 128), 64, 81, (8, 1), 12), (False, (192, 128), 64, 32, (32, 8), 12),
+    (False, (192, 128), 256, 8, (8, 2), 4), (False, (256, 256), 512, 24, (16, 4), 4), (False, (256, 256), 256, 32, (16, 4), 4), (False, (256, 256), 128, 2, (4, 1), 12),
+    # (and those that stay ahead)
+    (True, (128, 128), 512, 4, (8, 2), 5), (True, (128, 128), 128, 128, (16, 8), 4), (True, (128, 128), 256, 32, (16, 8), 8), (True, (128, 128), 768, 2, (4, 1), 8),
+    (True, (64, 64), 512, 64, (16, 8), 8), (True, (64, 64), 1024, 16, (16, 8), 8), (True, (64, 64), 1, 1, (1, 1), 1), (True, (192, 128), 128, 32, (16, 8), 8),
+    (True, (192, 128), 256, 16, (16, 8), 8), (True, (256, 256), 128, 2, (4, 1), 8), (True, (256, 256), 128, 32, (16, 4), 12)])
+def test_requests_are_taken_whole_only_where_no_lengths_make_that_slower(lib, whole, dims, tokens, B, heads, T):
+    from paper_2511_14617_amd import binding
+    pages = -(-tokens // 16)
+    name = binding.seer_verify_attention_kernel(_params(B=B, T=T, Hq=heads[0], Hkv=heads[1], Dqk=dims[0], Dv=dims[1], max_pages_per_seq=pages))
+    assert ("attn_short_kernel" in name) == whole, name

@@ -11,14 +11,14 @@ from gpu_util import assert_attention_close, attention_device_inputs
 pytestmark = pytest.mark.gpu
 
 SIZES = [(128, 128), (64, 64), (256, 256), (192, 128)]
-# one and more tiles per wave (four waves up to 128 tokens, else seven or eight; wide heads four), row blocks of 1, 32, 33 and 64 rows,
-# an odd number of tiles per wave, lengths at the edges of tiles, of a wave's tiles and of the table, lengths that cannot be used
+# one and two tiles per wave (four waves up to 128 tokens, else eight), row blocks of 1, 32, 33 and 64 rows, lengths at the
+# edges of tiles, of a wave's tiles and of the table, lengths that cannot be used; wide heads are taken whole up to 128 tokens
 SHAPES = {
     "one_tile_rows1": dict(B=3, Hq=2, Hkv=2, T=1, ctx=("fixed", (1, 31, 32))),
     "four_waves": dict(B=6, Hq=8, Hkv=2, T=8, ctx=("fixed", (8, 33, 64, 97, 127, 128))),
     "rows33": dict(B=5, Hq=3, Hkv=1, T=11, ctx=("fixed", (11, 225, 256, 257, 290))),
     "rows64_tree": dict(B=9, Hq=16, Hkv=2, T=8, tree=(1, 7), ctx=("uniform", 8, 500)),
-    "several_tiles": dict(B=16, Hq=16, Hkv=8, T=5, ctx=("uniform", 300, 1000)),
+    "several_tiles": dict(B=16, Hq=16, Hkv=8, T=5, ctx=("uniform", 300, 512)),
     "batch_70": dict(B=70, Hq=4, Hkv=1, T=9, tree=(2, 4), ctx=("uniform", 9, 450)),
     "common_prompt": dict(B=12, group_size=6, Hq=8, Hkv=2, T=3, ctx=("uniform", 140, 400), shared_prefix=128),
 }
@@ -34,6 +34,10 @@ def test_whole_requests_against_the_oracle_and_the_partition_kernels(name, page,
     kw = SHAPES[name]
     if page > 16 and "shared_prefix" in kw:
         kw = dict(kw, shared_prefix=2 * page)
+    most = (512 if dims[0] <= 128 else 128) // page * page
+    kw = dict(kw, ctx=("fixed", tuple(min(n, most) for n in kw["ctx"][1])) if kw["ctx"][0] == "fixed" else ("uniform", min(kw["ctx"][1], most // 2), min(kw["ctx"][2], most)))
+    if "shared_prefix" in kw and dims[0] > 128:
+        kw["shared_prefix"] = page
     cfg = W.CONFIGS[1].scaled(Dqk=dims[0], Dv=dims[1], page_size=page, **kw)
     pages = -(-(max(cfg.ctx[1]) if cfg.ctx[0] == "fixed" else cfg.ctx[2]) // page)
 
