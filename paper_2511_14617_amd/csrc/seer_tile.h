@@ -261,11 +261,11 @@ __device__ __forceinline__ void tile_add_rows(uint32_t left, const uint32_t (&te
         float pj = 0.f;
 #pragma unroll
         for (int k = TERMS - 1; k >= 0; --k) {
-            uint32_t pair = 0;
+            uint32_t pair = term[k][0];                         // (a chain of selections: as a sum of masked words it cost the loop scalar registers)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
+            for (int i = 1; i < 8; ++i) {
                 const uint32_t x = term[k][i];
-                pair |= (ij >> 1) == i ? x : 0u;
+                pair = (ij >> 1) == i ? x : pair;
             }
             pj += (ij & 1) ? bf16hi_to_f32(pair) : bf16lo_to_f32(pair);
         }
