@@ -416,7 +416,7 @@ constexpr int kDistinctLevels = 3;
 constexpr int kManyPlaces = 1 << 16;      // (numbers of places in 16 bits)
 // More than kSmall places are given up after the first kThreads if as many in proportion would be this many distinct ones
 // (later places repeat more; 2761 places with 2034 strings: whole call 155 us without the strings, 68 with; 3787 with 3058: 91, given up late 98).
-constexpr int kHopeless = kSmall * 3 / 2;
+constexpr int kHopeless = kSmall * 5 / 4;
 constexpr int kRankWave = 16;             // candidates of a level that are ranked one by one
 constexpr int kPeel = 4;                  // pairs that one wave takes one by one before it looks for the rest by hash
 constexpr int kMeetLog2 = 9;              // words it uses for that
@@ -1126,6 +1126,20 @@ __global__ __launch_bounds__(kThreads) void draft_expand_kernel(Args a) {
     if (x.gt.bad && tid == 0 && a.status) atomicOr(a.status, x.gt.bad);
     const int p_star = x.gt.n_seq > 0 ? x.best_len : 0;
     const int n_kept = p_star > 0 ? x.first[a.parts] : 0;        // >= the places of the longest match
+    const auto put_draft = [&]() {
+        if (tid < T) {
+            const size_t o = static_cast<size_t>(b) * T + tid;
+            a.draft_tokens[o] = x.tok[tid];
+            a.tree_parent[o] = x.par[tid];
+            a.tree_mask[o] = x.msk[tid];
+            if (a.node_count) a.node_count[o] = x.num[tid];
+        }
+        if (tid == 0 && a.match_len) a.match_len[b] = p_star;
+    };
+    if (uniform(n_kept) == 0) {                                  // no match: the empty draft
+        put_draft();
+        return;
+    }
     uint32_t* cur = a.list_b + static_cast<size_t>(b) * a.cap;
     uint32_t* nxt = a.list_a + static_cast<size_t>(b) * a.cap;
     bool handed_over = n_kept <= kSmall;
@@ -1350,14 +1364,7 @@ __global__ __launch_bounds__(kThreads) void draft_expand_kernel(Args a) {
     }
     __syncthreads();
 
-    if (tid < T) {
-        const size_t o = static_cast<size_t>(b) * T + tid;
-        a.draft_tokens[o] = x.tok[tid];
-        a.tree_parent[o] = x.par[tid];
-        a.tree_mask[o] = x.msk[tid];
-        if (a.node_count) a.node_count[o] = x.num[tid];
-    }
-    if (tid == 0 && a.match_len) a.match_len[b] = p_star;
+    put_draft();
 }
 
 }  // namespace draft
