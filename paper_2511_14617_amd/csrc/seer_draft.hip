@@ -413,6 +413,7 @@ constexpr int kPer = kSmall / kThreads;   // strings per thread, at most
 // Distinct strings stay distinct only as far as they are known: they are for the last kAhead levels, and cost what two
 // or three levels of the table do (two levels, 1207 places with 691 strings: whole call 37.8 us with them, 36.0 without).
 constexpr int kDistinctLevels = 3;
+constexpr int kSettled = 4;               // so many strings settled inside their waves say that at least three in four recur
 constexpr int kManyPlaces = 1 << 16;      // (numbers of places in 16 bits)
 // More than kSmall places are given up after the first kThreads if as many in proportion would be this many distinct ones
 // (later places repeat more; 2761 places with 2034 strings: whole call 155 us without the strings, 68 with; 3787 with 3058: 91, given up late 98).
@@ -551,18 +552,27 @@ struct Held {
     int t[kPer][kAhead], id[kPer], w[kPer], member[kPer];
 };
 
-// The words of a place's string from level d on, at most L; -1 behind its end, or if the place belongs to nobody.
-__device__ __forceinline__ void fetch_string(const Args& a, const Expand& x, uint32_t place, bool on, int d, int L, int (&t)[kAhead]) {
+// The words of a place's string from level d on, at most L: requested (returns how many there are), and as a string: -1 behind its
+// end, or if the place belongs to nobody.
+__device__ __forceinline__ int request_string(const Args& a, const Expand& x, uint32_t place, bool on, int d, int L, int (&t)[kAhead]) {
     const int j = place_seq(place), off = place_off(place) + d - 1;
     const int have = on ? min(x.gt.len[j] - off, L) : 0;
     const int at = have > 0 ? x.gt.start[j] + off : 0;           // (loads from clamped addresses do not wait for each other)
 #pragma unroll
-    for (int l = 0; l < kAhead; ++l) t[l] = a.tokens[at + min(l, max(have - 1, 0))];
+    for (int l = 0; l < kAhead; ++l) t[l] = l < 2 || L > 2 ? a.tokens[at + min(l, max(have - 1, 0))] : -1;
+    return have;
+}
+__device__ __forceinline__ void end_string(const Args& a, int have, int (&t)[kAhead]) {
+    bool on = true;
 #pragma unroll
     for (int l = 0; l < kAhead; ++l) {
         on = on && l < have && t[l] >= 0 && t[l] < a.vocab;      // (a token that cannot be proposed ends the string)
         t[l] = on ? t[l] : -1;
     }
+}
+__device__ __forceinline__ void fetch_string(const Args& a, const Expand& x, uint32_t place, bool on, int d, int L, int (&t)[kAhead]) {
+    const int have = request_string(a, x, place, on, d, L, t);
+    end_string(a, have, t);
 }
 __device__ __forceinline__ void put_string(int* row, const int (&t)[kAhead]) {
     static_assert(kAhead == 8, "two 16-byte words");
@@ -597,27 +607,52 @@ __device__ __forceinline__ void drop_word(Held& h) {
     }
 }
 
-// One string stays for all places that show the same, with their number as its weight.
-__device__ __forceinline__ void distinct_strings(Expand& x, Held& h, int n, int threads) {
+// The places that this lane's string stands for, of `live` lanes with one each: those that show what the first lane shows
+// are all that lane's (0: another lane's, or none).
+__device__ __forceinline__ int places_of_lane(int member, const int (&t)[kAhead], bool live) {
+    const uint64_t all = __ballot(live);
+    if (all == 0) return 0;
+    const int lead = __ffsll(static_cast<long long>(all)) - 1;
+    bool same = live && member == __builtin_amdgcn_readlane(member, lead);
+#pragma unroll
+    for (int l = 0; l < kAhead; ++l) same = same && t[l] == __builtin_amdgcn_readlane(t[l], lead);
+    const uint64_t equal = __ballot(same);
+    return !live ? 0 : (!same ? 1 : (lane_id() == lead ? __popcll(equal) : 0));
+}
+
+// One string stays for all places that show the same, with their number as its weight.  A wave's lanes that agree with its first one
+// are settled without the table; where hardly any do, nearly all strings differ and the table is left out (1426 places of seven tokens out of eight:
+// whole call 29.0 us with it, 23.0 without): false, and the strings stay where they are.
+__device__ __forceinline__ bool distinct_strings(Expand& x, Held& h, int n, int threads) {
     const int tid = static_cast<int>(threadIdx.x);
     // a slot of the table: the string that entered it, and 1 << 16 for every place that shows it
     int table = 2 * kFew;
     while (table < 2 * n) table <<= 1;
     const int shift = 32 - __builtin_ctz(static_cast<unsigned>(table));
     for (int i = tid; i < table; i += threads) x.distinct[i] = kEmpty;
+    int settled = 0;
 #pragma unroll
-    for (int u = 0; u < kPer; ++u)
+    for (int u = 0; u < kPer; ++u) {
+        const bool live = h.member[u] >= 0;
+        h.w[u] = places_of_lane(h.member[u], h.t[u], live);
+        settled += __popcll(__ballot(live && h.w[u] == 0));
+        if (h.w[u] == 0) h.member[u] = -1;
         if (h.member[u] >= 0) {
             put_string(x.row[tid + u * threads], h.t[u]);
             x.member[tid + u * threads] = static_cast<int8_t>(h.member[u]);
         }
+    }
+    if (lane_id() == 0) x.red[tid >> 6] = static_cast<uint64_t>(settled);
     __syncthreads();
+    settled = 0;
+    for (int w = 0; w < threads / 64; ++w) settled += static_cast<int>(x.red[w]);
+    if (uniform(settled) < kSettled) return false;
     uint32_t at[kPer], old[kPer];
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
         at[u] = hash_string(h.member[u], h.t[u]) >> shift;
         old[u] = kEmpty;
-        if (h.member[u] >= 0) old[u] = atomicCAS(&x.distinct[at[u]], kEmpty, (1u << 16) | static_cast<uint32_t>(tid + u * threads));
+        if (h.member[u] >= 0) old[u] = atomicCAS(&x.distinct[at[u]], kEmpty, (static_cast<uint32_t>(h.w[u]) << 16) | static_cast<uint32_t>(tid + u * threads));
     }
     bool own[kPer];
 #pragma unroll
@@ -627,12 +662,12 @@ __device__ __forceinline__ void distinct_strings(Expand& x, Held& h, int n, int 
         for (int probes = 0; old[u] != kEmpty && probes < table; ++probes) {
             const int j = static_cast<int>(old[u] & 0xffffu);
             if (x.member[j] == h.member[u] && same_string(x.row[j], h.t[u])) {
-                atomicAdd(&x.distinct[at[u]], 1u << 16);
+                atomicAdd(&x.distinct[at[u]], static_cast<uint32_t>(h.w[u]) << 16);
                 own[u] = false;
                 break;
             }
             at[u] = (at[u] + 1) & (table - 1);
-            old[u] = atomicCAS(&x.distinct[at[u]], kEmpty, (1u << 16) | static_cast<uint32_t>(tid + u * threads));
+            old[u] = atomicCAS(&x.distinct[at[u]], kEmpty, (static_cast<uint32_t>(h.w[u]) << 16) | static_cast<uint32_t>(tid + u * threads));
         }
     }
     __syncthreads();
@@ -641,6 +676,7 @@ __device__ __forceinline__ void distinct_strings(Expand& x, Held& h, int n, int 
         if (own[u]) h.w[u] = static_cast<int>(x.distinct[at[u]] >> 16);
         h.member[u] = own[u] ? h.member[u] : -1;
     }
+    return true;
 }
 
 // Threads that n strings are for, of those that are left.
@@ -688,23 +724,30 @@ __device__ __forceinline__ int distinct_listed(const Args& a, Expand& x, const u
     for (int i = tid; i < kTable; i += kThreads) x.distinct[i] = kEmpty;
     if (tid == 0) x.n_held = 0;
     __syncthreads();                                             // (the last level's list is written)
+    uint32_t place = list[min(tid, n - 1)];
+    int got[kAhead], have = request_string(a, x, place, tid < n, 1, L, got);
     for (int i0 = 0; i0 < n; i0 += kThreads) {
-        const uint32_t place = list[min(i0 + tid, n - 1)];
+        // (the next round's places are requested in front of this round's strings, its strings behind them)
+        place = list[min(i0 + kThreads + tid, n - 1)];
         int t[kAhead];
-        fetch_string(a, x, place, i0 + tid < n, 1, L, t);
-        bool own = t[0] >= 0;
+#pragma unroll
+        for (int l = 0; l < kAhead; ++l) t[l] = got[l];
+        end_string(a, have, t);
+        const int places = places_of_lane(0, t, t[0] >= 0);
+        bool own = places > 0;
         if (own) put_string(x.fresh[tid], t);
+        have = request_string(a, x, place, i0 + kThreads + tid < n, 1, L, got);
         __syncthreads();
         const int so_far = uniform(x.n_held);
         if (so_far > kSmall || (i0 == kThreads && so_far * n > kThreads * kHopeless)) return -1;
         uint32_t at = hash_string(0, t) >> kShift;
         if (own) {
-            const uint32_t enter = (1u << 16) | static_cast<uint32_t>(tid);
+            const uint32_t enter = (static_cast<uint32_t>(places) << 16) | static_cast<uint32_t>(tid);
             uint32_t old = atomicCAS(&x.distinct[at], kEmpty, enter);
             for (int probes = 0; old != kEmpty && probes < kTable; ++probes) {
                 const int j = static_cast<int>(old & 0xffffu);
                 if (same_string(j < kThreads ? x.fresh[j] : x.kept[j - kThreads], t)) {
-                    atomicAdd(&x.distinct[at], 1u << 16);
+                    atomicAdd(&x.distinct[at], static_cast<uint32_t>(places) << 16);
                     own = false;
                     break;
                 }
@@ -1046,10 +1089,7 @@ __device__ __forceinline__ void search_places(const Args& a, Expand& x, int d, i
             h.id[u] = i, h.w[u] = 1, h.member[u] = h.t[u][0] >= 0 ? own : -1;
         }
         int n_str = n;
-        if (n > kFew && d + L > levels && L >= kDistinctLevels) {
-            distinct_strings(x, h, n, threads);
-            n_str = pack_strings(x, h, threads);
-        }
+        if (n > kFew && d + L > levels && L >= kDistinctLevels && distinct_strings(x, h, n, threads)) n_str = pack_strings(x, h, threads);
         const bool ended = search_strings(a, x, h, d, L, least, n_str, threads);
         d += L;
         if (ended || d > levels) break;
