@@ -447,7 +447,8 @@ struct Expand {
     int8_t member[kSmall];                 //   and the rank of the member it belongs to
     __attribute__((aligned(16))) uint16_t list[kSmall];          // entries of the level's pairs (in one wave's search, the words of its hash)
     int lead[kAhead], lead_member;         // the string that the others are compared with
-    int n_list[2], n_held, n_left, n_on, common;
+    int n_list[2], n_held, n_left, common;
+    uint32_t n_on;
     uint32_t place[kSmall];                // hand-over of places between the phases
     int8_t owner[kSmall];                  // rank of the member a place belongs to, -1 = dropped
     int first[kMaxParts + 1];              // places of the longest match before part p
@@ -1017,40 +1018,58 @@ __device__ __forceinline__ bool search_lanes(const Args& a, Expand& x, Held& h, 
 }
 
 // L levels from level d on, over the first L words of the n_str strings that `threads` threads hold; threads that are no
-// longer needed end.  True if the search has ended.
-__device__ __forceinline__ bool search_strings(const Args& a, Expand& x, Held& h, int d, int L, int least, int n_str, int& threads) {
+// longer needed end.  `last`: no levels come behind them, so equal strings need no place each.  True if the search has ended.
+__device__ __forceinline__ bool search_strings(const Args& a, Expand& x, Held& h, int d, int L, bool last, int least, int n_str, int& threads) {
     const int tid = static_cast<int>(threadIdx.x);
     int lvl = 0;
     bool ended = n_str == 0;
     if (n_str > 64) {
-        // the levels on which all strings agree, for one member
-        if (tid == 0) {
+        // the levels on which all strings agree, for one member, as a string of the first wave shows them (one that goes on to the
+        // last, if there is one), and the places that show that string
+        bool holder = false;
+        if (tid < 64) {
+            bool full = h.member[0] >= 0;
 #pragma unroll
-            for (int l = 0; l < kAhead; ++l) x.lead[l] = h.t[0][l];
-            x.lead_member = h.member[0], x.common = L, x.n_on = 0;
+            for (int l = 0; l < kAhead; ++l) full = full && (l >= L || h.t[0][l] >= 0);
+            const uint64_t ready = __ballot(full);
+            holder = tid == (ready != 0 ? __ffsll(static_cast<long long>(ready)) - 1 : 0);
+            if (holder) {
+#pragma unroll
+                for (int l = 0; l < kAhead; ++l) x.lead[l] = h.t[0][l];
+                x.lead_member = h.member[0], x.common = L, x.n_on = 0;
+            }
         }
         __syncthreads();
         const int member = uniform(x.lead_member);
-        int all = member >= 0 ? L : 0, n_on = 0;
+        int all = member >= 0 ? L : 0;
+        bool same[kPer];
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) same[u] = h.member[u] >= 0 && h.member[u] == member;
 #pragma unroll
         for (int l = kAhead - 1; l >= 0; --l) {
             const int lead = x.lead[l];
             bool parts = lead < 0;
 #pragma unroll
-            for (int u = 0; u < kPer; ++u) parts = parts || (h.member[u] >= 0 && (h.member[u] != member || h.t[u][l] != lead));
+            for (int u = 0; u < kPer; ++u) {
+                const bool equal = h.t[u][l] == lead;
+                parts = parts || (h.member[u] >= 0 && (h.member[u] != member || !equal));
+                same[u] = same[u] && equal;
+            }
             if (l < all && __ballot(parts) != 0) all = l;
         }
+        uint32_t n_on = 0;                                       // places: those that show the string << 16 | all
 #pragma unroll
-        for (int u = 0; u < kPer; ++u) n_on += h.member[u] >= 0 ? h.w[u] : 0;
-        n_on = wave_sum(n_on);
+        for (int u = 0; u < kPer; ++u)
+            n_on += (h.member[u] >= 0 ? static_cast<uint32_t>(h.w[u]) : 0u) + (same[u] ? static_cast<uint32_t>(h.w[u]) << 16 : 0u);
+        n_on = static_cast<uint32_t>(wave_sum(static_cast<int>(n_on)));
         if (lane_id() == 0) {
             atomicMin(&x.common, all);
             atomicAdd(&x.n_on, n_on);
         }
         __syncthreads();
         lvl = uniform(x.common);
+        const int count = uniform(static_cast<int>(x.n_on & 0xffffu)), n_same = uniform(static_cast<int>(x.n_on >> 16));
         if (lvl > 0) {
-            const int count = uniform(x.n_on);
             if (count < least) ended = true;
             if (!ended && tid == 0)
                 for (int l = 0; l < lvl; ++l)
@@ -1060,6 +1079,14 @@ __device__ __forceinline__ bool search_strings(const Args& a, Expand& x, Held& h
 #pragma unroll
             for (int u = 0; u < kPer; ++u) h.member[u] = min(h.member[u], 0);
             for (int l = 0; l < lvl; ++l) drop_word(h);
+        }
+        // a string that half of the places show, or whose repeats are what is more than one wave's work, stays once
+        if (last && !ended && lvl < L && n_same > 1 && (2 * n_same >= count || n_str - n_same < 64)) {
+#pragma unroll
+            for (int u = 0; u < kPer; ++u)
+                if (same[u] && !(holder && u == 0)) h.member[u] = -1;
+            if (holder) h.w[0] = n_same;
+            n_str = pack_strings(x, h, threads);
         }
         while (!ended && lvl < L && n_str > 64) {
             lvl += count_levels(a, x, h, d + lvl, L - lvl, threads, least, threads > kFewThreads ? kPer / 2 * threads : 64, n_str);
@@ -1090,7 +1117,7 @@ __device__ __forceinline__ void search_places(const Args& a, Expand& x, int d, i
         }
         int n_str = n;
         if (n > kFew && d + L > levels && L >= kDistinctLevels && distinct_strings(x, h, n, threads)) n_str = pack_strings(x, h, threads);
-        const bool ended = search_strings(a, x, h, d, L, least, n_str, threads);
+        const bool ended = search_strings(a, x, h, d, L, d + L > levels, least, n_str, threads);
         d += L;
         if (ended || d > levels) break;
         // the places that go on, in front (each string is one place: distinct strings are for the last round)
@@ -1222,7 +1249,7 @@ __global__ __launch_bounds__(kThreads) void draft_expand_kernel(Args a) {
         int threads = kThreads;
         const int n_str = distinct_listed(a, x, cur, uniform(n_root), uniform(levels), h, threads);
         if (n_str >= 0) {
-            search_strings(a, x, h, 1, uniform(levels), least, n_str, threads);
+            search_strings(a, x, h, 1, uniform(levels), true, least, n_str, threads);
             done = true;
         }
     }
