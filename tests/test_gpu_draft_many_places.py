@@ -34,3 +34,41 @@ def test_a_match_at_many_places(places, distinct, gamma, top_k, conf):
     d.max_spec_tokens[1] = max(gamma - 1, 1)
     want = _compare(d, "%d places, %d continuations" % (places, distinct))
     assert want[3][0, 0] >= places
+
+
+@pytest.mark.parametrize("places,others,gamma,top_k,conf", [
+    (32767, 1, 8, 4, 0.0), (32768, 1, 8, 1, 0.0), (32768, 2, 8, 4, 0.0), (40000, 3, 5, 12, 0.01), (65535, 1, 3, 1, 0.5), (65535, 2, 8, 4, 0.0),
+    (65535, 2, 3, 1, 0.0), (65536, 1, 8, 4, 0.0), (65536, 2, 3, 1, 0.0), (70000, 2, 8, 4, 0.0), (2800, 30, 8, 4, 0.0)])
+def test_numbers_of_places_that_need_all_their_sixteen_bits(places, others, gamma, top_k, conf):
+    """One token before every place; the tokens behind it are drawn from it and `others` - 1 more, so that one string recurs that often (others = 1) or
+    hundreds recur hundreds of times and add up in a level's pairs.  From 65536 places on, the list in memory."""
+    rng = np.random.default_rng(places + others)
+    s = np.full(places + 1, 7)
+    if others > 1:
+        s = rng.choice([7] + list(range(100, 99 + others)), size=2 * others * places)
+        s = np.concatenate([s[: np.flatnonzero(s == 7)[places - 1] + 1], [100, 100, 100]])
+    d = _from_lists([[s.tolist()]], [0], [[7]], gamma_max=gamma, top_k=top_k, p_min=1, p_max=1, vocab=60000, min_confidence=conf)
+    want = _compare(d, "%d places of %d tokens" % (places, others))
+    assert want[3][0, 0] == places
+
+
+@pytest.mark.parametrize("n", [0, 1, 64, 65, 130, 512, 513, 1500, 2048, 2049, 4000])
+@pytest.mark.parametrize("tail", [0, 1, 5])
+@pytest.mark.parametrize("gamma,top_k", [(8, 4), (3, 1), (12, 2), (1, 8), (2, 3)])
+def test_one_string_that_most_places_show_beside_ends_and_others(n, tail, gamma, top_k):
+    """A phrase of period seven over sequences that end anywhere in it, with sequences of other tokens between: most places of a wave, or
+    of all waves, show one string; `n` places or none, `tail` sequences that differ."""
+    rng = np.random.default_rng(n + 31 * tail + gamma)
+    phrase = list(range(50, 57))
+    seqs, left = [], n
+    while left > 0:
+        k = min(left, int(rng.integers(1, 400)))
+        seqs.append(([phrase[i % 7] for i in range(7 * k)] + phrase[: int(rng.integers(1, 8))]))
+        left -= k
+    for i in range(tail):
+        seqs.insert(int(rng.integers(0, len(seqs) + 1)), phrase + rng.integers(100, 130, size=20).tolist())
+    seqs.append([900, 901])
+    if len(seqs) > 120:
+        seqs = seqs[:119] + [sum(seqs[119:], [])]
+    d = _from_lists([seqs], [0, 0], [phrase[5:] if n else [333], phrase[:3]], gamma_max=gamma, top_k=top_k, p_min=2, p_max=4, vocab=60000)
+    _compare(d, "%d places, %d others" % (n, tail))
