@@ -1,4 +1,5 @@
-// Cuts made from recorded shares of any contents, on the host: every line is covered once, and no stretch is far from an equal one.
+// Cuts on the host, by the functions that both planners use: from recorded shares of any contents every line is covered once, and no stretch is
+// far from an equal one; the sizes of stretches that end with their request cover every request and stay within a third of an equal one.
 #include <stdio.h>
 
 #include <random>
@@ -61,6 +62,33 @@ int main() {
                 if (prev != total) return printf("W %d kind %d: ends at %d of %d\n", W, kind, prev, total), 1;
             }
     }
+    // short lines: stretches of one size that end with their request
+    int whole = 0, one_more = 0;
+    for (int W : {1, 2, 31, 128, 256, 512, 1024})
+        for (int rep = 0; rep < 2000; ++rep) {
+            AttnArgs a{};
+            a.wgs_per_head = W, a.inv_wgs = reciprocal(W), a.max_splits = rep % 3 ? 256 : 2 + static_cast<int>(rng() % 255), a.inv_splits = reciprocal(a.max_splits - 1);
+            a.min_tiles = rep % 2 ? 1 : 4, a.fine_pieces = 1 << 28, a.B = 1 + static_cast<int>(rng() % kWholeRequests);
+            std::vector<int> tiles(a.B);
+            int total = 0, longest = 0;
+            for (int& t : tiles) t = static_cast<int>(rng() % 5 ? std::exp2(uniform(0., 7.)) : 0), total += t, longest = std::max(longest, t);
+            const Cut cut = cut_of(a, total, longest);
+            if (cut.weighted || cut.equal < 2) continue;
+            for (Cut tried = cut; tried.equal <= longest_whole(cut); ++tried.equal) {
+                int used = 0, pieces = 0;
+                for (int t : tiles) {
+                    const int own = stretches_of(tried, t);
+                    if (own * tried.equal < t || (own - 1) * tried.equal >= std::max(t, 1)) return printf("%d tiles in %d of %d\n", t, own, tried.equal), 1;
+                    used += own, pieces = std::max(pieces, own);
+                }
+                if (pieces > a.max_splits || 3 * tried.equal > 4 * cut.equal + 2 * (cut.equal < 3)) return printf("%d pieces, %d for %d tiles\n", pieces, tried.equal, cut.equal), 1;
+                if (used <= W) {
+                    tried.equal == cut.equal ? ++whole : ++one_more;
+                    break;
+                }
+            }
+        }
+    if (whole < 300 || one_more < 30) return printf("whole %d, one more %d\n", whole, one_more), 1;
     printf("used %d refused %d\n", used, refused);
     return used > 1000 && refused > 1000 ? 0 : 1;
 }
