@@ -46,7 +46,8 @@ __global__ __launch_bounds__(kCommitThreads) void kv_commit_kernel(CommitArgs a)
     __shared__ int s_path[SEER_MAX_T];
     __shared__ int2 s_page[SEER_MAX_T], s_slot[SEER_MAX_T];   // path node i: page and slot of its source and of its destination
     __shared__ int s_draft[SEER_MAX_T];
-    __shared__ int s_bad, s_moves;
+    __shared__ int s_flags;           // status bits, kMoves
+    constexpr int kMoves = 8;
     const int b = blockIdx.x;
     const int tid = threadIdx.x;
     const int T = a.T;
@@ -55,7 +56,7 @@ __global__ __launch_bounds__(kCommitThreads) void kv_commit_kernel(CommitArgs a)
     const int len = a.accepted_len[b];
     // (the tokens to emit are requested beside the lengths and the path, not behind them)
     const int bonus = a.emitted_tokens ? a.bonus_token[b] : 0;
-    if (tid == 0) s_bad = 0, s_moves = 0;
+    if (tid == 0) s_flags = 0;
     if (tid < T) {
         s_path[tid] = a.accepted_path[static_cast<size_t>(b) * T + tid];
         if (a.emitted_tokens) s_draft[tid] = a.draft_tokens[static_cast<size_t>(b) * T + tid];
@@ -69,19 +70,20 @@ __global__ __launch_bounds__(kCommitThreads) void kv_commit_kernel(CommitArgs a)
         const int node = s_path[tid];
         // a node is used as an index only once it is known to lie on an ascending path inside the T slots
         const bool node_ok = tid == 0 ? node == 0 : (node > s_path[tid - 1] && node > 0 && node < T);
-        if (!node_ok) atomicOr(&s_bad, 4);
+        if (!node_ok) atomicOr(&s_flags, 4);
         if (tid >= 1 && node_ok) {
             const int32_t* table = a.block_table + static_cast<size_t>(b) * a.max_pages;
             const int l_src = (n0 + node) / a.P, l_dst = (n0 + tid) / a.P;
             const int p_src = table[l_src], p_dst = table[l_dst];
-            if (node != tid) s_moves = 1;
-            if (p_src < 0 || p_src >= a.num_pages || p_dst < 0 || p_dst >= a.num_pages) atomicOr(&s_bad, 2);
+            if (node != tid) atomicOr(&s_flags, kMoves);
+            if (p_src < 0 || p_src >= a.num_pages || p_dst < 0 || p_dst >= a.num_pages) atomicOr(&s_flags, 2);
             s_page[tid] = make_int2(p_src, p_dst);
             s_slot[tid] = make_int2(n0 + node - l_src * a.P, n0 + tid - l_dst * a.P);
         }
     }
     __syncthreads();
-    bad |= s_bad;
+    const int flags = s_flags;       // (one read: a second word cost trees 0.1 us)
+    bad |= flags & ~kMoves;
     if (bad) {                       // uniform for the workgroup
         if (tid == 0 && a.status) atomicOr(a.status, bad);
         return;
@@ -92,7 +94,7 @@ __global__ __launch_bounds__(kCommitThreads) void kv_commit_kernel(CommitArgs a)
     const int per_tok = a.k_chunks + a.v_chunks;
     const int per_head = len * per_tok;
     const int heads_at_once = per_head ? min(a.Hkv, kCommitThreads * kCommitHold / per_head) : a.Hkv;
-    for (int h0 = 0; h0 < a.Hkv && s_moves; h0 += heads_at_once) {
+    for (int h0 = 0; h0 < a.Hkv && (flags & kMoves); h0 += heads_at_once) {
         const int total = min(heads_at_once, a.Hkv - h0) * per_head;
         u32x4 hold[kCommitHold];
         unsigned char* dst[kCommitHold];
