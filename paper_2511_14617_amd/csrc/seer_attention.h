@@ -154,9 +154,8 @@ inline int tile_rows_per_block(int rows, int Dqk) {
     return ((rows + nb - 1) / nb + 31) / 32 * 32;
 }
 
-// Requests taken whole, one workgroup per 32 query rows of a KV head (seer_attention_short.hip): the waves of such a workgroup, the
-// tiles that a table may have for them, and whether a call is one.  The block table's width is what the host knows of the lengths.
-constexpr int short_most_tiles(int Dqk, int waves) { return waves == 4 ? 4 : (Dqk == 64 ? 32 : (Dqk == 128 ? 24 : 8)); }
+// Requests taken whole, one workgroup per 32 query rows of a KV head (seer_attention_short.hip): the waves of such a workgroup by the tiles
+// that a table has for them, and whether a call is one.  The block table's width is what the host knows of the lengths.
 inline int short_waves(int Dqk, int tiles) { return Dqk == 256 || tiles <= 4 ? 4 : (Dqk == 192 ? 7 : 8); }
 constexpr int kShortTableEntries = 16384;      // page ids that one workgroup looks through for the status word
 inline int short_tiles(const seer_attn_params& p) {
@@ -259,7 +258,7 @@ struct AttnArgs {
     int32_t balanced;           // 0: one workgroup per request (max_splits == 1), slot = request, no history either
     int32_t min_tiles;          // tiles of a stretch, at least (see kMinTiles)
     int32_t fine_pieces;        // with more pieces than this in stretches of two or three tiles: four tiles (see kFinePartialsBelow)
-    int32_t short_waves;        // requests taken whole: waves of a workgroup
+    int32_t short_waves, short_tiles;   // requests taken whole: waves of a workgroup, tiles of the table
     uint32_t inv_pages;         // reciprocal() of max_pages
     int32_t stream_only;        // 1: the tiled D = 128 kernel only streams its tiles (diagnostic)
     int32_t stream_partials;    // 1: the tiled D = 128 kernel writes its partial results with non-temporal stores

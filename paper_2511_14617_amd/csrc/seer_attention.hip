@@ -613,7 +613,7 @@ int run_verify_attention(void* out, const void* q, const void* k_pages, const vo
 
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     if (seer::short_call(*p)) {
-        a.short_waves = seer::short_waves(p->Dqk, seer::short_tiles(*p));
+        a.short_tiles = seer::short_tiles(*p), a.short_waves = seer::short_waves(p->Dqk, a.short_tiles);
         a.inv_pages = seer::reciprocal(p->max_pages_per_seq);
         a.self_plan = 0, a.fixed_split = 1;      // (no stretches are timed: the speed history stays as it is)
         hipError_t err = hipSuccess;
