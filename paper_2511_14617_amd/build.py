@@ -13,7 +13,7 @@ HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fno-gpu-rdc",
     # only the C entry points declared in include/seer_verify.h are exported
     "-fvisibility=hidden",
-    # packed fp32 VALU forms are kept off on purpose on the test machines
+    # packed fp32 VALU forms are kept off on purpose: some of them have given wrong results
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
 ]

@@ -393,17 +393,21 @@ struct Member {            // one beam member of the current level
 // with the most places: an LDS atomic costs about a clock per lane, and an instruction of sixteen waves sixteen clocks.
 // So as few strings as can be go through as little as can be:
 //   - the levels on which all strings agree are settled at once;
-//   - more than kFew places are reduced to distinct strings first (a phrase that recurs a thousand times goes on in a
-//     few dozen ways);
+//   - the lanes of a wave that show what its first one shows are settled inside the wave; where that says that most recur,
+//     more than kFew places are reduced to distinct strings (a phrase that recurs a thousand times goes on in a
+//     few dozen ways); a string that half of the places show stays once, however many there are;
 //   - while more than a wave's worth of strings is left, a level counts its (member, token) pairs in a hash table
 //     and the beam drops the strings nobody goes on with (most of them, where strings part); up to kFew strings are
 //     four waves' work, up to twice as many eight waves', and the waves without work end;
 //   - up to 64 strings, one per lane, are searched by one wave in registers: the lanes that show what the first one left
 //     shows are one pair, found and counted with one ballot.
-// The expansion of 128 requests with four paths of eight, in a call whose request with the most places has 1477: 46.9 us
-// when each level was counted by the whole workgroup behind six barriers (7 .. 12 thousand clocks a level with sixteen waves,
-// 2 .. 3 thousand for one wave with up to 256 places), 29 now; whole calls over 16 draws of the histories
-// 67 .. 254 us, 46 .. 79 now (2 .. 4 of it the match scan).
+// When each level was counted by the whole workgroup behind six barriers (7 .. 12 thousand clocks a level with sixteen
+// waves, 2 .. 3 thousand for one wave with up to 256 places), whole calls of 128 requests with four paths of eight over 16
+// draws of the histories took 64 .. 212 us, 103 on average; 44 .. 74 and 52.5 now (16 of it the match scan); 300 requests
+// 170 us, 95 now, 1024 of shorter histories 123, 92 now.  Slower than that are more than eight levels of one phrase (141 places: 27 us, 38
+// now) and thousands of places with nearly as many strings over a few tokens (2450: 61, 74; 6701: 100, 125).
+// The search takes 152,480 bytes of LDS, so one workgroup per CU; sixteen waves of up to 128 registers leave no room
+// for a second one in any case.
 // Not kept: comparing all strings with each other (n^2 / 64 wave steps of some 60 instructions) and a trie of all
 // levels in one table (strings that the beam drops at the next level are entered all the way down).
 constexpr int kSlots = 4096;              // of the table of a level's pairs, at most
@@ -1424,7 +1428,7 @@ __global__ __launch_bounds__(kThreads) void draft_expand_kernel(Args a) {
         __syncthreads();
     }
 
-    // ---- few enough places: a trie ----
+    // ---- few enough places: strings ----
     if (handed_over && !done && d <= levels) {
         const int n_places = min(x.mem[x.nmem - 1].base + x.mem[x.nmem - 1].n, kSmall);
         search_places(a, x, uniform(d), uniform(levels), least, uniform(n_places));
